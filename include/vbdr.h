@@ -277,7 +277,8 @@ int vbdr_sketch_info(const vbdr_sketch *sk, vbdr_info *out);
  *                      tile of 2^15 BDRs, and the advance applies the records
  *                      from LDS while it streams the tile (default); 2 = the
  *                      scan updates the pool itself (direct or binned).
- *                      Up to 2 records per BDR per slice are deferred; the
+ *                      Up to 2 (pools of 2^26 BDRs) to 16 (2^23 and less)
+ *                      records per BDR per slice are deferred; the
  *                      rest are applied by the scan.  The sketch state seen
  *                      through vbdr_export_state is the same either way.
  */

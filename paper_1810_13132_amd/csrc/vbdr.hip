@@ -362,7 +362,7 @@ constexpr int kDeferPer = 32;
 constexpr uint32_t kDeferChunk = kDeferBlock * kDeferPer;
 constexpr uint32_t kDeferWords = kDeferTile / 32;  // bit words per plane of a tile
 static_assert(kDeferTile == kDeferBlock * 32, "one thread advances 32 BDRs of a tile");
-static_assert((kDeferSlots * kDeferTile) % 4 == 0, "record runs start 16-byte aligned");
+static_assert(kDeferTile % 16 == 0, "record runs start 16-byte aligned");
 static_assert(kPad % 32 == 0, "tiles of the deferred advance start on whole bit words");
 
 // Exclusive prefix sums of a[0..n) into out[0..n) by one workgroup of
@@ -1938,6 +1938,25 @@ namespace {
 // sorted chunk (s1 goes to LDS only if it fits beside them).
 size_t defer_scan_lds(uint32_t tiles) { return (size_t)(2 * tiles + kDeferChunk) * 4; }
 
+// Records a tile's run holds.  A slice of more pairs than that per tile is
+// applied pair by pair by the scan, one random read-modify-write of a line
+// each: at m = 2^24, g = 2048 and 2^27 pairs a slice (8 a BDR), runs of 2
+// slots per BDR left 3/4 of the records to that path (fast layout: scan 3.67
+// ms against 0.43, advance 0.17 against 0.27).  The runs of a sketch
+// therefore take 2^27 slots (512 MB) where that is at most 16 per BDR, so
+// that pools below 2^26 BDRs also hold slices of 2^27 pairs, with a quarter
+// tile to spare for uneven tiles.  Members of a batch (up to 256, each with
+// its own runs) take twice the smallest run up to 2^23 BDRs; any sketch
+// takes the smallest where the device has little memory left.
+uint32_t defer_run_cap(uint64_t m, bool lean) {
+  uint64_t slots = (kDeferBudget + m - 1) / m;
+  const uint64_t most = lean ? (m <= (1ull << 23) ? 2 * kDeferSlots : kDeferSlots) : kDeferSlotsMax;
+  slots = slots < kDeferSlots ? kDeferSlots : slots > most ? most : slots;
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b / 8 < slots * m * 4) slots = kDeferSlots;
+  return (uint32_t)slots * kDeferTile + (slots > kDeferSlots ? kDeferTile / 4 : 0);
+}
+
 // Hosts per block of the tiled estimate under the current tuning: the
 // default block (tl_B), or est_bin_hosts rounded down to whole sub-blocks.
 uint32_t tiled_block_hosts(const vbdr_sketch* sk) {
@@ -2043,13 +2062,13 @@ int create_sketch(uint64_t m, uint32_t g, uint32_t k, uint64_t hash_seed, int la
     // the binned scan needs 8 XCDs and pidx < 2^27 to pack its records
     const uint64_t bin_bytes =
         (!lean && layout != VBDR_LAYOUT_PACKED && sk->parts == 8 && m <= kBinMaxM) ? 8ull * kBinCap * 4 : 0;
-    // deferred scan records: kDeferSlots per BDR, for 2^22 <= m and 2^26 tile-rounded BDRs at most
+    // deferred scan records (defer_run_cap), for 2^22 <= m and 2^26 tile-rounded BDRs at most
     uint64_t def_bytes = 0;
     if ((!lean || defer_ok) && (m >= kPartMinM || layout == VBDR_LAYOUT_PACKED) && sk->mstride <= (1ull << 26)) {
       const uint32_t tiles = (uint32_t)((sk->mstride + kDeferTile - 1) / kDeferTile);
       if (defer_scan_lds(tiles) + 1024 <= (size_t)lds_max && (size_t)(33 - 1) * kDeferWords * 4 + 4096 <= (size_t)lds_max) {
         sk->def_tiles = tiles;
-        sk->def_cap = kDeferSlots * kDeferTile;
+        sk->def_cap = defer_run_cap(m, lean);
         def_bytes = (uint64_t)tiles * sk->def_cap * 4 + (uint64_t)(tiles + 1) * 8;
       }
     }

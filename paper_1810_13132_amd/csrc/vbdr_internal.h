@@ -17,7 +17,9 @@ constexpr uint64_t kBinMaxM = 1ull << 27;   // binned scan records pack (pidx <<
 constexpr uint32_t kBinChunk = 1u << 24;    // pairs per binned-scan pass (records stay cache resident)
 constexpr uint32_t kBinCap = kBinChunk / 8 + kBinChunk / 32 + 65536;  // records per bin per pass
 constexpr uint32_t kDeferTile = 1u << 15;   // BDRs per deferred-apply tile (one advance workgroup)
-constexpr uint32_t kDeferSlots = 2;         // record slots per BDR per slice before the direct fallback
+constexpr uint32_t kDeferSlots = 2;         // record slots per BDR per slice before the direct fallback, at least
+constexpr uint64_t kDeferBudget = 1ull << 27;  // record slots of a sketch where its pool needs fewer per BDR
+constexpr uint32_t kDeferSlotsMax = 16;
 
 struct vbdr_sketch {
   int device;

@@ -574,6 +574,28 @@ def test_import_over_saturated_planes(V, O, layout):
         assert_state_equal(a.state(), osk.state(), layout, f"slice {t} after import")
 
 
+@pytest.mark.parametrize("layout", ["fast", "small", "packed"])
+def test_record_runs_at_their_capacity(V, O, layout):
+    """Pools below 2^26 BDRs hold up to 16 records per BDR: one pair repeated
+    up to its tile's run (16 1/4 slots per BDR at m = 2^22) and past it in a
+    second call, with other pairs around it, against the oracle."""
+    m, g, k = 1 << 22, 64, 3
+    rng = np.random.default_rng(43)
+    Lc = 24 if layout == "packed" else 0
+    sk = V.Sketch(m, g, k, 9, layout, Lc=Lc)
+    osk = O.Sketch(m, g, k, 9, O.GPACKED if layout == "packed" else LAYOUT_CODE[layout], Lc=Lc)
+    run = 16 * (1 << 15) + (1 << 13)
+    for sizes in ((run, 0), (run - 100, 5000), (300, 200)):
+        for n in sizes:
+            other = rng.integers(0, 2**32, (1 << 16, 2), dtype=np.uint64).astype(np.uint32)
+            p_ = np.concatenate([other, np.tile(np.array([[11, 12]], np.uint32), (n, 1))])
+            sk.scan_slice(_dev(V, p_.reshape(-1)))
+            osk.scan(p_)
+        sk.advance_slice()
+        osk.advance()
+        assert_state_equal(sk.state(), osk.state(), layout, f"runs of {sizes}")
+
+
 def test_bad_arguments_on_device(V):
     sk = V.Sketch(5000, 16, 3, 1, "small")
     pairs = torch.zeros(8, dtype=torch.int32, device="cuda")
