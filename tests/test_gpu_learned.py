@@ -144,6 +144,22 @@ def test_train_gradient_matches_fp64(V, M):
     np.testing.assert_allclose(g, ref_g, rtol=1e-3, atol=1e-4 * scale)
 
 
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 64, 65, 8193])
+def test_train_gradient_batch_edges(V, M, n):
+    """Batches at the edges of the gradient kernel's tiles (16 samples), of a
+    workgroup's four tiles and of its grid, against float64; grads_out is
+    added to.  fp32 sums of n terms: the tolerance of the test above."""
+    rng = np.random.default_rng(n)
+    params = _random_params(M, 9)
+    feats = rng.uniform(0, 1, (n, 67)).astype(np.float32)
+    targets = rng.uniform(0, 9, n).astype(np.float32)
+    tr = V.Trainer(params, 1e-3)
+    g, loss = tr.grad(torch.from_numpy(feats).cuda(), torch.from_numpy(targets).cuda())
+    ref_loss, ref_g = M.loss_and_grad(params.astype(np.float64), feats.astype(np.float64), targets.astype(np.float64))
+    assert abs(float(loss.cpu()[0]) - ref_loss) <= 1e-4 * ref_loss
+    np.testing.assert_allclose(g.cpu().numpy().astype(np.float64), ref_g, rtol=1e-3, atol=1e-4 * np.abs(ref_g).max())
+
+
 def test_train_step_is_adam(V, M):
     rng = np.random.default_rng(1)
     params = _random_params(M, 10)
