@@ -23,6 +23,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "vbdr_internal.h"
@@ -98,18 +99,34 @@ __global__ void k_seeds(uint32_t* __restrict__ s1, uint32_t g, uint32_t A0) {
   if (i < g) s1[i] = mm3(i, A0);
 }
 
-__global__ void k_hist_reset(unsigned long long* __restrict__ hist, unsigned long long first,
-                             unsigned long long* __restrict__ psum) {
-  if (threadIdx.x < kBins) hist[threadIdx.x] = threadIdx.x == 0 ? first : 0ull;
-  if (psum && threadIdx.x == 0) *psum = 0;
+// E_m and the register sum from a histogram of which every lane's bin is in
+// `bins` (LDS), by one thread.
+__device__ __forceinline__ void pool_stats(const unsigned long long* bins, uint64_t m, unsigned long long* stats) {
+  unsigned long long sum = 0;
+  for (int r = 0; r < kBins; ++r) sum += bins[r] * (unsigned long long)r;
+  stats[kStatEm] = (unsigned long long)__double_as_longlong(pool_estimate(bins, (double)m));
+  stats[kStatSum] = sum;
 }
 
-// Adds the PCSA runs P[0..n) (four per word) of a thread to the pool's sum.
-template <int N>
-__device__ __forceinline__ void add_pcsa_sum(const uint32_t* P, unsigned long long* psum) {
+// Statistics of an empty pool (first: m) or, with first = 0, of the histogram in stats.
+__global__ void k_stats_init(unsigned long long* __restrict__ stats, unsigned long long first, uint64_t m) {
+  __shared__ unsigned long long bins[kBins];
+  const int i = threadIdx.x;
+  if (i < kBins) {
+    bins[i] = !first ? stats[i] : i == 0 ? first : 0ull;
+    stats[i] = bins[i];
+  }
+  __syncthreads();
+  if (i == 0) pool_stats(bins, m, stats);
+  for (int w = kStatAcc + i; w < kStatWords; w += blockDim.x) stats[w] = 0;
+}
+
+// Adds the PCSA runs P (four per word) of a thread to the pool's sum.
+template <int W>
+__device__ __forceinline__ void add_pcsa_sum(const DrWords<W>& P, unsigned long long* psum) {
   uint32_t t = 0;
 #pragma unroll
-  for (int w = 0; w < N; ++w) t += byte_sum(P[w]);
+  for (int w = 0; w < W; ++w) t += byte_sum(P.v[w]);
   const uint64_t s = wave_sum_u64(t);
   if ((threadIdx.x & 63) == 0 && s) atomicAdd(psum, (unsigned long long)s);
 }
@@ -128,9 +145,11 @@ template <bool FAST, bool STAGE, bool TEST>
 __global__ __launch_bounds__(kScanBlock) void k_scan(const u32x2* __restrict__ pairs, uint64_t n,
                                                      const uint32_t* __restrict__ s1g, uint32_t g, uint32_t b,
                                                      uint32_t A1, uint32_t m, uint8_t* __restrict__ dr,
-                                                     uint64_t mstride, uint32_t* __restrict__ seen, uint64_t wstride) {
+                                                     uint64_t mstride, uint32_t* __restrict__ seen, uint64_t wstride,
+                                                     unsigned long long* __restrict__ direct_flag) {
   extern __shared__ uint32_t s1_lds[];
   const uint32_t* s1 = s1g;
+  if (direct_flag && blockIdx.x == 0 && threadIdx.x == 0) *direct_flag = 1ull;  // for the advance: see k_scan_defer
   if constexpr (STAGE) {
     for (uint32_t i = threadIdx.x; i < g; i += kScanBlock) s1_lds[i] = s1g[i];
     __syncthreads();
@@ -303,67 +322,25 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_apply(const uint32_t* __res
   }
 }
 
-// -------------------------------------------------------------- advance
-// One thread per 16 consecutive BDRs; planes visited from LBP1 = L down to 1.
-// Fast layout (Alg. 6): slide every DR, then zero the DR of the highest LBP1
-// whose bsLBP1 bit is set, and clear bsLBP1.  Small layout (Alg. 8): slide
-// every DR; the window's register is read before the slide.  Register of a
-// BDR: the largest LBP1 whose DR is active (Alg. 2), i.e. DR <= k-1 at the
-// moment the window is read.  Each block histograms its registers in LDS.
-
-constexpr int kAdvBlock = 256;
-constexpr int kAdvBpt = 16;
-static_assert(kPad % (kAdvBlock * kAdvBpt) == 0, "plane padding must cover whole advance blocks");
-
-template <bool FAST>
-__global__ __launch_bounds__(kAdvBlock) void k_advance(uint8_t* __restrict__ dr, uint64_t mstride,
-                                                       uint32_t* __restrict__ seen, uint64_t wstride,
-                                                       uint8_t* __restrict__ reg, uint8_t* __restrict__ reg4,
-                                                       uint64_t m, uint32_t L, uint32_t thr,
-                                                       unsigned long long* __restrict__ hist,
-                                                       uint8_t* __restrict__ preg,
-                                                       unsigned long long* __restrict__ psum) {
-  __shared__ uint32_t lh[kAdvBlock / 64][kBins];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (lane < kBins) lh[wave][lane] = 0;
-  __syncthreads();
-  const uint64_t base = ((uint64_t)blockIdx.x * kAdvBlock + threadIdx.x) * kAdvBpt;
-  uint32_t R[4], P[4];
-  advance_group<FAST>(dr, mstride, seen, wstride, reg, reg4, base, L, swar_gt_bias(thr), R, preg, P);
-  if (!FAST && preg) add_pcsa_sum<4>(P, psum);  // padding BDRs have run 0
-#pragma unroll
-  for (int j = 0; j < kAdvBpt; ++j)
-    if (base + j < m) atomicAdd(&lh[wave][(R[j >> 2] >> (8 * (j & 3))) & 0xFFu], 1u);
-  __syncthreads();
-  if (threadIdx.x < kBins) {
-    uint32_t c = 0;
-    for (int w = 0; w < kAdvBlock / 64; ++w) c += lh[w][threadIdx.x];
-    if (c) atomicAdd(hist + threadIdx.x, (unsigned long long)c);
-  }
-}
-
 // ------------------------------------------- scan + advance, deferred apply
-// For large pools every scan update is a random access that misses every
-// cache.  Deferred: the scan only computes each pair's record
-// (pidx << 5 | LBP1-1), sorts a chunk of kDeferChunk records by tile of
-// kDeferTile BDRs in LDS and appends each tile's share to that tile's record
+// A scan that updates the pool itself makes one random access per pair.
+// Deferred: the scan only computes each pair's record
+// (pidx << 5 | LBP1-1), sorts a chunk of 1024 PER records by tile of 2^tshift
+// BDRs in LDS and appends each tile's share to that tile's record
 // run with one atomic per (chunk, tile).  The advance that closes the slice
 // runs one workgroup per tile: it ORs the tile's records into per-plane bit
 // words in LDS and applies them while it streams the tile's DRs, which it
 // reads and writes anyway.  Records beyond a run's capacity are applied by the
-// scan itself, as the direct scan would (fast layout: the last word of
-// `fill` then tells the advance to read the bsLBP1 planes too).  Updates are
-// idempotent (Sec. 4.2), so deferring them to the close of the slice leaves
-// the closed state unchanged.
+// scan itself, as the direct scan would (the last word of `fill` then tells
+// the advance to read the bsLBP1 planes too, and not to trust its saturation
+// masks).  Updates are idempotent (Sec. 4.2), so deferring them to the close
+// of the slice leaves the closed state unchanged.
 
 constexpr int kDeferBlock = 1024;
-constexpr int kHistCopies = 4;  // register histograms per wave in the deferred advances (a power of two)
-constexpr int kDeferPer = 32;
+constexpr int kHistCopies = 4;  // register histograms per wave in the advances (a power of two)
+constexpr int kDeferPer = 32;   // records per thread of a chunk, at most
 constexpr uint32_t kDeferChunk = kDeferBlock * kDeferPer;
-constexpr uint32_t kDeferWords = kDeferTile / 32;  // bit words per plane of a tile
-static_assert(kDeferTile == kDeferBlock * 32, "one thread advances 32 BDRs of a tile");
-static_assert(kDeferTile % 16 == 0, "record runs start 16-byte aligned");
-static_assert(kPad % 32 == 0, "tiles of the deferred advance start on whole bit words");
+static_assert(kPad % (1u << kMinTileShift) == 0, "tiles start on whole bit words");
 
 // Exclusive prefix sums of a[0..n) into out[0..n) by one workgroup of
 // BLOCK threads, n <= 4 * BLOCK; wsum holds BLOCK / 64 words.
@@ -384,16 +361,11 @@ __device__ void block_exclusive_scan(const uint32_t* a, uint32_t* out, uint32_t 
   }
   if (lane == 63) wsum[wave] = inc;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t run = 0;
-    for (int w = 0; w < BLOCK / 64; ++w) {
-      const uint32_t t = wsum[w];
-      wsum[w] = run;
-      run += t;
-    }
-  }
-  __syncthreads();
-  uint32_t off = wsum[wave] + inc - sum;
+  uint32_t before = lane < wave ? wsum[lane] : 0u;  // every wave adds the sums of the waves before it
+  static_assert(BLOCK / 64 <= 16, "one lane per wave sum");
+#pragma unroll
+  for (int d = 8; d > 0; d >>= 1) before += __shfl_xor(before, d, 16);
+  uint32_t off = __shfl(before, 0) + inc - sum;
 #pragma unroll
   for (uint32_t j = 0; j < 4; ++j)
     if (j < per && lo + j < n) {
@@ -419,36 +391,37 @@ __device__ __forceinline__ void apply_record(uint32_t rec, uint8_t* dr, uint64_t
   }
 }
 
-// One chunk of kDeferChunk pairs from c0 on: records (pidx << 5 | LBP1-1),
+// One chunk of 1024 PER pairs from c0 on: records (pidx << 5 | LBP1-1),
 // counted and ranked per tile in LDS, sorted by tile, appended to the tile
 // runs (one 64-bit atomic per (chunk, tile)); records past a run's capacity
 // are applied directly and flag the direct update.  LDS: cnt[tiles],
-// start[tiles], sorted[kDeferChunk]; s1 points to LDS when staged.
-template <bool FAST>
+// start[tiles], sorted[1024 PER]; s1 points to LDS when staged.
+template <bool FAST, int PER>
 __device__ __forceinline__ void scan_defer_chunk(const u32x2* __restrict__ pairs, uint64_t n, uint64_t c0,
                                                  const uint32_t* s1, uint32_t b, uint32_t A1, uint32_t m,
                                                  uint32_t tiles, uint32_t cap, uint32_t* __restrict__ recs,
                                                  unsigned long long* __restrict__ fill, uint8_t* __restrict__ dr,
                                                  uint64_t mstride, uint32_t* __restrict__ seen, uint64_t wstride,
-                                                 uint32_t Lc, uint32_t* __restrict__ bits, uint32_t z, uint32_t* lds,
-                                                 uint32_t* wsum) {
+                                                 uint32_t Lc, uint32_t* __restrict__ bits, uint32_t z,
+                                                 uint32_t tshift, uint32_t* lds, uint32_t* wsum) {
+  constexpr int kLoad = PER < 8 ? PER : 8;  // pair loads in flight per thread
   uint32_t* cnt = lds;
   uint32_t* start = lds + tiles;
   uint32_t* sorted = lds + 2 * tiles;
   for (uint32_t t = threadIdx.x; t < tiles; t += kDeferBlock) cnt[t] = 0;
   __syncthreads();
   // records and their ranks within the tile (< kDeferChunk, 16 bits each)
-  uint32_t rec[kDeferPer], rank[kDeferPer / 2];
+  uint32_t rec[PER], rank[PER / 2];
 #pragma unroll
-  for (int u0 = 0; u0 < kDeferPer; u0 += 8) {
-    u32x2 p[8];
+  for (int u0 = 0; u0 < PER; u0 += kLoad) {
+    u32x2 p[kLoad];
 #pragma unroll
-    for (int v = 0; v < 8; ++v) {
+    for (int v = 0; v < kLoad; ++v) {
       const uint64_t i = c0 + (uint64_t)(u0 + v) * kDeferBlock + threadIdx.x;
       p[v] = i < n ? __builtin_nontemporal_load(pairs + i) : u32x2{0u, 0u};
     }
 #pragma unroll
-    for (int v = 0; v < 8; ++v) {
+    for (int v = 0; v < kLoad; ++v) {
       const int u = u0 + v;
       const uint64_t i = c0 + (uint64_t)u * kDeferBlock + threadIdx.x;
       uint32_t r = 0;
@@ -457,7 +430,7 @@ __device__ __forceinline__ void scan_defer_chunk(const u32x2* __restrict__ pairs
         bip_map(p[v].y, A1, b, vidx, rho);
         const uint32_t pidx = reduce_m(mm3(p[v].x, s1[vidx]), m);
         rec[u] = (pidx << 5) | ((rho < Lc ? rho : Lc) - 1);  // LBP1 above Lc is recorded at Lc
-        r = atomicAdd(&cnt[pidx / kDeferTile], 1u);
+        r = atomicAdd(&cnt[pidx >> tshift], 1u);
       }
       if (u & 1) rank[u >> 1] |= r << 16;
       else rank[u >> 1] = r;
@@ -474,16 +447,16 @@ __device__ __forceinline__ void scan_defer_chunk(const u32x2* __restrict__ pairs
     }
   }
 #pragma unroll
-  for (int u = 0; u < kDeferPer; ++u) {
+  for (int u = 0; u < PER; ++u) {
     const uint64_t i = c0 + (uint64_t)u * kDeferBlock + threadIdx.x;
-    if (i < n) sorted[start[(rec[u] >> 5) / kDeferTile] + ((rank[u >> 1] >> (16 * (u & 1))) & 0xFFFFu)] = rec[u];
+    if (i < n) sorted[start[rec[u] >> (5 + tshift)] + ((rank[u >> 1] >> (16 * (u & 1))) & 0xFFFFu)] = rec[u];
   }
   __syncthreads();
-  const uint32_t total = n - c0 < kDeferChunk ? (uint32_t)(n - c0) : kDeferChunk;
+  const uint32_t total = n - c0 < PER * kDeferBlock ? (uint32_t)(n - c0) : PER * kDeferBlock;
   bool direct = false;
   for (uint32_t j = threadIdx.x; j < total; j += kDeferBlock) {
     const uint32_t r = sorted[j];
-    const uint32_t t = (r >> 5) / kDeferTile;
+    const uint32_t t = r >> (5 + tshift);
     const uint32_t pos = cnt[t] + (j - start[t]);
     if (pos < cap) {
       recs[(uint64_t)t * cap + pos] = r;
@@ -496,27 +469,27 @@ __device__ __forceinline__ void scan_defer_chunk(const u32x2* __restrict__ pairs
   __syncthreads();
 }
 
-// LDS: cnt[tiles], start[tiles], sorted[kDeferChunk], then s1 if staged.
-template <bool FAST, bool STAGE>
+// LDS: cnt[tiles], start[tiles], sorted[1024 PER], then s1 if staged.
+template <bool FAST, bool STAGE, int PER>
 __global__ __launch_bounds__(kDeferBlock) void k_scan_defer(const u32x2* __restrict__ pairs, uint64_t n,
-                                                            const uint32_t* __restrict__ s1g, uint32_t g, int stage,
-                                                            uint32_t b, uint32_t A1, uint32_t m, uint32_t tiles,
+                                                            const uint32_t* __restrict__ s1g, uint32_t g, uint32_t b, uint32_t A1, uint32_t m, uint32_t tiles,
                                                             uint32_t cap, uint32_t* __restrict__ recs,
                                                             unsigned long long* __restrict__ fill,
                                                             uint8_t* __restrict__ dr, uint64_t mstride,
                                                             uint32_t* __restrict__ seen, uint64_t wstride,
-                                                            uint32_t Lc, uint32_t* __restrict__ bits, uint32_t z) {
+                                                            uint32_t Lc, uint32_t* __restrict__ bits, uint32_t z,
+                                                            uint32_t tshift) {
   extern __shared__ uint32_t lds[];
   __shared__ uint32_t wsum[kDeferBlock / 64];
   // the seeds from LDS when staged (a pointer that may point to either makes
   // every seed read a flat load, waited for one at a time)
-  uint32_t* s1l = lds + 2 * tiles + kDeferChunk;
+  constexpr uint32_t chunk = PER * kDeferBlock;
+  uint32_t* s1l = lds + 2 * tiles + chunk;
   if (STAGE)
     for (uint32_t i = threadIdx.x; i < g; i += kDeferBlock) s1l[i] = s1g[i];
-  (void)stage;
-  for (uint64_t c0 = (uint64_t)blockIdx.x * kDeferChunk; c0 < n; c0 += (uint64_t)gridDim.x * kDeferChunk)
-    scan_defer_chunk<FAST>(pairs, n, c0, STAGE ? s1l : s1g, b, A1, m, tiles, cap, recs, fill, dr, mstride, seen,
-                           wstride, Lc, bits, z, lds, wsum);
+  for (uint64_t c0 = (uint64_t)blockIdx.x * chunk; c0 < n; c0 += (uint64_t)gridDim.x * chunk)
+    scan_defer_chunk<FAST, PER>(pairs, n, c0, STAGE ? s1l : s1g, b, A1, m, tiles, cap, recs, fill, dr, mstride, seen,
+                                wstride, Lc, bits, z, tshift, lds, wsum);
 }
 
 // OR a tile's n records into its LDS bit-planes (plane LBP1-1, bit = BDR in
@@ -524,112 +497,204 @@ __global__ __launch_bounds__(kDeferBlock) void k_scan_defer(const u32x2* __restr
 // 4), so each thread loads quads of records, four quads at a time, before the
 // LDS atomics: one load per record, waited for one at a time, left the
 // advance bound by load latency.
-__device__ __forceinline__ void records_to_planes(const uint32_t* __restrict__ r, uint32_t n, uint32_t* pm) {
-  for (uint32_t q0 = threadIdx.x; 4 * q0 < n; q0 += 4 * kDeferBlock) {
+__device__ __forceinline__ void records_to_planes(const uint32_t* __restrict__ r, uint32_t n, uint32_t tshift,
+                                                  uint32_t* pm) {
+  const uint32_t mask = (1u << tshift) - 1, words = 1u << (tshift - 5);
+  for (uint32_t q0 = threadIdx.x; 4 * q0 < n; q0 += 4 * blockDim.x) {
     u32x4 v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const uint32_t q = q0 + (uint32_t)u * kDeferBlock;
+      const uint32_t q = q0 + (uint32_t)u * blockDim.x;
       v[u] = 4 * q < n ? *reinterpret_cast<const u32x4*>(r + 4 * q) : u32x4{0u, 0u, 0u, 0u};
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const uint32_t q = q0 + (uint32_t)u * kDeferBlock;
+      const uint32_t q = q0 + (uint32_t)u * blockDim.x;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         if (4 * q + e < n) {
           const uint32_t rec = v[u][e];
-          const uint32_t p = (rec >> 5) & (kDeferTile - 1);
-          atomicOr(&pm[(rec & 31u) * kDeferWords + (p >> 5)], 1u << (p & 31));
+          const uint32_t p = (rec >> 5) & mask;
+          atomicOr(&pm[(rec & 31u) * words + (p >> 5)], 1u << (p & 31));
         }
       }
     }
   }
 }
 
-// The deferred advance of one tile by one workgroup: the tile's records
-// become L planes of kDeferWords bit words in LDS (pm), then every thread
-// slides 32 BDRs; lh holds the wave register histograms.
-template <bool FAST>
-__device__ __forceinline__ void advance_defer_tile(uint32_t tile, uint8_t* __restrict__ dr, uint64_t mstride,
-                                                   uint32_t* __restrict__ seen, uint64_t wstride,
-                                                   uint8_t* __restrict__ reg, uint8_t* __restrict__ reg4, uint64_t m,
-                                                   uint32_t L, uint32_t thr, unsigned long long* __restrict__ hist,
-                                                   const uint32_t* __restrict__ recs,
-                                                   unsigned long long* __restrict__ fill, uint32_t cap,
-                                                   uint32_t tiles, uint8_t* __restrict__ preg,
-                                                   unsigned long long* __restrict__ psum, uint32_t* __restrict__ sat,
-                                                   uint32_t* pm, uint32_t (*lh)[kHistCopies][kBins]) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (uint32_t i = threadIdx.x; i < L * kDeferWords; i += kDeferBlock) pm[i] = 0;
-  for (int i = lane; i < kHistCopies * kBins; i += 64) (&lh[wave][0][0])[i] = 0;
-  const unsigned long long f = fill[tile];
-  const uint32_t n = f < cap ? (uint32_t)f : cap;
-  const bool use_seen = FAST && fill[tiles] != 0;
-  // the saturation masks hold only if no DR changed outside the advance since the last one
-  const bool sat_ok = sat != nullptr && fill[tiles] == 0;
-  // the top plane's load goes out before the record phase
-  const uint64_t base = (uint64_t)tile * kDeferTile + (uint64_t)threadIdx.x * 32;
-  const bool live = base < mstride;
-  u32x4 top0 = {0u, 0u, 0u, 0u}, top1 = {0u, 0u, 0u, 0u};
-  if (live) {
-    const uint8_t* top = dr + (uint64_t)(L - 1) * mstride + base;
-    top0 = *reinterpret_cast<const u32x4*>(top);
-    top1 = *reinterpret_cast<const u32x4*>(top + 16);
+// The end of an advance: every workgroup adds its registers' histogram (lh,
+// one per wave and copy) to the pool's running sums; the last one to finish
+// moves them to the statistics, takes E_m, and leaves sums, count and the
+// direct-update flag zero for the next slice (every workgroup has read the
+// flag).  The sums are agent-scope atomics whose completion each workgroup
+// waits for before it counts itself, so no launch is needed before or after
+// the advance for resets (two launches of about 2.5 us less per slice).
+__device__ __forceinline__ void advance_finish(uint32_t (*lh)[kHistCopies][kBins], uint32_t waves,
+                                               unsigned long long* stats, uint64_t m, uint32_t tiles,
+                                               unsigned long long* psum, unsigned long long* flag) {
+  __shared__ uint32_t last;
+  __shared__ unsigned long long bins[kBins];
+  // the PCSA sums of every wave have arrived (each wave waits for its own)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    if (threadIdx.x < kBins) {
+      uint32_t c = 0;
+      for (uint32_t w = 0; w < waves; ++w)
+        for (int q = 0; q < kHistCopies; ++q) c += lh[w][q][threadIdx.x];
+      if (c) atomicAdd(stats + kStatAcc + threadIdx.x, (unsigned long long)c);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (threadIdx.x == 0)
+      last = atomicAdd(reinterpret_cast<uint32_t*>(stats + kStatTicket), 1u) == tiles - 1;
   }
   __syncthreads();
-  if (threadIdx.x == 0) fill[tile] = 0;  // every thread has read it
-  const uint32_t* r = recs + (uint64_t)tile * cap;
-  records_to_planes(r, n, pm);
-  __syncthreads();
-  uint32_t P[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (live) {
-    uint32_t R[8];
-    uint32_t* satw = sat ? sat + (base >> 5) : nullptr;
-    // windows of k <= 128 slices take the bit-7 active test (swar_lt_bit7)
-    const uint32_t kk = thr < 128u ? (thr + 1u) * 0x01010101u : 0u;
-    advance_group32<FAST>(dr, mstride, seen, wstride, reg, reg4, base, L, swar_gt_bias(thr), pm + threadIdx.x,
-                          kDeferWords, use_seen, top0, top1, R, preg, P, satw, sat_ok ? *satw : 0u, kk);
-#pragma unroll
-    for (int j = 0; j < 32; ++j)
-      if (base + j < m) atomicAdd(&lh[wave][lane & (kHistCopies - 1)][(R[j >> 2] >> (8 * (j & 3))) & 0xFFu], 1u);
-  }
-  if (!FAST && preg) add_pcsa_sum<8>(P, psum);  // every lane of the wave takes part
-  __syncthreads();
+  if (!last) return;
   if (threadIdx.x < kBins) {
-    uint32_t c = 0;
-    for (int w = 0; w < kDeferBlock / 64; ++w)
-      for (int q = 0; q < kHistCopies; ++q) c += lh[w][q][threadIdx.x];
-    if (c) atomicAdd(hist + threadIdx.x, (unsigned long long)c);
+    const unsigned long long c = atomicExch(stats + kStatAcc + threadIdx.x, 0ull);
+    bins[threadIdx.x] = c;
+    stats[threadIdx.x] = c;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    pool_stats(bins, m, stats);
+    stats[kStatTicket] = 0ull;
+    if (psum) psum[0] = atomicExch(psum + 1, 0ull);
+    if (flag) *flag = 0ull;
   }
 }
 
-// One workgroup per tile; LDS: L planes of kDeferWords bit words.
-template <bool FAST>
-__global__ __launch_bounds__(kDeferBlock) void k_advance_defer(uint8_t* __restrict__ dr, uint64_t mstride,
-                                                               uint32_t* __restrict__ seen, uint64_t wstride,
-                                                               uint8_t* __restrict__ reg, uint8_t* __restrict__ reg4,
-                                                               uint64_t m, uint32_t L, uint32_t thr,
-                                                               unsigned long long* __restrict__ hist,
-                                                               const uint32_t* __restrict__ recs,
-                                                               unsigned long long* __restrict__ fill, uint32_t cap,
-                                                               uint32_t tiles, uint8_t* __restrict__ preg,
-                                                               unsigned long long* __restrict__ psum,
-                                                               uint32_t* __restrict__ sat) {
+// The advance of one tile by one workgroup of 1024 threads: the tile's records
+// and bsLBP1 words become L planes of bit words in LDS (pm), then every thread
+// slides 1/SPLIT of the planes of 4 W BDRs; lh holds the wave register
+// histograms.  Tiles shrink with the pool, 32 BDRs a thread (W = 8) from 2^24,
+// 16 down to 2^22; below, where a tile's planes are short and a thread's chain
+// of plane loads would be all there is to wait for, the planes of 16 BDRs go to
+// 2 or 4 threads, whose results meet in LDS (part).  Streams bound it in large
+// pools (2^26 BDRs: 389 us, 0.41 of the pool's bytes read and written at copy
+// rate), the latency of a few dependent steps in small ones (2^18 BDRs: 10 us
+// where 64 workgroups of 16 BDRs a thread with resets around took 13).
+// G planes are loaded together.
+template <bool FAST, bool PCSA, int W, int SPLIT, int G>
+__device__ __forceinline__ void advance_tile(const AdvSketch& A, uint32_t tile, uint32_t* pm,
+                                             uint32_t (*lh)[kHistCopies][kBins], u32x4* part) {
+  constexpr uint32_t kGroups = kDeferBlock / SPLIT;  // threads of one share of the planes
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const uint32_t lw = A.tshift - 5, words = 1u << lw;
+  const bool direct = A.fill == nullptr || A.fill[A.tiles] != 0;  // updates were made outside the records
+  const uint64_t w0 = (uint64_t)tile << lw;
+  if (FAST && direct) {
+    for (uint32_t i = threadIdx.x; i < A.L << lw; i += kDeferBlock) {
+      const uint64_t w = w0 + (i & (words - 1));
+      uint32_t v = 0;
+      if (w < A.wstride) {
+        uint32_t* at = A.seen + (uint64_t)(i >> lw) * A.wstride + w;
+        v = *at;
+        if (v) *at = 0;
+      }
+      pm[i] = v;
+    }
+  } else {
+    for (uint32_t i = threadIdx.x; i < A.L << lw; i += kDeferBlock) pm[i] = 0;
+  }
+  for (int i = lane; i < kHistCopies * kBins; i += 64) (&lh[wave][0][0])[i] = 0;
+  const unsigned long long f = A.fill ? A.fill[tile] : 0ull;
+  const uint32_t n = f < A.cap ? (uint32_t)f : A.cap;
+  const uint32_t group = threadIdx.x % kGroups, share = threadIdx.x / kGroups;
+  const uint64_t base = ((uint64_t)tile << A.tshift) + (uint64_t)group * (4 * W);
+  const bool live = base < A.mstride;
+  uint32_t* satw = SPLIT == 1 && A.sat ? A.sat + base / (4 * W) : nullptr;
+  // the saturation masks hold only if no DR changed outside the advance since the last one
+  const uint32_t sat_in = satw && live && !direct ? *satw : 0u;
+  __syncthreads();
+  if (threadIdx.x == 0 && A.fill) A.fill[tile] = 0;  // every thread has read it
+  if (n) records_to_planes(A.recs + (uint64_t)tile * A.cap, n, A.tshift, pm);
+  __syncthreads();
+  DrWords<W> R = {}, P = {};
+  if (live) {
+    // windows of k <= 128 slices take the bit-7 active test (swar_lt_bit7)
+    const uint32_t kk = A.thr < 128u ? (A.thr + 1u) * 0x01010101u : 0u;
+    const uint32_t bit = group * (4 * W);  // of the tile
+    const uint32_t* my = pm + (bit >> 5);
+    const int planes = ((int)A.L + SPLIT - 1) / SPLIT, hi = (int)A.L - (int)share * planes;
+    const int lo = hi - planes + 1 > 1 ? hi - planes + 1 : 1;
+    uint32_t folded = 0, sat_out;
+    if (FAST && SPLIT > 1)
+      for (int r = (int)A.L; r > hi; --r) folded |= my[(uint32_t)(r - 1) << lw] >> (bit & 31u);
+    advance_words<FAST, PCSA, W, G>(A.dr, A.mstride, base, hi, lo, folded, swar_gt_bias(A.thr), kk, my, words, bit & 31u,
+                                    sat_in, sat_out, R, P);
+    if (satw) *satw = sat_out;  // always: sat_in is 0 when the stored masks were stale
+  }
+  if constexpr (SPLIT > 1) {  // the first share's threads take the other shares' results
+    static_assert(W == 4, "one vector per share");
+    auto meet = [&](DrWords<W>& v, auto join) {
+      if (share > 0) part[threadIdx.x - kGroups] = u32x4{v.v[0], v.v[1], v.v[2], v.v[3]};
+      __syncthreads();
+      if (share == 0)
+#pragma unroll
+        for (int q = 1; q < SPLIT; ++q) {
+          const u32x4 o = part[threadIdx.x + (q - 1) * kGroups];
+#pragma unroll
+          for (int w = 0; w < W; ++w) v.v[w] = join(v.v[w], o[w]);
+        }
+    };
+    meet(R, [](uint32_t high, uint32_t low) {  // bytes <= 32: the higher planes' register where there is one
+      return high | (low & ~((((high + 0x7F7F7F7Fu) & 0x80808080u) >> 7) * 0xFFu));
+    });
+    if constexpr (PCSA) {
+      __syncthreads();
+      meet(P, [](uint32_t a, uint32_t b) {
+        uint32_t least = 0;
+#pragma unroll
+        for (int e = 0; e < 32; e += 8) {
+          const uint32_t x = (a >> e) & 0xFFu, y = (b >> e) & 0xFFu;
+          least |= (x < y ? x : y) << e;
+        }
+        return least;
+      });
+    }
+  }
+  if (live && share == 0) {
+    store_dr<W>(A.reg + base, R);
+    store_nibbles<W>(A.reg4, base, R);
+    if constexpr (PCSA) {
+#pragma unroll
+      for (int w = 0; w < W; ++w)  // 255: no inactive DR, a run of L
+#pragma unroll
+        for (int e = 0; e < 32; e += 8)
+          if (((P.v[w] >> e) & 0xFFu) == 0xFFu) P.v[w] ^= (0xFFu ^ A.L) << e;
+      store_dr<W>(A.preg + base, P);
+    }
+#pragma unroll
+    for (int j = 0; j < 4 * W; ++j)
+      if (base + j < A.m) atomicAdd(&lh[wave][lane & (kHistCopies - 1)][(R.v[j >> 2] >> (8 * (j & 3))) & 0xFFu], 1u);
+  } else {
+    P = {};
+  }
+  if (PCSA && share == 0) add_pcsa_sum<W>(P, A.psum + 1);  // every lane of the wave takes part; padding BDRs have run 0
+  advance_finish(lh, kGroups / 64, A.stats, A.m, A.tiles, PCSA ? A.psum : nullptr,
+                 A.fill ? A.fill + A.tiles : nullptr);
+}
+
+// One workgroup per tile; LDS: L planes of 2^(tshift - 5) bit words.
+// At most 64 registers for tiles of 2^14 BDRs: two workgroups a CU, so that
+// one streams planes while the other applies records (smaller tiles: at most
+// one workgroup a CU, more planes in flight).
+template <bool FAST, bool PCSA, int W, int SPLIT>
+__global__ __launch_bounds__(kDeferBlock, W == 4 && SPLIT == 1 ? 8 : 4) void k_advance(AdvSketch A) {
   extern __shared__ uint32_t pm[];
+  __shared__ u32x4 part[SPLIT > 1 ? kDeferBlock - kDeferBlock / SPLIT : 1];
   // four copies of each wave's register histogram (lane & 3): registers crowd a
   // few values, and lanes adding to one LDS word are served one at a time
   __shared__ uint32_t lh[kDeferBlock / 64][kHistCopies][kBins];
-  advance_defer_tile<FAST>(blockIdx.x, dr, mstride, seen, wstride, reg, reg4, m, L, thr, hist, recs, fill, cap, tiles,
-                           preg, psum, sat, pm, lh);
+  advance_tile<FAST, PCSA, W, SPLIT, W == 8 ? 1 : SPLIT == 1 ? 2 : 4>(A, blockIdx.x, pm, lh, part);
 }
 
-// ------------------------------------------- batches: members with record runs
-// Batch members whose pools take deferred scans (2^22..2^26 BDRs) are scanned
-// and advanced by these two kernels instead of the batch's direct-update
-// ones: every deferred member's chunks of kDeferChunk pairs in one persistent
-// launch (items strided over the grid), then every member's tiles in one
-// launch (one workgroup per tile).  Inputs come from the device table.
+// ------------------------------------------------------------- batches
+// Batch members with record runs are scanned by the first of these kernels,
+// every such member's chunks of kDeferChunk pairs in one persistent launch
+// (items strided over the grid); the second advances all members, one
+// workgroup per tile.  Inputs come from the device table.
 
 // Last member s whose first item is <= item (members without items share
 // their successor's first item).
@@ -654,43 +719,49 @@ __global__ __launch_bounds__(kDeferBlock) void k_batch_scan_defer(const DeferIte
   const uint32_t total = hdr->scan_total;
   for (uint32_t item = blockIdx.x; item < total; item += gridDim.x) {
     const DeferItem& D = it[defer_member(first, S, item)];
+    const AdvSketch& A = D.adv;
     const uint64_t c0 = (uint64_t)(item - D.scan_item0) * kDeferChunk;
     const u32x2* pairs = reinterpret_cast<const u32x2*>(D.pairs);
-    if (D.layout == VBDR_LAYOUT_FAST)
-      scan_defer_chunk<true>(pairs, D.n_pairs, c0, D.s1, D.b, D.A1, (uint32_t)D.m, D.tiles, D.cap, D.recs, D.fill,
-                             D.dr, D.mstride, D.seen, D.wstride, D.L, nullptr, 0u, lds, wsum);
+    if (A.layout == VBDR_LAYOUT_FAST)
+      scan_defer_chunk<true, kDeferPer>(pairs, D.n_pairs, c0, D.s1, D.b, D.A1, (uint32_t)A.m, A.tiles, A.cap, D.recs,
+                                        A.fill, A.dr, A.mstride, A.seen, A.wstride, A.L, nullptr, 0u, A.tshift, lds,
+                                        wsum);
     else
-      scan_defer_chunk<false>(pairs, D.n_pairs, c0, D.s1, D.b, D.A1, (uint32_t)D.m, D.tiles, D.cap, D.recs, D.fill,
-                              D.dr, D.mstride, D.seen, D.wstride, D.L, nullptr, 0u, lds, wsum);
+      scan_defer_chunk<false, kDeferPer>(pairs, D.n_pairs, c0, D.s1, D.b, D.A1, (uint32_t)A.m, A.tiles, A.cap, D.recs,
+                                         A.fill, A.dr, A.mstride, A.seen, A.wstride, A.L, nullptr, 0u, A.tshift, lds,
+                                         wsum);
   }
 }
 
-// One workgroup per tile of every member; LDS: max L planes of kDeferWords words.
-__global__ __launch_bounds__(kDeferBlock) void k_batch_advance_defer(const DeferItem* __restrict__ it, uint32_t S) {
+// One workgroup per tile of every member; LDS: the largest member's planes of bit words.
+// BIG: some member has more than 2^25 BDRs (W = 8, twice the registers).
+template <bool FAST, bool BIG>
+__device__ __forceinline__ void advance_any(const AdvSketch& A, uint32_t tile, uint32_t* pm,
+                                            uint32_t (*lh)[kHistCopies][kBins], u32x4* part) {
+  if (A.tshift == 12) advance_tile<FAST, false, 4, 4, 2>(A, tile, pm, lh, part);
+  else if (A.tshift == 13) advance_tile<FAST, false, 4, 2, 2>(A, tile, pm, lh, part);
+  else if (!BIG || A.tshift == 14) advance_tile<FAST, false, 4, 1, 2>(A, tile, pm, lh, part);
+  else advance_tile<FAST, false, 8, 1, 1>(A, tile, pm, lh, part);
+}
+template <bool BIG>
+__global__ __launch_bounds__(kDeferBlock, BIG ? 4 : 8) void k_batch_advance(const DeferItem* __restrict__ it, uint32_t S) {
   extern __shared__ uint32_t pm[];
   __shared__ uint32_t lh[kDeferBlock / 64][kHistCopies][kBins];
   __shared__ uint32_t first[kMaxDeferMembers];
+  __shared__ u32x4 part[kDeferBlock * 3 / 4];
   for (uint32_t s = threadIdx.x; s < S; s += kDeferBlock) first[s] = it[s].adv_item0;
   __syncthreads();
   const DeferItem& D = it[defer_member(first, S, blockIdx.x)];
+  const AdvSketch& A = D.adv;
   const uint32_t tile = blockIdx.x - D.adv_item0;
-  if (D.layout == VBDR_LAYOUT_FAST)
-    advance_defer_tile<true>(tile, D.dr, D.mstride, D.seen, D.wstride, D.reg, D.reg4, D.m, D.L, D.thr, D.hist, D.recs,
-                             D.fill, D.cap, D.tiles, nullptr, nullptr, D.sat, pm, lh);
-  else
-    advance_defer_tile<false>(tile, D.dr, D.mstride, D.seen, D.wstride, D.reg, D.reg4, D.m, D.L, D.thr, D.hist,
-                              D.recs, D.fill, D.cap, D.tiles, nullptr, nullptr, D.sat, pm, lh);
-}
-
-// After every tile has read it: clear each member's direct-update flag.
-__global__ void k_batch_defer_flag(const DeferItem* __restrict__ it, uint32_t S) {
-  for (uint32_t s = threadIdx.x; s < S; s += blockDim.x) it[s].fill[it[s].tiles] = 0ull;
+  if (A.layout == VBDR_LAYOUT_FAST) advance_any<true, BIG>(A, tile, pm, lh, part);
+  else advance_any<false, BIG>(A, tile, pm, lh, part);
 }
 
 // Packed layout (Table 1's recorder sizes): DR r of BDR p is a z-bit counter
 // stored bit-sliced, bit b in bit-plane (r - 1) z + b at word p / 32, so one
 // 32-bit word holds one bit of 32 BDRs and every DR operation is a handful of
-// bitwise operations on z words.  One workgroup per tile, as k_advance_defer:
+// bitwise operations on z words.  One workgroup per tile, as k_advance:
 // the tile's records become per-plane bit words in LDS, then thread t sweeps
 // word t of every plane from LBP1 Lc down to 1: SetDR of the slice's records
 // (clear z bits), the window read (value < k, compared from the top bit down;
@@ -699,17 +770,19 @@ __global__ void k_batch_defer_flag(const DeferItem* __restrict__ it, uint32_t S)
 __global__ __launch_bounds__(kDeferBlock) void k_advance_packed(uint32_t* __restrict__ bits, uint64_t wstride,
                                                                 uint32_t z, uint32_t Lc, uint32_t k,
                                                                 uint8_t* __restrict__ reg, uint8_t* __restrict__ reg4,
-                                                                uint64_t m, unsigned long long* __restrict__ hist,
+                                                                uint64_t m, unsigned long long* __restrict__ stats,
                                                                 const uint32_t* __restrict__ recs,
                                                                 unsigned long long* __restrict__ fill, uint32_t cap,
-                                                                uint32_t tiles, uint32_t* __restrict__ sat) {
+                                                                uint32_t tiles, uint32_t tshift,
+                                                                uint32_t* __restrict__ sat) {
   extern __shared__ uint32_t pm[];
   // four copies of each wave's register histogram (lane & 3): registers crowd a
   // few values, and lanes adding to one LDS word are served one at a time
   __shared__ uint32_t lh[kDeferBlock / 64][kHistCopies][kBins];
   const uint32_t tile = blockIdx.x;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (uint32_t i = threadIdx.x; i < Lc * kDeferWords; i += kDeferBlock) pm[i] = 0;
+  const uint32_t words = 1u << (tshift - 5);  // one per thread of the block
+  for (uint32_t i = threadIdx.x; i < Lc * words; i += blockDim.x) pm[i] = 0;
   for (int i = lane; i < kHistCopies * kBins; i += 64) (&lh[wave][0][0])[i] = 0;
   const unsigned long long f = fill[tile];
   const uint32_t n = f < cap ? (uint32_t)f : cap;
@@ -718,9 +791,9 @@ __global__ __launch_bounds__(kDeferBlock) void k_advance_packed(uint32_t* __rest
   __syncthreads();
   if (threadIdx.x == 0) fill[tile] = 0;  // every thread has read it
   const uint32_t* r = recs + (uint64_t)tile * cap;
-  records_to_planes(r, n, pm);
+  records_to_planes(r, n, tshift, pm);
   __syncthreads();
-  const uint64_t w = (uint64_t)tile * kDeferWords + threadIdx.x;
+  const uint64_t w = (uint64_t)tile * words + threadIdx.x;
   if (w < wstride) {
     uint32_t R[8] = {0, 0, 0, 0, 0, 0, 0, 0}, done = 0;
     // bit rr-1: the 32 DR[rr] were all 2^z - 1 after the last advance; with no
@@ -728,7 +801,7 @@ __global__ __launch_bounds__(kDeferBlock) void k_advance_packed(uint32_t* __rest
     const uint32_t sat_in = sat_ok ? sat[w] : 0u;
     uint32_t sat_out = 0;
     auto skip = [&](int rr) -> bool {
-      return ((sat_in >> (rr - 1)) & 1u) && pm[(uint32_t)(rr - 1) * kDeferWords + threadIdx.x] == 0u;
+      return ((sat_in >> (rr - 1)) & 1u) && pm[(uint32_t)(rr - 1) * words + threadIdx.x] == 0u;
     };
     uint32_t dn[8];  // the next recorder's words load while this one is processed
     const bool skip_top = skip((int)Lc);
@@ -745,7 +818,7 @@ __global__ __launch_bounds__(kDeferBlock) void k_advance_packed(uint32_t* __rest
 #pragma unroll
         for (int b = 0; b < 8; ++b) dn[b] = (uint32_t)b < z ? (sk ? ~0u : bits[(pb - z + b) * wstride + w]) : 0u;
       }
-      const uint32_t set = pm[(uint32_t)(rr - 1) * kDeferWords + threadIdx.x];
+      const uint32_t set = pm[(uint32_t)(rr - 1) * words + threadIdx.x];
       {  // 32 DRs at 2^z - 1 (>= k: inactive) with no record stay so and are not stored
         uint32_t all = ~0u;
 #pragma unroll
@@ -804,13 +877,7 @@ __global__ __launch_bounds__(kDeferBlock) void k_advance_packed(uint32_t* __rest
     for (int j = 0; j < 32; ++j)
       if (base + j < m) atomicAdd(&lh[wave][lane & (kHistCopies - 1)][(R[j >> 2] >> (8 * (j & 3))) & 0xFFu], 1u);
   }
-  __syncthreads();
-  if (threadIdx.x < kBins) {
-    uint32_t c = 0;
-    for (int v = 0; v < kDeferBlock / 64; ++v)
-      for (int q = 0; q < kHistCopies; ++q) c += lh[v][q][threadIdx.x];
-    if (c) atomicAdd(hist + threadIdx.x, (unsigned long long)c);
-  }
+  advance_finish(lh, blockDim.x >> 6, stats, m, tiles, nullptr, fill + tiles);
 }
 
 // Apply the pending records of every tile to the pool (before a state export
@@ -859,20 +926,14 @@ __global__ __launch_bounds__(kEstBlock) void k_estimate(const uint32_t* __restri
                                                         float* __restrict__ out, double* __restrict__ raw,
                                                         uint32_t* __restrict__ hout) {
   extern __shared__ uint32_t s1_lds[];
-  __shared__ double em_sh;
   __shared__ uint32_t lh[kEstWaves][kBins];
   const uint32_t* s1 = s1g;
   if constexpr (STAGE) {
     for (uint32_t i = threadIdx.x; i < g; i += kEstBlock) s1_lds[i] = s1g[i];
     s1 = s1_lds;
   }
-  if (threadIdx.x == 0) {
-    uint64_t U = 0;
-    for (int r = 0; r < kBins; ++r) U += (uint64_t)hist[r] << (32 - r);
-    em_sh = hll_estimate(U, hist[0], (double)m);
-  }
   __syncthreads();
-  const double Em = em_sh;
+  const double Em = stat_em(hist);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   for (uint64_t h = (uint64_t)blockIdx.x * kEstWaves + wave; h < nh; h += (uint64_t)gridDim.x * kEstWaves) {
     const uint32_t kmix = mm3_key(hosts[h]);  // seed-independent half of H(aip, m, s1[i])
@@ -1015,13 +1076,6 @@ __global__ __launch_bounds__(256) void k_estimate_final(uint32_t nh, uint32_t g,
                                                         const uint32_t* __restrict__ part_v, uint32_t pstride,
                                                         const unsigned long long* __restrict__ ovf_u,
                                                         const uint32_t* __restrict__ ovf_v, float* __restrict__ out) {
-  __shared__ double em_sh;
-  if (threadIdx.x == 0) {
-    uint64_t U = 0;
-    for (int r = 0; r < kBins; ++r) U += (uint64_t)hist[r] << (32 - r);
-    em_sh = hll_estimate(U, hist[0], (double)m);
-  }
-  __syncthreads();
   const uint32_t h = blockIdx.x * 256 + threadIdx.x;
   if (h >= nh) return;
   uint64_t U = 0, V = 0;
@@ -1034,7 +1088,7 @@ __global__ __launch_bounds__(256) void k_estimate_final(uint32_t nh, uint32_t g,
     V += ovf_v[h];
   }
   const double Es = hll_estimate(U, V, (double)g);
-  const double n = noise_removed(Es, em_sh, (double)m, (double)g);
+  const double n = noise_removed(Es, stat_em(hist), (double)m, (double)g);
   out[h] = (float)(n > 0.0 ? n : 0.0);
 }
 
@@ -1199,27 +1253,29 @@ __global__ __launch_bounds__(kEstBlock) void k_estimate_sum(const uint32_t* __re
 // Fast layout only.  The open slice's LBP1 record is split between the
 // bsLBP1 bit-planes and, with deferred scans, the pending records of each
 // tile; export folds both into one byte per BDR (the highest LBP1), one
-// workgroup per tile of kDeferTile BDRs, 32 BDRs per thread.
+// workgroup per tile, 32 BDRs per thread.
 __global__ __launch_bounds__(kDeferBlock) void k_now_export(const uint32_t* __restrict__ seen, uint64_t wstride,
                                                             uint64_t mstride, uint64_t m, uint32_t L,
                                                             const uint32_t* __restrict__ recs,
                                                             const unsigned long long* __restrict__ fill, uint32_t cap,
+                                                            uint32_t tshift,
                                                             uint8_t* __restrict__ now) {
   extern __shared__ uint32_t pm[];
   const uint32_t tile = blockIdx.x;
-  for (uint32_t i = threadIdx.x; i < L * kDeferWords; i += kDeferBlock) pm[i] = 0;
+  const uint32_t words = 1u << (tshift - 5);  // one per thread of the block
+  for (uint32_t i = threadIdx.x; i < L * words; i += blockDim.x) pm[i] = 0;
   __syncthreads();
   if (recs) {
     const unsigned long long f = fill[tile];
     const uint32_t n = f < cap ? (uint32_t)f : cap;
-    records_to_planes(recs + (uint64_t)tile * cap, n, pm);
+    records_to_planes(recs + (uint64_t)tile * cap, n, tshift, pm);
   }
   __syncthreads();
-  const uint64_t base = (uint64_t)tile * kDeferTile + (uint64_t)threadIdx.x * 32;
+  const uint64_t base = ((uint64_t)tile << tshift) + (uint64_t)threadIdx.x * 32;
   if (base >= m) return;
   uint32_t R[8] = {0, 0, 0, 0, 0, 0, 0, 0}, done = 0;
   for (int i = (int)L; i >= 1; --i) {
-    const uint32_t bits = pm[(uint32_t)(i - 1) * kDeferWords + threadIdx.x] | seen[(uint64_t)(i - 1) * wstride + (base >> 5)];
+    const uint32_t bits = pm[(uint32_t)(i - 1) * words + threadIdx.x] | seen[(uint64_t)(i - 1) * wstride + (base >> 5)];
     const uint32_t fold = bits & ~done;
     done |= bits;
 #pragma unroll
@@ -1724,9 +1780,6 @@ __global__ __launch_bounds__(256) void k_est_tile_final(uint32_t nh, uint32_t g,
                                                         const uint32_t* __restrict__ part,
                                                         const unsigned long long* __restrict__ ovf,
                                                         float* __restrict__ out) {
-  __shared__ double em_sh;
-  if (threadIdx.x == 0) em_sh = pool_estimate(hist, (double)m);
-  __syncthreads();
   const uint32_t h = blockIdx.x * 256 + threadIdx.x;
   if (h >= nh) return;
   unsigned long long U = 0, V = 0;
@@ -1771,7 +1824,7 @@ __global__ __launch_bounds__(256) void k_est_tile_final(uint32_t nh, uint32_t g,
   }
   U += Us << 18;
   const double Es = hll_estimate(U, V, (double)g);
-  const double n = noise_removed(Es, em_sh, (double)m, (double)g);
+  const double n = noise_removed(Es, stat_em(hist), (double)m, (double)g);
   out[h] = (float)(n > 0.0 ? n : 0.0);
 }
 
@@ -1814,6 +1867,11 @@ uint64_t splitmix64_first(uint64_t state) {
   return z ^ (z >> 31);
 }
 
+// Words of the saturation masks: one per thread of the advance's tiles.
+uint64_t sat_words(const vbdr_sketch* sk) {
+  return sk->layout == VBDR_LAYOUT_PACKED ? sk->wstride : sk->mstride >> (sk->tshift - 10);
+}
+
 int init_state(vbdr_sketch* sk, hipStream_t st) {
   const uint32_t fill_grid = grid_cap(sk, (sk->L * sk->mstride / 4 + 255) / 256, 32);
   if (sk->dr) {
@@ -1835,16 +1893,15 @@ int init_state(vbdr_sketch* sk, hipStream_t st) {
     hipLaunchKernelGGL(k_fill_u32, dim3(fill_grid), dim3(256), 0, st, sk->seen, (uint64_t)sk->L * sk->wstride, 0u);
     VBDR_LAUNCHED("k_fill_u32(seen)");
   }
-  hipLaunchKernelGGL(k_hist_reset, dim3(1), dim3(64), 0, st, sk->hist, (unsigned long long)sk->m,
-                     (unsigned long long*)nullptr);
-  VBDR_LAUNCHED("k_hist_reset");
+  hipLaunchKernelGGL(k_stats_init, dim3(1), dim3(64), 0, st, sk->hist, (unsigned long long)sk->m, sk->m);
+  VBDR_LAUNCHED("k_stats_init");
   if (sk->def_fill) {
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, st, reinterpret_cast<uint32_t*>(sk->def_fill),
                        (uint64_t)(sk->def_tiles + 1) * 2, 0u);
     VBDR_LAUNCHED("k_fill_u32(def_fill)");
   }
   if (sk->sat) {  // no plane known saturated: the first advance reads every DR
-    hipLaunchKernelGGL(k_fill_u32, dim3(fill_grid), dim3(256), 0, st, sk->sat, sk->wstride, 0u);
+    hipLaunchKernelGGL(k_fill_u32, dim3(fill_grid), dim3(256), 0, st, sk->sat, sat_words(sk), 0u);
     VBDR_LAUNCHED("k_fill_u32(sat)");
   }
   return VBDR_OK;
@@ -1862,31 +1919,42 @@ int defer_flush(vbdr_sketch* sk, hipStream_t st) {
 
 }  // namespace
 
+// Whether the sketch's advances apply record runs.
+static bool has_runs(const vbdr_sketch* sk) {
+  return sk->def_rec && (sk->tune.scan_defer == 1 || sk->layout == VBDR_LAYOUT_PACKED);
+}
+
+static void adv_sketch(const vbdr_sketch* sk, bool runs, AdvSketch* a) {
+  std::memset(a, 0, sizeof(*a));
+  a->dr = sk->dr, a->seen = sk->seen, a->reg = sk->reg, a->reg4 = sk->reg4, a->preg = sk->preg, a->psum = sk->psum;
+  a->stats = sk->hist;
+  if (runs) a->recs = sk->def_rec, a->fill = sk->def_fill, a->sat = sk->sat, a->cap = sk->def_cap;
+  a->mstride = sk->mstride, a->wstride = sk->wstride, a->m = sk->m;
+  a->L = sk->L, a->thr = sk->k - 1, a->tiles = sk->tiles, a->tshift = sk->tshift;
+  a->layout = (uint32_t)sk->layout;
+}
+
 void vbdr_defer_member(const vbdr_sketch* sk, DeferItem* d) {
   std::memset(d, 0, sizeof(*d));
-  d->s1 = sk->s1, d->dr = sk->dr, d->seen = sk->seen, d->reg = sk->reg, d->reg4 = sk->reg4, d->hist = sk->hist;
-  d->recs = sk->def_rec, d->fill = sk->def_fill, d->sat = sk->sat;
-  d->mstride = sk->mstride, d->wstride = sk->wstride, d->m = sk->m;
-  d->b = sk->b, d->A1 = sk->A1, d->tiles = sk->def_tiles, d->cap = sk->def_cap, d->L = sk->L, d->thr = sk->k - 1;
-  d->layout = (uint32_t)sk->layout;
+  adv_sketch(sk, sk->def_rec != nullptr, &d->adv);  // a batch scans into the runs whatever the member's tuning
+  d->s1 = sk->s1, d->recs = sk->def_rec, d->b = sk->b, d->A1 = sk->A1;
 }
 
 uint32_t vbdr_defer_chunk_pairs() { return kDeferChunk; }
 
+uint32_t vbdr_adv_lds(const vbdr_sketch* sk) { return sk->Lc << (sk->tshift - 3); }
+
 int vbdr_launch_batch_defer(const DeferItem* items_dev, const DeferHdr* hdr_dev, uint32_t S, uint32_t max_tiles,
-                            uint32_t max_L, uint32_t adv_total, uint32_t grid, int phase, hipStream_t st) {
-  if (S == 0) return VBDR_OK;
-  if (S > kMaxDeferMembers) return vbdr_fail(VBDR_EINVAL, "more than %u members with record runs", kMaxDeferMembers);
+                            uint32_t adv_lds, uint32_t adv_total, bool big, uint32_t grid, int phase, hipStream_t st) {
+  if (S > kMaxDeferMembers) return vbdr_fail(VBDR_EINVAL, "more than %u members", kMaxDeferMembers);
   if (phase == 0) {
+    if (max_tiles == 0) return VBDR_OK;
     hipLaunchKernelGGL(k_batch_scan_defer, dim3(grid), dim3(kDeferBlock), (size_t)(2 * max_tiles + kDeferChunk) * 4,
                        st, items_dev, hdr_dev, S);
     VBDR_LAUNCHED("k_batch_scan_defer");
   } else {
-    hipLaunchKernelGGL(k_batch_advance_defer, dim3(adv_total), dim3(kDeferBlock), (size_t)max_L * kDeferWords * 4, st,
-                       items_dev, S);
-    VBDR_LAUNCHED("k_batch_advance_defer");
-    hipLaunchKernelGGL(k_batch_defer_flag, dim3(1), dim3(256), 0, st, items_dev, S);
-    VBDR_LAUNCHED("k_batch_defer_flag");
+    hipLaunchKernelGGL(big ? k_batch_advance<true> : k_batch_advance<false>, dim3(adv_total), dim3(kDeferBlock), adv_lds, st, items_dev, S);
+    VBDR_LAUNCHED("k_batch_advance");
   }
   return VBDR_OK;
 }
@@ -1934,9 +2002,23 @@ const char* vbdr_last_error(void) { return g_err.c_str(); }
 
 namespace {
 
-// Deferred scans need the LDS of k_scan_defer: two words per tile plus the
+// LDS of a scan chunk of `per` records a thread: two words per tile plus the
 // sorted chunk (s1 goes to LDS only if it fits beside them).
-size_t defer_scan_lds(uint32_t tiles) { return (size_t)(2 * tiles + kDeferChunk) * 4; }
+size_t defer_scan_lds(uint32_t tiles, uint32_t per) { return (size_t)(2 * tiles + per * kDeferBlock) * 4; }
+
+// Tiles of the advance, 2^s BDRs: at most 256 tiles (one per CU) of up to 2^13
+// BDRs for pools of up to 2^21, 2^14 (two workgroups share a CU's LDS) up to
+// 2^23, 2^15 above, where longer shares of a chunk count more (2^24 BDRs, 2^27
+// pairs: scan 425 us and advance 263, 441 and 278 with tiles of 2^14; 8e6 BDRs,
+// 2^23 pairs: 34 and 60 us, 34 and 54 with 2^14).  In a batch, whose tiles of
+// all members share the CUs, 2^14 up to 2^25 BDRs (32 members' advance 575 us,
+// 670 with 2^15 from 2^24 on).
+uint32_t tile_shift(uint64_t mstride, bool lean) {
+  uint32_t s = kMinTileShift;
+  const uint32_t most = mstride <= (lean ? 1ull << 25 : 1ull << 23) ? kMaxTileShift - 1 : kMaxTileShift;
+  while (s < most && (mstride >> s) > 256) s++;
+  return s;
+}
 
 // Records a tile's run holds.  A slice of more pairs than that per tile is
 // applied pair by pair by the scan, one random read-modify-write of a line
@@ -1945,16 +2027,19 @@ size_t defer_scan_lds(uint32_t tiles) { return (size_t)(2 * tiles + kDeferChunk)
 // ms against 0.43, advance 0.17 against 0.27).  The runs of a sketch
 // therefore take 2^27 slots (512 MB) where that is at most 16 per BDR, so
 // that pools below 2^26 BDRs also hold slices of 2^27 pairs, with a quarter
-// tile to spare for uneven tiles.  Members of a batch (up to 256, each with
+// tile to spare for uneven tiles; small pools take 2^22 slots (16 MB).  Members of a batch (up to 256, each with
 // its own runs) take twice the smallest run up to 2^23 BDRs; any sketch
 // takes the smallest where the device has little memory left.
-uint32_t defer_run_cap(uint64_t m, bool lean) {
+uint32_t defer_run_cap(uint64_t m, uint32_t tshift, bool lean) {
   uint64_t slots = (kDeferBudget + m - 1) / m;
   const uint64_t most = lean ? (m <= (1ull << 23) ? 2 * kDeferSlots : kDeferSlots) : kDeferSlotsMax;
   slots = slots < kDeferSlots ? kDeferSlots : slots > most ? most : slots;
+  const uint64_t least = kDeferLeast / m;  // small pools: more a BDR
+  if (slots < least) slots = least;
   size_t free_b = 0, total_b = 0;
   if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b / 8 < slots * m * 4) slots = kDeferSlots;
-  return (uint32_t)slots * kDeferTile + (slots > kDeferSlots ? kDeferTile / 4 : 0);
+  const uint32_t tile = 1u << tshift;
+  return (uint32_t)slots * tile + (slots > kDeferSlots ? tile / 4 : 0);
 }
 
 // Hosts per block of the tiled estimate under the current tuning: the
@@ -2005,8 +2090,12 @@ int alloc_tiled(vbdr_sketch* sk) {
   return VBDR_OK;
 }
 
+// Saturation masks pay off in pools whose DRs outgrow the caches (tiles of
+// 2^14 BDRs and more); the packed layout's masks cost one word in 32.
+bool wants_sat(const vbdr_sketch* sk) { return sk->layout == VBDR_LAYOUT_PACKED || sk->tshift >= 14; }
+
 // lean: no estimate workspaces (sketches of a batch); defer_ok: the record
-// runs of deferred scans all the same (lean batch members with large pools).
+// runs of deferred scans all the same (lean batch members).
 int create_sketch(uint64_t m, uint32_t g, uint32_t k, uint64_t hash_seed, int layout, bool lean, bool defer_ok,
                   uint32_t Lc, vbdr_sketch** out) {
   if (!out) return vbdr_fail(VBDR_EINVAL, "out is NULL");
@@ -2062,18 +2151,24 @@ int create_sketch(uint64_t m, uint32_t g, uint32_t k, uint64_t hash_seed, int la
     // the binned scan needs 8 XCDs and pidx < 2^27 to pack its records
     const uint64_t bin_bytes =
         (!lean && layout != VBDR_LAYOUT_PACKED && sk->parts == 8 && m <= kBinMaxM) ? 8ull * kBinCap * 4 : 0;
-    // deferred scan records (defer_run_cap), for 2^22 <= m and 2^26 tile-rounded BDRs at most
+    // Deferred scan records (defer_run_cap).  The small layout's plain byte stores into a pool of
+    // 2^18 BDRs are as fast as records (2^23 pairs: 51 us direct, 60 deferred); the fast layout's
+    // atomics are not (2^20 pairs 66 us direct, 15 deferred).
     uint64_t def_bytes = 0;
-    if ((!lean || defer_ok) && (m >= kPartMinM || layout == VBDR_LAYOUT_PACKED) && sk->mstride <= (1ull << 26)) {
-      const uint32_t tiles = (uint32_t)((sk->mstride + kDeferTile - 1) / kDeferTile);
-      if (defer_scan_lds(tiles) + 1024 <= (size_t)lds_max && (size_t)(33 - 1) * kDeferWords * 4 + 4096 <= (size_t)lds_max) {
+    sk->tshift = tile_shift(sk->mstride, lean);
+    sk->tiles = (uint32_t)((sk->mstride + (1ull << sk->tshift) - 1) >> sk->tshift);
+    const uint64_t runs_from = layout == VBDR_LAYOUT_PACKED ? 0 : lean || layout == VBDR_LAYOUT_FAST ? kDeferMinM : kDeferMinSmall;
+    if ((!lean || defer_ok) && m >= runs_from && sk->mstride <= (1ull << 26)) {
+      const uint32_t tiles = sk->tiles;
+      if (defer_scan_lds(tiles, kDeferPer) + 1024 <= (size_t)lds_max &&
+          ((size_t)32 << (sk->tshift - 3)) + 24576 <= (size_t)lds_max) {
         sk->def_tiles = tiles;
-        sk->def_cap = defer_run_cap(m, lean);
+        sk->def_cap = defer_run_cap(m, sk->tshift, lean);
         def_bytes = (uint64_t)tiles * sk->def_cap * 4 + (uint64_t)(tiles + 1) * 8;
       }
     }
     if (layout == VBDR_LAYOUT_PACKED && !def_bytes) {
-      rc = vbdr_fail(VBDR_EINVAL, "the packed layout needs %zu bytes of LDS per workgroup", defer_scan_lds(1));
+      rc = vbdr_fail(VBDR_EINVAL, "the packed layout needs %zu bytes of LDS per workgroup", defer_scan_lds(1, kDeferPer));
       break;
     }
     // binned estimate: runs of g/8 + g/16 + 32 slots per (range, host), <= 512 MiB of runs
@@ -2088,7 +2183,7 @@ int create_sketch(uint64_t m, uint32_t g, uint32_t k, uint64_t hash_seed, int la
     if ((dr_bytes && vbdr_malloc(&sk->dr, dr_bytes) != hipSuccess) ||
         (bits_bytes && vbdr_malloc(&sk->bits, bits_bytes) != hipSuccess) || vbdr_malloc(&sk->reg, sk->mstride) != hipSuccess ||
         vbdr_malloc(&sk->reg4, sk->mstride / 2) != hipSuccess ||
-        vbdr_malloc(&sk->hist, 64 * sizeof(unsigned long long)) != hipSuccess ||
+        vbdr_malloc(&sk->hist, kStatWords * sizeof(unsigned long long)) != hipSuccess ||
         vbdr_malloc(&sk->s1, (uint64_t)g * 4) != hipSuccess ||
         (seen_bytes && vbdr_malloc(&sk->seen, seen_bytes) != hipSuccess) ||
         (part_bytes && vbdr_malloc(&sk->part_u, (uint64_t)sk->parts * kPartChunk * 8) != hipSuccess) ||
@@ -2098,14 +2193,14 @@ int create_sketch(uint64_t m, uint32_t g, uint32_t k, uint64_t hash_seed, int la
 
         (def_bytes && vbdr_malloc(&sk->def_rec, (uint64_t)sk->def_tiles * sk->def_cap * 4) != hipSuccess) ||
         (def_bytes && vbdr_malloc(&sk->def_fill, (uint64_t)(sk->def_tiles + 1) * 8) != hipSuccess) ||
-        (def_bytes && vbdr_malloc(&sk->sat, sk->wstride * 4) != hipSuccess)) {
+        (def_bytes && wants_sat(sk) && vbdr_malloc(&sk->sat, sat_words(sk) * 4) != hipSuccess)) {
       (void)hipGetLastError();
       rc = vbdr_fail(VBDR_ENOMEM, "device allocation of %llu bytes failed",
                 (unsigned long long)(dr_bytes + seen_bytes + sk->mstride * 3 / 2 + part_bytes));
       break;
     }
-    sk->state_only = dr_bytes + bits_bytes + seen_bytes + sk->mstride * 3 / 2 + 64 * sizeof(unsigned long long) +
-                     (uint64_t)g * 4 + (sk->sat ? sk->wstride * 4 : 0);
+    sk->state_only = dr_bytes + bits_bytes + seen_bytes + sk->mstride * 3 / 2 + kStatWords * sizeof(unsigned long long) +
+                     (uint64_t)g * 4 + (sk->sat ? sat_words(sk) * 4 : 0);
     sk->bytes = sk->state_only + part_bytes + (uint64_t)sk->parts * kLearnChunk * kBins * 4 + (uint64_t)kLearnChunk * 4 +
                 def_bytes;
     sk->bin_ok = bin_bytes != 0;  // allocated when the variant is selected (vbdr_sketch_set_tuning)
@@ -2327,7 +2422,7 @@ int vbdr_sketch_info(const vbdr_sketch* sk, vbdr_info* out) {
   out->layout = sk->layout, out->A0 = sk->A0, out->A1 = sk->A1, out->t = sk->t;
   out->state_bytes = sk->bytes;
   out->est_parts = sk->parts;
-  out->scan_deferred = sk->def_rec && (sk->tune.scan_defer == 1 || sk->layout == VBDR_LAYOUT_PACKED);
+  out->scan_deferred = has_runs(sk) && (sk->m >= kPartMinM || sk->layout == VBDR_LAYOUT_PACKED);
   out->Lc = sk->Lc;
   out->dr_bits = sk->z;
   out->est_tiled = sk->tl_rec != nullptr && sk->tune.est_binned == 3;
@@ -2351,17 +2446,33 @@ int vbdr_scan_slice(vbdr_sketch* sk, const uint32_t* pairs_dev, uint64_t n, void
   const u32x2* p = reinterpret_cast<const u32x2*>(pairs_dev);
   const uint32_t m32 = (uint32_t)sk->m;
   const bool test = sk->tune.scan_test_first == 1;
-  if (sk->def_rec && (sk->tune.scan_defer == 1 || sk->layout == VBDR_LAYOUT_PACKED)) {
-    const size_t base_lds = defer_scan_lds(sk->def_tiles);
+  // Small slices of small pools update the pool themselves (no saturation
+  // masks to keep there): a chunk's sort and its run reservations take about
+  // 8 us (2^20 BDRs: 2^20 pairs 13 us either way in the small layout, 2^22 pairs
+  // 54 us direct, 25 deferred; fast layout, 2^18 BDRs: 2^17 pairs 10 us direct, 7 deferred).
+  const bool direct = sk->m < kPartMinM && sk->layout != VBDR_LAYOUT_PACKED &&
+                      n <= (sk->layout == VBDR_LAYOUT_FAST ? kDirectFast : kDirectSmall);
+  if (has_runs(sk) && !direct) {
+    // the longest chunks that still give every CU one
+    uint32_t per = 4;
+    while (per < (uint32_t)kDeferPer && n >= (uint64_t)2 * per * kDeferBlock * (uint64_t)sk->n_cu) per *= 2;
+    const size_t base_lds = defer_scan_lds(sk->def_tiles, per);
     int lds_max = 0;
     VBDR_HIP(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, sk->device));
-    const int stage_s1 = base_lds + (size_t)sk->g * 4 + 1024 <= (size_t)lds_max;
-    const uint32_t dgrid = grid_cap(sk, (n + kDeferChunk - 1) / kDeferChunk, 1);
-    auto kern = sk->layout == VBDR_LAYOUT_FAST ? (stage_s1 ? k_scan_defer<true, true> : k_scan_defer<true, false>)
-                                               : (stage_s1 ? k_scan_defer<false, true> : k_scan_defer<false, false>);
+    const bool stage_s1 = base_lds + (size_t)sk->g * 4 + 1024 <= (size_t)lds_max;
+    const uint32_t dgrid = grid_cap(sk, (n + per * kDeferBlock - 1) / (per * kDeferBlock), per <= 8 ? 2 : 1);
+    auto pick = [&](auto fast, auto staged) {
+      constexpr bool F = decltype(fast)::value, S = decltype(staged)::value;
+      return per == 4 ? k_scan_defer<F, S, 4> : per == 8 ? k_scan_defer<F, S, 8> : per == 16 ? k_scan_defer<F, S, 16>
+                                                                                            : k_scan_defer<F, S, 32>;
+    };
+    using T = std::true_type;
+    using N = std::false_type;
+    const auto kern = sk->layout == VBDR_LAYOUT_FAST ? (stage_s1 ? pick(T{}, T{}) : pick(T{}, N{}))
+                                                     : (stage_s1 ? pick(N{}, T{}) : pick(N{}, N{}));
     hipLaunchKernelGGL(kern, dim3(dgrid), dim3(kDeferBlock), base_lds + (stage_s1 ? (size_t)sk->g * 4 : 0), st, p, n,
-                       sk->s1, sk->g, stage_s1, sk->b, sk->A1, m32, sk->def_tiles, sk->def_cap, sk->def_rec,
-                       sk->def_fill, sk->dr, sk->mstride, sk->seen, sk->wstride, sk->Lc, sk->bits, sk->z);
+                       sk->s1, sk->g, sk->b, sk->A1, m32, sk->def_tiles, sk->def_cap, sk->def_rec, sk->def_fill, sk->dr,
+                       sk->mstride, sk->seen, sk->wstride, sk->Lc, sk->bits, sk->z, sk->tshift);
     VBDR_LAUNCHED("k_scan_defer");
     return VBDR_OK;
   }
@@ -2400,7 +2511,8 @@ int vbdr_scan_slice(vbdr_sketch* sk, const uint32_t* pairs_dev, uint64_t n, void
     kern = stage ? (test ? k_scan<false, true, true> : k_scan<false, true, false>)
                  : (test ? k_scan<false, false, true> : k_scan<false, false, false>);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kScanBlock), lds, st, p, n, sk->s1, sk->g, sk->b, sk->A1, m32, sk->dr,
-                     sk->mstride, sk->seen, sk->wstride);
+                     sk->mstride, sk->seen, sk->wstride,
+                     sk->def_fill && (sk->seen || sk->sat) ? sk->def_fill + sk->def_tiles : nullptr);
   VBDR_LAUNCHED("k_scan");
   return VBDR_OK;
 }
@@ -2409,35 +2521,29 @@ int vbdr_advance_slice(vbdr_sketch* sk, void* stream) {
   if (!sk) return vbdr_fail(VBDR_EINVAL, "sketch is NULL");
   if (int rc = vbdr_check_device(sk)) return rc;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(k_hist_reset, dim3(1), dim3(64), 0, st, sk->hist, 0ull, sk->psum);
-  VBDR_LAUNCHED("k_hist_reset");
-  if (sk->preg) sk->pcsa_valid = true;  // written by the launch below
   if (sk->layout == VBDR_LAYOUT_PACKED) {
-    hipLaunchKernelGGL(k_advance_packed, dim3(sk->def_tiles), dim3(kDeferBlock), (size_t)sk->Lc * kDeferWords * 4, st,
+    hipLaunchKernelGGL(k_advance_packed, dim3(sk->def_tiles), dim3(1u << (sk->tshift - 5)), vbdr_adv_lds(sk), st,
                        sk->bits, sk->wstride, sk->z, sk->Lc, sk->k, sk->reg, sk->reg4, sk->m, sk->hist, sk->def_rec,
-                       sk->def_fill, sk->def_cap, sk->def_tiles, sk->sat);
+                       sk->def_fill, sk->def_cap, sk->def_tiles, sk->tshift, sk->sat);
     VBDR_LAUNCHED("k_advance_packed");
-    hipLaunchKernelGGL(k_defer_flag, dim3(1), dim3(64), 0, st, sk->def_fill, sk->def_tiles, 0ull);
-    VBDR_LAUNCHED("k_defer_flag");
     sk->t++;
     return VBDR_OK;
   }
-  if (sk->def_rec && sk->tune.scan_defer == 1) {
-    auto kern = sk->layout == VBDR_LAYOUT_FAST ? k_advance_defer<true> : k_advance_defer<false>;
-    hipLaunchKernelGGL(kern, dim3(sk->def_tiles), dim3(kDeferBlock), (size_t)sk->L * kDeferWords * 4, st, sk->dr,
-                       sk->mstride, sk->seen, sk->wstride, sk->reg, sk->reg4, sk->m, sk->L, sk->k - 1, sk->hist,
-                       sk->def_rec, sk->def_fill, sk->def_cap, sk->def_tiles, sk->preg, sk->psum, sk->sat);
-    VBDR_LAUNCHED("k_advance_defer");
-    hipLaunchKernelGGL(k_defer_flag, dim3(1), dim3(64), 0, st, sk->def_fill, sk->def_tiles, 0ull);
-    VBDR_LAUNCHED("k_defer_flag");
-    sk->t++;
-    return VBDR_OK;
-  }
-  const uint32_t grid = (uint32_t)(sk->mstride / (kAdvBlock * kAdvBpt));
-  auto kern = sk->layout == VBDR_LAYOUT_FAST ? k_advance<true> : k_advance<false>;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kAdvBlock), 0, st, sk->dr, sk->mstride, sk->seen, sk->wstride, sk->reg,
-                     sk->reg4, sk->m, sk->L, sk->k - 1, sk->hist, sk->preg, sk->psum);
+  AdvSketch a;
+  adv_sketch(sk, has_runs(sk), &a);
+  auto pick = [&](auto fast, auto pcsa) {
+    constexpr bool F = decltype(fast)::value, P = decltype(pcsa)::value;
+    return sk->tshift == 12   ? k_advance<F, P, 4, 4>
+           : sk->tshift == 13 ? k_advance<F, P, 4, 2>
+           : sk->tshift == 14 ? k_advance<F, P, 4, 1>
+                              : k_advance<F, P, 8, 1>;
+  };
+  const std::true_type T;
+  const std::false_type N;
+  const auto kern = sk->layout == VBDR_LAYOUT_FAST ? pick(T, N) : sk->preg ? pick(N, T) : pick(N, N);
+  hipLaunchKernelGGL(kern, dim3(sk->tiles), dim3(kDeferBlock), vbdr_adv_lds(sk), st, a);
   VBDR_LAUNCHED("k_advance");
+  if (sk->preg) sk->pcsa_valid = true;  // written by the launch above
   sk->t++;
   return VBDR_OK;
 }
@@ -2602,21 +2708,24 @@ int vbdr_enable_pcsa(vbdr_sketch* sk, int on) {
   if (int rc = vbdr_check_device(sk)) return rc;
   VBDR_HIP(hipDeviceSynchronize());
   if (on && !sk->preg) {
-    if (vbdr_malloc(&sk->preg, sk->mstride) != hipSuccess || vbdr_malloc(&sk->psum, 8) != hipSuccess) {
+    if (vbdr_malloc(&sk->preg, sk->mstride) != hipSuccess || vbdr_malloc(&sk->psum, 16) != hipSuccess) {
       (void)hipGetLastError();
       if (sk->preg) (void)hipFree(sk->preg);
       if (sk->psum) (void)hipFree(sk->psum);
       sk->preg = nullptr, sk->psum = nullptr;
-      return vbdr_fail(VBDR_ENOMEM, "device allocation of %llu bytes failed", (unsigned long long)sk->mstride + 8);
+      return vbdr_fail(VBDR_ENOMEM, "device allocation of %llu bytes failed", (unsigned long long)sk->mstride + 16);
     }
-    sk->bytes += sk->mstride + 8;
-    sk->state_only += sk->mstride + 8;
+    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, nullptr, reinterpret_cast<uint32_t*>(sk->psum), (uint64_t)4, 0u);
+    VBDR_LAUNCHED("k_fill_u32(psum)");
+    VBDR_HIP(hipDeviceSynchronize());
+    sk->bytes += sk->mstride + 16;
+    sk->state_only += sk->mstride + 16;
   } else if (!on && sk->preg) {
     (void)hipFree(sk->preg);
     (void)hipFree(sk->psum);
     sk->preg = nullptr, sk->psum = nullptr;
-    sk->bytes -= sk->mstride + 8;
-    sk->state_only -= sk->mstride + 8;
+    sk->bytes -= sk->mstride + 16;
+    sk->state_only -= sk->mstride + 16;
   }
   sk->pcsa_valid = false;
   return VBDR_OK;
@@ -2674,9 +2783,9 @@ int vbdr_export_now(vbdr_sketch* sk, uint8_t* now_dev, void* stream) {
   if (sk->layout != VBDR_LAYOUT_FAST) return vbdr_fail(VBDR_EINVAL, "max-LBP1 maps need the fast layout");
   if (int rc = vbdr_check_device(sk)) return rc;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  const uint32_t tiles = (uint32_t)((sk->mstride + kDeferTile - 1) / kDeferTile);
-  hipLaunchKernelGGL(k_now_export, dim3(tiles), dim3(kDeferBlock), (size_t)sk->L * kDeferWords * 4, st, sk->seen,
-                     sk->wstride, sk->mstride, sk->m, sk->L, sk->def_rec, sk->def_fill, sk->def_cap, now_dev);
+  hipLaunchKernelGGL(k_now_export, dim3(sk->tiles), dim3(1u << (sk->tshift - 5)), vbdr_adv_lds(sk), st, sk->seen,
+                     sk->wstride, sk->mstride, sk->m, sk->L, sk->def_rec, sk->def_fill, sk->def_cap, sk->tshift,
+                     now_dev);
   VBDR_LAUNCHED("k_now_export");
   return VBDR_OK;
 }
@@ -2842,6 +2951,8 @@ int vbdr_import_state(vbdr_sketch* sk, const uint8_t* dr_host, const uint32_t* b
     hipLaunchKernelGGL(k_defer_flag, dim3(1), dim3(64), 0, nullptr, sk->def_fill, sk->def_tiles, 1ull);
     VBDR_LAUNCHED("k_defer_flag");
   }
+  hipLaunchKernelGGL(k_stats_init, dim3(1), dim3(64), 0, nullptr, sk->hist, 0ull, sk->m);
+  VBDR_LAUNCHED("k_stats_init");
   hipLaunchKernelGGL(k_pack_reg4, dim3(grid_cap(sk, (sk->mstride / 2 + 255) / 256, 8)), dim3(256), 0, nullptr, sk->reg,
                      sk->reg4, sk->mstride / 2);
   VBDR_LAUNCHED("k_pack_reg4");

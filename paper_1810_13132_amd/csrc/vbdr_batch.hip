@@ -1,9 +1,9 @@
 // Many independent sketches (uneven streams, pools, windows, g, layouts)
-// advanced per slice by three persistent work-queue kernels -- scan, advance,
-// estimate -- that pull (sketch, tile) items from device counters.  Members
-// with pools of 2^22..2^26 BDRs instead write sorted record runs in their scan
-// and apply them in their advance, as a single sketch does (two more kernels
-// over all such members, in vbdr.hip).  Each sketch's per-slice inputs live in
+// advanced per slice by a few kernels over all of them: members with record
+// runs (pools of 2^16..2^26 BDRs) scan in sorted chunks and all members
+// advance tile by tile, as a single sketch does (both in vbdr.hip); the other
+// members' scans and all estimates are persistent work-queue kernels that
+// pull (sketch, tile) items from device counters.  Each sketch's per-slice inputs live in
 // a device descriptor table refreshed by one host-to-device copy per step, so
 // the kernel sequence is captured once into a hipGraph and replayed.  Every
 // block leaves its loop when the queue is drained, so a launch always
@@ -22,7 +22,6 @@ namespace {
 
 constexpr uint32_t kMaxBatch = 256;
 constexpr int kBBlock = 256;
-constexpr uint32_t kAdvTile = 256 * 16;  // BDRs per advance item (one block of 16-BDR groups)
 
 struct BatchDesc {
   uint8_t* dr;
@@ -38,13 +37,12 @@ struct BatchDesc {
   const uint32_t* hosts;
   uint64_t n_hosts;
   float* out;
-  uint32_t scan_item0, adv_item0, est_item0, pad;
+  uint32_t scan_item0, est_item0;
 };
 
 struct BatchHdr {
-  uint32_t scan_total, adv_total, est_total, pad0;
-  uint32_t counter[3];  // reset to 0 by every step's table upload
-  uint32_t pad1;
+  uint32_t scan_total, est_total;
+  uint32_t counter[2];  // reset to 0 by every step's table upload
 };
 
 __device__ __forceinline__ uint32_t find_sketch(const uint32_t* starts, uint32_t S, uint32_t item) {
@@ -100,65 +98,19 @@ __global__ __launch_bounds__(kBBlock) void k_batch_scan(const BatchDesc* __restr
   }
 }
 
-__global__ void k_batch_hist_reset(const BatchDesc* __restrict__ d) {
-  if (threadIdx.x < kBins) d[blockIdx.x].hist[threadIdx.x] = 0ull;
-}
-
-__global__ __launch_bounds__(kBBlock) void k_batch_advance(const BatchDesc* __restrict__ d,
-                                                           BatchHdr* __restrict__ hdr, uint32_t S) {
-  __shared__ uint32_t starts[kMaxBatch];
-  __shared__ uint32_t cur;
-  // four histogram copies per wave (lane & 3): registers crowd a few values
-  __shared__ uint32_t lh[kBBlock / 64][4][kBins];
-  for (uint32_t s = threadIdx.x; s < S; s += kBBlock) starts[s] = d[s].adv_item0;
-  const uint32_t total = hdr->adv_total;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (;;) {
-    // next_item's barrier also orders the previous item's histogram read
-    // before this item's reset
-    const uint32_t item = next_item(&hdr->counter[1], &cur);
-    if (item >= total) break;
-    for (int i = lane; i < 4 * kBins; i += 64) (&lh[wave][0][0])[i] = 0;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    const uint32_t s = find_sketch(starts, S, item);
-    const BatchDesc& D = d[s];
-    const uint64_t base = (uint64_t)(item - starts[s]) * kAdvTile + threadIdx.x * 16u;
-    uint32_t R[4];
-    const uint32_t bias = swar_gt_bias(D.k - 1);
-    if (D.layout == VBDR_LAYOUT_FAST)
-      advance_group<true>(D.dr, D.mstride, D.seen, D.wstride, D.reg, D.reg4, base, D.L, bias, R);
-    else
-      advance_group<false>(D.dr, D.mstride, D.seen, D.wstride, D.reg, D.reg4, base, D.L, bias, R);
-#pragma unroll
-    for (int j = 0; j < 16; ++j)
-      if (base + j < D.m) atomicAdd(&lh[wave][lane & 3][(R[j >> 2] >> (8 * (j & 3))) & 0xFFu], 1u);
-    __syncthreads();
-    if (threadIdx.x < kBins) {
-      uint32_t c = 0;
-      for (int w = 0; w < kBBlock / 64; ++w)
-        for (int q = 0; q < 4; ++q) c += lh[w][q][threadIdx.x];
-      if (c) atomicAdd(D.hist + threadIdx.x, (unsigned long long)c);
-    }
-  }
-}
-
 __global__ __launch_bounds__(kBBlock) void k_batch_estimate(const BatchDesc* __restrict__ d,
                                                             BatchHdr* __restrict__ hdr, uint32_t S, uint32_t tile) {
   __shared__ uint32_t starts[kMaxBatch];
   __shared__ uint32_t cur;
-  __shared__ double em;
   for (uint32_t s = threadIdx.x; s < S; s += kBBlock) starts[s] = d[s].est_item0;
   const uint32_t total = hdr->est_total;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   for (;;) {
-    const uint32_t item = next_item(&hdr->counter[2], &cur);
+    const uint32_t item = next_item(&hdr->counter[1], &cur);
     if (item >= total) break;
     const uint32_t s = find_sketch(starts, S, item);
     const BatchDesc& D = d[s];
-    if (threadIdx.x == 0) em = pool_estimate(D.hist, (double)D.m);
-    __syncthreads();
-    const double Em = em;
+    const double Em = stat_em(D.hist);
     const uint64_t lo = (uint64_t)(item - starts[s]) * tile;
     const uint64_t hi = lo + tile < D.n_hosts ? lo + tile : D.n_hosts;
     for (uint64_t h = lo + wave; h < hi; h += kBBlock / 64) {
@@ -191,44 +143,40 @@ struct vbdr_batch {
   hipGraph_t graph;
   hipGraphExec_t exec;
   vbdr_batch_tuning tune;
-  // members with deferred scans: index in the deferred table, or ~0u
-  std::vector<uint32_t> defer_of;
-  uint32_t n_defer, defer_max_tiles, defer_max_L, defer_tiles;
+  uint32_t runs_max_tiles;     // most tiles of a member with record runs; 0: none has any
+  uint32_t adv_lds, adv_tiles; // the advance's LDS bytes (largest member) and tiles (all members)
+  bool direct, big;            // some member scans without record runs; has tiles of 2^kMaxTileShift BDRs
   // learned estimators by member (NULL: plain), owned by the caller
   std::vector<const vbdr_mlp*> mlp;
 };
 
 namespace {
 
-// Device table: [S] BatchDesc, BatchHdr, [n_defer] DeferItem, DeferHdr.
-size_t table_bytes(uint32_t S, uint32_t n_defer) {
-  return sizeof(BatchDesc) * S + sizeof(BatchHdr) + sizeof(DeferItem) * n_defer + sizeof(DeferHdr);
+// Device table: [S] BatchDesc, BatchHdr, [S] DeferItem, DeferHdr.
+size_t table_bytes(uint32_t S) {
+  return sizeof(BatchDesc) * S + sizeof(BatchHdr) + sizeof(DeferItem) * S + sizeof(DeferHdr);
 }
 DeferItem* defer_items(uint8_t* table, uint32_t S) {
   return reinterpret_cast<DeferItem*>(table + sizeof(BatchDesc) * S + sizeof(BatchHdr));
 }
-DeferHdr* defer_hdr(uint8_t* table, uint32_t S, uint32_t n_defer) {
-  return reinterpret_cast<DeferHdr*>(table + sizeof(BatchDesc) * S + sizeof(BatchHdr) + sizeof(DeferItem) * n_defer);
+DeferHdr* defer_hdr(uint8_t* table, uint32_t S) {
+  return reinterpret_cast<DeferHdr*>(table + sizeof(BatchDesc) * S + sizeof(BatchHdr) + sizeof(DeferItem) * S);
 }
 
 int launch_step_kernels(vbdr_batch* bt) {
   const uint32_t grid = (uint32_t)bt->n_cu * bt->tune.blocks_per_cu;
-  hipLaunchKernelGGL(k_batch_scan, dim3(grid), dim3(kBBlock), 0, bt->st, bt->desc_dev, bt->hdr_dev, bt->S,
-                     bt->tune.scan_tile);
-  VBDR_LAUNCHED("k_batch_scan");
+  if (bt->direct) {
+    hipLaunchKernelGGL(k_batch_scan, dim3(grid), dim3(kBBlock), 0, bt->st, bt->desc_dev, bt->hdr_dev, bt->S,
+                       bt->tune.scan_tile);
+    VBDR_LAUNCHED("k_batch_scan");
+  }
   uint8_t* table = reinterpret_cast<uint8_t*>(bt->desc_dev);
   DeferItem* ditems = defer_items(table, bt->S);
-  DeferHdr* dhdr = defer_hdr(table, bt->S, bt->n_defer);
-  if (int rc = vbdr_launch_batch_defer(ditems, dhdr, bt->n_defer, bt->defer_max_tiles, bt->defer_max_L,
-                                       bt->defer_tiles, (uint32_t)bt->n_cu, 0, bt->st))
-    return rc;
-  hipLaunchKernelGGL(k_batch_hist_reset, dim3(bt->S), dim3(64), 0, bt->st, bt->desc_dev);
-  VBDR_LAUNCHED("k_batch_hist_reset");
-  hipLaunchKernelGGL(k_batch_advance, dim3(grid), dim3(kBBlock), 0, bt->st, bt->desc_dev, bt->hdr_dev, bt->S);
-  VBDR_LAUNCHED("k_batch_advance");
-  if (int rc = vbdr_launch_batch_defer(ditems, dhdr, bt->n_defer, bt->defer_max_tiles, bt->defer_max_L,
-                                       bt->defer_tiles, (uint32_t)bt->n_cu, 1, bt->st))
-    return rc;
+  DeferHdr* dhdr = defer_hdr(table, bt->S);
+  for (int phase = 0; phase < 2; ++phase)
+    if (int rc = vbdr_launch_batch_defer(ditems, dhdr, bt->S, bt->runs_max_tiles, bt->adv_lds, bt->adv_tiles, bt->big,
+                                         (uint32_t)bt->n_cu, phase, bt->st))
+      return rc;
   hipLaunchKernelGGL(k_batch_estimate, dim3(grid), dim3(kBBlock), 0, bt->st, bt->desc_dev, bt->hdr_dev, bt->S,
                      bt->tune.est_tile);
   VBDR_LAUNCHED("k_batch_estimate");
@@ -258,6 +206,7 @@ int vbdr_batch_create(uint32_t n_sketches, const vbdr_batch_params* params, vbdr
   bt->tune.blocks_per_cu = 8;
   bt->tune.use_graph = 1;
   int rc = VBDR_OK;
+  uint64_t total_tiles = 0;
   do {
     if (hipGetDevice(&bt->device) != hipSuccess ||
         hipDeviceGetAttribute(&bt->n_cu, hipDeviceAttributeMultiprocessorCount, bt->device) != hipSuccess) {
@@ -269,19 +218,21 @@ int vbdr_batch_create(uint32_t n_sketches, const vbdr_batch_params* params, vbdr
       const vbdr_batch_params& p = params[i];
       if ((rc = vbdr_sketch_create_lean(p.m, p.g, p.k, p.hash_seed, p.layout, true, &s)) != VBDR_OK) break;
       bt->sk.push_back(s);
-      // members with record runs scan and advance through the deferred kernels
       bt->mlp.push_back(nullptr);
-      if (s->def_rec) {
-        bt->defer_of.push_back(bt->n_defer++);
-        bt->defer_max_tiles = bt->defer_max_tiles > s->def_tiles ? bt->defer_max_tiles : s->def_tiles;
-        bt->defer_max_L = bt->defer_max_L > s->L ? bt->defer_max_L : s->L;
-        bt->defer_tiles += s->def_tiles;
-      } else {
-        bt->defer_of.push_back(~0u);
-      }
+      if (!s->def_rec) bt->direct = true;
+      else if (bt->runs_max_tiles < s->def_tiles) bt->runs_max_tiles = s->def_tiles;
+      const uint32_t lds = vbdr_adv_lds(s);
+      bt->adv_lds = bt->adv_lds > lds ? bt->adv_lds : lds;
+      total_tiles += s->tiles;
+      bt->big |= s->tshift == kMaxTileShift;
     }
     if (rc != VBDR_OK) break;
-    const size_t tb = table_bytes(n_sketches, bt->n_defer);
+    if (total_tiles >= (1ull << 31)) {
+      rc = vbdr_fail(VBDR_EINVAL, "the batch's pools have too many tiles");
+      break;
+    }
+    bt->adv_tiles = (uint32_t)total_tiles;
+    const size_t tb = table_bytes(n_sketches);
     if (vbdr_malloc(&bt->desc_dev, tb) != hipSuccess || hipHostMalloc(&bt->staging[0], tb) != hipSuccess ||
         hipHostMalloc(&bt->staging[1], tb) != hipSuccess) {
       rc = vbdr_fail(VBDR_ENOMEM, "batch table allocation failed");
@@ -362,16 +313,15 @@ int vbdr_batch_step(vbdr_batch* bt, const uint32_t* const* pairs_dev, const uint
   VBDR_HIP(hipGetDevice(&cur));
   if (cur != bt->device) return vbdr_fail(VBDR_EINVAL, "batch lives on device %d", bt->device);
   const uint32_t S = bt->S;
-  uint64_t scan_total = 0, adv_total = 0, est_total = 0;
+  uint64_t scan_total = 0, est_total = 0;
   for (uint32_t s = 0; s < S; ++s) {
     if (n_pairs[s] && (!pairs_dev[s] || (reinterpret_cast<uintptr_t>(pairs_dev[s]) & 7u)))
       return vbdr_fail(VBDR_EINVAL, "sketch %u: pairs must be non-NULL and 8-byte aligned", s);
     if (n_hosts[s] && (!hosts_dev[s] || !out_dev[s])) return vbdr_fail(VBDR_EINVAL, "sketch %u: NULL hosts or out", s);
     scan_total += (n_pairs[s] + bt->tune.scan_tile - 1) / bt->tune.scan_tile;
-    adv_total += bt->sk[s]->mstride / kAdvTile;
     est_total += (n_hosts[s] + bt->tune.est_tile - 1) / bt->tune.est_tile;
   }
-  if (scan_total >= (1ull << 31) || adv_total >= (1ull << 31) || est_total >= (1ull << 31))
+  if (scan_total >= (1ull << 31) || est_total >= (1ull << 31))
     return vbdr_fail(VBDR_EINVAL, "too many work items in one step");
   // fill a pinned staging table (wait until its previous upload has run)
   const int buf = bt->next;
@@ -380,20 +330,18 @@ int vbdr_batch_step(vbdr_batch* bt, const uint32_t* const* pairs_dev, const uint
   BatchDesc* desc = reinterpret_cast<BatchDesc*>(bt->staging[buf]);
   BatchHdr* hdr = reinterpret_cast<BatchHdr*>(bt->staging[buf] + sizeof(BatchDesc) * S);
   DeferItem* ditems = defer_items(bt->staging[buf], S);
-  DeferHdr* dhdr = defer_hdr(bt->staging[buf], S, bt->n_defer);
+  DeferHdr* dhdr = defer_hdr(bt->staging[buf], S);
   const uint32_t chunk = vbdr_defer_chunk_pairs();
-  uint32_t si = 0, ai = 0, ei = 0, dsi = 0, dai = 0;
+  uint32_t si = 0, ei = 0, dsi = 0, dai = 0;
   for (uint32_t s = 0; s < S; ++s) {
     const vbdr_sketch* k = bt->sk[s];
-    const uint32_t di = bt->defer_of[s];
-    if (di != ~0u) {  // scanned and advanced by the deferred kernels: no items in the direct ones
-      DeferItem& I = ditems[di];
-      vbdr_defer_member(k, &I);
-      I.pairs = pairs_dev[s], I.n_pairs = n_pairs[s];
-      I.scan_item0 = dsi, I.adv_item0 = dai;
-      dsi += (uint32_t)((n_pairs[s] + chunk - 1) / chunk);
-      dai += k->def_tiles;
-    }
+    const bool runs = k->def_rec != nullptr;  // scanned in chunks, no items in the direct scan
+    DeferItem& I = ditems[s];
+    vbdr_defer_member(k, &I);
+    I.pairs = pairs_dev[s], I.n_pairs = n_pairs[s];
+    I.scan_item0 = dsi, I.adv_item0 = dai;
+    if (runs) dsi += (uint32_t)((n_pairs[s] + chunk - 1) / chunk);
+    dai += k->tiles;
     BatchDesc& D = desc[s];
     D.dr = k->dr, D.seen = k->seen, D.reg = k->reg, D.reg4 = k->reg4, D.hist = k->hist, D.s1 = k->s1;
     D.mstride = k->mstride, D.wstride = k->wstride;
@@ -401,24 +349,21 @@ int vbdr_batch_step(vbdr_batch* bt, const uint32_t* const* pairs_dev, const uint
     D.A1 = k->A1, D.test = k->tune.scan_test_first == 1;
     D.pairs = pairs_dev[s], D.n_pairs = n_pairs[s];
     D.hosts = hosts_dev[s], D.n_hosts = n_hosts[s], D.out = out_dev[s];
-    D.scan_item0 = si, D.adv_item0 = ai, D.est_item0 = ei, D.pad = 0;
+    D.scan_item0 = si, D.est_item0 = ei;
     // members with a learned estimator are estimated after the step's kernels
     const uint64_t n_plain = bt->mlp[s] ? 0 : n_hosts[s];
-    if (di == ~0u) {
-      si += (uint32_t)((n_pairs[s] + bt->tune.scan_tile - 1) / bt->tune.scan_tile);
-      ai += (uint32_t)(k->mstride / kAdvTile);
-    }
+    if (!runs) si += (uint32_t)((n_pairs[s] + bt->tune.scan_tile - 1) / bt->tune.scan_tile);
     ei += (uint32_t)((n_plain + bt->tune.est_tile - 1) / bt->tune.est_tile);
   }
   std::memset(hdr, 0, sizeof(*hdr));
-  hdr->scan_total = si, hdr->adv_total = ai, hdr->est_total = ei;
+  hdr->scan_total = si, hdr->est_total = ei;
   std::memset(dhdr, 0, sizeof(*dhdr));
   dhdr->scan_total = dsi;
   // order after the caller's stream, run on the batch stream, order the caller after it
   hipStream_t user = reinterpret_cast<hipStream_t>(stream);
   VBDR_HIP(hipEventRecord(bt->ev_in, user));
   VBDR_HIP(hipStreamWaitEvent(bt->st, bt->ev_in, 0));
-  VBDR_HIP(hipMemcpyAsync(bt->desc_dev, bt->staging[buf], table_bytes(S, bt->n_defer), hipMemcpyHostToDevice, bt->st));
+  VBDR_HIP(hipMemcpyAsync(bt->desc_dev, bt->staging[buf], table_bytes(S), hipMemcpyHostToDevice, bt->st));
   VBDR_HIP(hipEventRecord(bt->staged[buf], bt->st));
   if (bt->tune.use_graph) {
     if (!bt->exec) {

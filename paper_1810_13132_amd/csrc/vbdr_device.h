@@ -127,30 +127,12 @@ __device__ __forceinline__ double hll_estimate(uint64_t U, uint64_t V, double q)
 
 // ---- per-item bodies shared by the single-sketch and the batched kernels ----
 
-// Scan one pair (Alg. 7 / Alg. 9 with the hashing of Alg. 4 and getPhyIdx of
-// Alg. 3).  Fast layout: set bit pidx of bsLBP1 bit-plane LBP1-1 with a
-// device-scope atomic OR; small layout: store 0 into DR[LBP1] of BDR pidx.
-// TEST: read first and skip an update that is already made.
-template <bool FAST, bool TEST>
-__device__ __forceinline__ void scan_pair(uint32_t aip, uint32_t bip, const uint32_t* s1, uint32_t b, uint32_t A1,
-                                          uint32_t m, uint8_t* dr, uint64_t mstride, uint32_t* seen,
-                                          uint64_t wstride) {
-  uint32_t vidx, rho;
-  bip_map(bip, A1, b, vidx, rho);
-  const uint32_t pidx = reduce_m(mm3(aip, s1[vidx]), m);
-  if constexpr (FAST) {
-    uint32_t* w = seen + (uint64_t)(rho - 1) * wstride + (pidx >> 5);
-    const uint32_t bit = 1u << (pidx & 31);
-    if (!TEST || !(*w & bit)) atomicOr(w, bit);
-  } else {
-    uint8_t* d = dr + (uint64_t)(rho - 1) * mstride + pidx;
-    if (!TEST || *d != 0) *d = 0;
-  }
-}
-
-// scan_pair for N pairs at once (valid where ok[v]): the state words of all N
-// are located first and, with TEST, read together, so that the N random reads
-// overlap instead of each waiting for the one before.
+// Scan N pairs (Alg. 7 / Alg. 9 with the hashing of Alg. 4 and getPhyIdx of
+// Alg. 3), valid where ok[v].  Fast layout: set bit pidx of bsLBP1 bit-plane
+// LBP1-1 with a device-scope atomic OR; small layout: store 0 into DR[LBP1] of
+// BDR pidx.  TEST: read first and skip an update that is already made.  The
+// state words of all N are located first and, with TEST, read together, so
+// that the N random reads overlap instead of each waiting for the one before.
 template <bool FAST, bool TEST, int N>
 __device__ __forceinline__ void scan_pairs(const u32x2* p, const bool* ok, const uint32_t* s1, uint32_t b, uint32_t A1,
                                            uint32_t m, uint8_t* dr, uint64_t mstride, uint32_t* seen,
@@ -183,213 +165,175 @@ __device__ __forceinline__ void scan_pairs(const u32x2* p, const bool* ok, const
   }
 }
 
-// Advance 16 consecutive BDRs starting at `base` (a multiple of 16), planes
-// visited from LBP1 = L down to 1 with a one-plane prefetch.  Fast layout
-// (Alg. 6): slide every DR, zero the DR of the slice's highest LBP1, clear
-// bsLBP1.  Small layout (Alg. 8): slide every DR, the window's register read
-// before the slide.  Register (Alg. 2): the largest LBP1 whose DR is active,
-// DR <= k-1 at the moment the window is read.  R receives the 16 registers
-// (byte j of R[w] = BDR base + 4w + j); they are also stored to reg and reg4.
-// With 16 BDRs per thread, the two threads sharing a bsLBP1 word are
-// adjacent lanes of one wave and both consume it before the even one clears it.
-// With `preg` (small layout), also the PCSA run of each BDR, the number of
-// consecutive active DRs from LBP1 1 (the lowest inactive LBP1 minus 1),
-// stored to preg; P receives the 16 runs like R.
-template <bool FAST>
-__device__ __forceinline__ void advance_group(uint8_t* dr, uint64_t mstride, uint32_t* seen, uint64_t wstride,
-                                              uint8_t* reg, uint8_t* reg4, uint64_t base, uint32_t L,
-                                              uint32_t gt_bias, uint32_t R[4], uint8_t* preg = nullptr,
-                                              uint32_t* P = nullptr) {
-  uint32_t M[4] = {0, 0, 0, 0}, Q[4];
-  R[0] = R[1] = R[2] = R[3] = 0;
-  Q[0] = Q[1] = Q[2] = Q[3] = L * 0x01010101u;
-  uint32_t folded = 0;
-  u32x4 dn = *reinterpret_cast<const u32x4*>(dr + (uint64_t)(L - 1) * mstride + base);
-  uint32_t sn = 0;
-  if constexpr (FAST) sn = seen[(uint64_t)(L - 1) * wstride + (base >> 5)];
-  for (int i = (int)L; i >= 1; --i) {
-    const u32x4 d = dn;
-    const uint32_t s = sn;
-    if (i > 1) {
-      dn = *reinterpret_cast<const u32x4*>(dr + (uint64_t)(i - 2) * mstride + base);
-      if constexpr (FAST) sn = seen[(uint64_t)(i - 2) * wstride + (base >> 5)];
-    }
-    uint32_t fold = 0;
-    if constexpr (FAST) {
-      const uint32_t bits = (s >> (base & 31)) & 0xFFFFu;
-      fold = bits & ~folded;  // only the slice's highest LBP1 is recorded
-      folded |= bits;
-    }
-    // 16 DRs at 255 with no record this slice stay 255 and none is active:
-    // nothing to compute or store (decided from the loaded bytes)
-    if ((d[0] & d[1] & d[2] & d[3]) == ~0u && fold == 0u) {
-      if (!FAST && preg)
+// 4 W consecutive bytes (DRs, registers), four to a word; W = 4 or 8 (2: nibbles of 16).
+template <int W>
+struct DrWords {
+  uint32_t v[W];
+};
+template <int W>
+__device__ __forceinline__ DrWords<W> load_dr(const uint8_t* p) {
+  DrWords<W> d;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) Q[w] = (uint32_t)(i - 1) * 0x01010101u;
-      continue;
-    }
-    u32x4 nd;
+  for (int q = 0; q < W / 4; ++q) {
+    const u32x4 t = *reinterpret_cast<const u32x4*>(p + 16 * q);
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const uint32_t x = d[w];
-      uint32_t y = swar_sat_inc(x);                                                // SlideDR
-      if constexpr (FAST) y &= ~swar_nibble_to_bytes((fold >> (4 * w)) & 0xFu);  // SetDR
-      const uint32_t act = swar_le_mask(FAST ? y : x, gt_bias);                   // IsActiveDR
-      R[w] |= act & ~M[w] & ((uint32_t)i * 0x01010101u);
-      M[w] |= act;
-      if (!FAST && preg) Q[w] = (Q[w] & act) | (~act & ((uint32_t)(i - 1) * 0x01010101u));
-      nd[w] = y;
-    }
-    if ((nd[0] ^ d[0]) | (nd[1] ^ d[1]) | (nd[2] ^ d[2]) | (nd[3] ^ d[3]))  // saturated, unset DRs stay 255
-      *reinterpret_cast<u32x4*>(dr + (uint64_t)(i - 1) * mstride + base) = nd;
+    for (int w = 0; w < 4; ++w) d.v[4 * q + w] = t[w];
   }
-  if (!FAST && preg) {
-    *reinterpret_cast<u32x4*>(preg + base) = u32x4{Q[0], Q[1], Q[2], Q[3]};
+  return d;
+}
+template <int W>
+__device__ __forceinline__ void store_dr(uint8_t* p, const DrWords<W>& d) {
+  if constexpr (W == 2) {
+    *reinterpret_cast<u32x2*>(p) = u32x2{d.v[0], d.v[1]};
+  } else {
 #pragma unroll
-    for (int w = 0; w < 4; ++w) P[w] = Q[w];
+    for (int o = 0; o < W; o += 4)
+      *reinterpret_cast<u32x4*>(p + 4 * o) = u32x4{d.v[o], d.v[o + 1], d.v[o + 2], d.v[o + 3]};
   }
-  if constexpr (FAST) {
-    if ((base & 31) == 0)
-      for (uint32_t i = 0; i < L; ++i) seen[(uint64_t)i * wstride + (base >> 5)] = 0;
-  }
-  *reinterpret_cast<u32x4*>(reg + base) = u32x4{R[0], R[1], R[2], R[3]};
-  uint64_t nib = 0;
+}
+// Store d, vector by vector, where it differs from what was loaded: a
+// saturated DR that was not set this slice stays 255, so most of the high
+// planes, whose DRs are rarely set, are not written back.
+template <int W>
+__device__ __forceinline__ void store_dr_changed(uint8_t* p, const DrWords<W>& d, const DrWords<W>& was) {
 #pragma unroll
-  for (int w = 0; w < 4; ++w) nib |= (uint64_t)swar_pack_nibbles(R[w]) << (16 * w);
-  *reinterpret_cast<uint64_t*>(reg4 + base / 2) = nib;
+  for (int q = 0; q < W / 4; ++q) {
+    const int o = 4 * q;
+    if ((d.v[o] ^ was.v[o]) | (d.v[o + 1] ^ was.v[o + 1]) | (d.v[o + 2] ^ was.v[o + 2]) | (d.v[o + 3] ^ was.v[o + 3]))
+      *reinterpret_cast<u32x4*>(p + 16 * q) = u32x4{d.v[o], d.v[o + 1], d.v[o + 2], d.v[o + 3]};
+  }
 }
 
-// Advance 32 consecutive BDRs starting at `base` (a multiple of 32) as
-// advance_group does, with the slice's LBP1 bits of those BDRs also given as
-// one word per plane, pm[(i - 1) * pm_stride] bit j <-> BDR base + j (the
-// deferred scan records of the tile, gathered in LDS).  Small layout: a set
-// bit means DR[i] was set to 0 during the slice (Alg. 9), so it is zeroed
-// before the slide.  Fast layout: the bits join bsLBP1 (Alg. 7) and the
-// slice's highest LBP1 is set after the slide (Alg. 6).  use_seen: the
-// bsLBP1 bit-planes in memory may hold bits too (fast layout); they are
-// read and cleared.  dn0, dn1: the 32 DRs of plane L, loaded by the caller
-// (so that the load can be issued early).  R receives the 32 registers, byte j
-// of R[w] = BDR base + 4w + j; they are also stored to reg and reg4.
-template <bool FAST>
-__device__ __forceinline__ void advance_group32(uint8_t* dr, uint64_t mstride, uint32_t* seen, uint64_t wstride,
-                                                uint8_t* reg, uint8_t* reg4, uint64_t base, uint32_t L,
-                                                uint32_t gt_bias, const uint32_t* pm, uint32_t pm_stride,
-                                                bool use_seen, u32x4 dn0, u32x4 dn1, uint32_t R[8],
-                                                uint8_t* preg = nullptr, uint32_t* P = nullptr,
-                                                uint32_t* satw = nullptr, uint32_t sat_in = 0u, uint32_t kk = 0u) {
-  uint32_t M[8], Q[8];
+// Advance planes hi down to lo of 4 W consecutive BDRs starting at `base` (a
+// multiple of 4 W); the planes of a BDR may be split over several threads.  The slice's LBP1 bits of those BDRs come as
+// one word per plane, pm[(i - 1) * pm_stride] bit sh + j <-> BDR base + j (the
+// tile's records and bsLBP1 words, gathered in LDS).  Small layout (Alg. 8): a
+// set bit means DR[i] was set to 0 during the slice (Alg. 9), so it is zeroed;
+// the window is read, then the DRs slide.  Fast layout (Alg. 6): every DR
+// slides, then the DR of the slice's highest LBP1 is zeroed and the window is
+// read (folded: the slice's bits of the planes above hi).  Register (Alg. 2):
+// the largest LBP1 whose DR is active, DR <= k-1 at the moment the window is
+// read.  R receives it for these planes, 0 if none is active (byte j of word w
+// = BDR base + 4w + j).  With PCSA (small layout) Q receives the lowest
+// inactive LBP1 of these planes minus 1, 255 if all are active: the least over
+// all planes, at most L, is the run of consecutive active DRs from LBP1 1.
+// G planes are loaded together, one group ahead of the one being processed, in
+// two register buffers (a rotation by copies would wait for the loads just
+// issued).  Bit r-1 of sat_in: these DR[r] were all 255 after the last advance
+// and nothing but the advance has written DRs since; with no record of this
+// slice in that plane they are 255 now and stay 255, so they are neither
+// loaded nor stored.
+template <bool FAST, bool PCSA, int W, int G>
+__device__ __forceinline__ void advance_words(uint8_t* dr, uint64_t mstride, uint64_t base, int hi, int lo,
+                                              uint32_t folded, uint32_t gt_bias, uint32_t kk, const uint32_t* pm,
+                                              uint32_t pm_stride, uint32_t sh, uint32_t sat_in, uint32_t& sat_out,
+                                              DrWords<W>& Rd, DrWords<W>& Qd) {
+  uint32_t(&R)[W] = Rd.v;
+  uint32_t(&Q)[W] = Qd.v;
+  constexpr uint32_t mask = W == 8 ? ~0u : (1u << (4 * (W & 7))) - 1u;
+  uint32_t M[W];
 #pragma unroll
-  for (int w = 0; w < 8; ++w) {
+  for (int w = 0; w < W; ++w) {
     M[w] = R[w] = 0;
-    Q[w] = L * 0x01010101u;
+    Q[w] = ~0u;
   }
-  uint32_t folded = 0;
-  uint32_t sn = 0;
-  if (FAST && use_seen) sn = seen[(uint64_t)(L - 1) * wstride + (base >> 5)];
-  // Loads run ahead of the plane being processed: plane i-2's load is issued
-  // before plane i's work.  The buffers rotate by copies, so the compiler
-  // waits for that load at the end of the step; about one plane is in flight
-  // while a plane is processed.  Deeper lookahead (three planes in fixed
-  // registers, bounded buffer loads and stores) measured the same time: the
-  // sweep is bound by its streams, not by this latency.
-  // Bit r-1 of sat_in: the 32 DR[r] were all 255 after the last advance and
-  // nothing but the advance has written DRs since; with no record of this
-  // slice in that plane they are 255 now and stay 255, so they are neither
-  // loaded nor stored.
-  const u32x4 ff = {~0u, ~0u, ~0u, ~0u};
-  auto skip = [&](int r) -> bool { return ((sat_in >> (r - 1)) & 1u) && pm[(uint32_t)(r - 1) * pm_stride] == 0u; };
-  u32x4 nn0 = ff, nn1 = ff;
-  if (L >= 2 && !skip((int)L - 1)) {
-    const uint8_t* nx = dr + (uint64_t)(L - 2) * mstride + base;
-    nn0 = *reinterpret_cast<const u32x4*>(nx);
-    nn1 = *reinterpret_cast<const u32x4*>(nx + 16);
-  }
-  uint32_t sat_out = 0;
-  for (int i = (int)L; i >= 1; --i) {
-    const u32x4 d0 = dn0, d1 = dn1;
-    const uint32_t s = sn;
-    dn0 = nn0, dn1 = nn1;
-    if (i > 2) {
-      if (skip(i - 2)) {
-        nn0 = ff, nn1 = ff;
+  uint32_t sat = 0;
+  auto bits_of = [&](int r) -> uint32_t { return (pm[(uint32_t)(r - 1) * pm_stride] >> sh) & mask; };
+  auto load_group = [&](int top, DrWords<W>(&d)[G]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+      const int r = top - j;
+      if (r >= lo && !(((sat_in >> (r - 1)) & 1u) && bits_of(r) == 0u)) {
+        d[j] = load_dr<W>(dr + (uint64_t)(r - 1) * mstride + base);
       } else {
-        const uint8_t* nx = dr + (uint64_t)(i - 3) * mstride + base;
-        nn0 = *reinterpret_cast<const u32x4*>(nx);
-        nn1 = *reinterpret_cast<const u32x4*>(nx + 16);
+#pragma unroll
+        for (int w = 0; w < W; ++w) d[j].v[w] = ~0u;
       }
     }
-    if (i > 1 && FAST && use_seen) sn = seen[(uint64_t)(i - 2) * wstride + (base >> 5)];
-    const uint32_t bits = s | pm[(uint32_t)(i - 1) * pm_stride];
-    uint32_t fold = 0;
-    if constexpr (FAST) {
-      fold = bits & ~folded;  // only the slice's highest LBP1 is recorded
-      folded |= bits;
-    }
-    // 32 DRs at 255 with no record this slice stay 255, none is active and
-    // nothing is stored: the SWAR work below is skipped, by whole waves for
-    // most of the high planes.  Decided from the loaded bytes, so it holds
-    // whether or not the saturation masks were trusted.
-    if (bits == 0u && (d0[0] & d0[1] & d0[2] & d0[3] & d1[0] & d1[1] & d1[2] & d1[3]) == ~0u) {
-      sat_out |= 1u << (i - 1);
-      if (!FAST && preg)
+  };
+  auto process = [&](int top, const DrWords<W>(&d)[G]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int w = 0; w < 8; ++w) Q[w] = (uint32_t)(i - 1) * 0x01010101u;  // no active DR: the run restarts below
-      continue;
-    }
-    u32x4 nd0, nd1;
-    if (kk) {  // k <= 128: the active test on bit 7; M holds bit-7 flags of the BDRs whose register is found
+    for (int j = 0; j < G; ++j) {
+      const int i = top - j;
+      if (i < lo) break;
+      const uint32_t bits = bits_of(i);
+      uint32_t fold = 0;
+      if constexpr (FAST) {
+        fold = bits & ~folded;  // only the slice's highest LBP1 is recorded
+        folded |= bits;
+      }
+      // DRs at 255 with no record this slice stay 255, none is active and
+      // nothing is stored: the SWAR work below is skipped, by whole waves for
+      // most of the high planes.  Decided from the loaded bytes, so it holds
+      // whether or not the saturation masks were trusted.
+      uint32_t all = ~0u;
 #pragma unroll
-      for (int w = 0; w < 8; ++w) {
-        uint32_t x = w < 4 ? d0[w] : d1[w - 4];
-        if constexpr (!FAST) x &= ~swar_nibble_to_bytes((bits >> (4 * w)) & 0xFu);  // SetDR of the slice
-        uint32_t y = swar_sat_inc(x);                                                // SlideDR
-        if constexpr (FAST) y &= ~swar_nibble_to_bytes((fold >> (4 * w)) & 0xFu);   // SetDR
-        const uint32_t a7 = swar_lt_bit7(FAST ? y : x, kk);                          // IsActiveDR
-        R[w] += ((a7 & ~M[w]) >> 7) * (uint32_t)i;  // bytes still 0 take i: no carry between bytes
-        M[w] |= a7;
-        if (!FAST && preg) {
-          const uint32_t act = (a7 >> 7) * 0xFFu;
-          Q[w] = (Q[w] & act) | (~act & ((uint32_t)(i - 1) * 0x01010101u));
+      for (int w = 0; w < W; ++w) all &= d[j].v[w];
+      if (bits == 0u && all == ~0u) {
+        sat |= 1u << (i - 1);
+        if (PCSA)
+#pragma unroll
+          for (int w = 0; w < W; ++w) Q[w] = (uint32_t)(i - 1) * 0x01010101u;  // no active DR: the run restarts below
+        continue;
+      }
+      DrWords<W> nd;
+      if (kk) {  // k <= 128: the active test on bit 7; M holds bit-7 flags of the BDRs whose register is found
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+          uint32_t x = d[j].v[w];
+          if constexpr (!FAST) x &= ~swar_nibble_to_bytes((bits >> (4 * w)) & 0xFu);  // SetDR of the slice
+          uint32_t y = swar_sat_inc(x);                                                // SlideDR
+          if constexpr (FAST) y &= ~swar_nibble_to_bytes((fold >> (4 * w)) & 0xFu);   // SetDR
+          const uint32_t a7 = swar_lt_bit7(FAST ? y : x, kk);                          // IsActiveDR
+          R[w] += ((a7 & ~M[w]) >> 7) * (uint32_t)i;  // bytes still 0 take i: no carry between bytes
+          M[w] |= a7;
+          if (PCSA) {
+            const uint32_t act = (a7 >> 7) * 0xFFu;
+            Q[w] = (Q[w] & act) | (~act & ((uint32_t)(i - 1) * 0x01010101u));
+          }
+          nd.v[w] = y;
         }
-        if (w < 4) nd0[w] = y; else nd1[w - 4] = y;
-      }
-    } else {
+      } else {
 #pragma unroll
-      for (int w = 0; w < 8; ++w) {
-        uint32_t x = w < 4 ? d0[w] : d1[w - 4];
-        if constexpr (!FAST) x &= ~swar_nibble_to_bytes((bits >> (4 * w)) & 0xFu);  // SetDR of the slice
-        uint32_t y = swar_sat_inc(x);                                                // SlideDR
-        if constexpr (FAST) y &= ~swar_nibble_to_bytes((fold >> (4 * w)) & 0xFu);   // SetDR
-        const uint32_t act = swar_le_mask(FAST ? y : x, gt_bias);                    // IsActiveDR
-        R[w] |= act & ~M[w] & ((uint32_t)i * 0x01010101u);
-        M[w] |= act;
-        if (!FAST && preg) Q[w] = (Q[w] & act) | (~act & ((uint32_t)(i - 1) * 0x01010101u));
-        if (w < 4) nd0[w] = y; else nd1[w - 4] = y;
+        for (int w = 0; w < W; ++w) {
+          uint32_t x = d[j].v[w];
+          if constexpr (!FAST) x &= ~swar_nibble_to_bytes((bits >> (4 * w)) & 0xFu);  // SetDR of the slice
+          uint32_t y = swar_sat_inc(x);                                                // SlideDR
+          if constexpr (FAST) y &= ~swar_nibble_to_bytes((fold >> (4 * w)) & 0xFu);   // SetDR
+          const uint32_t act = swar_le_mask(FAST ? y : x, gt_bias);                    // IsActiveDR
+          R[w] |= act & ~M[w] & ((uint32_t)i * 0x01010101u);
+          M[w] |= act;
+          if (PCSA) Q[w] = (Q[w] & act) | (~act & ((uint32_t)(i - 1) * 0x01010101u));
+          nd.v[w] = y;
+        }
       }
+      store_dr_changed<W>(dr + (uint64_t)(i - 1) * mstride + base, nd, d[j]);
+      all = ~0u;
+#pragma unroll
+      for (int w = 0; w < W; ++w) all &= nd.v[w];
+      if (all == ~0u) sat |= 1u << (i - 1);
     }
-    // a saturated DR that was not set this slice stays 255: vectors that did not
-    // change are not written back (most of the high planes, whose DRs are rarely set)
-    uint8_t* out = dr + (uint64_t)(i - 1) * mstride + base;
-    if ((nd0[0] ^ d0[0]) | (nd0[1] ^ d0[1]) | (nd0[2] ^ d0[2]) | (nd0[3] ^ d0[3])) *reinterpret_cast<u32x4*>(out) = nd0;
-    if ((nd1[0] ^ d1[0]) | (nd1[1] ^ d1[1]) | (nd1[2] ^ d1[2]) | (nd1[3] ^ d1[3]))
-      *reinterpret_cast<u32x4*>(out + 16) = nd1;
-    if ((nd0[0] & nd0[1] & nd0[2] & nd0[3] & nd1[0] & nd1[1] & nd1[2] & nd1[3]) == ~0u) sat_out |= 1u << (i - 1);
+  };
+  DrWords<W> a[G], b[G];
+  load_group(hi, a);
+  for (int top = hi; top >= lo; top -= 2 * G) {
+    load_group(top - G, b);
+    process(top, a);
+    if (top - G < lo) break;
+    load_group(top - 2 * G, a);
+    process(top - G, b);
   }
-  if (satw) *satw = sat_out;  // always: sat_in is 0 when the stored masks were stale
-  if (FAST && use_seen)
-    for (uint32_t i = 0; i < L; ++i) seen[(uint64_t)i * wstride + (base >> 5)] = 0;
-  *reinterpret_cast<u32x4*>(reg + base) = u32x4{R[0], R[1], R[2], R[3]};
-  *reinterpret_cast<u32x4*>(reg + base + 16) = u32x4{R[4], R[5], R[6], R[7]};
-  if (!FAST && preg) {
-    *reinterpret_cast<u32x4*>(preg + base) = u32x4{Q[0], Q[1], Q[2], Q[3]};
-    *reinterpret_cast<u32x4*>(preg + base + 16) = u32x4{Q[4], Q[5], Q[6], Q[7]};
+  sat_out = sat;
+}
+
+// The registers of 4 W BDRs as nibbles min(r, 15).
+template <int W>
+__device__ __forceinline__ void store_nibbles(uint8_t* reg4, uint64_t base, const DrWords<W>& R) {
+  DrWords<W / 2> nib;
 #pragma unroll
-    for (int w = 0; w < 8; ++w) P[w] = Q[w];
-  }
-  u32x4 nib;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) nib[q] = swar_pack_nibbles(R[2 * q]) | (swar_pack_nibbles(R[2 * q + 1]) << 16);
-  *reinterpret_cast<u32x4*>(reg4 + base / 2) = nib;
+  for (int q = 0; q < W / 2; ++q)
+    nib.v[q] = swar_pack_nibbles(R.v[2 * q]) | (swar_pack_nibbles(R.v[2 * q + 1]) << 16);
+  store_dr<W / 2>(reg4 + base / 2, nib);
 }
 
 // Sum of the four bytes of x when it is below 256.
@@ -410,6 +354,15 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
 __device__ __forceinline__ double noise_removed(double Es, double Em, double m, double g) {
 #pragma clang fp contract(off)
   return (m * Es - g * Em) / (m - g);
+}
+
+// A sketch's pool statistics (kStatWords uint64): the register histogram of
+// the last closed window, its E_m (bits of a double) and the sum of all
+// registers; then the running sums of an advance in flight and its count of
+// finished workgroups, zero between advances.
+constexpr int kStatEm = 33, kStatSum = 34, kStatAcc = 64, kStatTicket = kStatAcc + kBins, kStatWords = 128;
+__device__ __forceinline__ double stat_em(const unsigned long long* stats) {
+  return __longlong_as_double((long long)stats[kStatEm]);
 }
 
 // E_m: the HyperLogLog estimate over all m registers from their histogram.

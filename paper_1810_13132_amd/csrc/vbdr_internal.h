@@ -16,10 +16,16 @@ constexpr uint32_t kLearnChunk = 1u << 15;  // hosts per histogram pass of the l
 constexpr uint64_t kBinMaxM = 1ull << 27;   // binned scan records pack (pidx << 5) | (LBP1 - 1)
 constexpr uint32_t kBinChunk = 1u << 24;    // pairs per binned-scan pass (records stay cache resident)
 constexpr uint32_t kBinCap = kBinChunk / 8 + kBinChunk / 32 + 65536;  // records per bin per pass
-constexpr uint32_t kDeferTile = 1u << 15;   // BDRs per deferred-apply tile (one advance workgroup)
+// BDRs per tile (one advance workgroup of 1024 threads): 2^12 .. 2^15
+constexpr uint32_t kMinTileShift = 12, kMaxTileShift = 15;
+constexpr uint64_t kDeferMinM = 1ull << 16;       // pools that keep record runs (fast layout, batch members)
+constexpr uint64_t kDeferMinSmall = 1ull << 19;   // the same, small layout
 constexpr uint32_t kDeferSlots = 2;         // record slots per BDR per slice before the direct fallback, at least
 constexpr uint64_t kDeferBudget = 1ull << 27;  // record slots of a sketch where its pool needs fewer per BDR
 constexpr uint32_t kDeferSlotsMax = 16;
+constexpr uint64_t kDeferLeast = 1ull << 22;   // record slots of a sketch, at least
+// Pairs of a scan up to which pools below 2^22 BDRs are updated directly.
+constexpr uint64_t kDirectSmall = 1ull << 20, kDirectFast = 1ull << 16;
 
 struct vbdr_sketch {
   int device;
@@ -35,7 +41,7 @@ struct vbdr_sketch {
   uint32_t z, Lc;                 // packed layout: bits per DR, recorders per BDR (else 8 and L)
   uint32_t* seen;
   uint8_t* reg;
-  unsigned long long* hist;
+  unsigned long long* hist;       // pool statistics (kStatWords words)
   uint32_t* s1;
   uint8_t* reg4;               // registers as nibbles, min(reg, 15); 15 = read reg
   int parts;                   // XCD partitions of the estimate (1 = direct gather)
@@ -65,9 +71,10 @@ struct vbdr_sketch {
   uint32_t* sat;                  // deferred scans: [wstride] bit r-1 = DR[r] of all 32 BDRs saturated (255, or 2^z - 1)
   unsigned long long* def_fill;   // [def_tiles + 1] records per tile; the last word flags direct updates
   uint32_t def_tiles, def_cap;
+  uint32_t tshift, tiles;         // the advance's tiles: 2^tshift BDRs, tiles of them (def_tiles of them have record runs)
   bool lean;                      // no optional workspaces (sketches owned by a batch)
   uint8_t* preg;                  // small layout, on request: PCSA run of each BDR, last closed window
-  unsigned long long* psum;       // sum of preg over the pool
+  unsigned long long* psum;       // sum of preg over the pool, then the running sum of an advance in flight
   bool pcsa_valid;                // preg was written by an advance since it was enabled
   uint64_t bytes;                 // device bytes held: the window state plus every workspace
   uint64_t state_only;            // of which the window state: DRs, bsLBP1, registers, masks, seeds, PCSA runs
@@ -79,27 +86,37 @@ struct vbdr_sketch {
 int vbdr_sketch_create_lean(uint64_t m, uint32_t g, uint32_t k, uint64_t hash_seed, int layout, bool defer,
                             vbdr_sketch** out);
 
-// A batch member whose scans defer their updates, as the batch's deferred
-// scan and advance kernels read it from device memory.  pairs, n_pairs and
-// scan_item0 change every step; the rest is the sketch's.
+// What the advance of one sketch works on (a kernel argument, or an entry of
+// a batch's table).  Without record runs (recs, fill and sat NULL) the bsLBP1
+// planes hold the whole slice.
+struct AdvSketch {
+  uint8_t* dr;
+  uint32_t* seen;  // fast layout, else NULL
+  uint8_t* reg;
+  uint8_t* reg4;
+  uint8_t* preg;   // PCSA runs, or NULL
+  unsigned long long* psum;
+  unsigned long long* stats;
+  const uint32_t* recs;
+  unsigned long long* fill;
+  uint32_t* sat;   // tiles of 2^14 BDRs and more, else NULL
+  uint64_t mstride, wstride, m;
+  uint32_t L, thr, cap, tiles, tshift, layout;
+};
+
+// A batch member as the batch's scan and advance kernels read it from device
+// memory.  pairs, n_pairs and scan_item0 change every step; the rest is the
+// sketch's.  Members without record runs have no scan items here.
 constexpr uint32_t kMaxDeferMembers = 256;
 struct DeferItem {
+  AdvSketch adv;
   const uint32_t* pairs;
   uint64_t n_pairs;
   const uint32_t* s1;
-  uint8_t* dr;
-  uint32_t* seen;
-  uint8_t* reg;
-  uint8_t* reg4;
-  unsigned long long* hist;
   uint32_t* recs;
-  unsigned long long* fill;
-  uint32_t* sat;
-  uint64_t mstride, wstride, m;
-  uint32_t b, A1, tiles, cap, L, thr, layout;
+  uint32_t b, A1;
   uint32_t scan_item0;  // first scan item (chunk) of the member this step
   uint32_t adv_item0;   // first advance item (tile) of the member
-  uint32_t pad;
 };
 struct DeferHdr {
   uint32_t scan_total;  // scan items of the step
@@ -108,12 +125,16 @@ struct DeferHdr {
 
 // The sketch's fields of its DeferItem (pairs, n_pairs and the item offsets zero).
 void vbdr_defer_member(const vbdr_sketch* sk, DeferItem* d);
-// Pairs per scan item of a deferred member.
+// Pairs per scan item of a member with record runs.
 uint32_t vbdr_defer_chunk_pairs();
-// Phase 0: the deferred members' scans (grid workgroups over hdr->scan_total
-// items); phase 1: their advances (adv_total tiles) and the flag reset.
+// Phase 0: the scans of members with record runs (grid workgroups over
+// hdr->scan_total items; max_tiles of them at most, 0: none); phase 1: the
+// advances of all members (adv_total tiles, adv_lds bytes of bit words; big:
+// some member's tiles are of 2^kMaxTileShift BDRs).
 int vbdr_launch_batch_defer(const DeferItem* items_dev, const DeferHdr* hdr_dev, uint32_t S, uint32_t max_tiles,
-                            uint32_t max_L, uint32_t adv_total, uint32_t grid, int phase, hipStream_t st);
+                            uint32_t adv_lds, uint32_t adv_total, bool big, uint32_t grid, int phase, hipStream_t st);
+// LDS bytes of a sketch's advance.
+uint32_t vbdr_adv_lds(const vbdr_sketch* sk);
 
 constexpr uint64_t kPackedMaxM = 1ull << 26;  // packed pools: records' tiles must fit the deferred scan's LDS
 

@@ -139,7 +139,7 @@ __global__ __launch_bounds__(kInfBlock) __attribute__((amdgpu_waves_per_eu(5))) 
     senv_hi[threadIdx.x] = mlp->has_env ? mlp->env_hi[threadIdx.x] : INFINITY;
   }
   if (threadIdx.x == 0) {
-    sem = pool_estimate(hist, (double)m);
+    sem = stat_em(hist);
     spool_bad = 0;
   }
   if constexpr (DIRECT)

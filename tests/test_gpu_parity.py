@@ -596,6 +596,41 @@ def test_record_runs_at_their_capacity(V, O, layout):
         assert_state_equal(sk.state(), osk.state(), layout, f"runs of {sizes}")
 
 
+@pytest.mark.parametrize("layout", ["fast", "small"])
+@pytest.mark.parametrize("m,g,k", [((1 << 16) - 1, 64, 3), (1 << 16, 65536 // 64, 200), ((1 << 18) + 4097, 256, 2),
+                                   ((1 << 20) - 7, 128, 129), ((1 << 20) + 1, 2, 128), ((1 << 21) + 9, 512, 254),
+                                   ((1 << 22) - 1, 1024, 1)])
+def test_tile_sizes_and_scan_routes(V, O, layout, m, g, k):
+    """Pools at the edges of the advance's tile sizes (2^12 BDRs up to 2^20, then
+    2^13 and 2^14; planes of a tile split over 4, 2 and 1 threads), of the
+    record runs' range and of both active tests (k up to 128 and above).  One
+    slice mixes scans that update the pool directly and scans through records;
+    the sizes sit at the chunks' edges (4096 pairs times powers of two).
+    State after every slice against the oracle, PCSA runs included."""
+    rng = np.random.default_rng(m % 1000 + g)
+    aips = rng.integers(0, 2**32, 3000, dtype=np.uint64).astype(np.uint32)
+    sk = V.Sketch(m, g, k, 13, layout)
+    if layout == "small":
+        sk.enable_pcsa()
+    osk = O.Sketch(m, g, k, 13, LAYOUT_CODE[layout])
+    for sizes in ((1, 1 << 16, (1 << 16) + 1), ((1 << 20) + 1,), (0,), (4097, (1 << 17) - 1)):
+        for n in sizes:
+            p_ = np.stack([aips[rng.integers(0, len(aips), n)],
+                           rng.integers(0, 2**32, n, dtype=np.uint64).astype(np.uint32)], 1).astype(np.uint32)
+            sk.scan_slice(_dev(V, p_.reshape(-1)))
+            osk.scan(p_)
+        sk.advance_slice()
+        osk.advance()
+        st = osk.state()
+        assert_state_equal(sk.state(), st, layout, f"{sizes}")
+        if layout == "small":  # a run: active DRs (<= k-1 before the slide, <= k after) from LBP1 1 on
+            act = st["dr"] <= k
+            run = np.cumprod(act, axis=1).sum(1)
+            assert np.array_equal(sk.pcsa_registers(), run.astype(np.uint8)), sizes
+    hosts = aips[:300]
+    assert_estimates_close(V, O, sk, osk, hosts)
+
+
 def test_bad_arguments_on_device(V):
     sk = V.Sketch(5000, 16, 3, 1, "small")
     pairs = torch.zeros(8, dtype=torch.int32, device="cuda")
