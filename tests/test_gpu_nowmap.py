@@ -73,6 +73,49 @@ def test_replicas_merge_to_one_sketch(V, O, m):
     assert all(torch.equal(sk.estimate(hd), e0) for sk in reps[1:])
 
 
+@pytest.mark.parametrize("off", [0, 1])
+@pytest.mark.parametrize("m", [5001, (1 << 18) + 3, (1 << 20) + 5, (1 << 22) + 1, (1 << 23) + 4099])
+def test_map_round_trips(V, O, m, off):
+    """Export and import at every tile size, with maps at aligned and odd
+    addresses: the scanned slice's map, then maps imported over pending
+    records, over planes that hold bits and after an advance that emptied
+    them come back as they are (entries above L set nothing), and the
+    advance after them gives the registers of the maps."""
+    g, seed, k = 64, 5, 2
+    rng = np.random.default_rng(m)
+    sk = V.Sketch(m, g, k, seed, "fast")
+    buf = torch.zeros(m + 16, dtype=torch.uint8, device="cuda")[off:off + m]
+    n = 90_000
+    pairs = rng.integers(0, 2**32, (n, 2), dtype=np.uint64).astype(np.uint32)
+    sk.scan_slice(V.to_device_u32(pairs.reshape(-1)))
+    ref = _now_ref(O, m, g, seed, pairs)
+    assert np.array_equal(sk.export_now(buf).cpu().numpy(), ref)
+    regs = []
+    for step in range(4):
+        now = (rng.geometric(0.5, m) - 1).clip(0, sk.L).astype(np.uint8)
+        now[rng.integers(0, m, 5)] = sk.L + 1  # sets nothing
+        buf.copy_(torch.from_numpy(now))
+        sk.import_now(buf)
+        want = np.where(now > sk.L, 0, now).astype(np.uint8)
+        assert np.array_equal(sk.export_now(buf).cpu().numpy(), want), step
+        if step >= 1:
+            sk.advance_slice()
+            regs.append(want)
+            assert np.array_equal(sk.registers()[0], np.max(regs[-k:], axis=0)), step
+
+
+@pytest.mark.parametrize("n,off", [(1, 0), (15, 0), (16, 3), (4099, 0), (100_001, 1), (1 << 20, 0)])
+def test_now_max_sizes_and_alignment(V, n, off):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    a = torch.randint(0, 256, (n + 16,), dtype=torch.uint8, device="cuda", generator=g)[:n]
+    b = torch.randint(0, 256, (n + 16,), dtype=torch.uint8, device="cuda", generator=g)[off:off + n]
+    assert torch.equal(V.now_max(a, b), torch.maximum(a, b))
+    want = torch.maximum(a, b)
+    V.now_max(a, b, out=a)  # the result may take an input's place
+    assert torch.equal(a, want)
+
+
 def test_small_layout_rejects_maps(V):
     sk = V.Sketch(5000, 16, 3, 1, "small")
     with pytest.raises(V.VbdrError):
