@@ -84,7 +84,8 @@ typedef struct vbdr_info {
     uint64_t t;           /* slices closed so far */
     uint64_t state_bytes; /* device bytes held by the sketch: window_state_bytes + workspace_bytes */
     int32_t est_parts;    /* pool ranges of the estimate's XCD-partitioned gathers (1 = direct) */
-    int32_t scan_deferred; /* 1 when scans defer their updates to the advance (scan_defer = 1) */
+    int32_t scan_deferred; /* 1 when all scans defer their updates to the advance (scan_defer = 1; pools of
+                              2^16 up to 2^22 BDRs decide by the size of the scan) */
     uint32_t Lc;          /* recorders per BDR (L except for the packed layout) */
     uint32_t dr_bits;     /* bits per DR: 8, or z for the packed layout */
     int32_t est_tiled;    /* 1 when plain estimates take the LDS-tiled path (est_binned = 3, eligible pool) */
@@ -155,11 +156,11 @@ int vbdr_estimate_ex(vbdr_sketch *sk, const uint32_t *hosts_dev, uint64_t n_host
  * vbdr_estimate for callers that cannot allocate device memory or touch the
  * sketch's estimate workspaces: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same arguments and the same
- * results as vbdr_estimate, bit for bit.  Pools of 2^22 BDRs and more take
+ * results as vbdr_estimate, bit for bit.  Pools of more than 2^23 BDRs take
  * the XCD-partitioned estimate with its per-range partial sums in a static
  * device array of the library (6 MiB; each device the library runs on holds
- * its own until the process ends), 65536 hosts per pass; smaller pools take
- * the direct estimate, which needs no scratch memory.  The array's device
+ * its own until the process ends), 65536 hosts per pass; smaller pools and few
+ * hosts take the direct estimate, which needs no scratch memory.  The array's device
  * address is looked up on the first call on each device; no call allocates.
  * Every call on one device shares that device's array: two calls that
  * overlap in time on one device (any sketches, any streams) race and give
@@ -251,15 +252,17 @@ int vbdr_sketch_info(const vbdr_sketch *sk, vbdr_info *out);
  *                      (default: 2);
  *   est_binned         for pools of 2^22 BDRs and more: 1 = hash every
  *                      (host, i) once and bin the gathers by XCD range;
- *                      2 = hash on every XCD and gather only the own range;
+ *                      2 = gather from the L2s, directly or (nibbles of more
+ *                      than 4 MB) hashing on 2 to 8 XCDs and gathering only the
+ *                      own range;
  *                      3 = hash every (host, i) once into runs per tile of
  *                      at most 2^18 registers, gather every register from a
  *                      tile held in LDS, add per-tile sums (pools of at most
  *                      2^26 BDRs, 64 <= g <= 8192; elsewhere 3 acts as 2)
- *                      (default: 3 for pools of 2^24 BDRs and more, else 2);
- *   est_parts          pool ranges of the XCD-partitioned estimate, 8 (one
- *                      per XCD, default) or 4 (two XCDs per range: half the
- *                      hashing, twice the cache footprint per XCD);
+ *                      (default: 3 for pools of 2^24 BDRs and more, for
+ *                      estimates of some 10^7 register gathers and more; else 2);
+ *   est_parts          pool ranges of the XCD-partitioned estimate at most, 8
+ *                      (default) or 4; it takes as few as its caches allow;
  *   est_bin_hosts      hosts per pass of the binned estimate (its gather
  *                      runs take about 4*g bytes per host; default: as many
  *                      as the run buffer holds); for the tiled estimate,

@@ -30,10 +30,8 @@
 
 using namespace vbdr;
 
-// Pools from 2^24 BDRs take the LDS-tiled estimate by default (measured at
-// m = 2^26, g = 1024: tiled 1.65 ms, partitioned 2.39 ms; at m = 2^24,
-// g = 2048: tiled 0.60 ms, partitioned 0.80 ms).  Below, the partitioned
-// gather's per-XCD ranges are at most 512 KB and stay in the L2s.
+// Pools from 2^24 BDRs keep the workspaces of the LDS-tiled estimate by
+// default and use it for estimates of many hosts (kTileMinGathers).
 constexpr uint64_t kTileDefaultMinM = 1ull << 24;
 
 static vbdr_tuning default_tuning(int layout, uint64_t m) {
@@ -977,6 +975,37 @@ __global__ __launch_bounds__(kEstBlock) void k_estimate(const uint32_t* __restri
   }
 }
 
+// The direct estimate without extra outputs (g up to kStageMaxG, estimate_hosts).
+// TABLE: workgroups of 1024 threads that keep the first tab_n registers' nibbles
+// in LDS, all of them for pools of up to about 2^18 BDRs: an LDS gather costs
+// a tenth of an L2 tag lookup.  Otherwise every gather is an L2 request (at most
+// about 2.5e11 a second).  STAGE: seeds in LDS (many hosts a workgroup).
+constexpr int kRowBlock = 256, kTabBlock = 1024;
+template <int LPH, bool TABLE, bool STAGE>
+__global__ __launch_bounds__(TABLE ? kTabBlock : kRowBlock) void k_estimate_rows(
+    const uint32_t* __restrict__ hosts, uint64_t nh, uint32_t per_wave, const uint32_t* __restrict__ s1g, uint32_t g,
+    uint32_t m, const uint8_t* __restrict__ reg, const uint8_t* __restrict__ reg4, uint32_t tab_n,
+    const unsigned long long* __restrict__ stats, float* __restrict__ out) {
+  extern __shared__ uint32_t lds[];
+  uint32_t* tab = lds;
+  uint32_t* s1l = lds + (TABLE ? tab_n / 8 : 0);
+  constexpr int kBlock = TABLE ? kTabBlock : kRowBlock, kWaves = kBlock / 64;
+  if constexpr (TABLE) {  // tab_n: a multiple of 32 registers
+    const u32x4* src = reinterpret_cast<const u32x4*>(reg4);
+    for (uint32_t q = threadIdx.x; q < tab_n / 32; q += kBlock) reinterpret_cast<u32x4*>(tab)[q] = src[q];
+  }
+  if constexpr (STAGE)
+    for (uint32_t i = threadIdx.x; i < g; i += kBlock) s1l[i] = s1g[i];
+  if constexpr (TABLE || STAGE) __syncthreads();
+  const double Em = stat_em(stats);
+  const uint64_t wave = (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6), step = (uint64_t)gridDim.x * kWaves * per_wave;
+  for (uint64_t h = wave * per_wave; h < nh; h += step) {
+    const uint32_t n = nh - h < per_wave ? (uint32_t)(nh - h) : per_wave;
+    estimate_hosts<LPH, TABLE>(hosts + h, n, STAGE ? s1l : s1g, g, m, reg, reg4,
+                               reinterpret_cast<const uint8_t*>(tab), tab_n, Em, out + h);
+  }
+}
+
 // ------------------------------------------- estimate, XCD-partitioned
 // The register array of a large pool does not fit one XCD's L2, so direct
 // gathers pull a whole line from the memory side per byte used.  Here the
@@ -1066,6 +1095,33 @@ __global__ __launch_bounds__(kEstBlock) void k_estimate_part(const uint32_t* __r
         part_u[(uint64_t)x * pstride + h] = U;
         part_v[(uint64_t)x * pstride + h] = V;
       }
+    }
+  }
+}
+
+// The same for g <= kStageMaxG without histograms, 16 lanes a host.
+__global__ __launch_bounds__(kRowBlock) void k_estimate_part_rows(const uint32_t* __restrict__ hosts, uint32_t nh,
+                                                                  uint32_t per_wave, const uint32_t* __restrict__ s1g,
+                                                                  uint32_t g, uint32_t m,
+                                                                  const uint8_t* __restrict__ reg,
+                                                                  const uint8_t* __restrict__ reg4, uint32_t parts,
+                                                                  uint32_t part_shift,
+                                                                  unsigned long long* __restrict__ part_u,
+                                                                  uint32_t* __restrict__ part_v, uint32_t pstride) {
+  extern __shared__ uint32_t lds[];
+  for (uint32_t i = threadIdx.x; i < g; i += kRowBlock) lds[i] = s1g[i];
+  __syncthreads();
+  const uint32_t x = blockIdx.x % parts, lane = threadIdx.x & 63;
+  const uint32_t wave = (blockIdx.x / parts) * (kRowBlock / 64) + (threadIdx.x >> 6);
+  const uint32_t step = gridDim.x / parts * (kRowBlock / 64) * per_wave;
+  for (uint32_t h = wave * per_wave; h < nh; h += step) {
+    const uint32_t n = nh - h < per_wave ? nh - h : per_wave;
+    uint64_t U;
+    uint32_t V;
+    gather_hosts<16, false, true>(hosts + h, n, lds, g, m, reg, reg4, nullptr, 0u, x, part_shift, U, V);
+    if (lane < n) {
+      part_u[(uint64_t)x * pstride + h + lane] = U;
+      part_v[(uint64_t)x * pstride + h + lane] = V;
     }
   }
 }
@@ -2309,28 +2365,88 @@ int create_sketch(uint64_t m, uint32_t g, uint32_t k, uint64_t hash_seed, int la
 
 namespace {
 
+// Pool ranges of the XCD-partitioned gathers: as few as let a range's nibbles
+// fit one XCD's L2 (4 MB), since every range hashes every (host, i).
+uint32_t gather_parts(const vbdr_sketch* sk) {
+  uint32_t p = 1;
+  while (p < 8u && (sk->mstride / 2) / p > kRangeBytes) p *= 2;
+  const uint32_t most = (uint32_t)(sk->parts == 8 ? sk->tune.est_parts : sk->parts);
+  return p < most ? p : most;
+}
+
 // The XCD-partitioned estimate: hosts in chunks of pstride, per-range partial
 // sums in part_u / part_v ([parts][pstride] each), then the FP64 epilogue.
 int estimate_partitioned(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_hosts, float* out_dev,
                          unsigned long long* part_u, uint32_t* part_v, uint32_t pstride, hipStream_t st) {
   const bool stage = sk->g <= kStageMaxG;
   const size_t lds = stage ? (size_t)sk->g * 4 : 0;
-  const uint32_t parts = (uint32_t)(sk->parts == 8 ? sk->tune.est_parts : sk->parts);
-  const uint32_t shift = parts == 8 ? 29u : 30u;
-  auto kern = stage ? k_estimate_part<true, false> : k_estimate_part<false, false>;
+  const uint32_t parts = gather_parts(sk);
+  uint32_t shift = 32;
+  while ((1u << (32 - shift)) < parts) --shift;
   for (uint64_t c = 0; c < n_hosts; c += pstride) {
     const uint32_t nh = (uint32_t)(n_hosts - c < pstride ? n_hosts - c : pstride);
-    const uint64_t want = (nh + kEstWaves - 1) / kEstWaves;
     const uint64_t cap = (uint64_t)sk->n_cu * sk->tune.est_blocks_per_cu / parts;
-    const uint32_t tiles = (uint32_t)(want < cap ? want : (cap ? cap : 1));
-    hipLaunchKernelGGL(kern, dim3(tiles * parts), dim3(kEstBlock), lds, st, hosts_dev + c, nh, sk->s1, sk->g,
-                       (uint32_t)sk->m, sk->reg, sk->reg4, parts, shift, part_u, part_v, pstride, nullptr);
-    VBDR_LAUNCHED("k_estimate_part");
+    if (stage) {
+      const uint64_t waves = (uint64_t)sk->n_cu * 32 / parts;  // in flight on one range's CUs
+      const uint64_t per = ((nh + waves - 1) / waves + 3) / 4 * 4;
+      const uint32_t per_wave = (uint32_t)(per > 64 ? 64 : per);
+      const uint64_t want = ((nh + per_wave - 1) / per_wave + kRowBlock / 64 - 1) / (kRowBlock / 64);
+      const uint32_t tiles = (uint32_t)(want < cap ? want : (cap ? cap : 1));
+      hipLaunchKernelGGL(k_estimate_part_rows, dim3(tiles * parts), dim3(kRowBlock), lds, st, hosts_dev + c, nh,
+                         per_wave, sk->s1, sk->g, (uint32_t)sk->m, sk->reg, sk->reg4, parts, shift, part_u, part_v,
+                         pstride);
+      VBDR_LAUNCHED("k_estimate_part_rows");
+    } else {
+      const uint64_t want = (nh + kEstWaves - 1) / kEstWaves;
+      const uint32_t tiles = (uint32_t)(want < cap ? want : (cap ? cap : 1));
+      hipLaunchKernelGGL((k_estimate_part<false, false>), dim3(tiles * parts), dim3(kEstBlock), 0, st, hosts_dev + c, nh,
+                         sk->s1, sk->g, (uint32_t)sk->m, sk->reg, sk->reg4, parts, shift, part_u, part_v, pstride,
+                         nullptr);
+      VBDR_LAUNCHED("k_estimate_part");
+    }
     hipLaunchKernelGGL(k_estimate_final, dim3((nh + 255) / 256), dim3(256), 0, st, nh, sk->g, (uint32_t)sk->m, parts,
                        sk->hist, part_u, part_v, pstride, (const unsigned long long*)nullptr, (const uint32_t*)nullptr,
                        out_dev + c);
     VBDR_LAUNCHED("k_estimate_final");
   }
+  return VBDR_OK;
+}
+
+// Estimates gathered from L2 (or memory): directly where the nibbles fit one
+// XCD's L2 or there are too few gathers for it to matter, else partitioned.
+bool gathers_direct(const vbdr_sketch* sk, uint64_t n_hosts) {
+  return gather_parts(sk) == 1 || n_hosts * sk->g < kPartMinGathers;
+}
+
+// LDS bytes of k_estimate_rows.
+constexpr size_t kRowsLds = 152u << 10;
+
+// The direct estimate without extra outputs, g <= kStageMaxG.
+int estimate_rows(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_hosts, float* out_dev, hipStream_t st) {
+  const uint32_t g = sk->g;
+  // 16 lanes a host once that fills the CUs with waves; a wave a host below
+  const uint64_t fill = (uint64_t)sk->n_cu * (kTabBlock / 64);
+  const bool rows = n_hosts >= fill;
+  // a table in LDS pays where it holds a good part of the registers and a CU gathers more than it loads
+  uint64_t tab = (kRowsLds - (size_t)g * 4) * 2 / 32 * 32;
+  if (tab > sk->mstride) tab = sk->mstride;
+  const bool table = sk->m <= kTableMaxM && n_hosts * g >= tab * kTableMinUse;
+  const uint32_t waves = table ? kTabBlock / 64 : kRowBlock / 64;
+  const uint32_t least = rows ? 4 : 1;
+  const uint64_t cap_waves = (uint64_t)sk->n_cu * (table ? kTabBlock / 64 : 2048 / 64);
+  uint64_t per = (n_hosts + cap_waves - 1) / cap_waves;
+  per = (per + least - 1) / least * least;
+  const uint32_t per_wave = (uint32_t)(per < least ? least : per > 64 ? 64 : per);
+  const uint64_t want = ((n_hosts + per_wave - 1) / per_wave + waves - 1) / waves;
+  const uint32_t grid = (uint32_t)(want < cap_waves / waves ? want : cap_waves / waves);
+  const bool stage = table || per_wave * waves >= 16;
+  const size_t lds = (table ? tab / 2 : 0) + (stage ? (size_t)g * 4 : 0);
+  const auto kern = table ? (rows ? k_estimate_rows<16, true, true> : k_estimate_rows<64, true, true>)
+                  : stage ? (rows ? k_estimate_rows<16, false, true> : k_estimate_rows<64, false, true>)
+                          : k_estimate_rows<64, false, false>;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(table ? kTabBlock : kRowBlock), lds, st, hosts_dev, n_hosts, per_wave,
+                     sk->s1, g, (uint32_t)sk->m, sk->reg, sk->reg4, (uint32_t)tab, sk->hist, out_dev);
+  VBDR_LAUNCHED("k_estimate_rows");
   return VBDR_OK;
 }
 
@@ -2340,6 +2456,7 @@ int estimate_direct(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_hosts
                     uint32_t* hist_dev, hipStream_t st) {
   const bool stage = sk->g <= kStageMaxG;
   const bool extra = raw_es_dev || hist_dev;
+  if (stage && !extra) return estimate_rows(sk, hosts_dev, n_hosts, out_dev, st);
   const size_t lds = stage ? (size_t)sk->g * 4 : 0;
   const uint32_t grid = grid_cap(sk, (n_hosts + kEstWaves - 1) / kEstWaves, sk->tune.est_blocks_per_cu);
   auto kern = stage ? (extra ? k_estimate<true, true> : k_estimate<true, false>)
@@ -2429,6 +2546,7 @@ int vbdr_sketch_set_tuning(vbdr_sketch* sk, const vbdr_tuning* tuning) {
   if (tuning->est_blocks_per_cu) sk->tune.est_blocks_per_cu = tuning->est_blocks_per_cu;
   if (tuning->scan_binned) sk->tune.scan_binned = tuning->scan_binned;
   if (tuning->est_binned) sk->tune.est_binned = tuning->est_binned;
+  sk->tl_always = tuning->est_binned == 3;
   if (tuning->est_parts) sk->tune.est_parts = tuning->est_parts;
   if (tuning->est_bin_hosts) sk->tune.est_bin_hosts = tuning->est_bin_hosts;
   if (tuning->est_bin_cap) sk->tune.est_bin_cap = tuning->est_bin_cap;
@@ -2617,7 +2735,8 @@ int vbdr_estimate_ex(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_host
   if (int rc = vbdr_check_device(sk)) return rc;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const bool extra = raw_es_dev || hist_dev;
-  if (sk->tl_rec && sk->tune.est_binned == 3 && !extra && n_hosts < (1ull << 32)) {
+  if (sk->tl_rec && sk->tune.est_binned == 3 && !extra && n_hosts < (1ull << 32) &&
+      (sk->tl_always || n_hosts * sk->g >= (gather_parts(sk) < 8 ? kTileMinGathers : kTileMinGathers8))) {
     uint32_t B = sk->tl_Balloc;  // the block the workspace holds (tiled_block_hosts of the tuning)
     {  // blocks of equal size (whole sub-blocks): no small last block (line rate: 2^19 + 102,494 hosts 1.85 ms,
        // 2 x 313,391 1.81 ms)
@@ -2695,7 +2814,7 @@ int vbdr_estimate_ex(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_host
     }
     return VBDR_OK;
   }
-  if (sk->parts > 1 && !extra)
+  if (!extra && !gathers_direct(sk, n_hosts))
     return estimate_partitioned(sk, hosts_dev, n_hosts, out_dev, sk->part_u, sk->part_v, kPartChunk, st);
   return estimate_direct(sk, hosts_dev, n_hosts, out_dev, raw_es_dev, hist_dev, st);
 }
@@ -2750,8 +2869,8 @@ int vbdr_estimate_noalloc(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n
   if (n_hosts >= (1ull << 40)) return vbdr_fail(VBDR_EINVAL, "n_hosts too large");
   if (int rc = vbdr_check_device(sk)) return rc;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  if (sk->parts <= 1) return estimate_direct(sk, hosts_dev, n_hosts, out_dev, nullptr, nullptr, st);
-  const uint32_t parts = (uint32_t)(sk->parts == 8 ? sk->tune.est_parts : sk->parts);
+  if (gathers_direct(sk, n_hosts)) return estimate_direct(sk, hosts_dev, n_hosts, out_dev, nullptr, nullptr, st);
+  const uint32_t parts = gather_parts(sk);
   if ((uint64_t)parts * kNoAllocHosts * (8 + 4) > kNoAllocBytes)
     return vbdr_fail(VBDR_EINVAL, "%u pool ranges need more than the %llu bytes of static scratch", parts,
                      (unsigned long long)kNoAllocBytes);

@@ -104,7 +104,7 @@ __global__ __launch_bounds__(kBBlock) void k_batch_estimate(const BatchDesc* __r
   __shared__ uint32_t cur;
   for (uint32_t s = threadIdx.x; s < S; s += kBBlock) starts[s] = d[s].est_item0;
   const uint32_t total = hdr->est_total;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
   for (;;) {
     const uint32_t item = next_item(&hdr->counter[1], &cur);
     if (item >= total) break;
@@ -113,16 +113,9 @@ __global__ __launch_bounds__(kBBlock) void k_batch_estimate(const BatchDesc* __r
     const double Em = stat_em(D.hist);
     const uint64_t lo = (uint64_t)(item - starts[s]) * tile;
     const uint64_t hi = lo + tile < D.n_hosts ? lo + tile : D.n_hosts;
-    for (uint64_t h = lo + wave; h < hi; h += kBBlock / 64) {
-      uint64_t U;
-      uint32_t V;
-      host_harmonic<8>(mm3_key(D.hosts[h]), D.s1, D.g, D.m, D.reg4, D.reg, lane, U, V);
-      if (lane == 0) {
-        const double Es = hll_estimate(U, V, (double)D.g);
-        const double n = noise_removed(Es, Em, (double)D.m, (double)D.g);
-        D.out[h] = (float)(n > 0.0 ? n : 0.0);
-      }
-    }
+    for (uint64_t h = lo + 4 * wave; h < hi; h += 4 * (kBBlock / 64))
+      estimate_hosts<16, false>(D.hosts + h, hi - h < 4 ? (uint32_t)(hi - h) : 4u, D.s1, D.g, D.m, D.reg, D.reg4,
+                                nullptr, 0u, Em, D.out + h);
   }
 }
 

@@ -9,6 +9,13 @@ namespace vbdr {
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+struct TrueType {
+  static constexpr bool value = true;
+};
+struct FalseType {
+  static constexpr bool value = false;
+};
+
 constexpr int kBins = 33;     // register values 0..32
 constexpr uint32_t kSat = 255; // DR saturation value (InitDR with z = 8)
 
@@ -372,38 +379,98 @@ __device__ __forceinline__ double pool_estimate(const unsigned long long* hist, 
   return hll_estimate(U, hist[0], m);
 }
 
-// Exact harmonic sum U = sum 2^(32-R) and zero count V of one host's g
-// registers (getPhyIdx of Alg. 3, register gathers of Alg. 5), summed over
-// the wave; kmix = mm3_key(aip).  Every lane returns the totals.  The
-// registers are read from their nibble copy reg4, half the bytes of reg, so
-// that a larger share of a big pool stays in each XCD's L2; a nibble of 15
-// stands for 15 and more and is read again from reg.
-template <int UNROLL>
-__device__ __forceinline__ void host_harmonic(uint32_t kmix, const uint32_t* s1, uint32_t g, uint32_t m,
-                                              const uint8_t* reg4, const uint8_t* reg, int lane, uint64_t& U,
-                                              uint32_t& V) {
+// Sum over the LPH lanes (16 or 64) that share a host; every lane gets it.
+template <int LPH, class T>
+__device__ __forceinline__ T row_sum(T v) {
+#pragma unroll
+  for (int d = 1; d < LPH; d <<= 1) v += __shfl_xor(v, d);
+  return v;
+}
+
+// One wave's part of a register-gathering estimate: n <= 64 consecutive hosts,
+// LPH lanes each, 64 / LPH at a time.  The hosts' registers (getPhyIdx of
+// Alg. 3, gathers of Alg. 5) are read from their nibble copy, of which the
+// first tab_n are also in LDS (tab, with TABLE); a nibble of 15 stands for 15
+// and more and is read again from the byte array.  The harmonic sum is an
+// exact integer: registers below 15 add 2^(32-r) = 2^18 2^(14-r), at most
+// g 2^14 <= 2^30 in units of 2^18, to Us; the others add 2^(32-r) to Ux.  Each host's sums move to
+// the lane of its place (U and V of host `lane`), so that what follows runs
+// once for all of them, a lane per host.  PART: only registers of pool range
+// `part` (the hash's bits from part_shift up) are gathered.
+template <int LPH, bool TABLE, bool PART>
+__device__ __forceinline__ void gather_hosts(const uint32_t* __restrict__ hosts, uint32_t n, const uint32_t* s1,
+                                             uint32_t g, uint32_t m, const uint8_t* __restrict__ reg,
+                                             const uint8_t* __restrict__ reg4, const uint8_t* tab, uint32_t tab_n,
+                                             uint32_t part, uint32_t part_shift, uint64_t& U, uint32_t& V) {
+  constexpr int kRows = 64 / LPH, kFlight = LPH == 64 ? 4 : 8;  // hosts at a time; gathers in flight per lane
+  const int lane = threadIdx.x & 63, q = lane / LPH, ql = lane % LPH;
+  const uint32_t kmix = mm3_key((uint32_t)lane < n ? hosts[lane] : 0u);
   U = 0;
   V = 0;
-  for (uint32_t i0 = lane; i0 < g; i0 += 64 * UNROLL) {
-    uint32_t p[UNROLL], r[UNROLL];
+  for (uint32_t t = 0; t * kRows < n; ++t) {
+    const uint32_t km = (uint32_t)__shfl((int)kmix, (int)(t * kRows) + q);
+    uint32_t Us = 0, Vs = 0;
+    unsigned long long Ux = 0;
+    auto gathers = [&](auto guard) __attribute__((always_inline)) {
+      constexpr bool GUARD = decltype(guard)::value;
+      for (uint32_t i0 = (uint32_t)ql; i0 < g; i0 += LPH * kFlight) {
+        uint32_t p[kFlight], nib[kFlight];
+        bool mine[kFlight];
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-      const uint32_t i = i0 + 64u * u;
-      p[u] = i < g ? reduce_m(mm3_seeded(kmix, s1[i]), m) : 0u;
-      r[u] = i < g ? ((uint32_t)reg4[p[u] >> 1] >> ((p[u] & 1u) << 2)) & 0xFu : 255u;
-    }
+        for (int u = 0; u < kFlight; ++u) {
+          const uint32_t i = i0 + (uint32_t)(LPH * u);
+          const uint32_t h = mm3_seeded(km, s1[!GUARD || i < g ? i : 0u]);
+          p[u] = reduce_m(h, m);
+          if (PART) mine[u] = h >> part_shift == part;
+        }
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u)
-      if (r[u] == 15u) r[u] = reg[p[u]];
+        for (int u = 0; u < kFlight; ++u) {
+          if (TABLE) nib[u] = p[u] < tab_n ? (uint32_t)tab[p[u] >> 1] : (uint32_t)reg4[p[u] >> 1];
+          else nib[u] = !PART || mine[u] ? (uint32_t)reg4[p[u] >> 1] : 0u;
+        }
+        bool wide = false;
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u)
-      if (r[u] != 255u) {
-        U += 1ull << (32 - r[u]);
-        V += r[u] == 0;
+        for (int u = 0; u < kFlight; ++u) {
+          nib[u] = __builtin_amdgcn_ubfe(nib[u], (p[u] & 1u) << 2, 4);
+          if ((GUARD && i0 + (uint32_t)(LPH * u) >= g) || (PART && !mine[u])) nib[u] = 16;  // adds nothing below
+          Us += 0x4000u >> nib[u];
+          Vs += nib[u] == 0u;
+          wide |= nib[u] == 15u;
+        }
+        if (wide)
+#pragma unroll
+          for (int u = 0; u < kFlight; ++u)
+            if (nib[u] == 15u) Ux += 1ull << (32 - reg[p[u]]);
       }
+    };
+    if (g % (LPH * kFlight) == 0) gathers(FalseType{});
+    else gathers(TrueType{});
+    Us = row_sum<LPH>(Us);
+    Vs = row_sum<LPH>(Vs);
+    // lane l keeps host l: row l % kRows of step l / kRows
+    const int from = (lane % kRows) * LPH;
+    uint64_t u64 = (uint64_t)(uint32_t)__shfl((int)Us, from) << 18;
+    if (__builtin_amdgcn_ballot_w64(Ux != 0ull)) u64 += __shfl(row_sum<LPH>(Ux), from);
+    const uint32_t vs = (uint32_t)__shfl((int)Vs, from);
+    if ((uint32_t)lane / kRows == t) U = u64, V = vs;
   }
-  U = wave_sum_u64(U);
-  V = (uint32_t)wave_sum_u64(V);
+}
+
+// The estimates of n <= 64 consecutive hosts by one wave.
+template <int LPH, bool TABLE>
+__device__ __forceinline__ void estimate_hosts(const uint32_t* __restrict__ hosts, uint32_t n, const uint32_t* s1,
+                                               uint32_t g, uint32_t m, const uint8_t* __restrict__ reg,
+                                               const uint8_t* __restrict__ reg4, const uint8_t* tab, uint32_t tab_n,
+                                               double Em, float* __restrict__ out) {
+  uint64_t U;
+  uint32_t V;
+  gather_hosts<LPH, TABLE, false>(hosts, n, s1, g, m, reg, reg4, tab, tab_n, 0u, 0u, U, V);
+  const uint32_t lane = threadIdx.x & 63;
+  if (lane < n) {
+    const double Es = hll_estimate(U, V, (double)g);
+    const double e = noise_removed(Es, Em, (double)m, (double)g);
+    out[lane] = (float)(e > 0.0 ? e : 0.0);
+  }
 }
 
 }  // namespace vbdr

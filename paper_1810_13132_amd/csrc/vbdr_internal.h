@@ -27,6 +27,24 @@ constexpr uint64_t kDeferLeast = 1ull << 22;   // record slots of a sketch, at l
 // Pairs of a scan up to which pools below 2^22 BDRs are updated directly.
 constexpr uint64_t kDirectSmall = 1ull << 20, kDirectFast = 1ull << 16;
 
+// Which estimate gathers how (g <= kStageMaxG, no extra outputs), each line
+// with both sides measured at g = 512 (gathers a second, large host lists):
+//   up to 2^21 BDRs directly, nibbles in LDS (2^18: 1.28e12, 2^20: 4.0e11, 2^21:
+//     3.1e11; all gathers from L2: 3.0e11, 2.7e11, 2.6e11);
+//   up to 2^23 directly, the nibbles in every XCD's L2 (2.6e11; ranges on
+//     8 XCDs: 1.7e11);
+//   above in 2, 4 or 8 ranges by XCD (2^24: 2.6e11, 2^26: 2.0e11; 8 ranges:
+//     1.7e11, directly: 1.2e11, 0.65e11), directly below 2^20 gathers;
+//   from 2^24 BDRs and enough gathers the LDS-tiled passes (2.9e11; 16384
+//     hosts at 2^24: tiled 58 us, ranges 41; 65536: 131 and 139; at 2^26 65
+//     and 59, 139 and 199).
+constexpr uint64_t kTableMaxM = 1ull << 21;       // pools whose direct estimate may keep registers in LDS
+constexpr uint64_t kTableMinUse = 6;              // gathers per register of that table, at least (2^18 BDRs: a step of 2^20
+                                                  // pairs, 4096 hosts, g = 256 28.6 us with the table, 27.1 without)
+constexpr uint64_t kRangeBytes = 4ull << 20;      // nibbles of a range: an XCD's L2
+constexpr uint64_t kPartMinGathers = 1ull << 20;  // gathers of an estimate below which one range will do
+constexpr uint64_t kTileMinGathers = 3ull << 23, kTileMinGathers8 = 10ull << 20;  // from which tiles pay (8 ranges)
+
 struct vbdr_sketch {
   int device;
   int n_cu;
@@ -57,6 +75,7 @@ struct vbdr_sketch {
   uint32_t* ovf_v;             // [est_hc]
   uint32_t est_cap, est_hc;
   bool bin_ok, est_ok;            // the binned scan / estimate workspaces may be allocated (on request)
+  bool tl_always;                 // est_binned = 3 was asked for: also for few hosts
   bool tl_ok;                     // the LDS-tiled estimate fits this pool (workspaces on request)
   uint32_t tl_shift, tl_nt, tl_B, tl_cap;  // tile = 2^tl_shift registers; tiles; hosts per block; records per run
   uint32_t tl_capb;               // entries per LDS bucket of a (chunk, tile) in the first pass

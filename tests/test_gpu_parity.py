@@ -631,6 +631,35 @@ def test_tile_sizes_and_scan_routes(V, O, layout, m, g, k):
     assert_estimates_close(V, O, sk, osk, hosts)
 
 
+@pytest.mark.parametrize("m,g", [(300, 2), (5000, 16), (70001, 64), (1 << 18, 512), ((1 << 18) + 1, 8192),
+                                 ((1 << 20) - 3, 128), ((1 << 21) + 5, 1024), (100_000, 16384),
+                                 ((1 << 22) + 7, 256), ((1 << 23) + 4097, 512), ((1 << 25) + 1, 64)])
+def test_estimate_routes(V, O, m, g):
+    """Direct gathers with and without registers in LDS, a wave or 16 lanes a
+    host, and gathers in 2 and 8 ranges: host counts at the edges of rows,
+    waves and workgroups give the bits of estimate_ex, which gathers every
+    byte from memory, and estimate_noalloc too.  Pools up to 2^20 hold planted registers, a
+    tenth of them 15 and more."""
+    rng = np.random.default_rng(g)
+    sk = V.Sketch(m, g, 3, 21, "small")
+    if m < 1 << 20:
+        reg = rng.integers(0, min(sk.L, 14) + 1, m).astype(np.uint8)
+        wide = rng.random(m) < 0.1
+        reg[wide] = rng.integers(min(15, sk.L), sk.L + 1, int(wide.sum()))
+        hist = np.bincount(reg, minlength=33).astype(np.uint64)
+        sk.load_state({"dr": np.full((m, sk.L), 255, np.uint8), "reg": reg, "hist": hist, "t": 1})
+    else:
+        for t in range(2):
+            sk.scan_slice(_dev(V, rng.integers(0, 2**32, (m // 2, 2), dtype=np.uint64).astype(np.uint32).reshape(-1)))
+            sk.advance_slice()
+    hosts = rng.integers(0, 2**32, 70_001, dtype=np.uint64).astype(np.uint32)
+    ref = sk.estimate_ex(_dev(V, hosts))[0]
+    for n in (1, 3, 4, 65, 1023, 8191, 8193, 33_000, 70_001):
+        hd = _dev(V, hosts[:n])
+        assert torch.equal(sk.estimate(hd), ref[:n]), n
+        assert torch.equal(sk.estimate_noalloc(hd, torch.empty(n, dtype=torch.float32, device="cuda")), ref[:n]), n
+
+
 def test_bad_arguments_on_device(V):
     sk = V.Sketch(5000, 16, 3, 1, "small")
     pairs = torch.zeros(8, dtype=torch.int32, device="cuda")
