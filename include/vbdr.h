@@ -413,7 +413,7 @@ int vbdr_trainer_params(vbdr_trainer *tr, float *params_host, void *stream);
  * its own pool size, g, k, seed and layout, stepped together.  One step =
  * for every sketch, scan its slice, close it, estimate its host list --
  * vbdr_scan_slice + vbdr_advance_slice + vbdr_estimate semantics per sketch,
- * run as three persistent work-queue kernels over all sketches, captured once
+ * run as a few kernels over all sketches, captured once
  * into a HIP graph and replayed.  At most 256 sketches per batch.
  * ---------------------------------------------------------------------- */
 typedef struct vbdr_batch vbdr_batch;
@@ -426,9 +426,11 @@ typedef struct vbdr_batch_params {
 } vbdr_batch_params;
 
 /* Launch shape of a batch step (no effect on results):
- *   scan_tile      pairs per scan work item (256 .. 2^22);
- *   est_tile       hosts per estimate work item (4 .. 2^16);
- *   blocks_per_cu  workgroups per compute unit of each persistent kernel (1..32);
+ *   scan_tile      pairs per work item of the direct scan (256 .. 2^22);
+ *   est_tile       members with est_tile / 4 hosts and more per compute unit are
+ *                  estimated by all workgroups one after the other, the
+ *                  others side by side (4 .. 2^16);
+ *   blocks_per_cu  workgroups per compute unit of the direct scan (1..32);
  *   use_graph      1 = capture the kernel sequence once and replay it. */
 typedef struct vbdr_batch_tuning {
     uint32_t scan_tile;
@@ -451,7 +453,7 @@ vbdr_sketch *vbdr_batch_sketch(vbdr_batch *bt, uint32_t i);
  * mlp = NULL returns the member to plain estimates.  The model stays the
  * caller's and must outlive the steps that use it; it must live on the
  * batch's device.  The member's learned estimate runs after the step's
- * persistent kernels, on the batch's stream.  Waits for steps in flight. */
+ * kernels, on the batch's stream.  Waits for steps in flight. */
 int vbdr_batch_set_mlp(vbdr_batch *bt, uint32_t i, const vbdr_mlp *mlp);
 
 int vbdr_batch_set_tuning(vbdr_batch *bt, const vbdr_batch_tuning *tuning);

@@ -37,12 +37,24 @@ struct BatchDesc {
   const uint32_t* hosts;
   uint64_t n_hosts;
   float* out;
-  uint32_t scan_item0, est_item0;
+  uint32_t scan_item0;
+  // estimate: what part of the kernel takes the member (EstPart), and its cost there
+  uint32_t est_part;
+  uint32_t each;               // cost of a host
+  uint64_t cost0;              // cost of the members before in that part
+  uint32_t parts, part_shift;  // L2 members: pool ranges, the hash bits that choose one
+  uint32_t part_off;           // ... first host in the partial sums (ranges > 1)
+  uint32_t tab_n;              // LDS members: registers in LDS
 };
 
+// Spread: gathers from L2, over all workgroups; L2, LDS: stretches cut by cost.
+enum EstPart : uint32_t { kEstNone = 0, kEstSpread = 1, kEstL2 = 2, kEstLdsPart = 3 };
+
 struct BatchHdr {
-  uint32_t scan_total, est_total;
-  uint32_t counter[2];  // reset to 0 by every step's table upload
+  uint64_t cost[2];     // cost of all L2 members on one XCD, of all LDS members
+  uint32_t scan_total;  // items of the scan
+  uint32_t counter;     // scan items taken; reset to 0 by every step's table upload
+  uint32_t pad[2];
 };
 
 __device__ __forceinline__ uint32_t find_sketch(const uint32_t* starts, uint32_t S, uint32_t item) {
@@ -70,7 +82,7 @@ __global__ __launch_bounds__(kBBlock) void k_batch_scan(const BatchDesc* __restr
   for (uint32_t s = threadIdx.x; s < S; s += kBBlock) starts[s] = d[s].scan_item0;
   const uint32_t total = hdr->scan_total;
   for (;;) {
-    const uint32_t item = next_item(&hdr->counter[0], &cur);
+    const uint32_t item = next_item(&hdr->counter, &cur);
     if (item >= total) break;
     const uint32_t s = find_sketch(starts, S, item);
     const BatchDesc& D = d[s];
@@ -98,24 +110,118 @@ __global__ __launch_bounds__(kBBlock) void k_batch_scan(const BatchDesc* __restr
   }
 }
 
-__global__ __launch_bounds__(kBBlock) void k_batch_estimate(const BatchDesc* __restrict__ d,
-                                                            BatchHdr* __restrict__ hdr, uint32_t S, uint32_t tile) {
-  __shared__ uint32_t starts[kMaxBatch];
-  __shared__ uint32_t cur;
-  for (uint32_t s = threadIdx.x; s < S; s += kBBlock) starts[s] = d[s].est_item0;
-  const uint32_t total = hdr->est_total;
-  const int wave = threadIdx.x >> 6;
-  for (;;) {
-    const uint32_t item = next_item(&hdr->counter[1], &cur);
-    if (item >= total) break;
-    const uint32_t s = find_sketch(starts, S, item);
+// Estimates of all members by one workgroup per CU.  Work is handed out by
+// position alone (a counter for items of a few hosts served one wave every 20 ns:
+// 858 us).  First the members whose gathers go to L2: an XCD takes a range of
+// the pool where its nibbles outgrow a part of the L2 (8 / parts XCDs share a
+// range, each takes its share of the hosts; k_batch_estimate_final adds the
+// ranges' sums), many hosts are spread over all workgroups, one member after
+// the other, so that they share the L2, few are cut by cost.  Then the members
+// with (part of) their registers in LDS: a workgroup takes one stretch of all
+// their hosts, so that it loads one or two members' tables.
+// 1.29e8 gathers of 32 members: 837 us with every gather from L2, one host a
+// wave; 392 us now.
+constexpr int kEBlock = 1024, kEWaves = kEBlock / 64;
+constexpr uint32_t kEstLds = 152u << 10;     // seeds and table
+constexpr uint64_t kEstTableM = 1ull << 20;  // pools up to this keep registers in LDS
+constexpr uint64_t kEstRange = 2ull << 20;   // nibbles of a range: half an L2, which a few members share
+constexpr uint32_t kPartEntries = 1u << 19;  // (range, host) sums of a step; members past that gather directly
+__global__ __launch_bounds__(kEBlock) void k_batch_estimate(const BatchDesc* __restrict__ d,
+                                                            const BatchHdr* __restrict__ hdr, uint32_t S,
+                                                            unsigned long long* __restrict__ part_u,
+                                                            uint32_t* __restrict__ part_v) {
+  extern __shared__ uint32_t lds[];
+  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const uint32_t xcd = blockIdx.x & 7u;  // workgroups are dispatched round-robin over the 8 XCDs
+  const uint32_t mine = blockIdx.x >> 3, per_xcd = gridDim.x >> 3;
+  auto work = [&](const BatchDesc& D, uint64_t lo, uint64_t hi, auto in_lds) __attribute__((always_inline)) {
+    constexpr bool TABLE = decltype(in_lds)::value;
+    const uint32_t g = D.g;
+    const bool staged = g <= kStageMaxG;
+    uint32_t* tab = lds + g;  // 16-byte aligned: g >= 4
+    __syncthreads();          // nobody reads the member's before any more
+    if (staged)
+      for (uint32_t i = threadIdx.x; i < g; i += kEBlock) lds[i] = D.s1[i];
+    if (TABLE) {
+      const u32x4* src = reinterpret_cast<const u32x4*>(D.reg4);
+      for (uint32_t q = threadIdx.x; q < D.tab_n / 32; q += kEBlock) reinterpret_cast<u32x4*>(tab)[q] = src[q];
+    }
+    __syncthreads();
+    const uint64_t n = hi - lo;
+    uint64_t per = ((n + kEWaves - 1) / kEWaves + 3) / 4 * 4;
+    per = per > 64 ? 64 : per;
+    for (uint64_t h = wave * per; h < n; h += kEWaves * per) {
+      const uint32_t c = n - h < per ? (uint32_t)(n - h) : (uint32_t)per;
+      const uint32_t* hosts = D.hosts + lo + h;
+      float* out = D.out + lo + h;
+      if (TABLE) {
+        estimate_hosts<16, true>(hosts, c, lds, g, D.m, D.reg, D.reg4, reinterpret_cast<const uint8_t*>(tab), D.tab_n,
+                                 stat_em(D.hist), out);
+      } else if (D.parts > 1) {
+        const uint32_t part = xcd % D.parts;
+        uint64_t U;
+        uint32_t V;
+        gather_hosts<16, false, true>(hosts, c, lds, g, D.m, D.reg, D.reg4, nullptr, 0u, part, D.part_shift, U, V);
+        if (lane < c) {
+          const uint64_t at = D.part_off + part * D.n_hosts + lo + h + lane;
+          part_u[at] = U;
+          part_v[at] = V;
+        }
+      } else if (staged) {
+        estimate_hosts<16, false>(hosts, c, lds, g, D.m, D.reg, D.reg4, nullptr, 0u, stat_em(D.hist), out);
+      } else {
+        estimate_hosts<16, false>(hosts, c, D.s1, g, D.m, D.reg, D.reg4, nullptr, 0u, stat_em(D.hist), out);
+      }
+    }
+  };
+  for (uint32_t s = 0; s < S; ++s) {
     const BatchDesc& D = d[s];
-    const double Em = stat_em(D.hist);
-    const uint64_t lo = (uint64_t)(item - starts[s]) * tile;
-    const uint64_t hi = lo + tile < D.n_hosts ? lo + tile : D.n_hosts;
-    for (uint64_t h = lo + 4 * wave; h < hi; h += 4 * (kBBlock / 64))
-      estimate_hosts<16, false>(D.hosts + h, hi - h < 4 ? (uint32_t)(hi - h) : 4u, D.s1, D.g, D.m, D.reg, D.reg4,
-                                nullptr, 0u, Em, D.out + h);
+    if (D.est_part != kEstSpread) continue;
+    const uint64_t shares = 8u / D.parts * per_xcd, share = xcd / D.parts * per_xcd + mine;
+    const uint64_t lo = D.n_hosts * share / shares, hi = D.n_hosts * (share + 1) / shares;
+    if (lo < hi) work(D, lo, hi, FalseType{});
+  }
+  // the hosts of a member whose cost starts in [from, to), of hosts first .. first + n
+  auto stretch = [&](const BatchDesc& D, uint64_t from, uint64_t to, uint64_t first, uint64_t n, auto in_lds)
+                     __attribute__((always_inline)) {
+    const uint64_t end = D.cost0 + D.each * n;
+    if (end <= from || D.cost0 >= to) return;
+    const uint64_t lo = from <= D.cost0 ? 0 : (from - D.cost0 + D.each - 1) / D.each;
+    const uint64_t hi = to >= end ? n : (to - D.cost0 + D.each - 1) / D.each;
+    if (lo < hi) work(D, first + lo, first + hi, in_lds);
+  };
+  for (uint32_t s = 0; s < S; ++s) {
+    const BatchDesc& D = d[s];
+    if (D.est_part != kEstL2) continue;
+    const uint64_t shares = 8u / D.parts, share = xcd / D.parts;  // this XCD's hosts
+    const uint64_t first = D.n_hosts * share / shares, past = D.n_hosts * (share + 1) / shares;
+    stretch(D, hdr->cost[0] * mine / per_xcd, hdr->cost[0] * (mine + 1) / per_xcd, first, past - first, FalseType{});
+  }
+  for (uint32_t s = 0; s < S; ++s) {
+    const BatchDesc& D = d[s];
+    if (D.est_part != kEstLdsPart) continue;
+    stretch(D, hdr->cost[1] * blockIdx.x / gridDim.x, hdr->cost[1] * (blockIdx.x + 1) / gridDim.x, 0, D.n_hosts,
+            TrueType{});
+  }
+}
+
+// The estimates of members gathered in ranges, from their ranges' sums.
+__global__ __launch_bounds__(256) void k_batch_estimate_final(const BatchDesc* __restrict__ d, uint32_t S,
+                                                              const unsigned long long* __restrict__ part_u,
+                                                              const uint32_t* __restrict__ part_v) {
+  for (uint32_t s = blockIdx.y; s < S; s += gridDim.y) {
+    const BatchDesc& D = d[s];
+    if (D.parts < 2) continue;  // also members without hosts
+    for (uint64_t h = blockIdx.x * 256 + threadIdx.x; h < D.n_hosts; h += gridDim.x * 256) {
+      uint64_t U = 0, V = 0;
+      for (uint32_t x = 0; x < D.parts; ++x) {
+        U += part_u[D.part_off + x * D.n_hosts + h];
+        V += part_v[D.part_off + x * D.n_hosts + h];
+      }
+      const double Es = hll_estimate(U, V, (double)D.g);
+      const double e = noise_removed(Es, stat_em(D.hist), (double)D.m, (double)D.g);
+      D.out[h] = (float)(e > 0.0 ? e : 0.0);
+    }
   }
 }
 
@@ -139,6 +245,9 @@ struct vbdr_batch {
   uint32_t runs_max_tiles;     // most tiles of a member with record runs; 0: none has any
   uint32_t adv_lds, adv_tiles; // the advance's LDS bytes (largest member) and tiles (all members)
   bool direct, big;            // some member scans without record runs; has tiles of 2^kMaxTileShift BDRs
+  // sums of members whose gathers are partitioned (NULL: there is none), [kPartEntries]
+  unsigned long long* part_u;
+  uint32_t* part_v;
   // learned estimators by member (NULL: plain), owned by the caller
   std::vector<const vbdr_mlp*> mlp;
 };
@@ -156,9 +265,52 @@ DeferHdr* defer_hdr(uint8_t* table, uint32_t S) {
   return reinterpret_cast<DeferHdr*>(table + sizeof(BatchDesc) * S + sizeof(BatchHdr) + sizeof(DeferItem) * S);
 }
 
+// Ranges of a member's gathers.
+uint32_t member_parts(const vbdr_sketch* k) {
+  uint32_t p = 1;
+  while (p < 8u && (k->mstride / 2) / p > kEstRange) p *= 2;
+  return k->g > kStageMaxG || k->n_cu < (int)(8 * kCusPerXcd) ? 1u : p;
+}
+
+// Where a member is estimated.  A host costs its gathers, weighted by their
+// rate: registers in LDS (up to kEstTableM BDRs) 4 where all are (1.28e12 a
+// second), 6 at 2^19 (8.2e11), 13 at 2^20 (4.0e11); from L2 in p ranges 1 / p
+// and the hashes.  Members with est_tile / 4 hosts and more for every workgroup are
+// spread over all of them (32 members: 392 us with 16 hosts, 442 with 64, 412
+// with 2).  part_used: (range, host) sums taken so far.
+void estimate_plan(const vbdr_batch* bt, const vbdr_sketch* k, uint64_t n_plain, uint32_t* part_used, uint64_t cost[2],
+                   BatchDesc* D) {
+  D->est_part = kEstNone, D->each = 0, D->cost0 = 0;
+  D->parts = 1, D->part_shift = D->part_off = D->tab_n = 0;
+  if (n_plain == 0) return;
+  if (k->m <= kEstTableM && k->g >= 4 && k->g <= kStageMaxG) {
+    const uint64_t most = (kEstLds - k->g * 4u) * 2ull / 32 * 32;
+    D->tab_n = (uint32_t)(most < k->mstride ? most : k->mstride);
+    D->est_part = kEstLdsPart;
+    D->each = k->g * (most >= k->m ? 4u : k->m <= (1ull << 19) ? 6u : 13u);
+    D->cost0 = cost[1];
+    cost[1] += n_plain * D->each;
+    return;
+  }
+  const uint32_t parts = bt->part_u ? member_parts(k) : 1u;
+  if (parts > 1 && (uint64_t)*part_used + n_plain * parts <= kPartEntries) {
+    D->parts = parts, D->part_shift = 32u - (parts == 8 ? 3u : parts == 4 ? 2u : 1u), D->part_off = *part_used;
+    *part_used += (uint32_t)n_plain * parts;
+  }
+  const uint64_t shares = 8u / D->parts, hosts = (n_plain + shares - 1) / shares;  // of one XCD
+  if (hosts >= (uint64_t)bt->tune.est_tile * (uint32_t)(bt->n_cu / 8) / 4) {
+    D->est_part = kEstSpread;
+    return;
+  }
+  D->est_part = kEstL2;
+  D->each = k->g * (16u / D->parts + 4u);
+  D->cost0 = cost[0];
+  cost[0] += hosts * D->each;
+}
+
 int launch_step_kernels(vbdr_batch* bt) {
-  const uint32_t grid = (uint32_t)bt->n_cu * bt->tune.blocks_per_cu;
   if (bt->direct) {
+    const uint32_t grid = (uint32_t)bt->n_cu * bt->tune.blocks_per_cu;
     hipLaunchKernelGGL(k_batch_scan, dim3(grid), dim3(kBBlock), 0, bt->st, bt->desc_dev, bt->hdr_dev, bt->S,
                        bt->tune.scan_tile);
     VBDR_LAUNCHED("k_batch_scan");
@@ -170,9 +322,14 @@ int launch_step_kernels(vbdr_batch* bt) {
     if (int rc = vbdr_launch_batch_defer(ditems, dhdr, bt->S, bt->runs_max_tiles, bt->adv_lds, bt->adv_tiles, bt->big,
                                          (uint32_t)bt->n_cu, phase, bt->st))
       return rc;
-  hipLaunchKernelGGL(k_batch_estimate, dim3(grid), dim3(kBBlock), 0, bt->st, bt->desc_dev, bt->hdr_dev, bt->S,
-                     bt->tune.est_tile);
+  hipLaunchKernelGGL(k_batch_estimate, dim3((uint32_t)bt->n_cu < 8 ? 8 : (uint32_t)bt->n_cu / 8 * 8), dim3(kEBlock), kEstLds, bt->st, bt->desc_dev,
+                     bt->hdr_dev, bt->S, bt->part_u, bt->part_v);
   VBDR_LAUNCHED("k_batch_estimate");
+  if (bt->part_u) {
+    hipLaunchKernelGGL(k_batch_estimate_final, dim3(64, bt->S), dim3(256), 0, bt->st, bt->desc_dev, bt->S, bt->part_u,
+                       bt->part_v);
+    VBDR_LAUNCHED("k_batch_estimate_final");
+  }
   return VBDR_OK;
 }
 
@@ -231,6 +388,14 @@ int vbdr_batch_create(uint32_t n_sketches, const vbdr_batch_params* params, vbdr
       rc = vbdr_fail(VBDR_ENOMEM, "batch table allocation failed");
       break;
     }
+    bool parts = false;
+    for (const vbdr_sketch* s : bt->sk) parts |= member_parts(s) > 1;
+    if (parts && (vbdr_malloc(&bt->part_u, kPartEntries * 8ull) != hipSuccess ||
+                  vbdr_malloc(&bt->part_v, kPartEntries * 4ull) != hipSuccess)) {
+      (void)hipGetLastError();
+      rc = vbdr_fail(VBDR_ENOMEM, "allocation of the batch's partial sums failed");
+      break;
+    }
     bt->hdr_dev = reinterpret_cast<BatchHdr*>(reinterpret_cast<uint8_t*>(bt->desc_dev) + sizeof(BatchDesc) * n_sketches);
     if (hipStreamCreateWithFlags(&bt->st, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&bt->ev_in, hipEventDisableTiming) != hipSuccess ||
@@ -255,6 +420,8 @@ void vbdr_batch_destroy(vbdr_batch* bt) {
   drop_graph(bt);
   for (vbdr_sketch* s : bt->sk) vbdr_sketch_destroy(s);
   if (bt->desc_dev) (void)hipFree(bt->desc_dev);
+  if (bt->part_u) (void)hipFree(bt->part_u);
+  if (bt->part_v) (void)hipFree(bt->part_v);
   for (int i = 0; i < 2; ++i) {
     if (bt->staging[i]) (void)hipHostFree(bt->staging[i]);
     if (bt->staged[i]) (void)hipEventDestroy(bt->staged[i]);
@@ -325,7 +492,8 @@ int vbdr_batch_step(vbdr_batch* bt, const uint32_t* const* pairs_dev, const uint
   DeferItem* ditems = defer_items(bt->staging[buf], S);
   DeferHdr* dhdr = defer_hdr(bt->staging[buf], S);
   const uint32_t chunk = vbdr_defer_chunk_pairs();
-  uint32_t si = 0, ei = 0, dsi = 0, dai = 0;
+  uint32_t si = 0, dsi = 0, dai = 0, part_used = 0;
+  uint64_t cost[2] = {0, 0};
   for (uint32_t s = 0; s < S; ++s) {
     const vbdr_sketch* k = bt->sk[s];
     const bool runs = k->def_rec != nullptr;  // scanned in chunks, no items in the direct scan
@@ -342,14 +510,14 @@ int vbdr_batch_step(vbdr_batch* bt, const uint32_t* const* pairs_dev, const uint
     D.A1 = k->A1, D.test = k->tune.scan_test_first == 1;
     D.pairs = pairs_dev[s], D.n_pairs = n_pairs[s];
     D.hosts = hosts_dev[s], D.n_hosts = n_hosts[s], D.out = out_dev[s];
-    D.scan_item0 = si, D.est_item0 = ei;
+    D.scan_item0 = si;
     // members with a learned estimator are estimated after the step's kernels
     const uint64_t n_plain = bt->mlp[s] ? 0 : n_hosts[s];
     if (!runs) si += (uint32_t)((n_pairs[s] + bt->tune.scan_tile - 1) / bt->tune.scan_tile);
-    ei += (uint32_t)((n_plain + bt->tune.est_tile - 1) / bt->tune.est_tile);
+    estimate_plan(bt, k, n_plain, &part_used, cost, &D);
   }
   std::memset(hdr, 0, sizeof(*hdr));
-  hdr->scan_total = si, hdr->est_total = ei;
+  hdr->scan_total = si, hdr->cost[0] = cost[0], hdr->cost[1] = cost[1];
   std::memset(dhdr, 0, sizeof(*dhdr));
   dhdr->scan_total = dsi;
   // order after the caller's stream, run on the batch stream, order the caller after it

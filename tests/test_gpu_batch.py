@@ -232,3 +232,33 @@ def test_batch_learned_members(V):
         ref2 = singles[2].estimate(hd[2]) if t == 4 else singles[2].estimate_learned(mlp, hd[2])
         assert torch.equal(outs[2], ref2), t
         assert not torch.equal(outs[1], singles[1].estimate(hd[1]))
+
+
+def test_batch_estimate_parts(V):
+    """Members of every kind of the batch's estimate: registers wholly and
+    partly in LDS, gathers from L2 in one and in several ranges, few hosts and
+    many, more (range, host) sums than the batch keeps, seeds that do not fit
+    LDS, no hosts.  Bit for bit the same sketches stepped alone."""
+    conf = [(1 << 24, 64, 140_000), ((1 << 24) + 5, 512, 5000), ((1 << 23) + 77, 256, 33), ((1 << 22) + 3, 128, 40_000),
+            (1 << 20, 512, 9001), ((1 << 19) + 1, 1024, 700), (1 << 16, 256, 20_000), (5000, 64, 17), (100_000, 16384, 300),
+            (3000, 2, 1001), (1 << 18, 128, 0), (1 << 21, 256, 2)]
+    rng = np.random.default_rng(29)
+    params = [dict(m=m, g=g, k=3, hash_seed=i, layout="fast" if i % 2 else "small") for i, (m, g, _) in enumerate(conf)]
+    bt = V.Batch(params)
+    single = [V.Sketch(p["m"], p["g"], p["k"], p["hash_seed"], p["layout"]) for p in params]
+    hosts = [V.to_device_u32(rng.integers(0, 2**32, n, dtype=np.uint64).astype(np.uint32)) for _, _, n in conf]
+    outs = [torch.empty(n, dtype=torch.float32, device="cuda") for _, _, n in conf]
+    for t in range(3):
+        pairs = [V.to_device_u32(rng.integers(0, 2**32, 2 * min(m, 300_000), dtype=np.uint64).astype(np.uint32))
+                 for m, _, _ in conf]
+        bt.step(pairs, hosts, outs)
+        for i, sk in enumerate(single):
+            sk.scan_slice(pairs[i])
+            sk.advance_slice()
+            assert torch.equal(outs[i], sk.estimate(hosts[i])), (t, conf[i])
+    bt.set_tuning(est_tile=4)
+    bt.step(pairs, hosts, outs)
+    for i, sk in enumerate(single):
+        sk.scan_slice(pairs[i])
+        sk.advance_slice()
+        assert torch.equal(outs[i], sk.estimate(hosts[i])), conf[i]
