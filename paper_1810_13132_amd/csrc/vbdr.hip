@@ -703,7 +703,7 @@ __device__ __forceinline__ uint32_t defer_member(const uint32_t* first, uint32_t
     if (first[mid] <= item) lo = mid;
     else hi = mid - 1;
   }
-  return lo;
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);  // the whole workgroup's
 }
 
 // LDS: cnt[max tiles], start[max tiles], sorted[kDeferChunk].

@@ -64,7 +64,7 @@ __device__ __forceinline__ uint32_t find_sketch(const uint32_t* starts, uint32_t
     if (starts[mid] <= item) lo = mid;
     else hi = mid - 1;
   }
-  return lo;
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);  // the whole workgroup's
 }
 
 // Next work item of a queue, shared by the whole block.

@@ -71,16 +71,33 @@ __device__ __forceinline__ void bip_map(uint32_t bip, uint32_t A1, uint32_t b, u
 
 // ---- byte-wise (SWAR) operations on four one-byte DRs held in a uint32 ----
 
-// Saturating increment of every byte (SlideDR): bytes below 255 gain 1.
+// Saturating increment of every byte (SlideDR): bytes below 255 gain 1.  On the
+// device each byte sits in the high half of a 16-bit lane for a packed add that
+// saturates at 0xFFFF, and v_perm collects the four high bytes: 4 instructions.
 __host__ __device__ __forceinline__ uint32_t swar_sat_inc(uint32_t x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  const u16x2 one = {0x0100, 0x0100};
+  const uint32_t odd = __builtin_bit_cast(uint32_t, __builtin_elementwise_add_sat(__builtin_bit_cast(u16x2, x), one));
+  const uint32_t even = __builtin_bit_cast(uint32_t, __builtin_elementwise_add_sat(__builtin_bit_cast(u16x2, x << 8), one));
+  return __builtin_amdgcn_perm(odd, even, 0x07030501u);
+#else
   const uint32_t t = ~x;  // a byte of t is zero exactly where x holds 255
   const uint32_t not_sat = (((t & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | t) & 0x80808080u;
   return x + (not_sat >> 7);
+#endif
 }
 
 // 0xFF in byte j for each set bit j of a 4-bit mask.
 __host__ __device__ __forceinline__ uint32_t swar_nibble_to_bytes(uint32_t f4) {
   return ((f4 * 0x00204081u) & 0x01010101u) * 0xFFu;
+}
+
+// x with byte j zeroed for each set bit j of a 4-bit mask (SetDR): the mask's
+// bits, 4 to a byte, turn a byte selector from x's bytes to zero's.
+__device__ __forceinline__ uint32_t swar_zero_bytes(uint32_t x, uint32_t f4) {
+  const uint32_t spread = __umul24(f4, 0x00204081u) & 0x01010101u;
+  return __builtin_amdgcn_perm(0u, x, 0x03020100u + (spread << 2));
 }
 
 // Bias for swar_le_mask: each byte value v sits in its own 16-bit lane, where
@@ -245,6 +262,11 @@ __device__ __forceinline__ void advance_words(uint8_t* dr, uint64_t mstride, uin
     Q[w] = ~0u;
   }
   uint32_t sat = 0;
+  // M: bit 7 of the BDRs with an active DR at or above the plane; the planes down to 1 with it count the register
+  auto found = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int w = 0; w < W; ++w) R[w] += M[w] >> 7;
+  };
   auto bits_of = [&](int r) -> uint32_t { return (pm[(uint32_t)(r - 1) * pm_stride] >> sh) & mask; };
   auto load_group = [&](int top, DrWords<W>(&d)[G]) __attribute__((always_inline)) {
 #pragma unroll
@@ -278,42 +300,41 @@ __device__ __forceinline__ void advance_words(uint8_t* dr, uint64_t mstride, uin
       for (int w = 0; w < W; ++w) all &= d[j].v[w];
       if (bits == 0u && all == ~0u) {
         sat |= 1u << (i - 1);
+        found();
         if (PCSA)
 #pragma unroll
           for (int w = 0; w < W; ++w) Q[w] = (uint32_t)(i - 1) * 0x01010101u;  // no active DR: the run restarts below
         continue;
       }
-      DrWords<W> nd;
-      if (kk) {  // k <= 128: the active test on bit 7; M holds bit-7 flags of the BDRs whose register is found
+      DrWords<W> x = d[j], nd;
+      if constexpr (!FAST) {
+        if (bits)
 #pragma unroll
-        for (int w = 0; w < W; ++w) {
-          uint32_t x = d[j].v[w];
-          if constexpr (!FAST) x &= ~swar_nibble_to_bytes((bits >> (4 * w)) & 0xFu);  // SetDR of the slice
-          uint32_t y = swar_sat_inc(x);                                                // SlideDR
-          if constexpr (FAST) y &= ~swar_nibble_to_bytes((fold >> (4 * w)) & 0xFu);   // SetDR
-          const uint32_t a7 = swar_lt_bit7(FAST ? y : x, kk);                          // IsActiveDR
-          R[w] += ((a7 & ~M[w]) >> 7) * (uint32_t)i;  // bytes still 0 take i: no carry between bytes
-          M[w] |= a7;
-          if (PCSA) {
-            const uint32_t act = (a7 >> 7) * 0xFFu;
-            Q[w] = (Q[w] & act) | (~act & ((uint32_t)(i - 1) * 0x01010101u));
-          }
-          nd.v[w] = y;
-        }
+          for (int w = 0; w < W; ++w) x.v[w] = swar_zero_bytes(x.v[w], (bits >> (4 * w)) & 0xFu);  // SetDR of the slice
+      }
+#pragma unroll
+      for (int w = 0; w < W; ++w) nd.v[w] = swar_sat_inc(x.v[w]);  // SlideDR
+      if constexpr (FAST) {
+        if (fold)
+#pragma unroll
+          for (int w = 0; w < W; ++w) nd.v[w] = swar_zero_bytes(nd.v[w], (fold >> (4 * w)) & 0xFu);  // SetDR
+      }
+      const DrWords<W>& v = FAST ? nd : x;  // the DRs that the window is read from
+      uint32_t a7[W];                      // IsActiveDR: bit 7
+      if (kk) {
+#pragma unroll
+        for (int w = 0; w < W; ++w) a7[w] = swar_lt_bit7(v.v[w], kk);
       } else {
 #pragma unroll
-        for (int w = 0; w < W; ++w) {
-          uint32_t x = d[j].v[w];
-          if constexpr (!FAST) x &= ~swar_nibble_to_bytes((bits >> (4 * w)) & 0xFu);  // SetDR of the slice
-          uint32_t y = swar_sat_inc(x);                                                // SlideDR
-          if constexpr (FAST) y &= ~swar_nibble_to_bytes((fold >> (4 * w)) & 0xFu);   // SetDR
-          const uint32_t act = swar_le_mask(FAST ? y : x, gt_bias);                    // IsActiveDR
-          R[w] |= act & ~M[w] & ((uint32_t)i * 0x01010101u);
-          M[w] |= act;
-          if (PCSA) Q[w] = (Q[w] & act) | (~act & ((uint32_t)(i - 1) * 0x01010101u));
-          nd.v[w] = y;
-        }
+        for (int w = 0; w < W; ++w) a7[w] = swar_le_mask(v.v[w], gt_bias) & 0x80808080u;
       }
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        M[w] |= a7[w];
+        // an inactive DR: the run restarts below; an active one keeps it
+        if (PCSA) Q[w] = __builtin_amdgcn_perm((uint32_t)(i - 1) * 0x01010101u, Q[w], 0x07060504u - (a7[w] >> 5));
+      }
+      found();
       store_dr_changed<W>(dr + (uint64_t)(i - 1) * mstride + base, nd, d[j]);
       all = ~0u;
 #pragma unroll
@@ -331,6 +352,9 @@ __device__ __forceinline__ void advance_words(uint8_t* dr, uint64_t mstride, uin
     process(top - G, b);
   }
   sat_out = sat;
+  if (lo > 1)  // the planes below lo count too
+#pragma unroll
+    for (int w = 0; w < W; ++w) R[w] += (M[w] >> 7) * (uint32_t)(lo - 1);
 }
 
 // The registers of 4 W BDRs as nibbles min(r, 15).
