@@ -1058,7 +1058,7 @@ __global__ __launch_bounds__(kEstBlock) void k_estimate_part(const uint32_t* __r
                                                              uint32_t part_shift,
                                                              unsigned long long* __restrict__ part_u,
                                                              uint32_t* __restrict__ part_v, uint32_t pstride,
-                                                             uint32_t* __restrict__ hout) {
+                                                             uint32_t* __restrict__ hout, uint32_t hstride) {
   extern __shared__ uint32_t s1_lds[];
   __shared__ uint32_t lh[kEstWaves][kBins];
   const uint32_t* s1 = s1g;
@@ -1086,7 +1086,7 @@ __global__ __launch_bounds__(kEstBlock) void k_estimate_part(const uint32_t* __r
     if constexpr (HIST) {
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      if (lane < kBins) hout[((uint64_t)x * kLearnChunk + h) * kBins + lane] = lh[wave][lane];
+      if (lane < kBins) hout[((uint64_t)x * hstride + h) * kBins + lane] = lh[wave][lane];
       __builtin_amdgcn_wave_barrier();
     } else {
       U = wave_sum_u64(U);
@@ -1123,6 +1123,39 @@ __global__ __launch_bounds__(kRowBlock) void k_estimate_part_rows(const uint32_t
       part_u[(uint64_t)x * pstride + h + lane] = U;
       part_v[(uint64_t)x * pstride + h + lane] = V;
     }
+  }
+}
+
+// Register histograms (hist_hosts) of nh hosts, [x][h][33]; with PART those of the
+// registers in range x = blockIdx mod parts.
+template <int LPH, bool PART>
+__global__ __launch_bounds__(kRowBlock) void k_hist_rows(const uint32_t* __restrict__ hosts, uint32_t nh,
+                                                         const uint32_t* __restrict__ s1g, uint32_t g, uint32_t m,
+                                                         const uint8_t* __restrict__ reg,
+                                                         const uint8_t* __restrict__ reg4, uint32_t parts,
+                                                         uint32_t part_shift, uint32_t* __restrict__ hout,
+                                                         uint32_t hstride) {
+  extern __shared__ uint32_t lds[];
+  constexpr int kRows = 64 / LPH, kWaves = kRowBlock / 64;
+  __shared__ uint32_t rows[kWaves][kRows * kBins];
+  for (uint32_t i = threadIdx.x; i < g; i += kRowBlock) lds[i] = s1g[i];
+  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  for (uint32_t i = lane; i < kRows * kBins; i += 64) rows[wave][i] = 0;
+  __syncthreads();
+  const uint32_t x = blockIdx.x % parts, tiles = gridDim.x / parts;
+  for (uint32_t h0 = ((blockIdx.x / parts) * kWaves + wave) * kRows; h0 < nh; h0 += tiles * kWaves * kRows) {
+    const uint32_t h = h0 + lane / LPH;
+    hist_hosts<LPH, PART>(mm3_key(hosts[h < nh ? h : nh - 1]), lds, g, m, reg, reg4, x, part_shift,
+                          rows[wave] + lane / LPH * kBins);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t n = (nh - h0 < kRows ? nh - h0 : kRows) * kBins;  // the hosts' rows are contiguous
+    for (uint32_t i = lane; i < kRows * kBins; i += 64) {
+      if (i < n) hout[((uint64_t)x * hstride + h0) * kBins + i] = rows[wave][i];
+      rows[wave][i] = 0;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
@@ -2083,27 +2116,58 @@ int vbdr_check_device(const vbdr_sketch* sk) {
   return VBDR_OK;
 }
 
+// Pool ranges of the XCD-partitioned gathers: as few as let a range's nibbles
+// fit one XCD's L2 (4 MB), since every range hashes every (host, i).
+uint32_t vbdr_gather_parts(const vbdr_sketch* sk) {
+  uint32_t p = 1;
+  while (p < 8u && (sk->mstride / 2) / p > kRangeBytes) p *= 2;
+  const uint32_t most = (uint32_t)(sk->parts == 8 ? sk->tune.est_parts : sk->parts);
+  return p < most ? p : most;
+}
+
+uint32_t vbdr_hist_chunk(const vbdr_sketch* sk) {  // est_parts may shrink the ranges, never hist_ws
+  return kLearnChunk * ((uint32_t)sk->parts / vbdr_gather_parts(sk));
+}
+
 int vbdr_hist_pass(vbdr_sketch* sk, const uint32_t* hosts_dev, uint32_t nh, hipStream_t st) {
   if (nh == 0) return VBDR_OK;
-  if (nh > kLearnChunk) return vbdr_fail(VBDR_EINVAL, "histogram pass of %u hosts exceeds %u", nh, kLearnChunk);
-  const bool stage = sk->g <= kStageMaxG;
-  const size_t lds = stage ? (size_t)sk->g * 4 : 0;
-  if (sk->parts > 1) {
-    const uint32_t parts = (uint32_t)sk->parts, shift = parts == 8 ? 29u : 30u;
-    const uint64_t want = (nh + kEstWaves - 1) / kEstWaves;
-    const uint64_t cap = (uint64_t)sk->n_cu * sk->tune.est_blocks_per_cu / parts;
-    const uint32_t tiles = (uint32_t)(want < cap ? want : (cap ? cap : 1));
-    auto kern = stage ? k_estimate_part<true, true> : k_estimate_part<false, true>;
-    hipLaunchKernelGGL(kern, dim3(tiles * parts), dim3(kEstBlock), lds, st, hosts_dev, nh, sk->s1, sk->g,
-                       (uint32_t)sk->m, sk->reg, sk->reg4, parts, shift, sk->part_u, sk->part_v, kPartChunk,
-                       sk->hist_ws);
+  const uint32_t parts = vbdr_gather_parts(sk), chunk = vbdr_hist_chunk(sk), g = sk->g;
+  if (nh > chunk) return vbdr_fail(VBDR_EINVAL, "histogram pass of %u hosts exceeds %u", nh, chunk);
+  uint32_t shift = 31;
+  while (parts > 1 && (1u << (32 - shift)) < parts) --shift;
+  const uint64_t cap = (uint64_t)sk->n_cu * 8 / parts;
+  if (g <= kStageMaxG && parts <= kHistRowsParts) {
+    // 16 lanes a host (hist_hosts: at most 128 registers a lane); a wave a host while that keeps its waves
+    // few (features of 64 hosts, g = 2048: 23.2 us with 16 lanes, 12.4 with a wave, host path included)
+    const bool rows = g <= 2048 && nh >= (uint32_t)sk->n_cu * 8;
+    const uint32_t per = (rows ? 4u : 1u) * (kRowBlock / 64);
+    const uint64_t want = (nh + per - 1) / per;
+    const uint32_t tiles = (uint32_t)(want < cap ? want : cap);
+    const auto kern = parts > 1 ? (rows ? k_hist_rows<16, true> : k_hist_rows<64, true>)
+                                : (rows ? k_hist_rows<16, false> : k_hist_rows<64, false>);
+    hipLaunchKernelGGL(kern, dim3(tiles * parts), dim3(kRowBlock), (size_t)g * 4, st, hosts_dev, nh, sk->s1, g,
+                       (uint32_t)sk->m, sk->reg, sk->reg4, parts, shift, sk->hist_ws, chunk);
+    VBDR_LAUNCHED("k_hist_rows");
+    return VBDR_OK;
+  }
+  const uint64_t want = (nh + kEstWaves - 1) / kEstWaves;
+  if (parts > 1) {
+    const bool stage = g <= kStageMaxG;
+    const uint64_t most = (uint64_t)sk->n_cu * sk->tune.est_blocks_per_cu / parts;
+    const uint32_t tiles = (uint32_t)(want < most ? want : (most ? most : 1));
+    const auto kern = stage ? k_estimate_part<true, true> : k_estimate_part<false, true>;
+    hipLaunchKernelGGL(kern, dim3(tiles * parts), dim3(kEstBlock), stage ? (size_t)g * 4 : 0, st, hosts_dev, nh,
+                       sk->s1, g, (uint32_t)sk->m, sk->reg, sk->reg4, parts, shift, sk->part_u, sk->part_v, kPartChunk,
+                       sk->hist_ws, chunk);
     VBDR_LAUNCHED("k_estimate_part(hist)");
   } else {
-    const uint32_t grid = grid_cap(sk, (nh + kEstWaves - 1) / kEstWaves, sk->tune.est_blocks_per_cu);
-    auto kern = stage ? k_estimate<true, true> : k_estimate<false, true>;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kEstBlock), lds, st, hosts_dev, (uint64_t)nh, sk->s1, sk->g,
-                       (uint32_t)sk->m, sk->reg, sk->hist, sk->est_ws, nullptr, sk->hist_ws);
-    VBDR_LAUNCHED("k_estimate(hist)");
+    for (uint32_t c = 0; c < nh; c += kLearnChunk) {  // est_ws holds that many
+      const uint32_t n = nh - c < kLearnChunk ? nh - c : kLearnChunk;
+      hipLaunchKernelGGL((k_estimate<false, true>), dim3(grid_cap(sk, (n + kEstWaves - 1) / kEstWaves,
+                         sk->tune.est_blocks_per_cu)), dim3(kEstBlock), 0, st, hosts_dev + c, (uint64_t)n, sk->s1, g,
+                         (uint32_t)sk->m, sk->reg, sk->hist, sk->est_ws, nullptr, sk->hist_ws + (uint64_t)c * kBins);
+      VBDR_LAUNCHED("k_estimate(hist)");
+    }
   }
   return VBDR_OK;
 }
@@ -2365,22 +2429,13 @@ int create_sketch(uint64_t m, uint32_t g, uint32_t k, uint64_t hash_seed, int la
 
 namespace {
 
-// Pool ranges of the XCD-partitioned gathers: as few as let a range's nibbles
-// fit one XCD's L2 (4 MB), since every range hashes every (host, i).
-uint32_t gather_parts(const vbdr_sketch* sk) {
-  uint32_t p = 1;
-  while (p < 8u && (sk->mstride / 2) / p > kRangeBytes) p *= 2;
-  const uint32_t most = (uint32_t)(sk->parts == 8 ? sk->tune.est_parts : sk->parts);
-  return p < most ? p : most;
-}
-
 // The XCD-partitioned estimate: hosts in chunks of pstride, per-range partial
 // sums in part_u / part_v ([parts][pstride] each), then the FP64 epilogue.
 int estimate_partitioned(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_hosts, float* out_dev,
                          unsigned long long* part_u, uint32_t* part_v, uint32_t pstride, hipStream_t st) {
   const bool stage = sk->g <= kStageMaxG;
   const size_t lds = stage ? (size_t)sk->g * 4 : 0;
-  const uint32_t parts = gather_parts(sk);
+  const uint32_t parts = vbdr_gather_parts(sk);
   uint32_t shift = 32;
   while ((1u << (32 - shift)) < parts) --shift;
   for (uint64_t c = 0; c < n_hosts; c += pstride) {
@@ -2401,7 +2456,7 @@ int estimate_partitioned(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_
       const uint32_t tiles = (uint32_t)(want < cap ? want : (cap ? cap : 1));
       hipLaunchKernelGGL((k_estimate_part<false, false>), dim3(tiles * parts), dim3(kEstBlock), 0, st, hosts_dev + c, nh,
                          sk->s1, sk->g, (uint32_t)sk->m, sk->reg, sk->reg4, parts, shift, part_u, part_v, pstride,
-                         nullptr);
+                         nullptr, 0u);
       VBDR_LAUNCHED("k_estimate_part");
     }
     hipLaunchKernelGGL(k_estimate_final, dim3((nh + 255) / 256), dim3(256), 0, st, nh, sk->g, (uint32_t)sk->m, parts,
@@ -2415,7 +2470,7 @@ int estimate_partitioned(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_
 // Estimates gathered from L2 (or memory): directly where the nibbles fit one
 // XCD's L2 or there are too few gathers for it to matter, else partitioned.
 bool gathers_direct(const vbdr_sketch* sk, uint64_t n_hosts) {
-  return gather_parts(sk) == 1 || n_hosts * sk->g < kPartMinGathers;
+  return vbdr_gather_parts(sk) == 1 || n_hosts * sk->g < kPartMinGathers;
 }
 
 // LDS bytes of k_estimate_rows.
@@ -2424,21 +2479,28 @@ constexpr size_t kRowsLds = 152u << 10;
 // The direct estimate without extra outputs, g <= kStageMaxG.
 int estimate_rows(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_hosts, float* out_dev, hipStream_t st) {
   const uint32_t g = sk->g;
-  // 16 lanes a host once that fills the CUs with waves; a wave a host below
-  const uint64_t fill = (uint64_t)sk->n_cu * (kTabBlock / 64);
-  const bool rows = n_hosts >= fill;
-  // a table in LDS pays where it holds a good part of the registers and a CU gathers more than it loads
+  const uint64_t fill = (uint64_t)sk->n_cu * (kTabBlock / 64);  // waves that fill the CUs
+  // A table in LDS pays where it holds a good part of the registers, a CU gathers more than it loads and
+  // has most of its waves (g = 2048, 1000 hosts, 0.9 2^21 BDRs: with a table 18.8 us, without 12.2; 3000: 27.0, 27.3)
   uint64_t tab = (kRowsLds - (size_t)g * 4) * 2 / 32 * 32;
   if (tab > sk->mstride) tab = sk->mstride;
-  const bool table = sk->m <= kTableMaxM && n_hosts * g >= tab * kTableMinUse;
+  const bool table = sk->m <= kTableMaxM && n_hosts * g >= tab * kTableMinUse &&
+                     n_hosts >= (sk->m <= tab ? fill * 3 / 8 : fill * 5 / 8);
+  // A host takes 16 lanes where that still fills the CUs, else a wave (4096 hosts, g = 2048, 0.9 2^20 BDRs: 45
+  // and 25 us).  A CU has one workgroup with a table, so there the whole rounds count too: a wave's round of
+  // four hosts against four rounds of one, where the gathers and not the sums fill them (20000 hosts, 0.9 2^20
+  // BDRs, g = 2048: 127 and 106 us; 50000, 0.9 2^16, g = 128: 11.6 and 19.9).
+  const uint64_t rounds16 = (n_hosts + 4 * fill - 1) / (4 * fill), rounds64 = (n_hosts + fill - 1) / fill;
+  const bool rows = n_hosts >= 4 * fill && (!table || g <= 256 || 4 * rounds16 <= rounds64);
   const uint32_t waves = table ? kTabBlock / 64 : kRowBlock / 64;
   const uint32_t least = rows ? 4 : 1;
-  const uint64_t cap_waves = (uint64_t)sk->n_cu * (table ? kTabBlock / 64 : 2048 / 64);
+  const uint64_t cap_waves = table ? fill : (uint64_t)sk->n_cu * (2048 / 64);
   uint64_t per = (n_hosts + cap_waves - 1) / cap_waves;
   per = (per + least - 1) / least * least;
-  const uint32_t per_wave = (uint32_t)(per < least ? least : per > 64 ? 64 : per);
+  const uint64_t most = table ? 64 : 4;  // without a table, many workgroups that the CUs even out
+  const uint32_t per_wave = (uint32_t)(per < least ? least : per > most ? most : per);
   const uint64_t want = ((n_hosts + per_wave - 1) / per_wave + waves - 1) / waves;
-  const uint32_t grid = (uint32_t)(want < cap_waves / waves ? want : cap_waves / waves);
+  const uint32_t grid = grid_cap(sk, want, table ? 1 : 1024);
   const bool stage = table || per_wave * waves >= 16;
   const size_t lds = (table ? tab / 2 : 0) + (stage ? (size_t)g * 4 : 0);
   const auto kern = table ? (rows ? k_estimate_rows<16, true, true> : k_estimate_rows<64, true, true>)
@@ -2736,7 +2798,7 @@ int vbdr_estimate_ex(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_host
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const bool extra = raw_es_dev || hist_dev;
   if (sk->tl_rec && sk->tune.est_binned == 3 && !extra && n_hosts < (1ull << 32) &&
-      (sk->tl_always || n_hosts * sk->g >= (gather_parts(sk) < 8 ? kTileMinGathers : kTileMinGathers8))) {
+      (sk->tl_always || n_hosts * sk->g >= (vbdr_gather_parts(sk) < 8 ? kTileMinGathers : kTileMinGathers8))) {
     uint32_t B = sk->tl_Balloc;  // the block the workspace holds (tiled_block_hosts of the tuning)
     {  // blocks of equal size (whole sub-blocks): no small last block (line rate: 2^19 + 102,494 hosts 1.85 ms,
        // 2 x 313,391 1.81 ms)
@@ -2870,7 +2932,7 @@ int vbdr_estimate_noalloc(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n
   if (int rc = vbdr_check_device(sk)) return rc;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (gathers_direct(sk, n_hosts)) return estimate_direct(sk, hosts_dev, n_hosts, out_dev, nullptr, nullptr, st);
-  const uint32_t parts = gather_parts(sk);
+  const uint32_t parts = vbdr_gather_parts(sk);
   if ((uint64_t)parts * kNoAllocHosts * (8 + 4) > kNoAllocBytes)
     return vbdr_fail(VBDR_EINVAL, "%u pool ranges need more than the %llu bytes of static scratch", parts,
                      (unsigned long long)kNoAllocBytes);

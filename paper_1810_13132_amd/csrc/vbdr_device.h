@@ -15,6 +15,10 @@ struct TrueType {
 struct FalseType {
   static constexpr bool value = false;
 };
+template <int N>
+struct Int {
+  static constexpr int value = N;
+};
 
 constexpr int kBins = 33;     // register values 0..32
 constexpr uint32_t kSat = 255; // DR saturation value (InitDR with z = 8)
@@ -426,7 +430,7 @@ __device__ __forceinline__ void gather_hosts(const uint32_t* __restrict__ hosts,
                                              uint32_t g, uint32_t m, const uint8_t* __restrict__ reg,
                                              const uint8_t* __restrict__ reg4, const uint8_t* tab, uint32_t tab_n,
                                              uint32_t part, uint32_t part_shift, uint64_t& U, uint32_t& V) {
-  constexpr int kRows = 64 / LPH, kFlight = LPH == 64 ? 4 : 8;  // hosts at a time; gathers in flight per lane
+  constexpr int kRows = 64 / LPH;  // hosts at a time
   const int lane = threadIdx.x & 63, q = lane / LPH, ql = lane % LPH;
   const uint32_t kmix = mm3_key((uint32_t)lane < n ? hosts[lane] : 0u);
   U = 0;
@@ -435,8 +439,9 @@ __device__ __forceinline__ void gather_hosts(const uint32_t* __restrict__ hosts,
     const uint32_t km = (uint32_t)__shfl((int)kmix, (int)(t * kRows) + q);
     uint32_t Us = 0, Vs = 0;
     unsigned long long Ux = 0;
-    auto gathers = [&](auto guard) __attribute__((always_inline)) {
+    auto gathers = [&](auto guard, auto flight) __attribute__((always_inline)) {
       constexpr bool GUARD = decltype(guard)::value;
+      constexpr int kFlight = decltype(flight)::value;  // gathers in flight per lane
       for (uint32_t i0 = (uint32_t)ql; i0 < g; i0 += LPH * kFlight) {
         uint32_t p[kFlight], nib[kFlight];
         bool mine[kFlight];
@@ -467,8 +472,9 @@ __device__ __forceinline__ void gather_hosts(const uint32_t* __restrict__ hosts,
             if (nib[u] == 15u) Ux += 1ull << (32 - reg[p[u]]);
       }
     };
-    if (g % (LPH * kFlight) == 0) gathers(FalseType{});
-    else gathers(TrueType{});
+    if (g % (LPH * 8) == 0) gathers(FalseType{}, Int<8>{});
+    else if (LPH == 16) gathers(TrueType{}, Int<8>{});
+    else gathers(TrueType{}, Int<4>{});
     Us = row_sum<LPH>(Us);
     Vs = row_sum<LPH>(Vs);
     // lane l keeps host l: row l % kRows of step l / kRows
@@ -477,6 +483,76 @@ __device__ __forceinline__ void gather_hosts(const uint32_t* __restrict__ hosts,
     if (__builtin_amdgcn_ballot_w64(Ux != 0ull)) u64 += __shfl(row_sum<LPH>(Ux), from);
     const uint32_t vs = (uint32_t)__shfl((int)Vs, from);
     if ((uint32_t)lane / kRows == t) U = u64, V = vs;
+  }
+}
+
+// Register histograms of 64 / LPH hosts by one wave, LPH lanes each (kmix: the
+// key of this lane's host), added to this lane's host's row of 33 counts in LDS,
+// which is zero before.  Each lane counts nibbles below 15 in registers: four bits a
+// value over eight gathers, then bytes (a lane sees at most 128 registers), then
+// the lanes' 16-bit sums, halving the values each lane keeps; registers of 15
+// and more are read from the byte array and counted with LDS atomics (an LDS
+// atomic per register kept whole waves on a few values).  PART as in
+// gather_hosts.  g <= 128 LPH.
+template <int LPH, bool PART>
+__device__ __forceinline__ void hist_hosts(uint32_t kmix, const uint32_t* s1, uint32_t g, uint32_t m,
+                                           const uint8_t* __restrict__ reg, const uint8_t* __restrict__ reg4,
+                                           uint32_t part, uint32_t part_shift, uint32_t* row) {
+  const uint32_t ql = threadIdx.x % LPH;
+  uint64_t even = 0, odd = 0;  // byte j: count of value 2j, 2j + 1
+  auto gathers = [&](auto flight) __attribute__((always_inline)) {
+    constexpr int kFlight = decltype(flight)::value;  // gathers in flight per lane
+    for (uint32_t i0 = ql; i0 < g; i0 += LPH * kFlight) {
+      uint32_t p[kFlight], nib[kFlight];
+      bool mine[kFlight];
+#pragma unroll
+      for (int u = 0; u < kFlight; ++u) {
+        const uint32_t i = i0 + (uint32_t)(LPH * u);
+        const uint32_t h = mm3_seeded(kmix, s1[i < g ? i : 0u]);
+        p[u] = reduce_m(h, m);
+        mine[u] = i < g && (!PART || h >> part_shift == part);
+      }
+#pragma unroll
+      for (int u = 0; u < kFlight; ++u) nib[u] = mine[u] ? (uint32_t)reg4[p[u] >> 1] : 0u;
+      uint64_t acc = 0;
+      bool wide = false;
+#pragma unroll
+      for (int u = 0; u < kFlight; ++u) {
+        nib[u] = __builtin_amdgcn_ubfe(nib[u], (p[u] & 1u) << 2, 4);
+        acc += (uint64_t)mine[u] << (4 * nib[u]);
+        wide |= mine[u] && nib[u] == 15u;
+      }
+      even += acc & 0x0F0F0F0F0F0F0F0Full;
+      odd += acc >> 4 & 0x0F0F0F0F0F0F0F0Full;
+      if (wide)
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u)
+          if (mine[u] && nib[u] == 15u) atomicAdd(&row[reg[p[u]]], 1u);
+    }
+  };
+  if (!PART && g <= LPH * 4) gathers(Int<4>{});  // PART with both: 36 registers a lane for 32, 677 us for 630
+  else gathers(Int<8>{});
+  constexpr uint64_t kLow = 0x00FF00FF00FF00FFull;
+  const uint64_t v[4] = {even & kLow, even >> 8 & kLow, odd & kLow, odd >> 8 & kLow};
+  uint32_t w[8];  // two values a word: 0 4 | 8 12 | 2 6 | 10 14 | 1 5 | 9 13 | 3 7 | 11 15
+#pragma unroll
+  for (int q = 0; q < 4; ++q) w[2 * q] = (uint32_t)v[q], w[2 * q + 1] = (uint32_t)(v[q] >> 32);
+#pragma unroll
+  for (int d = 1, n = 4; d < 8; d <<= 1, n >>= 1) {  // lanes with bit d keep the upper half
+    const bool up = ql & d;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (q >= n) break;
+      const uint32_t got = (uint32_t)__shfl_xor((int)(up ? w[q] : w[q + n]), d);
+      w[q] = (up ? w[q + n] : w[q]) + got;
+    }
+  }
+#pragma unroll
+  for (int d = 8; d < LPH; d <<= 1) w[0] += (uint32_t)__shfl_xor((int)w[0], d);
+  if (ql < 8) {
+    const uint32_t value = (ql & 1u) + (ql & 2u) + 2u * (ql & 4u);
+    atomicAdd(&row[value], w[0] & 0xFFFFu);
+    if (value != 11u) atomicAdd(&row[value + 4u], w[0] >> 16);
   }
 }
 

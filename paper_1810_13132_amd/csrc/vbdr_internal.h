@@ -12,7 +12,10 @@ constexpr uint32_t kStageMaxG = 8192;       // s1 staged in LDS up to 32 KiB
 constexpr uint32_t kCusPerXcd = 32;         // gfx950: 8 XCDs x 32 CUs
 constexpr uint64_t kPartMinM = 1ull << 22;  // pools whose registers outgrow one XCD's L2
 constexpr uint32_t kPartChunk = 1u << 20;   // hosts per partitioned-estimate pass
-constexpr uint32_t kLearnChunk = 1u << 15;  // hosts per histogram pass of the learned estimate
+// Histograms counted in registers up to this many ranges, with LDS atomics above, where most lanes of a gather idle
+// (g = 2048: 2 ranges 2.4e11 gathers a second and 2.0e11, 8 ranges 1.2e11 and 1.6e11).
+constexpr uint32_t kHistRowsParts = 2;
+constexpr uint32_t kLearnChunk = 1u << 15;  // hosts per histogram pass whose histograms come in sk->parts ranges
 constexpr uint64_t kBinMaxM = 1ull << 27;   // binned scan records pack (pidx << 5) | (LBP1 - 1)
 constexpr uint32_t kBinChunk = 1u << 24;    // pairs per binned-scan pass (records stay cache resident)
 constexpr uint32_t kBinCap = kBinChunk / 8 + kBinChunk / 32 + 65536;  // records per bin per pass
@@ -65,7 +68,7 @@ struct vbdr_sketch {
   int parts;                   // XCD partitions of the estimate (1 = direct gather)
   unsigned long long* part_u;  // [parts][kPartChunk] partial harmonic sums
   uint32_t* part_v;            // [parts][kPartChunk] partial zero counts
-  uint32_t* hist_ws;           // [parts][kLearnChunk][33] per-host (partial) histograms
+  uint32_t* hist_ws;           // per-host (partial) histograms of a pass, parts * kLearnChunk * 33 counts
   float* est_ws;               // [kLearnChunk] plain estimates of a histogram pass
   uint32_t* bins;              // [parts][kBinCap] binned scan records (large pools)
   uint32_t* bin_fill;          // [parts] records written per bin
@@ -183,7 +186,9 @@ inline hipError_t vbdr_malloc(T** p, size_t bytes) {
 // VBDR_EINVAL unless the sketch's device is current.
 int vbdr_check_device(const vbdr_sketch* sk);
 
-// Register histograms of nh <= kLearnChunk hosts into sk->hist_ws: with
-// sk->parts == 1 one full histogram per host ([h][33]); otherwise one partial
-// histogram per XCD range ([x][h][33]), to be summed over x.
+// Register histograms of nh <= vbdr_hist_chunk(sk) hosts into sk->hist_ws: one
+// partial histogram per pool range, [x][vbdr_hist_chunk(sk)][33], to be summed
+// over the vbdr_gather_parts(sk) ranges x.
+uint32_t vbdr_gather_parts(const vbdr_sketch* sk);
+uint32_t vbdr_hist_chunk(const vbdr_sketch* sk);
 int vbdr_hist_pass(vbdr_sketch* sk, const uint32_t* hosts_dev, uint32_t nh, hipStream_t st);

@@ -65,20 +65,23 @@ __device__ __forceinline__ float gelu_inf(float x) {
 }
 
 // ------------------------------------------------------------ features
-// fp32 features of nh hosts from the histogram pass: [h][67].
-__global__ __launch_bounds__(256) void k_features(uint32_t nh, uint32_t parts, const uint32_t* __restrict__ hws,
+// fp32 features of nh hosts from the histogram pass: [h][67], a thread per value.
+__global__ __launch_bounds__(256) void k_features(uint32_t nh, uint32_t parts, uint32_t hstride,
+                                                  const uint32_t* __restrict__ hws,
                                                   const unsigned long long* __restrict__ hist, uint32_t g, uint32_t m,
                                                   float* __restrict__ feats) {
-  const uint32_t h = blockIdx.x * 256 + threadIdx.x;
-  if (h >= nh) return;
-  float* f = feats + (uint64_t)h * kIn;
-  for (int r = 0; r < kBins; ++r) {
-    uint32_t c = 0;
-    for (uint32_t x = 0; x < parts; ++x) c += hws[((uint64_t)x * kLearnChunk + h) * kBins + r];
-    f[r] = (float)((double)c / (double)g);
-    f[kBins + r] = (float)((double)hist[r] / (double)m);
+  const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (uint64_t)nh * kIn) return;
+  const uint32_t h = (uint32_t)(i / kIn), c = (uint32_t)(i - (uint64_t)h * kIn);
+  if (c < kBins) {
+    uint32_t n = 0;
+    for (uint32_t x = 0; x < parts; ++x) n += hws[((uint64_t)x * hstride + h) * kBins + c];
+    feats[i] = (float)((double)n / (double)g);
+  } else if (c < 2 * kBins) {
+    feats[i] = (float)((double)hist[c - kBins] / (double)m);
+  } else {
+    feats[i] = (float)log((double)g / (double)m);
   }
-  f[2 * kBins] = (float)log((double)g / (double)m);
 }
 
 // ----------------------------------------------------------- inference
@@ -107,28 +110,35 @@ __device__ __forceinline__ bf16x8 pack8(const float* v) {
 
 // DIRECT: each wave gathers its 16 hosts' registers itself (pools whose
 // registers are cache resident) into an LDS histogram per host; otherwise
-// the histograms come from a histogram pass (hws, summed over parts).  Five
-// waves per SIMD (at most 102 registers) keep enough gathers in flight.
-template <bool DIRECT>
-__global__ __launch_bounds__(kInfBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_learned(uint32_t nh, uint32_t parts, const uint32_t* __restrict__ hws,
-                                                       const uint32_t* __restrict__ hosts,
-                                                       const uint32_t* __restrict__ s1g, const uint8_t* __restrict__ reg,
-                                                       const unsigned long long* __restrict__ hist, uint32_t g,
-                                                       uint32_t m, const MlpDev* __restrict__ mlp,
-                                                       float* __restrict__ out, uint8_t* __restrict__ used_fallback) {
+// the histograms come from a histogram pass (hws, summed over parts).
+// SPREAD, for few hosts: a workgroup of 16 waves gathers one tile, a wave a host,
+// and its first wave goes on; four rounds of four hosts by one wave left the
+// chip idle behind a chain of gathers (64 hosts, host path included: g = 64
+// 13.8 -> 10.9 us, g = 1024 42.8 -> 15.4, g = 2048 70.3 -> 22.8; 8192 hosts and
+// g = 1024: 50.4 -> 46.3, but g = 256: 21.7 -> 22.2).  At most 128 registers a
+// thread: 96 (five waves a SIMD) spilled, 50000 hosts and g = 64 26.4 -> 22.3 us.
+constexpr int kSpreadBlock = 16 * 64;
+constexpr uint32_t kSpreadWideG = 1024;  // from which two workgroups a CU still pay
+template <bool DIRECT, bool SPREAD = false>
+__global__ __launch_bounds__(SPREAD ? kSpreadBlock : kInfBlock) __attribute__((amdgpu_waves_per_eu(4)))
+void k_learned(uint32_t nh, uint32_t parts, uint32_t hstride, const uint32_t* __restrict__ hws,
+               const uint32_t* __restrict__ hosts, const uint32_t* __restrict__ s1g, const uint8_t* __restrict__ reg,
+               const uint8_t* __restrict__ reg4, const unsigned long long* __restrict__ hist, uint32_t g, uint32_t m,
+               const MlpDev* __restrict__ mlp, float* __restrict__ out, uint8_t* __restrict__ used_fallback) {
+  constexpr int kBlock = SPREAD ? kSpreadBlock : kInfBlock, kTiles = SPREAD ? 1 : kInfWaves;
   extern __shared__ uint32_t s1_lds[];
   __shared__ __attribute__((aligned(16))) uint16_t sw1[kHid * kInPad];
   __shared__ __attribute__((aligned(16))) uint16_t sw2[kHid * kHid];
-  __shared__ __attribute__((aligned(16))) uint32_t lh[kInfWaves][16 * kHistStride];
+  __shared__ __attribute__((aligned(16))) uint32_t lh[kTiles][16 * kHistStride];
   __shared__ __attribute__((aligned(16))) uint16_t sconst[kInPad];  // bf16 features 33..95 (pool, ln(g/m), 0)
   __shared__ float sb1[kHid], sb2[kHid], sw3[kHid], senv_lo[kBins], senv_hi[kBins];
   __shared__ int spool_bad;
   __shared__ double sem;
-  for (int i = threadIdx.x; i < kHid * kInPad / 8; i += kInfBlock)
+  for (int i = threadIdx.x; i < kHid * kInPad / 8; i += kBlock)
     reinterpret_cast<uint4*>(sw1)[i] = reinterpret_cast<const uint4*>(mlp->w1)[i];
-  for (int i = threadIdx.x; i < kHid * kHid / 8; i += kInfBlock)
+  for (int i = threadIdx.x; i < kHid * kHid / 8; i += kBlock)
     reinterpret_cast<uint4*>(sw2)[i] = reinterpret_cast<const uint4*>(mlp->w2p)[i];
-  for (int i = threadIdx.x; i < kInfWaves * 16 * kHistStride; i += kInfBlock) (&lh[0][0])[i] = 0;
+  for (int i = threadIdx.x; i < kTiles * 16 * kHistStride; i += kBlock) (&lh[0][0])[i] = 0;
   if (threadIdx.x < kHid) {
     sb1[threadIdx.x] = mlp->b1[threadIdx.x];
     sb2[threadIdx.x] = mlp->b2[threadIdx.x];
@@ -143,7 +153,7 @@ __global__ __launch_bounds__(kInfBlock) __attribute__((amdgpu_waves_per_eu(5))) 
     spool_bad = 0;
   }
   if constexpr (DIRECT)
-    for (uint32_t i = threadIdx.x; i < g; i += kInfBlock) s1_lds[i] = s1g[i];
+    for (uint32_t i = threadIdx.x; i < g; i += kBlock) s1_lds[i] = s1g[i];
   __syncthreads();
   if (threadIdx.x < kInPad) {
     const int c = threadIdx.x;
@@ -159,9 +169,9 @@ __global__ __launch_bounds__(kInfBlock) __attribute__((amdgpu_waves_per_eu(5))) 
   const float inv_g = 1.0f / (float)g;  // g is a power of two: c * inv_g == c / g exactly
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int col = lane & 15, q = lane >> 4;
-  uint32_t* H = lh[wave];
+  uint32_t* H = lh[SPREAD ? 0 : wave];
   const uint32_t ntiles = (nh + 15) / 16;
-  for (uint32_t tile = blockIdx.x * kInfWaves + wave; tile < ntiles; tile += gridDim.x * kInfWaves) {
+  for (uint32_t tile = blockIdx.x * kTiles + (SPREAD ? 0 : wave); tile < ntiles; tile += gridDim.x * kTiles) {
     // An offset opaque to the compiler: the weights, biases and envelope are
     // read from LDS per tile instead of being pinned in ~150 registers across
     // the loop, which would cut the waves available to hide gather latency.
@@ -169,21 +179,24 @@ __global__ __launch_bounds__(kInfBlock) __attribute__((amdgpu_waves_per_eu(5))) 
     asm volatile("" : "+v"(woff));
     // 1. register histograms of the tile's hosts
     if constexpr (DIRECT) {
-      for (int row = 0; row < 16; ++row) {
-        const uint32_t h = tile * 16 + row;
-        if (h >= nh) break;
-        const uint32_t kmix = mm3_key(hosts[h]);
-        uint32_t* my = H + row * kHistStride;
-        for (uint32_t i0 = lane; i0 < g; i0 += 64 * 4) {
-          uint32_t r[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const uint32_t i = i0 + 64u * u;
-            r[u] = i < g ? (uint32_t)reg[reduce_m(mm3_seeded(kmix, s1_lds[i]), m)] : 255u;
-          }
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (r[u] != 255u) atomicAdd(&my[r[u]], 1u);
+      const uint32_t last = nh - 1;  // rows past it repeat its host and are not used
+      if constexpr (SPREAD) {
+        const uint32_t h = tile * 16 + wave;
+        hist_hosts<64, false>(mm3_key(hosts[h < last ? h : last]), s1_lds, g, m, reg, reg4, 0u, 0u,
+                              H + wave * kHistStride);
+        __syncthreads();
+        if (wave != 0) continue;  // one tile a workgroup
+      } else if (g <= 2048) {
+        for (int r0 = 0; r0 < 16; r0 += 4) {
+          const uint32_t h = tile * 16 + r0 + q;
+          hist_hosts<16, false>(mm3_key(hosts[h < last ? h : last]), s1_lds, g, m, reg, reg4, 0u, 0u,
+                                H + (r0 + q) * kHistStride);
+        }
+      } else {
+        for (int row = 0; row < 16; ++row) {
+          const uint32_t h = tile * 16 + row;
+          hist_hosts<64, false>(mm3_key(hosts[h < last ? h : last]), s1_lds, g, m, reg, reg4, 0u, 0u,
+                                H + row * kHistStride);
         }
       }
     } else {
@@ -192,7 +205,7 @@ __global__ __launch_bounds__(kInfBlock) __attribute__((amdgpu_waves_per_eu(5))) 
         const uint32_t h = tile * 16 + row;
         uint32_t c = 0;
         if (h < nh)
-          for (uint32_t x = 0; x < parts; ++x) c += hws[((uint64_t)x * kLearnChunk + h) * kBins + r];
+          for (uint32_t x = 0; x < parts; ++x) c += hws[((uint64_t)x * hstride + h) * kBins + r];
         H[row * kHistStride + r] = c;
       }
     }
@@ -581,11 +594,12 @@ int vbdr_features(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_hosts, 
   if (!hosts_dev || !feats_dev) return vbdr_fail(VBDR_EINVAL, "hosts_dev and feats_dev must not be NULL");
   if (int rc = vbdr_check_device(sk)) return rc;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  for (uint64_t c = 0; c < n_hosts; c += kLearnChunk) {
-    const uint32_t nh = (uint32_t)(n_hosts - c < kLearnChunk ? n_hosts - c : kLearnChunk);
+  const uint32_t chunk = vbdr_hist_chunk(sk), parts = vbdr_gather_parts(sk);
+  for (uint64_t c = 0; c < n_hosts; c += chunk) {
+    const uint32_t nh = (uint32_t)(n_hosts - c < chunk ? n_hosts - c : chunk);
     if (int rc = vbdr_hist_pass(sk, hosts_dev + c, nh, st)) return rc;
-    hipLaunchKernelGGL(k_features, dim3((nh + 255) / 256), dim3(256), 0, st, nh, (uint32_t)sk->parts, sk->hist_ws,
-                       sk->hist, sk->g, (uint32_t)sk->m, feats_dev + c * kIn);
+    hipLaunchKernelGGL(k_features, dim3((uint32_t)(((uint64_t)nh * kIn + 255) / 256)), dim3(256), 0, st, nh, parts, chunk,
+                       sk->hist_ws, sk->hist, sk->g, (uint32_t)sk->m, feats_dev + c * kIn);
     VBDR_LAUNCHED("k_features");
   }
   return VBDR_OK;
@@ -599,27 +613,30 @@ int vbdr_estimate_learned(vbdr_sketch* sk, const vbdr_mlp* mlp, const uint32_t* 
   if (mlp->device != sk->device) return vbdr_fail(VBDR_EINVAL, "mlp and sketch live on different devices");
   if (int rc = vbdr_check_device(sk)) return rc;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  if (sk->parts == 1 && sk->g <= kStageMaxG && n_hosts < (1ull << 32)) {
+  const uint32_t parts = vbdr_gather_parts(sk), chunk = vbdr_hist_chunk(sk);
+  if (parts == 1 && sk->g <= kStageMaxG && n_hosts < (1ull << 32)) {
     // registers cache resident: one fused launch, gathers feed the MLP tile directly
     const uint32_t nh = (uint32_t)n_hosts;
     const uint32_t tiles = (uint32_t)((n_hosts + 15) / 16);
     const uint32_t want = (tiles + kInfWaves - 1) / kInfWaves;
     const uint32_t cap = (uint32_t)sk->n_cu * 8;
-    hipLaunchKernelGGL(k_learned<true>, dim3(want < cap ? want : cap), dim3(kInfBlock), (size_t)sk->g * 4, st, nh, 1u,
-                       (const uint32_t*)nullptr, hosts_dev, sk->s1, sk->reg, sk->hist, sk->g, (uint32_t)sk->m,
+    const bool spread = tiles <= (uint32_t)sk->n_cu * (sk->g >= kSpreadWideG ? 2 : 1);
+    hipLaunchKernelGGL((spread ? k_learned<true, true> : k_learned<true>), dim3(spread ? tiles : want < cap ? want : cap),
+                       dim3(spread ? kSpreadBlock : kInfBlock), (size_t)sk->g * 4, st, nh, 1u, 0u,
+                       (const uint32_t*)nullptr, hosts_dev, sk->s1, sk->reg, sk->reg4, sk->hist, sk->g, (uint32_t)sk->m,
                        mlp->dev, out_dev, used_fallback_dev);
     VBDR_LAUNCHED("k_learned(direct)");
     return VBDR_OK;
   }
-  for (uint64_t c = 0; c < n_hosts; c += kLearnChunk) {
-    const uint32_t nh = (uint32_t)(n_hosts - c < kLearnChunk ? n_hosts - c : kLearnChunk);
+  for (uint64_t c = 0; c < n_hosts; c += chunk) {
+    const uint32_t nh = (uint32_t)(n_hosts - c < chunk ? n_hosts - c : chunk);
     if (int rc = vbdr_hist_pass(sk, hosts_dev + c, nh, st)) return rc;
     const uint32_t tiles = (nh + 15) / 16;
     const uint32_t want = (tiles + kInfWaves - 1) / kInfWaves;
     const uint32_t cap = (uint32_t)sk->n_cu * 4;
     hipLaunchKernelGGL(k_learned<false>, dim3(want < cap ? want : cap), dim3(kInfBlock), 0, st, nh,
-                       (uint32_t)sk->parts, sk->hist_ws, (const uint32_t*)nullptr, (const uint32_t*)nullptr,
-                       (const uint8_t*)nullptr, sk->hist, sk->g, (uint32_t)sk->m, mlp->dev, out_dev + c,
+                       parts, chunk, sk->hist_ws, (const uint32_t*)nullptr, (const uint32_t*)nullptr,
+                       (const uint8_t*)nullptr, (const uint8_t*)nullptr, sk->hist, sk->g, (uint32_t)sk->m, mlp->dev, out_dev + c,
                        used_fallback_dev ? used_fallback_dev + c : nullptr);
     VBDR_LAUNCHED("k_learned");
   }

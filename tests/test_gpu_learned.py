@@ -185,3 +185,36 @@ def test_training_reduces_loss(V, M):
         tr.step(fd, td)
     last = float(tr.grad(fd, td)[1].cpu()[0])
     assert last < 0.05 * first
+
+
+@pytest.mark.parametrize("m,g", [(300, 2), (5000, 16), (70_001, 2048), (70_001, 4096), (1 << 17, 8192), (100_000, 16384),
+                                 ((1 << 22) + 1, 64), ((1 << 23) + 9, 256), ((1 << 24) + 1, 512), ((1 << 25) + 5, 128)])
+def test_histogram_routes(V, M, m, g):
+    """Histograms counted in registers (16 and 64 lanes a host, up to 128
+    registers a lane), with LDS atomics and in 1, 2 and 4 pool ranges: the
+    features are the ones of estimate_ex's histograms, and a network that
+    rejects every host returns the plain estimates.  Small pools hold planted
+    registers, a tenth of them 15 and more, and most others one value."""
+    rng = np.random.default_rng(g)
+    sk = V.Sketch(m, g, 3, 21, "small")
+    if m < 1 << 20:
+        reg = np.full(m, 3, np.uint8)
+        other = rng.random(m) < 0.3
+        reg[other] = rng.integers(0, sk.L + 1, int(other.sum()))
+        hist = np.bincount(reg, minlength=33).astype(np.uint64)
+        sk.load_state({"dr": np.full((m, sk.L), 255, np.uint8), "reg": reg, "hist": hist, "t": 1})
+    else:
+        sk.scan_slice(V.to_device_u32(rng.integers(0, 2**32, m, dtype=np.uint64).astype(np.uint32)[: m // 2 * 2]))
+        sk.advance_slice()
+    hosts = rng.integers(0, 2**32, 33_001, dtype=np.uint64).astype(np.uint32)
+    plain, _, hist = sk.estimate_ex(V.to_device_u32(hosts))
+    pool = torch.from_numpy(sk.registers()[1].astype(np.float64) / m).float().cuda()
+    want = (hist.double() / g).float()
+    mlp = V.MLP(_random_params(M, 3), np.full(67, 2.0, np.float32), np.full(67, 1.0, np.float32))
+    for n in (1, 3, 17, 1025, 4_097, 8_193, 32_768, 33_001):
+        hd = V.to_device_u32(hosts[:n])
+        f = sk.features(hd)
+        assert torch.equal(f[:, :33], want[:n]) and torch.equal(f[:, 33:66], pool.expand(n, 33)), n
+        assert torch.equal(f[:, 66], torch.full((n,), float(np.float32(np.log(g / m))), device="cuda")), n
+        est, fb = sk.estimate_learned(mlp, hd, with_fallback=True)
+        assert bool((fb == 1).all()) and torch.equal(est, plain[:n]), n
