@@ -1306,36 +1306,70 @@ __global__ __launch_bounds__(kEstBlock) void k_est_gather(uint32_t nh, const uin
 
 // ------------------------------------------- LogLog and PCSA on the pool
 // The pool serves other estimators than HyperLogLog (the text after Alg. 5,
-// Sec. 5).  One wave per host gathers the host's g values -- registers for
-// LogLog (Alg. 5's literal sum), PCSA runs for PCSA -- and sums them; E_s =
-// c_g * g * 2^(S/g) with c = alpha_g (LogLog) or 1/0.77351 (PCSA), E_m the
-// same over the pool, then the noise removal of the HyperLogLog path.
-__global__ __launch_bounds__(kEstBlock) void k_estimate_sum(const uint32_t* __restrict__ hosts, uint64_t nh,
-                                                            const uint32_t* __restrict__ s1, uint32_t g, uint32_t m,
-                                                            const uint8_t* __restrict__ val, double cg, double Em,
-                                                            float* __restrict__ out, double* __restrict__ raw) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (uint64_t h = (uint64_t)blockIdx.x * kEstWaves + wave; h < nh; h += (uint64_t)gridDim.x * kEstWaves) {
-    const uint32_t kmix = mm3_key(hosts[h]);
-    uint32_t S = 0;
-    for (uint32_t i0 = lane; i0 < g; i0 += 64 * 4) {
-      uint32_t v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const uint32_t i = i0 + 64u * u;
-        v[u] = i < g ? (uint32_t)val[reduce_m(mm3_seeded(kmix, s1[i]), m)] : 0u;
-      }
-      S += v[0] + v[1] + v[2] + v[3];
-    }
-    S = (uint32_t)wave_sum_u64(S);
-    if (lane == 0) {
+// Sec. 5): S is the sum of a host's g values -- registers for LogLog (Alg. 5's
+// literal sum), PCSA runs for PCSA -- E_s = c_g * g * 2^(S/g) with c = alpha_g
+// (LogLog) or 1/0.77351 (PCSA), E_m the same over the pool from *pool, its sum
+// of values, then the noise removal of the HyperLogLog path.
+struct SumEst {
+  double cg, cm;
+  const unsigned long long* pool;
+  float* out;
+  double* raw;  // E_s, nullable
+};
+
+__device__ __forceinline__ double sum_pool(const SumEst& E, uint32_t m) {
 #pragma clang fp contract(off)
-      const double Es = cg * (double)g * exp2((double)S / (double)g);
-      const double n = noise_removed(Es, Em, (double)m, (double)g);
-      out[h] = (float)(n > 0.0 ? n : 0.0);
-      if (raw) raw[h] = Es;
+  return E.cm * (double)m * exp2((double)*E.pool / (double)m);
+}
+
+__device__ __forceinline__ void sum_estimate(const SumEst& E, double Em, uint64_t h, uint32_t S, uint32_t g, uint32_t m) {
+#pragma clang fp contract(off)
+  const double Es = E.cg * (double)g * exp2((double)S / (double)g);
+  const double n = noise_removed(Es, Em, (double)m, (double)g);
+  E.out[h] = (float)(n > 0.0 ? n : 0.0);
+  if (E.raw) E.raw[h] = Es;
+}
+
+// LPH lanes a host, per_wave hosts a wave.  PART: workgroup b sums the values
+// of range b mod parts into psum, [parts][pstride], for k_sum_final; otherwise
+// the estimates.  STAGE: seeds in LDS.  Gathers bound it, at an L2's tag rate
+// where the values fit one: 20000 hosts, g = 512, 2^22 runs, call included,
+// 43.5 us (63.5 with four gathers in flight and the pool's sum read on the host
+// before the launch); 1e5 hosts, g = 2048, 0.9 2^25 runs: 819 us in 8 ranges,
+// 3062 directly.
+template <int LPH, bool NIB, bool PART, bool STAGE>
+__global__ __launch_bounds__(kRowBlock) void k_estimate_sum(const uint32_t* __restrict__ hosts, uint64_t nh,
+                                                            uint32_t per_wave, const uint32_t* __restrict__ s1g,
+                                                            uint32_t g, uint32_t m, const uint8_t* __restrict__ val,
+                                                            const uint8_t* __restrict__ val4, uint32_t parts,
+                                                            uint32_t part_shift, uint32_t* __restrict__ psum,
+                                                            uint32_t pstride, SumEst E) {
+  extern __shared__ uint32_t lds[];
+  if constexpr (STAGE) {
+    for (uint32_t i = threadIdx.x; i < g; i += kRowBlock) lds[i] = s1g[i];
+    __syncthreads();
+  }
+  const uint32_t x = PART ? blockIdx.x % parts : 0u, tile = PART ? blockIdx.x / parts : blockIdx.x;
+  const uint32_t tiles = PART ? gridDim.x / parts : gridDim.x, lane = threadIdx.x & 63;
+  const double Em = PART ? 0.0 : sum_pool(E, m);
+  const uint64_t step = (uint64_t)tiles * (kRowBlock / 64) * per_wave;
+  for (uint64_t h = ((uint64_t)tile * (kRowBlock / 64) + (threadIdx.x >> 6)) * per_wave; h < nh; h += step) {
+    const uint32_t n = nh - h < per_wave ? (uint32_t)(nh - h) : per_wave;
+    const uint32_t S = sum_hosts<LPH, PART, NIB>(hosts + h, n, STAGE ? lds : s1g, g, m, val, val4, x, part_shift);
+    if (lane < n) {
+      if constexpr (PART) psum[(uint64_t)x * pstride + h + lane] = S;
+      else sum_estimate(E, Em, h + lane, S, g, m);
     }
   }
+}
+
+__global__ __launch_bounds__(256) void k_sum_final(uint32_t nh, uint32_t g, uint32_t m, uint32_t parts,
+                                                   const uint32_t* __restrict__ psum, uint32_t pstride, SumEst E) {
+  const uint32_t h = blockIdx.x * 256 + threadIdx.x;
+  if (h >= nh) return;
+  uint32_t S = 0;
+  for (uint32_t x = 0; x < parts; ++x) S += psum[(uint64_t)x * pstride + h];
+  sum_estimate(E, sum_pool(E, m), h, S, g, m);
 }
 
 // ------------------------------------------------- per-slice max-LBP1 map
@@ -2118,12 +2152,14 @@ int vbdr_check_device(const vbdr_sketch* sk) {
 
 // Pool ranges of the XCD-partitioned gathers: as few as let a range's nibbles
 // fit one XCD's L2 (4 MB), since every range hashes every (host, i).
-uint32_t vbdr_gather_parts(const vbdr_sketch* sk) {
+static uint32_t gather_parts_of(const vbdr_sketch* sk, uint64_t bytes) {
   uint32_t p = 1;
-  while (p < 8u && (sk->mstride / 2) / p > kRangeBytes) p *= 2;
+  while (p < 8u && bytes / p > kRangeBytes) p *= 2;
   const uint32_t most = (uint32_t)(sk->parts == 8 ? sk->tune.est_parts : sk->parts);
   return p < most ? p : most;
 }
+
+uint32_t vbdr_gather_parts(const vbdr_sketch* sk) { return gather_parts_of(sk, sk->mstride / 2); }
 
 uint32_t vbdr_hist_chunk(const vbdr_sketch* sk) {  // est_parts may shrink the ranges, never hist_ws
   return kLearnChunk * ((uint32_t)sk->parts / vbdr_gather_parts(sk));
@@ -2983,29 +3019,42 @@ int vbdr_estimate_kind(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_ho
   if (!hosts_dev || !out_dev) return vbdr_fail(VBDR_EINVAL, "hosts_dev and out_dev must not be NULL");
   if (int rc = vbdr_check_device(sk)) return rc;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  // the pool's sum of values: registers from the histogram, PCSA runs from the advance's sum
-  double pool_sum = 0.0;
-  if (kind == VBDR_EST_LOGLOG) {
-    uint64_t hist[kBins];
-    VBDR_HIP(hipMemcpyAsync(hist, sk->hist, sizeof(hist), hipMemcpyDeviceToHost, st));
-    VBDR_HIP(hipStreamSynchronize(st));
-    uint64_t s = 0;
-    for (int r = 0; r < kBins; ++r) s += hist[r] * (uint64_t)r;
-    pool_sum = (double)s;
-  } else {
-    unsigned long long s = 0;
-    VBDR_HIP(hipMemcpyAsync(&s, sk->psum, sizeof(s), hipMemcpyDeviceToHost, st));
-    VBDR_HIP(hipStreamSynchronize(st));
-    pool_sum = (double)s;
-  }
+  const bool nib = kind == VBDR_EST_LOGLOG;
   const double q = (double)sk->m, g = (double)sk->g;
-  const double cg = kind == VBDR_EST_LOGLOG ? loglog_alpha(g) : 1.0 / 0.77351;
-  const double cm = kind == VBDR_EST_LOGLOG ? loglog_alpha(q) : 1.0 / 0.77351;
-  const double Em = cm * q * std::exp2(pool_sum / q);
-  const uint32_t grid = grid_cap(sk, (n_hosts + kEstWaves - 1) / kEstWaves, sk->tune.est_blocks_per_cu);
-  hipLaunchKernelGGL(k_estimate_sum, dim3(grid), dim3(kEstBlock), 0, st, hosts_dev, n_hosts, sk->s1, sk->g,
-                     (uint32_t)sk->m, kind == VBDR_EST_LOGLOG ? sk->reg : sk->preg, cg, Em, out_dev, raw_es_dev);
-  VBDR_LAUNCHED("k_estimate_sum");
+  const SumEst E{nib ? loglog_alpha(g) : 1.0 / 0.77351, nib ? loglog_alpha(q) : 1.0 / 0.77351,
+                 nib ? sk->hist + kStatSum : sk->psum, out_dev, raw_es_dev};
+  const uint8_t* val = nib ? sk->reg : sk->preg;
+  const uint32_t m32 = (uint32_t)sk->m;
+  const bool stage = sk->g <= kStageMaxG;
+  const size_t lds = stage ? (size_t)sk->g * 4 : 0;
+  // ranges as in the HyperLogLog estimate, of bytes for PCSA runs
+  const uint32_t parts = stage && n_hosts * sk->g >= kPartMinGathers ? gather_parts_of(sk, sk->mstride >> nib) : 1;
+  uint32_t shift = 31;
+  while (parts > 1 && (1u << (32 - shift)) < parts) --shift;
+  const uint64_t chunk = parts > 1 ? kPartChunk : n_hosts;
+  for (uint64_t c = 0; c < n_hosts; c += chunk) {
+    const uint64_t nh = n_hosts - c < chunk ? n_hosts - c : chunk, waves = (uint64_t)sk->n_cu * 32 / parts;
+    const bool rows = stage && (parts > 1 || nh >= (uint64_t)sk->n_cu * 64);  // 16 lanes a host, else a wave
+    uint64_t per = (nh + waves - 1) / waves;
+    per = rows ? 4 : per > 4 ? 4 : per;
+    const uint64_t want = ((nh + per - 1) / per + kRowBlock / 64 - 1) / (kRowBlock / 64);
+    const uint32_t grid = grid_cap(sk, want, 1024) * parts;
+    SumEst e = E;
+    e.out += c;
+    if (e.raw) e.raw += c;
+    const auto kern =
+        parts > 1 ? (nib ? k_estimate_sum<16, true, true, true> : k_estimate_sum<16, false, true, true>)
+        : rows    ? (nib ? k_estimate_sum<16, true, false, true> : k_estimate_sum<16, false, false, true>)
+        : stage   ? (nib ? k_estimate_sum<64, true, false, true> : k_estimate_sum<64, false, false, true>)
+                  : (nib ? k_estimate_sum<64, true, false, false> : k_estimate_sum<64, false, false, false>);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kRowBlock), lds, st, hosts_dev + c, nh, (uint32_t)per, sk->s1, sk->g, m32,
+                       val, sk->reg4, parts, shift, sk->part_v, kPartChunk, e);
+    VBDR_LAUNCHED("k_estimate_sum");
+    if (parts == 1) continue;
+    hipLaunchKernelGGL(k_sum_final, dim3((uint32_t)((nh + 255) / 256)), dim3(256), 0, st, (uint32_t)nh, sk->g, m32, parts,
+                       sk->part_v, kPartChunk, e);
+    VBDR_LAUNCHED("k_sum_final");
+  }
   return VBDR_OK;
 }
 

@@ -486,6 +486,49 @@ __device__ __forceinline__ void gather_hosts(const uint32_t* __restrict__ hosts,
   }
 }
 
+// Sums of n <= 64 consecutive hosts' values by one wave, laid out as in
+// gather_hosts: lane l < n returns host l's.  The values are the bytes val, or
+// with NIB registers, read from their nibbles val4 where below 15.
+template <int LPH, bool PART, bool NIB>
+__device__ __forceinline__ uint32_t sum_hosts(const uint32_t* __restrict__ hosts, uint32_t n, const uint32_t* s1,
+                                              uint32_t g, uint32_t m, const uint8_t* __restrict__ val,
+                                              const uint8_t* __restrict__ val4, uint32_t part, uint32_t part_shift) {
+  constexpr int kRows = 64 / LPH, kFlight = 8;
+  const int lane = threadIdx.x & 63, q = lane / LPH, ql = lane % LPH;
+  const uint32_t kmix = mm3_key((uint32_t)lane < n ? hosts[lane] : 0u);
+  uint32_t sum = 0;
+  for (uint32_t t = 0; t * kRows < n; ++t) {
+    const uint32_t km = (uint32_t)__shfl((int)kmix, (int)(t * kRows) + q);
+    uint32_t S = 0;
+    for (uint32_t i0 = (uint32_t)ql; i0 < g; i0 += LPH * kFlight) {
+      uint32_t p[kFlight], v[kFlight];
+      bool mine[kFlight];
+#pragma unroll
+      for (int u = 0; u < kFlight; ++u) {
+        const uint32_t i = i0 + (uint32_t)(LPH * u);
+        const uint32_t h = mm3_seeded(km, s1[i < g ? i : 0u]);
+        p[u] = reduce_m(h, m);
+        mine[u] = i < g && (!PART || h >> part_shift == part);
+      }
+#pragma unroll
+      for (int u = 0; u < kFlight; ++u) v[u] = mine[u] ? (uint32_t)(NIB ? val4[p[u] >> 1] : val[p[u]]) : 0u;
+      bool wide = false;
+#pragma unroll
+      for (int u = 0; u < kFlight; ++u) {
+        if (NIB) v[u] = __builtin_amdgcn_ubfe(v[u], (p[u] & 1u) << 2, 4), wide |= v[u] == 15u;
+        S += v[u];
+      }
+      if (NIB && wide)
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u)
+          if (v[u] == 15u) S += (uint32_t)val[p[u]] - 15u;
+    }
+    S = (uint32_t)__shfl((int)row_sum<LPH>(S), (lane % kRows) * LPH);  // lane l keeps host l
+    if ((uint32_t)lane / kRows == t) sum = S;
+  }
+  return sum;
+}
+
 // Register histograms of 64 / LPH hosts by one wave, LPH lanes each (kmix: the
 // key of this lane's host), added to this lane's host's row of 33 counts in LDS,
 // which is zero before.  Each lane counts nibbles below 15 in registers: four bits a

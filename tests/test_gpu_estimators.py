@@ -123,3 +123,33 @@ def test_failed_pcsa_allocation_leaves_sketch_whole(V):
     sk.advance_slice()
     assert sk.estimate_kind(hd, "pcsa").shape == (len(aips),)
     sk.close()
+
+
+@pytest.mark.parametrize("m,g", [(5000, 4), (70_001, 128), (100_000, 32768), ((1 << 22) + 1, 64), ((1 << 23) + 9, 2048),
+                                 ((1 << 24) + 1, 256), ((1 << 25) + 5, 1024)])
+def test_sum_routes(V, m, g):
+    """The sums of LogLog and PCSA by a wave a host, 16 lanes a host and in pool
+    ranges: LogLog's raw E_s is the one of estimate_ex's histograms, up to the
+    rounding of its constant, and of either kind a host's results do not depend
+    on the hosts it is estimated with (a few take the direct gathers)."""
+    rng = np.random.default_rng(g + 1)
+    sk = V.Sketch(m, g, 3, 21, "small")
+    sk.enable_pcsa(True)
+    for _ in range(2):
+        sk.scan_slice(V.to_device_u32(rng.integers(0, 2**32, min(m, 1 << 24) * 2, dtype=np.uint64).astype(np.uint32)))
+        sk.advance_slice()
+    hosts = rng.integers(0, 2**32, 33_001, dtype=np.uint64).astype(np.uint32)
+    hd = V.to_device_u32(hosts)
+    few = min(len(hosts), max(1, ((1 << 20) - 1) // g))  # fewer gathers than ranges need
+    _, _, hist = sk.estimate_ex(hd[:few])
+    S = (hist.double().cpu() * torch.arange(33, dtype=torch.float64)).sum(1)
+    lit = (g * torch.exp2(S / g)).numpy()
+    for kind in ("pcsa", "loglog"):
+        out, raw = sk.estimate_kind(hd, kind, with_raw=True)
+        if kind == "loglog":
+            ratio = raw[:few].cpu().numpy() / lit
+            assert np.ptp(ratio) <= 1e-13 * ratio[0]
+        for n in (1, 3, 17, 255, 16_385):
+            a, b = (0, n) if n <= few else (len(hosts) - n, len(hosts))
+            o, r = sk.estimate_kind(hd[a:b].contiguous(), kind, with_raw=True)
+            assert torch.equal(o, out[a:b]) and torch.equal(r, raw[a:b]), (kind, n)
