@@ -337,7 +337,7 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_apply(const uint32_t* __res
 constexpr int kDeferBlock = 1024;
 constexpr int kHistCopies = 4;  // register histograms per wave in the advances (a power of two)
 constexpr int kDeferPer = 32;   // records per thread of a chunk, at most
-constexpr uint32_t kDeferChunk = kDeferBlock * kDeferPer;
+static_assert(kDeferChunk == kDeferBlock * kDeferPer, "a chunk of the longest");
 static_assert(kPad % (1u << kMinTileShift) == 0, "tiles start on whole bit words");
 
 // Exclusive prefix sums of a[0..n) into out[0..n) by one workgroup of
@@ -389,24 +389,30 @@ __device__ __forceinline__ void apply_record(uint32_t rec, uint8_t* dr, uint64_t
   }
 }
 
-// One chunk of 1024 PER pairs from c0 on: records (pidx << 5 | LBP1-1),
-// counted and ranked per tile in LDS, sorted by tile, appended to the tile
-// runs (one 64-bit atomic per (chunk, tile)); records past a run's capacity
+// A chunk of n <= 1024 PER pairs (FULL: all of them): records (pidx << 5 |
+// LBP1-1), counted and ranked per tile in LDS, sorted by tile, appended to the
+// tile runs (one 64-bit atomic per (chunk, tile)); records past a run's capacity
 // are applied directly and flag the direct update.  LDS: cnt[tiles],
-// start[tiles], sorted[1024 PER]; s1 points to LDS when staged.
-template <bool FAST, int PER>
-__device__ __forceinline__ void scan_defer_chunk(const u32x2* __restrict__ pairs, uint64_t n, uint64_t c0,
-                                                 const uint32_t* s1, uint32_t b, uint32_t A1, uint32_t m,
-                                                 uint32_t tiles, uint32_t cap, uint32_t* __restrict__ recs,
-                                                 unsigned long long* __restrict__ fill, uint8_t* __restrict__ dr,
-                                                 uint64_t mstride, uint32_t* __restrict__ seen, uint64_t wstride,
-                                                 uint32_t Lc, uint32_t* __restrict__ bits, uint32_t z,
-                                                 uint32_t tshift, uint32_t* lds, uint32_t* wsum) {
-  constexpr int kLoad = PER < 8 ? PER : 8;  // pair loads in flight per thread
+// start[tiles], sorted[1024 PER]; s1 points to LDS when staged.  Writing the
+// chunk's share of each run bounds it (2^27 pairs, 512 tiles: 372 us; 2^26,
+// 2048 tiles and a quarter of the share: 236; two workgroups of half the chunk
+// a CU: 430 us for the first).  Without FULL every record is a branch of its
+// own that waits for its own loads (2^27 pairs: 424 us; 2^22 pairs 22 us, now 18).
+template <bool FAST, int PER, bool FULL>
+__device__ __forceinline__ void scan_defer_part(const u32x2* __restrict__ pairs, uint32_t n, const uint32_t* s1,
+                                                uint32_t b, uint32_t A1, uint32_t m, uint32_t tiles, uint32_t cap,
+                                                uint32_t* __restrict__ recs, unsigned long long* __restrict__ fill,
+                                                uint8_t* __restrict__ dr, uint64_t mstride,
+                                                uint32_t* __restrict__ seen, uint64_t wstride, uint32_t Lc,
+                                                uint32_t* __restrict__ bits, uint32_t z, uint32_t tshift,
+                                                uint32_t* lds, uint32_t* wsum) {
+  constexpr int kLoad = PER == 32 ? 16 : PER < 8 ? PER : 8;  // pair loads in flight per thread
   uint32_t* cnt = lds;
   uint32_t* start = lds + tiles;
   uint32_t* sorted = lds + 2 * tiles;
+  __shared__ uint32_t over;
   for (uint32_t t = threadIdx.x; t < tiles; t += kDeferBlock) cnt[t] = 0;
+  if (threadIdx.x == 0) over = 0;
   __syncthreads();
   // records and their ranks within the tile (< kDeferChunk, 16 bits each)
   uint32_t rec[PER], rank[PER / 2];
@@ -415,56 +421,83 @@ __device__ __forceinline__ void scan_defer_chunk(const u32x2* __restrict__ pairs
     u32x2 p[kLoad];
 #pragma unroll
     for (int v = 0; v < kLoad; ++v) {
-      const uint64_t i = c0 + (uint64_t)(u0 + v) * kDeferBlock + threadIdx.x;
-      p[v] = i < n ? __builtin_nontemporal_load(pairs + i) : u32x2{0u, 0u};
+      const uint32_t i = (uint32_t)(u0 + v) * kDeferBlock + threadIdx.x;
+      p[v] = FULL || i < n ? __builtin_nontemporal_load(pairs + i) : u32x2{0u, 0u};
     }
+    uint32_t r[kLoad];
 #pragma unroll
     for (int v = 0; v < kLoad; ++v) {
-      const int u = u0 + v;
-      const uint64_t i = c0 + (uint64_t)u * kDeferBlock + threadIdx.x;
-      uint32_t r = 0;
-      if (i < n) {
-        uint32_t vidx, rho;
-        bip_map(p[v].y, A1, b, vidx, rho);
-        const uint32_t pidx = reduce_m(mm3(p[v].x, s1[vidx]), m);
-        rec[u] = (pidx << 5) | ((rho < Lc ? rho : Lc) - 1);  // LBP1 above Lc is recorded at Lc
-        r = atomicAdd(&cnt[pidx >> tshift], 1u);
-      }
-      if (u & 1) rank[u >> 1] |= r << 16;
-      else rank[u >> 1] = r;
+      const uint32_t i = (uint32_t)(u0 + v) * kDeferBlock + threadIdx.x;
+      uint32_t vidx, rho;
+      bip_map(p[v].y, A1, b, vidx, rho);
+      const uint32_t pidx = reduce_m(mm3(p[v].x, s1[vidx]), m);
+      rec[u0 + v] = (pidx << 5) | ((rho < Lc ? rho : Lc) - 1);  // LBP1 above Lc is recorded at Lc
+      r[v] = FULL || i < n ? atomicAdd(&cnt[pidx >> tshift], 1u) : 0u;
     }
+#pragma unroll
+    for (int v = 0; v < kLoad; v += 2) rank[(u0 + v) >> 1] = r[v] | r[v + 1] << 16;
   }
   __syncthreads();
   block_exclusive_scan(cnt, start, tiles, wsum);
-  // one run segment per (chunk, tile); cnt[t] becomes the segment's run offset
+  // one run segment per (chunk, tile); cnt[t] becomes the record slot of the
+  // sorted chunk's record 0 if all were the tile's (slots are below 2^32)
   for (uint32_t t = threadIdx.x; t < tiles; t += kDeferBlock) {
     const uint32_t c = cnt[t];
     if (c) {
       const unsigned long long at = atomicAdd(fill + t, (unsigned long long)c);
-      cnt[t] = at < cap ? (uint32_t)at : cap;
+      cnt[t] = t * cap + (at < cap ? (uint32_t)at : cap) - start[t];
+      if (at + c > cap) over = 1;
     }
   }
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
-    const uint64_t i = c0 + (uint64_t)u * kDeferBlock + threadIdx.x;
-    if (i < n) sorted[start[rec[u] >> (5 + tshift)] + ((rank[u >> 1] >> (16 * (u & 1))) & 0xFFFFu)] = rec[u];
+    const uint32_t i = (uint32_t)u * kDeferBlock + threadIdx.x;
+    if (FULL || i < n) sorted[start[rec[u] >> (5 + tshift)] + ((rank[u >> 1] >> (16 * (u & 1))) & 0xFFFFu)] = rec[u];
   }
   __syncthreads();
-  const uint32_t total = n - c0 < PER * kDeferBlock ? (uint32_t)(n - c0) : PER * kDeferBlock;
-  bool direct = false;
-  for (uint32_t j = threadIdx.x; j < total; j += kDeferBlock) {
-    const uint32_t r = sorted[j];
-    const uint32_t t = r >> (5 + tshift);
-    const uint32_t pos = cnt[t] + (j - start[t]);
-    if (pos < cap) {
-      recs[(uint64_t)t * cap + pos] = r;
-    } else {
-      apply_record<FAST>(r, dr, mstride, seen, wstride, bits, z);
-      direct = true;
+  if (!over) {
+    constexpr int kOut = PER < 8 ? PER : 8;
+    for (int u0 = 0; u0 < PER; u0 += kOut) {
+      uint32_t r[kOut], at[kOut];
+#pragma unroll
+      for (int v = 0; v < kOut; ++v) {
+        const uint32_t j = (uint32_t)(u0 + v) * kDeferBlock + threadIdx.x;
+        r[v] = FULL || j < n ? sorted[j] : 0u;
+      }
+#pragma unroll
+      for (int v = 0; v < kOut; ++v) at[v] = cnt[r[v] >> (5 + tshift)];
+#pragma unroll
+      for (int v = 0; v < kOut; ++v) {
+        const uint32_t j = (uint32_t)(u0 + v) * kDeferBlock + threadIdx.x;
+        if (FULL || j < n) recs[at[v] + j] = r[v];
+      }
     }
+  } else {  // a run is full: its records go to the pool
+    for (uint32_t j = threadIdx.x; j < n; j += kDeferBlock) {
+      const uint32_t r = sorted[j], t = r >> (5 + tshift), at = cnt[t] + j;
+      if (at - t * cap < cap) recs[at] = r;
+      else apply_record<FAST>(r, dr, mstride, seen, wstride, bits, z);
+    }
+    if (threadIdx.x == 0) fill[tiles] = 1ull;  // fast: the advance reads bsLBP1; small: its saturation masks are stale
   }
-  if (direct) fill[tiles] = 1ull;  // fast: the advance reads bsLBP1; small: its saturation masks are stale
   __syncthreads();
+}
+
+template <bool FAST, int PER>
+__device__ __forceinline__ void scan_defer_chunk(const u32x2* __restrict__ pairs, uint64_t n, uint64_t c0,
+                                                 const uint32_t* s1, uint32_t b, uint32_t A1, uint32_t m,
+                                                 uint32_t tiles, uint32_t cap, uint32_t* __restrict__ recs,
+                                                 unsigned long long* __restrict__ fill, uint8_t* __restrict__ dr,
+                                                 uint64_t mstride, uint32_t* __restrict__ seen, uint64_t wstride,
+                                                 uint32_t Lc, uint32_t* __restrict__ bits, uint32_t z,
+                                                 uint32_t tshift, uint32_t* lds, uint32_t* wsum) {
+  constexpr uint32_t kFull = PER * kDeferBlock;
+  if (n - c0 >= kFull)
+    scan_defer_part<FAST, PER, true>(pairs + c0, kFull, s1, b, A1, m, tiles, cap, recs, fill, dr, mstride, seen, wstride,
+                                     Lc, bits, z, tshift, lds, wsum);
+  else
+    scan_defer_part<FAST, PER, false>(pairs + c0, (uint32_t)(n - c0), s1, b, A1, m, tiles, cap, recs, fill, dr, mstride,
+                                      seen, wstride, Lc, bits, z, tshift, lds, wsum);
 }
 
 // LDS: cnt[tiles], start[tiles], sorted[1024 PER], then s1 if staged.
@@ -707,27 +740,32 @@ __device__ __forceinline__ uint32_t defer_member(const uint32_t* first, uint32_t
 }
 
 // LDS: cnt[max tiles], start[max tiles], sorted[kDeferChunk].
+template <bool STAGE>
 __global__ __launch_bounds__(kDeferBlock) void k_batch_scan_defer(const DeferItem* __restrict__ it,
-                                                                  const DeferHdr* __restrict__ hdr, uint32_t S) {
+                                                                  const DeferHdr* __restrict__ hdr, uint32_t S,
+                                                                  uint32_t max_tiles) {
   extern __shared__ uint32_t lds[];
   __shared__ uint32_t wsum[kDeferBlock / 64];
   __shared__ uint32_t first[kMaxDeferMembers];
   for (uint32_t s = threadIdx.x; s < S; s += kDeferBlock) first[s] = it[s].scan_item0;
   __syncthreads();
   const uint32_t total = hdr->scan_total;
+  uint32_t* s1l = lds + 2 * max_tiles + kDeferChunk;
   for (uint32_t item = blockIdx.x; item < total; item += gridDim.x) {
     const DeferItem& D = it[defer_member(first, S, item)];
     const AdvSketch& A = D.adv;
     const uint64_t c0 = (uint64_t)(item - D.scan_item0) * kDeferChunk;
     const u32x2* pairs = reinterpret_cast<const u32x2*>(D.pairs);
+    if (STAGE)
+      for (uint32_t i = threadIdx.x; i < 1u << D.b; i += kDeferBlock) s1l[i] = D.s1[i];
     if (A.layout == VBDR_LAYOUT_FAST)
-      scan_defer_chunk<true, kDeferPer>(pairs, D.n_pairs, c0, D.s1, D.b, D.A1, (uint32_t)A.m, A.tiles, A.cap, D.recs,
-                                        A.fill, A.dr, A.mstride, A.seen, A.wstride, A.L, nullptr, 0u, A.tshift, lds,
-                                        wsum);
+      scan_defer_chunk<true, kDeferPer>(pairs, D.n_pairs, c0, STAGE ? s1l : D.s1, D.b, D.A1, (uint32_t)A.m, A.tiles,
+                                        A.cap, D.recs, A.fill, A.dr, A.mstride, A.seen, A.wstride, A.L, nullptr, 0u,
+                                        A.tshift, lds, wsum);
     else
-      scan_defer_chunk<false, kDeferPer>(pairs, D.n_pairs, c0, D.s1, D.b, D.A1, (uint32_t)A.m, A.tiles, A.cap, D.recs,
-                                         A.fill, A.dr, A.mstride, A.seen, A.wstride, A.L, nullptr, 0u, A.tshift, lds,
-                                         wsum);
+      scan_defer_chunk<false, kDeferPer>(pairs, D.n_pairs, c0, STAGE ? s1l : D.s1, D.b, D.A1, (uint32_t)A.m, A.tiles,
+                                         A.cap, D.recs, A.fill, A.dr, A.mstride, A.seen, A.wstride, A.L, nullptr, 0u,
+                                         A.tshift, lds, wsum);
   }
 }
 
@@ -2123,17 +2161,20 @@ void vbdr_defer_member(const vbdr_sketch* sk, DeferItem* d) {
   d->s1 = sk->s1, d->recs = sk->def_rec, d->b = sk->b, d->A1 = sk->A1;
 }
 
-uint32_t vbdr_defer_chunk_pairs() { return kDeferChunk; }
+
+size_t vbdr_batch_scan_lds(uint32_t max_tiles, uint32_t max_g) {
+  return (size_t)(2 * max_tiles + kDeferChunk + max_g + kMaxDeferMembers + kDeferBlock / 64 + 1) * 4;
+}
 
 uint32_t vbdr_adv_lds(const vbdr_sketch* sk) { return sk->Lc << (sk->tshift - 3); }
 
 int vbdr_launch_batch_defer(const DeferItem* items_dev, const DeferHdr* hdr_dev, uint32_t S, uint32_t max_tiles,
-                            uint32_t adv_lds, uint32_t adv_total, bool big, uint32_t grid, int phase, hipStream_t st) {
+                            uint32_t max_g, uint32_t adv_lds, uint32_t adv_total, bool big, uint32_t grid, int phase, hipStream_t st) {
   if (S > kMaxDeferMembers) return vbdr_fail(VBDR_EINVAL, "more than %u members", kMaxDeferMembers);
   if (phase == 0) {
     if (max_tiles == 0) return VBDR_OK;
-    hipLaunchKernelGGL(k_batch_scan_defer, dim3(grid), dim3(kDeferBlock), (size_t)(2 * max_tiles + kDeferChunk) * 4,
-                       st, items_dev, hdr_dev, S);
+    hipLaunchKernelGGL(max_g ? k_batch_scan_defer<true> : k_batch_scan_defer<false>, dim3(grid), dim3(kDeferBlock),
+                       (size_t)(2 * max_tiles + kDeferChunk + max_g) * 4, st, items_dev, hdr_dev, S, max_tiles);
     VBDR_LAUNCHED("k_batch_scan_defer");
   } else {
     hipLaunchKernelGGL(big ? k_batch_advance<true> : k_batch_advance<false>, dim3(adv_total), dim3(kDeferBlock), adv_lds, st, items_dev, S);

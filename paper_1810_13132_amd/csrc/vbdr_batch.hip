@@ -243,6 +243,7 @@ struct vbdr_batch {
   hipGraphExec_t exec;
   vbdr_batch_tuning tune;
   uint32_t runs_max_tiles;     // most tiles of a member with record runs; 0: none has any
+  uint32_t runs_max_g;         // largest g of these members if their seeds fit the scan's LDS, else 0
   uint32_t adv_lds, adv_tiles; // the advance's LDS bytes (largest member) and tiles (all members)
   bool direct, big;            // some member scans without record runs; has tiles of 2^kMaxTileShift BDRs
   // sums of members whose gathers are partitioned (NULL: there is none), [kPartEntries]
@@ -319,7 +320,7 @@ int launch_step_kernels(vbdr_batch* bt) {
   DeferItem* ditems = defer_items(table, bt->S);
   DeferHdr* dhdr = defer_hdr(table, bt->S);
   for (int phase = 0; phase < 2; ++phase)
-    if (int rc = vbdr_launch_batch_defer(ditems, dhdr, bt->S, bt->runs_max_tiles, bt->adv_lds, bt->adv_tiles, bt->big,
+    if (int rc = vbdr_launch_batch_defer(ditems, dhdr, bt->S, bt->runs_max_tiles, bt->runs_max_g, bt->adv_lds, bt->adv_tiles, bt->big,
                                          (uint32_t)bt->n_cu, phase, bt->st))
       return rc;
   hipLaunchKernelGGL(k_batch_estimate, dim3((uint32_t)bt->n_cu < 8 ? 8 : (uint32_t)bt->n_cu / 8 * 8), dim3(kEBlock), kEstLds, bt->st, bt->desc_dev,
@@ -370,13 +371,20 @@ int vbdr_batch_create(uint32_t n_sketches, const vbdr_batch_params* params, vbdr
       bt->sk.push_back(s);
       bt->mlp.push_back(nullptr);
       if (!s->def_rec) bt->direct = true;
-      else if (bt->runs_max_tiles < s->def_tiles) bt->runs_max_tiles = s->def_tiles;
+      else {
+        if (bt->runs_max_tiles < s->def_tiles) bt->runs_max_tiles = s->def_tiles;
+        if (bt->runs_max_g < s->g) bt->runs_max_g = s->g;
+      }
       const uint32_t lds = vbdr_adv_lds(s);
       bt->adv_lds = bt->adv_lds > lds ? bt->adv_lds : lds;
       total_tiles += s->tiles;
       bt->big |= s->tshift == kMaxTileShift;
     }
     if (rc != VBDR_OK) break;
+    int lds_max = 0;
+    if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, bt->device) != hipSuccess ||
+        vbdr_batch_scan_lds(bt->runs_max_tiles, bt->runs_max_g) > (size_t)lds_max)
+      bt->runs_max_g = 0;
     if (total_tiles >= (1ull << 31)) {
       rc = vbdr_fail(VBDR_EINVAL, "the batch's pools have too many tiles");
       break;
@@ -491,7 +499,7 @@ int vbdr_batch_step(vbdr_batch* bt, const uint32_t* const* pairs_dev, const uint
   BatchHdr* hdr = reinterpret_cast<BatchHdr*>(bt->staging[buf] + sizeof(BatchDesc) * S);
   DeferItem* ditems = defer_items(bt->staging[buf], S);
   DeferHdr* dhdr = defer_hdr(bt->staging[buf], S);
-  const uint32_t chunk = vbdr_defer_chunk_pairs();
+  const uint32_t chunk = kDeferChunk;
   uint32_t si = 0, dsi = 0, dai = 0, part_used = 0;
   uint64_t cost[2] = {0, 0};
   for (uint32_t s = 0; s < S; ++s) {

@@ -23,35 +23,15 @@ struct Int {
 constexpr int kBins = 33;     // register values 0..32
 constexpr uint32_t kSat = 255; // DR saturation value (InitDR with z = 8)
 
-// MurmurHash3_x86_32 of one 4-byte little-endian key: H(x, 2^32, A)
-// (Sec. 4.1 leaves the hash family open; this is the chosen member).
-__device__ __forceinline__ uint32_t mm3(uint32_t x, uint32_t seed) {
-  uint32_t k = x * 0xcc9e2d51u;
-  k = (k << 15) | (k >> 17);
-  k *= 0x1b873593u;
-  uint32_t h = seed ^ k;
-  h = (h << 13) | (h >> 19);
-  h = h * 5u + 0xe6546b64u;
-  h ^= 4u;
-  h ^= h >> 16;
-  h *= 0x85ebca6bu;
-  h ^= h >> 13;
-  h *= 0xc2b2ae35u;
-  h ^= h >> 16;
-  return h;
-}
-
-// MurmurHash3_x86_32 split for many seeds over one key: mm3_key(x) is the
-// seed-independent block mix, mm3_seeded(mm3_key(x), A) == mm3(x, A).
-__device__ __forceinline__ uint32_t mm3_key(uint32_t x) {
-  uint32_t k = x * 0xcc9e2d51u;
-  k = (k << 15) | (k >> 17);
-  return k * 0x1b873593u;
-}
+// MurmurHash3_x86_32 of one 4-byte little-endian key, H(x, 2^32, A)
+// (Sec. 4.1 leaves the hash family open; this is the chosen member), split for
+// many seeds over one key: mm3_key(x) is the seed-independent block mix,
+// mm3_seeded(mm3_key(x), A) == mm3(x, A).  Rotations by v_alignbit: from
+// shifts the compiler makes a second multiply of mm3_key's (scans 1 % longer).
+__device__ __forceinline__ uint32_t rotl32(uint32_t x, uint32_t r) { return __builtin_amdgcn_alignbit(x, x, 32u - r); }
+__device__ __forceinline__ uint32_t mm3_key(uint32_t x) { return rotl32(x * 0xcc9e2d51u, 15) * 0x1b873593u; }
 __device__ __forceinline__ uint32_t mm3_seeded(uint32_t kmix, uint32_t seed) {
-  uint32_t h = seed ^ kmix;
-  h = (h << 13) | (h >> 19);
-  h = h * 5u + 0xe6546b64u;
+  uint32_t h = rotl32(seed ^ kmix, 13) * 5u + 0xe6546b64u;
   h ^= 4u;
   h ^= h >> 16;
   h *= 0x85ebca6bu;
@@ -60,6 +40,7 @@ __device__ __forceinline__ uint32_t mm3_seeded(uint32_t kmix, uint32_t seed) {
   h ^= h >> 16;
   return h;
 }
+__device__ __forceinline__ uint32_t mm3(uint32_t x, uint32_t seed) { return mm3_seeded(mm3_key(x), seed); }
 
 // H(x, m, A) for m < 2^32: the top 32 bits of the 64-bit product h * m.
 __device__ __forceinline__ uint32_t reduce_m(uint32_t h, uint32_t m) { return __umulhi(h, m); }

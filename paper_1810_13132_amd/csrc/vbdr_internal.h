@@ -147,14 +147,17 @@ struct DeferHdr {
 
 // The sketch's fields of its DeferItem (pairs, n_pairs and the item offsets zero).
 void vbdr_defer_member(const vbdr_sketch* sk, DeferItem* d);
-// Pairs per scan item of a member with record runs.
-uint32_t vbdr_defer_chunk_pairs();
+constexpr uint32_t kDeferChunk = 1u << 15;  // pairs per scan item of a member with record runs
 // Phase 0: the scans of members with record runs (grid workgroups over
-// hdr->scan_total items; max_tiles of them at most, 0: none); phase 1: the
+// hdr->scan_total items; max_tiles of them at most, 0: none; max_g: their
+// largest g where their seeds fit in LDS, else 0); phase 1: the
 // advances of all members (adv_total tiles, adv_lds bytes of bit words; big:
 // some member's tiles are of 2^kMaxTileShift BDRs).
 int vbdr_launch_batch_defer(const DeferItem* items_dev, const DeferHdr* hdr_dev, uint32_t S, uint32_t max_tiles,
-                            uint32_t adv_lds, uint32_t adv_total, bool big, uint32_t grid, int phase, hipStream_t st);
+                            uint32_t max_g, uint32_t adv_lds, uint32_t adv_total, bool big, uint32_t grid, int phase,
+                            hipStream_t st);
+// LDS bytes of the scans, static ones included.
+size_t vbdr_batch_scan_lds(uint32_t max_tiles, uint32_t max_g);
 // LDS bytes of a sketch's advance.
 uint32_t vbdr_adv_lds(const vbdr_sketch* sk);
 

@@ -262,3 +262,28 @@ def test_batch_estimate_parts(V):
         sk.scan_slice(pairs[i])
         sk.advance_slice()
         assert torch.equal(outs[i], sk.estimate(hosts[i])), conf[i]
+
+
+@pytest.mark.parametrize("g", [128, 16384])  # seeds of every member in LDS; not
+def test_batch_scan_chunks(V, g):
+    """Scans of members whose pairs end at, before and after a whole chunk
+    (2^15): the state is the one of the same sketch stepped alone."""
+    sizes = [1, 1023, 1024, 32_767, 32_768, 32_769, 65_536, 98_309, 0]
+    ms = [1 << 16, 70_001, (1 << 18) + 3, 1 << 20, 100_000, (1 << 22) + 1, 65_536, 1 << 19, 66_000]
+    rng = np.random.default_rng(g)
+    params = [dict(m=m, g=g if i == 2 else 64 << i % 3, k=3, hash_seed=i, layout="fast" if i % 2 else "small")
+              for i, m in enumerate(ms)]
+    bt = V.Batch(params)
+    single = [V.Sketch(p["m"], p["g"], p["k"], p["hash_seed"], p["layout"]) for p in params]
+    hosts = [V.to_device_u32(rng.integers(0, 2**32, 300, dtype=np.uint64).astype(np.uint32)) for _ in ms]
+    outs = [torch.empty(300, dtype=torch.float32, device="cuda") for _ in ms]
+    for t in range(2):
+        pairs = [V.to_device_u32(rng.integers(0, 2**32, 2 * n, dtype=np.uint64).astype(np.uint32)) for n in sizes]
+        bt.step(pairs, hosts, outs)
+        for i, sk in enumerate(single):
+            sk.scan_slice(pairs[i])
+            sk.advance_slice()
+            assert torch.equal(outs[i], sk.estimate(hosts[i])), (t, ms[i])
+            reg, hist = sk.registers()
+            assert np.array_equal(np.bincount(reg, minlength=33).astype(np.uint64), hist), (t, ms[i])
+        sizes = sizes[1:] + sizes[:1]
