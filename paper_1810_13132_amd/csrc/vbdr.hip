@@ -1585,8 +1585,9 @@ constexpr uint32_t kTileSub = 1u << kTileSlotBits;  // hosts per sub-block
 // accumulator that is never read, and its bounded loads return it past the
 // end of a run.
 constexpr uint32_t kTilePad = 0u;
-__device__ __forceinline__ uint32_t tile_rec(uint32_t off, uint32_t slot) {
-  return (off << 31) | ((slot + 1u) << 17) | (off >> 1);
+// Of pool index p, offset p & tmask (tmask != 0), rmask = (tmask >> 1) | 1u << 31.
+__device__ __forceinline__ uint32_t tile_rec(uint32_t p, uint32_t rmask, uint32_t slot) {
+  return (__builtin_amdgcn_alignbit(p, p, 1) & rmask) | ((slot + 1u) << 17);
 }
 __device__ __forceinline__ uint32_t tile_rec_acc(uint32_t rec) { return (rec >> 17) & 0xFFFu; }  // slot + 1; 0 for padding
 __device__ __forceinline__ uint32_t tile_rec_slot(uint32_t rec) { return tile_rec_acc(rec) - 1u; }
@@ -1597,6 +1598,7 @@ constexpr int kTileBinLog = 10;
 constexpr int kTileBinBlock = 1 << kTileBinLog;  // pass 1 workgroup
 constexpr int kTilePer = 16;              // (host, i) pairs per thread and chunk of pass 1
 constexpr uint32_t kTileChunk = kTileBinBlock * kTilePer;
+constexpr uint32_t kTileMaxCapb = 508, kTileZeroBit = 23;  // bucket entries at most; zero counts of pass 2's sums
 
 __host__ __device__ __forceinline__ uint32_t tile_chunk_hosts(uint32_t lg) {
   const uint32_t h = kTileChunk >> lg;
@@ -1675,7 +1677,7 @@ __global__ __launch_bounds__(kTileBinBlock) __attribute__((amdgpu_waves_per_eu(4
   uint32_t* kmix = cnt + nt + 1;
   uint32_t* s1l = kmix + 64;
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const uint32_t tmask = (1u << shift) - 1;
+  const uint32_t rmask = ((1u << shift) - 1) >> 1 | 1u << 31;
   const uint32_t xcd = blockIdx.x & 7, per_xcd = gridDim.x >> 3;  // the grid is a multiple of 8
   const uint32_t cps = kTileSub / hpc, nsb = (nh + kTileSub - 1) / kTileSub;
   // first host of the k-th chunk of this XCD (sub-blocks xcd, xcd + 8, ...), ~0u past the end
@@ -1707,6 +1709,29 @@ __global__ __launch_bounds__(kTileBinBlock) __attribute__((amdgpu_waves_per_eu(4
     auto pool_index = [&](uint32_t h) -> uint32_t { return POW2 ? h >> mshift : reduce_m(h, m); };
     const bool whole = npairs == kTileChunk;  // a full chunk: no pair is padding
     bool full = false;
+    // Counts and places a full chunk's records; cnt counts bytes.  A wave none of whose buckets
+    // is full, nearly every one, places them without clamps (stress shape: 219 -> 206 us, and
+    // 191 without the guards and slots of ragged chunks; g = 1024: 427 -> 422).
+    auto place = [&](auto slot_of) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < kTilePer; ++u) qv[u] = atomicAdd(&cnt[pv[u] >> shift], 4u);
+      uint32_t most = 0;
+#pragma unroll
+      for (int u = 0; u < kTilePer; ++u) most = qv[u] > most ? qv[u] : most;
+      if (__builtin_amdgcn_ballot_w64(most >= 4 * capb) == 0) {
+#pragma unroll
+        for (int u = 0; u < kTilePer; ++u)
+          *reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(bucket) + __umul24(pv[u] >> shift, 4 * bstride) + qv[u]) =
+              tile_rec(pv[u], rmask, slot_of(u));
+      } else {
+        full = true;
+#pragma unroll
+        for (int u = 0; u < kTilePer; ++u) {
+          const uint32_t q = qv[u] >> 2;
+          bucket[__umul24(pv[u] >> shift, bstride) + (q < capb ? q : capb)] = tile_rec(pv[u], rmask, slot_of(u));
+        }
+      }
+    };
     if (lg == kTileBinLog && whole) {
       // g = kTileBinBlock: pair u of every lane is (host u of the chunk,
       // virtual index tx), so the host keys are uniform and sit in registers
@@ -1716,47 +1741,40 @@ __global__ __launch_bounds__(kTileBinBlock) __attribute__((amdgpu_waves_per_eu(4
       for (int u = 0; u < kTilePer; ++u) km[u] = kmix[u];
 #pragma unroll
       for (int u = 0; u < kTilePer; ++u) pv[u] = pool_index(mm3_seeded(km[u], sv));
+      place([&](int u) { return slot0 + (uint32_t)u; });
+    } else if (lg > kTileBinLog && whole) {  // one host for g / kTileBinBlock consecutive u
+      const uint32_t gw = g >> kTileBinLog, hs = lg - kTileBinLog;
 #pragma unroll
-      for (int u = 0; u < kTilePer; ++u) qv[u] = atomicAdd(&cnt[pv[u] >> shift], 1u);
+      for (int u = 0; u < kTilePer; ++u)
+        pv[u] = pool_index(mm3_seeded(kmix[(uint32_t)u >> hs], s1l[(((uint32_t)u & (gw - 1)) << kTileBinLog) + tx]));
+      place([&](int u) { return slot0 + ((uint32_t)u >> hs); });
+    } else if (whole) {  // one seed per thread; hosts (tx >> lg) + u * (kTileBinBlock >> lg)
+      const uint32_t sv = s1l[tx & (g - 1)], kst = kTileBinBlock >> lg, first = slot0 + (tx >> lg);
+      const uint32_t* kp = kmix + (tx >> lg);
 #pragma unroll
-      for (int u = 0; u < kTilePer; ++u) {
-        const uint32_t p = pv[u];
-        bucket[__umul24(p >> shift, bstride) + (qv[u] < capb ? qv[u] : capb)] = tile_rec(p & tmask, slot0 + (uint32_t)u);
-        full |= qv[u] >= capb;
-      }
+      for (int u = 0; u < kTilePer; ++u) pv[u] = pool_index(mm3_seeded(kp[u * kst], sv));
+      place([&](int u) { return first + (uint32_t)u * kst; });
     } else {
-      if (lg <= kTileBinLog) {  // one seed per thread; hosts (tx >> lg) + u * (kTileBinBlock >> lg)
-        const uint32_t sv = s1l[tx & (g - 1)];
-        const uint32_t* kp = kmix + (tx >> lg);
-        const uint32_t kst = kTileBinBlock >> lg;
 #pragma unroll
-        for (int u = 0; u < kTilePer; ++u) {  // branch-free: kmix is zero past the chunk's hosts
-          const uint32_t p = pool_index(mm3_seeded(kp[(u * kst) & 63u], sv));
-          pv[u] = whole || (uint32_t)u * kTileBinBlock + tx < npairs ? p : ~0u;
-        }
-      } else {  // one host for g / kTileBinBlock consecutive u
-        const uint32_t gw = g >> kTileBinLog, hs = lg - kTileBinLog;
-#pragma unroll
-        for (int u = 0; u < kTilePer; ++u) {
-          const uint32_t p =
-              pool_index(mm3_seeded(kmix[(uint32_t)u >> hs], s1l[(((uint32_t)u & (gw - 1)) << kTileBinLog) + tx]));
-          pv[u] = whole || (uint32_t)u * kTileBinBlock + tx < npairs ? p : ~0u;
-        }
+      for (int u = 0; u < kTilePer; ++u) {  // branch-free: kmix is zero past the chunk's hosts
+        const uint32_t e = (uint32_t)u * kTileBinBlock + tx;
+        const uint32_t p = pool_index(mm3_seeded(kmix[(e >> lg) & 63u], s1l[e & (g - 1)]));
+        pv[u] = e < npairs ? p : ~0u;
       }
 #pragma unroll
-      for (int u = 0; u < kTilePer; ++u) qv[u] = atomicAdd(&cnt[pv[u] != ~0u ? pv[u] >> shift : nt], 1u);
+      for (int u = 0; u < kTilePer; ++u) qv[u] = atomicAdd(&cnt[pv[u] != ~0u ? pv[u] >> shift : nt], 4u);
 #pragma unroll
       for (int u = 0; u < kTilePer; ++u) {
-        const uint32_t p = pv[u], hl = ((uint32_t)u * kTileBinBlock + tx) >> lg;
+        const uint32_t p = pv[u], q = qv[u] >> 2;
         const uint32_t t = p != ~0u ? p >> shift : nt;
-        bucket[__umul24(t, bstride) + (qv[u] < capb ? qv[u] : capb)] = tile_rec(p & tmask, slot0 + hl);
-        full |= p != ~0u && qv[u] >= capb;
+        bucket[__umul24(t, bstride) + (q < capb ? q : capb)] = tile_rec(p, rmask, slot0 + (((uint32_t)u * kTileBinBlock + tx) >> lg));
+        full |= p != ~0u && q >= capb;
       }
     }
     if (full) {  // rare: entries beyond a bucket's capacity are gathered directly
 #pragma unroll
       for (int u = 0; u < kTilePer; ++u)
-        if (pv[u] != ~0u && qv[u] >= capb)
+        if (pv[u] != ~0u && qv[u] >= 4 * capb)
           atomicAdd(ovf_sb + slot0 + (((uint32_t)u * kTileBinBlock + tx) >> lg), sum_term(reg[pv[u]]));
     }
     __syncthreads();
@@ -1768,7 +1786,7 @@ __global__ __launch_bounds__(kTileBinBlock) __attribute__((amdgpu_waves_per_eu(4
       const uint32_t bpw = (nt + 15) >> 4, t0 = wave * bpw;  // nt <= 256
       uint32_t c_l = 0, b_l = 0;
       if (lane < bpw && t0 + lane < nt) {
-        const uint32_t t = t0 + lane, c = cnt[t];
+        const uint32_t t = t0 + lane, c = cnt[t] >> 2;
         c_l = c < capb ? c : capb;
         cnt[t] = 0;
         if (c_l) b_l = atomicAdd(&fill[sb * nt + t], (c_l + 3u) & ~3u);  // whole quads
@@ -1814,10 +1832,13 @@ __global__ __launch_bounds__(kTileBinBlock) __attribute__((amdgpu_waves_per_eu(4
 // global load here waits behind the prefetched runs; a record past the
 // list's capacity is gathered at once.  Every record, padding included,
 // takes the same branch-free steps (a byte read, a nibble extract, one LDS
-// add); zero and wide registers take a branch that a wave skips unless one
-// of its lanes holds one.  Runs are prefetched two sub-blocks ahead.
-constexpr uint32_t kTileAccU = kTileSub + 1, kTileAccV = kTileSub / 2;
-inline size_t tile_gather_lds(uint32_t shift) { return ((size_t)1 << shift) / 2 + 8 * (size_t)(kTileAccU + kTileAccV) + 16; }
+// add that also counts a zero register); wide registers take a branch that a
+// wave skips unless one of its lanes holds one.  Zero counts of their own took
+// that branch in nearly every wave of a window with 1 % zeros (315000 hosts,
+// g = 1024, 2^26 BDRs: 447 us, now 388, 4.2 TB/s of records and sums).  Runs
+// are prefetched two sub-blocks ahead.
+constexpr uint32_t kTileAcc = kTileSub + 1;
+inline size_t tile_gather_lds(uint32_t shift) { return ((size_t)1 << shift) / 2 + 8 * (size_t)kTileAcc + 16; }
 constexpr uint64_t kTileWideTotal = 1ull << 24;  // wide-list entries over all tiles (8 bytes each)
 template <int PRE>
 __global__ __launch_bounds__(kDeferBlock) void k_est_tile_gather(const uint8_t* __restrict__ reg4,
@@ -1833,12 +1854,16 @@ __global__ __launch_bounds__(kDeferBlock) void k_est_tile_gather(const uint8_t* 
                                                                  uint64_t m) {
   extern __shared__ uint32_t tile_w[];
   const bool narrow = tile_part_narrow(hist, m);  // 16-bit sums
-  // per-host sums in units of 2^18 (host slot s at s + 1; 0 takes the
-  // padding) and zero counts, double-buffered (one barrier per sub-block)
+  // per-host sums (host slot s at s + 1; 0 takes the padding), double-buffered
+  // (one barrier per sub-block): the terms in units of 2^18, at most 2^14
+  // each, and from bit kTileZeroBit the zero count.  A host has at most
+  // kTileMaxCapb records in a run (its chunk's bucket), so neither part
+  // overflows
+  static_assert(kTileMaxCapb << 14 < 1u << kTileZeroBit && (uint64_t)(kTileMaxCapb + 1) << kTileZeroBit <= 1ull << 32,
+                "sums of one host and tile");
   uint32_t* accu2 = tile_w + (1u << shift) / 8;
-  uint32_t* accv2 = accu2 + 2 * kTileAccU;
-  uint32_t* wide_n = accv2 + 2 * kTileAccV;  // entries in this tile's wide list
-  for (uint32_t q = threadIdx.x; q < 2 * (kTileAccU + kTileAccV) + 1; q += kDeferBlock) accu2[q] = 0;
+  uint32_t* wide_n = accu2 + 2 * kTileAcc;  // entries in this tile's wide list
+  for (uint32_t q = threadIdx.x; q < 2 * kTileAcc + 1; q += kDeferBlock) accu2[q] = 0;
   const uint32_t t = blockIdx.x;
   wide += (uint64_t)t * wcap;
   const uint64_t tbase = (uint64_t)t << shift;
@@ -1892,31 +1917,24 @@ __global__ __launch_bounds__(kDeferBlock) void k_est_tile_gather(const uint8_t* 
   };
   // gathers sub-block sbk from cur, then starts the load of sub-block sbk + 2 into nxt2
   auto sub_block = [&](uint32_t sbk, u32x4(&cur)[PQ], u32x4(&nxt2)[PQ]) __attribute__((always_inline)) {
-    uint32_t* accu = accu2 + (sbk & 1) * kTileAccU;
-    uint32_t* accv = accv2 + (sbk & 1) * kTileAccV;
+    uint32_t* accu = accu2 + (sbk & 1) * kTileAcc;
     unsigned long long* ovf_sb = ovf + (uint64_t)sbk * kTileSub;
     const uint32_t n = run_len(sbk);
     // one record: the register's term 2^(14-r) added to its host (0 for
     // r >= 15), given the byte that holds its nibble; returns the nibble
     auto gather = [&](uint32_t rec, uint32_t byte) -> uint32_t {
       const uint32_t nib = __builtin_amdgcn_ubfe(byte, rec >> 29, 4);
-      atomicAdd(&accu[tile_rec_acc(rec)], 0x4000u >> nib);
+      atomicAdd(&accu[tile_rec_acc(rec)], nib == 0u ? 0x4000u | 1u << kTileZeroBit : 0x4000u >> nib);
       return nib;
     };
-    // zero count of a record's host (nib == 0), or its wide register (nib
-    // == 15) put on the wide list; padding is skipped
+    // a record's wide register (nib == 15) put on the wide list; padding is skipped
     auto rare = [&](uint32_t rec, uint32_t nib) {
-      if (rec == kTilePad) return;
-      const uint32_t q = tile_rec_slot(rec);
-      if (nib == 0) {
-        atomicAdd(&accv[q >> 1], 1u << ((q & 1u) << 4));
-      } else if (nib == 15) {
-        const uint32_t at = atomicAdd(wide_n, 1u);
-        if (at < wcap)
-          wide[at] = make_uint2(sbk, rec);
-        else
-          atomicAdd(ovf_sb + q, sum_term(reg[tbase + tile_rec_off(rec)]));
-      }
+      if (rec == kTilePad || nib != 15u) return;
+      const uint32_t at = atomicAdd(wide_n, 1u);
+      if (at < wcap)
+        wide[at] = make_uint2(sbk, rec);
+      else
+        atomicAdd(ovf_sb + tile_rec_slot(rec), sum_term(reg[tbase + tile_rec_off(rec)]));
     };
     load_run(sbk + 2, nxt2);
     if (sbk == 0) __syncthreads();  // the tile and the zeroed accumulators
@@ -1935,7 +1953,7 @@ __global__ __launch_bounds__(kDeferBlock) void k_est_tile_gather(const uint8_t* 
       for (int e = 0; e < 4; ++e) nib[e] = gather(r4[e], by[e]);
       bool any = false;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) any |= nib[e] == 0u || nib[e] == 15u;
+      for (int e = 0; e < 4; ++e) any |= nib[e] == 15u;
       if (__builtin_amdgcn_ballot_w64(any)) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) rare(r4[e], nib[e]);
@@ -1946,22 +1964,22 @@ __global__ __launch_bounds__(kDeferBlock) void k_est_tile_gather(const uint8_t* 
       rare(rec, gather(rec, tl[rec & 0x1FFFFu]));
     }
     __syncthreads();
-    {  // thread w packs hosts 2w and 2w + 1 (one zero-count word) and clears
-       // them for the sub-block two on, after the next barrier (the spare
-       // slot is never read)
-      static_assert(kDeferBlock == kTileSub / 2, "one zero-count word per thread");
-      const uint32_t w = threadIdx.x, v = accv[w], h = sbk * kTileSub + 2 * w;
+    {  // thread w packs hosts 2w and 2w + 1 and clears them for the sub-block
+       // two on, after the next barrier (the spare slot is never read)
+      static_assert(kDeferBlock == kTileSub / 2, "two hosts per thread");
+      constexpr uint32_t kLow = (1u << kTileZeroBit) - 1;
+      const uint32_t w = threadIdx.x, h = sbk * kTileSub + 2 * w, a = accu[2 * w + 1], b = accu[2 * w + 2];
       if (narrow) {
-        const uint32_t lo = pack_part16(accu[2 * w + 1], v & 0xFFFFu, ovf + h),
-                       hi = pack_part16(accu[2 * w + 2], v >> 16, ovf + h + 1);
+        const uint32_t lo = pack_part16(a & kLow, a >> kTileZeroBit, ovf + h),
+                       hi = pack_part16(b & kLow, b >> kTileZeroBit, ovf + h + 1);
         *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(part) + (uint64_t)t * B + h) = lo | hi << 16;
       } else {
         uint2 pr;
-        pr.x = pack_part32(accu[2 * w + 1], v & 0xFFFFu, ovf + h);
-        pr.y = pack_part32(accu[2 * w + 2], v >> 16, ovf + h + 1);
+        pr.x = pack_part32(a & kLow, a >> kTileZeroBit, ovf + h);
+        pr.y = pack_part32(b & kLow, b >> kTileZeroBit, ovf + h + 1);
         *reinterpret_cast<uint2*>(part + (uint64_t)t * B + h) = pr;
       }
-      accu[2 * w + 1] = 0, accu[2 * w + 2] = 0, accv[w] = 0;
+      accu[2 * w + 1] = 0, accu[2 * w + 2] = 0;
     }
   };
   load_run(0, ra);
@@ -2478,7 +2496,7 @@ int create_sketch(uint64_t m, uint32_t g, uint32_t k, uint64_t hash_seed, int la
       const uint32_t capb = ((uint32_t)(Eb + 4.0 * std::sqrt(Eb) + 4.0) + 3u) & ~3u;
       const size_t lds1 = tile_bin_lds(nt, capb, g);
       const size_t lds2 = tile_gather_lds(sh);  // the tile and two accumulator buffers
-      if (sh <= kTileMaxShift && B >= kTileSub && lds1 + 1024 <= (size_t)lds_max && lds2 <= (size_t)lds_max) {
+      if (sh <= kTileMaxShift && capb <= kTileMaxCapb && B >= kTileSub && lds1 + 1024 <= (size_t)lds_max && lds2 <= (size_t)lds_max) {
         const double E = (double)kTileSub * g * (double)(1ull << sh) / (double)m;
         sk->tl_ok = true;
         sk->tl_shift = sh, sk->tl_nt = nt, sk->tl_B = (uint32_t)B, sk->tl_capb = capb;

@@ -660,6 +660,25 @@ def test_estimate_routes(V, O, m, g):
         assert torch.equal(sk.estimate_noalloc(hd, torch.empty(n, dtype=torch.float32, device="cuda")), ref[:n]), n
 
 
+@pytest.mark.parametrize("g", [64, 512, 1024, 2048, 16384])
+@pytest.mark.parametrize("m", [1 << 22, (1 << 22) + 4099])
+def test_tiled_chunks_and_zero_counts(V, O, m, g):
+    """The LDS-tiled estimate with a host's g pairs below, at and above a
+    workgroup's threads, whole chunks and ragged ones, in an almost empty pool
+    (every gather a zero count) and a filled one: the bits of estimate_ex."""
+    rng = np.random.default_rng(g + m)
+    sk = V.Sketch(m, g, 3, 21, "small")
+    sk.set_tuning(est_binned=3)
+    hosts = rng.integers(0, 2**32, 6_151, dtype=np.uint64).astype(np.uint32)
+    for pairs in (1000, 3 * m):
+        sk.scan_slice(_dev(V, rng.integers(0, 2**32, (pairs, 2), dtype=np.uint64).astype(np.uint32).reshape(-1)))
+        sk.advance_slice()
+        assert sk.info().est_tiled == 1 or g == 16384  # whose seeds leave the buckets too little LDS
+        ref = sk.estimate_ex(_dev(V, hosts))[0]
+        for n in (1, 2048, 4099, 6_151):
+            assert torch.equal(sk.estimate(_dev(V, hosts[:n])), ref[:n]), (pairs, n)
+
+
 def test_bad_arguments_on_device(V):
     sk = V.Sketch(5000, 16, 3, 1, "small")
     pairs = torch.zeros(8, dtype=torch.int32, device="cuda")
