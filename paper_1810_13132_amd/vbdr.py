@@ -141,19 +141,22 @@ def _check(rc: int):
         raise VbdrError(rc, lib().vbdr_last_error().decode())
 
 
-def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+def _stream(stream=None) -> int:
+    """The stream's handle.  torch.cuda.current_stream() makes a Stream object of it,
+    2.6 us of a small call's 7; the raw handle takes 0.3."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
-def _dev_ptr(t: torch.Tensor, dtypes, name: str):
+def _dev_ptr(t: torch.Tensor, dtypes, name: str) -> int:
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
     if t.dtype not in dtypes:
         raise ValueError(f"{name} has dtype {t.dtype}, expected one of {dtypes}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 _U32 = (torch.int32, torch.uint32)
@@ -257,7 +260,7 @@ class Sketch:
         n = pairs.numel() // 2
         if pairs.numel() != 2 * n:
             raise ValueError("pairs must hold an even number of uint32")
-        ptr = _dev_ptr(pairs, _U32, "pairs") if n else C.c_void_p()
+        ptr = _dev_ptr(pairs, _U32, "pairs") if n else None
         _check(lib().vbdr_scan_slice(self._h, ptr, n, _stream(stream)))
 
     def advance_slice(self, stream=None):
@@ -528,12 +531,12 @@ class Batch:
             (C.c_void_p * n)()
         for i in range(n):
             npairs = pairs[i].numel() // 2
-            P[i] = _dev_ptr(pairs[i], _U32, "pairs").value if npairs else None
+            P[i] = _dev_ptr(pairs[i], _U32, "pairs") if npairs else None
             NP[i] = npairs
             nh = hosts[i].numel()
             if outs[i].numel() != nh:
                 raise ValueError("out must have one float per host")
-            Hh[i] = _dev_ptr(hosts[i], _U32, "hosts").value if nh else None
-            O[i] = _dev_ptr(outs[i], (torch.float32,), "out").value if nh else None
+            Hh[i] = _dev_ptr(hosts[i], _U32, "hosts") if nh else None
+            O[i] = _dev_ptr(outs[i], (torch.float32,), "out") if nh else None
             NH[i] = nh
         _check(lib().vbdr_batch_step(self._h, P, NP, Hh, NH, O, _stream(stream)))
