@@ -2616,8 +2616,7 @@ int estimate_direct(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_hosts
   if (stage && !extra) return estimate_rows(sk, hosts_dev, n_hosts, out_dev, st);
   const size_t lds = stage ? (size_t)sk->g * 4 : 0;
   const uint32_t grid = grid_cap(sk, (n_hosts + kEstWaves - 1) / kEstWaves, sk->tune.est_blocks_per_cu);
-  auto kern = stage ? (extra ? k_estimate<true, true> : k_estimate<true, false>)
-                    : (extra ? k_estimate<false, true> : k_estimate<false, false>);
+  const auto kern = stage ? k_estimate<true, true> : extra ? k_estimate<false, true> : k_estimate<false, false>;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kEstBlock), lds, st, hosts_dev, n_hosts, sk->s1, sk->g, (uint32_t)sk->m,
                      sk->reg, sk->hist, out_dev, raw_es_dev, hist_dev);
   VBDR_LAUNCHED("k_estimate");
