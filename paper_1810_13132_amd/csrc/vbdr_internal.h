@@ -104,7 +104,7 @@ struct vbdr_sketch {
 };
 
 // vbdr_sketch_create_layout without the optional large-pool workspaces;
-// with defer, pools of 2^22..2^26 BDRs keep the record runs of deferred scans.
+// with defer, pools that scan through records keep their runs.
 int vbdr_sketch_create_lean(uint64_t m, uint32_t g, uint32_t k, uint64_t hash_seed, int layout, bool defer,
                             vbdr_sketch** out);
 
