@@ -2230,7 +2230,9 @@ int vbdr_hist_pass(vbdr_sketch* sk, const uint32_t* hosts_dev, uint32_t nh, hipS
   if (nh > chunk) return vbdr_fail(VBDR_EINVAL, "histogram pass of %u hosts exceeds %u", nh, chunk);
   uint32_t shift = 31;
   while (parts > 1 && (1u << (32 - shift)) < parts) --shift;
-  const uint64_t cap = (uint64_t)sk->n_cu * 8 / parts;
+  // four workgroups for each that fits the CUs, so that the CUs even out (30000 hosts, g = 2048, 2^24 BDRs, learned:
+  // 311 us with one, in two rounds of which the second was not full, now 306; 65552: 646, 631)
+  const uint64_t cap = (uint64_t)sk->n_cu * 32 / parts;
   if (g <= kStageMaxG && parts <= kHistRowsParts) {
     // 16 lanes a host (hist_hosts: at most 128 registers a lane); a wave a host while that keeps its waves
     // few (features of 64 hosts, g = 2048: 23.2 us with 16 lanes, 12.4 with a wave, host path included)
