@@ -188,8 +188,10 @@ int vbdr_estimate_noalloc(vbdr_sketch *sk, const uint32_t *hosts_dev, uint64_t n
  * E_m is the same estimator over the pool; the sharing noise is removed
  * with (m E_s - g E_m)/(m - g), clamped at 0, FP64 then FP32, as for
  * HyperLogLog.  raw_es_dev (n_hosts double, nullable) receives E_s.
- * Stream-ordered, workspaces as in vbdr_estimate.  VBDR_ESTATE for PCSA
- * before runs exist.
+ * Stream-ordered.  LogLog and PCSA use no workspace of the sketch (partial
+ * sums live in out_dev, which must not overlap hosts_dev): such estimates of
+ * one sketch may run beside each other and beside vbdr_estimate on other
+ * streams.  VBDR_ESTATE for PCSA before runs exist.
  * vbdr_export_pcsa copies the m PCSA runs of the last closed window to host
  * memory (synchronous).  vbdr_enable_pcsa(sk, 0) frees the runs.
  */

@@ -1368,9 +1368,10 @@ __device__ __forceinline__ void sum_estimate(const SumEst& E, double Em, uint64_
   if (E.raw) E.raw[h] = Es;
 }
 
-// LPH lanes a host, per_wave hosts a wave.  PART: workgroup b sums the values
-// of range b mod parts into psum, [parts][pstride], for k_sum_final; otherwise
-// the estimates.  STAGE: seeds in LDS.  Gathers bound it, at an L2's tag rate
+// LPH lanes a host, per_wave hosts a wave.  PART: workgroup b adds the values
+// of range b mod parts to the host's entry of out, a whole number until
+// k_sum_final makes the estimate of it (out, cleared before, is the call's own:
+// estimates on other streams share nothing with it); otherwise the estimates.  STAGE: seeds in LDS.  Gathers bound it, at an L2's tag rate
 // where the values fit one: 20000 hosts, g = 512, 2^22 runs, call included,
 // 43.5 us (63.5 with four gathers in flight and the pool's sum read on the host
 // before the launch); 1e5 hosts, g = 2048, 0.9 2^25 runs: 819 us in 8 ranges,
@@ -1380,8 +1381,7 @@ __global__ __launch_bounds__(kRowBlock) void k_estimate_sum(const uint32_t* __re
                                                             uint32_t per_wave, const uint32_t* __restrict__ s1g,
                                                             uint32_t g, uint32_t m, const uint8_t* __restrict__ val,
                                                             const uint8_t* __restrict__ val4, uint32_t parts,
-                                                            uint32_t part_shift, uint32_t* __restrict__ psum,
-                                                            uint32_t pstride, SumEst E) {
+                                                            uint32_t part_shift, SumEst E) {
   extern __shared__ uint32_t lds[];
   if constexpr (STAGE) {
     for (uint32_t i = threadIdx.x; i < g; i += kRowBlock) lds[i] = s1g[i];
@@ -1395,19 +1395,15 @@ __global__ __launch_bounds__(kRowBlock) void k_estimate_sum(const uint32_t* __re
     const uint32_t n = nh - h < per_wave ? (uint32_t)(nh - h) : per_wave;
     const uint32_t S = sum_hosts<LPH, PART, NIB>(hosts + h, n, STAGE ? lds : s1g, g, m, val, val4, x, part_shift);
     if (lane < n) {
-      if constexpr (PART) psum[(uint64_t)x * pstride + h + lane] = S;
+      if constexpr (PART) atomicAdd(reinterpret_cast<uint32_t*>(E.out) + h + lane, S);
       else sum_estimate(E, Em, h + lane, S, g, m);
     }
   }
 }
 
-__global__ __launch_bounds__(256) void k_sum_final(uint32_t nh, uint32_t g, uint32_t m, uint32_t parts,
-                                                   const uint32_t* __restrict__ psum, uint32_t pstride, SumEst E) {
+__global__ __launch_bounds__(256) void k_sum_final(uint32_t nh, uint32_t g, uint32_t m, SumEst E) {
   const uint32_t h = blockIdx.x * 256 + threadIdx.x;
-  if (h >= nh) return;
-  uint32_t S = 0;
-  for (uint32_t x = 0; x < parts; ++x) S += psum[(uint64_t)x * pstride + h];
-  sum_estimate(E, sum_pool(E, m), h, S, g, m);
+  if (h < nh) sum_estimate(E, sum_pool(E, m), h, __float_as_uint(E.out[h]), g, m);
 }
 
 // ------------------------------------------------- per-slice max-LBP1 map
@@ -3107,12 +3103,16 @@ int vbdr_estimate_kind(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_ho
         : rows    ? (nib ? k_estimate_sum<16, true, false, true> : k_estimate_sum<16, false, false, true>)
         : stage   ? (nib ? k_estimate_sum<64, true, false, true> : k_estimate_sum<64, false, false, true>)
                   : (nib ? k_estimate_sum<64, true, false, false> : k_estimate_sum<64, false, false, false>);
+    if (parts > 1) {
+      hipLaunchKernelGGL(k_fill_u32, dim3(grid_cap(sk, (nh + 255) / 256, 8)), dim3(256), 0, st,
+                         reinterpret_cast<uint32_t*>(e.out), nh, 0u);
+      VBDR_LAUNCHED("k_fill_u32(sums)");
+    }
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kRowBlock), lds, st, hosts_dev + c, nh, (uint32_t)per, sk->s1, sk->g, m32,
-                       val, sk->reg4, parts, shift, sk->part_v, kPartChunk, e);
+                       val, sk->reg4, parts, shift, e);
     VBDR_LAUNCHED("k_estimate_sum");
     if (parts == 1) continue;
-    hipLaunchKernelGGL(k_sum_final, dim3((uint32_t)((nh + 255) / 256)), dim3(256), 0, st, (uint32_t)nh, sk->g, m32, parts,
-                       sk->part_v, kPartChunk, e);
+    hipLaunchKernelGGL(k_sum_final, dim3((uint32_t)((nh + 255) / 256)), dim3(256), 0, st, (uint32_t)nh, sk->g, m32, e);
     VBDR_LAUNCHED("k_sum_final");
   }
   return VBDR_OK;

@@ -153,3 +153,27 @@ def test_sum_routes(V, m, g):
             a, b = (0, n) if n <= few else (len(hosts) - n, len(hosts))
             o, r = sk.estimate_kind(hd[a:b].contiguous(), kind, with_raw=True)
             assert torch.equal(o, out[a:b]) and torch.equal(r, raw[a:b]), (kind, n)
+
+
+@pytest.mark.parametrize("m,g,nh", [((1 << 24) + 1, 256, 30_001), ((1 << 25) + 5, 1024, 9_000)])
+def test_sums_share_nothing_between_streams(V, m, g, nh):
+    """LogLog, PCSA and HyperLogLog estimates of one sketch on three streams at
+    once, in pool ranges (different hosts each): the results of one after the other."""
+    rng = np.random.default_rng(g + 2)
+    sk = V.Sketch(m, g, 3, 21, "small")
+    sk.enable_pcsa(True)
+    sk.scan_slice(V.to_device_u32(rng.integers(0, 2**32, m // 2 * 2, dtype=np.uint64).astype(np.uint32)))
+    sk.advance_slice()
+    hosts = [V.to_device_u32(rng.integers(0, 2**32, nh, dtype=np.uint64).astype(np.uint32)) for _ in range(3)]
+    kinds = ("loglog", "pcsa", "hll")
+    alone = [sk.estimate_kind(h, k) for h, k in zip(hosts, kinds)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in kinds]
+    for _ in range(10):
+        outs = []
+        for h, k, s in zip(hosts, kinds, streams):
+            with torch.cuda.stream(s):
+                outs.append(sk.estimate_kind(h, k))
+        torch.cuda.synchronize()
+        for a, o, k in zip(alone, outs, kinds):
+            assert torch.equal(a, o), k
