@@ -2300,19 +2300,21 @@ uint32_t tile_shift(uint64_t mstride, bool lean) {
 // ms against 0.43, advance 0.17 against 0.27).  The runs of a sketch
 // therefore take 2^27 slots (512 MB) where that is at most 16 per BDR, so
 // that pools below 2^26 BDRs also hold slices of 2^27 pairs, with a quarter
-// tile to spare for uneven tiles; small pools take 2^22 slots (16 MB).  Members of a batch (up to 256, each with
-// its own runs) take twice the smallest run up to 2^23 BDRs; any sketch
-// takes the smallest where the device has little memory left.
-uint32_t defer_run_cap(uint64_t m, uint32_t tshift, bool lean) {
+// tile to spare for uneven tiles; pools from 2^16 BDRs take 2^22 slots (16 MB)
+// at least.  Members of a batch (up to 256, each with its own runs) take twice
+// the smallest run up to 2^23 BDRs; any sketch takes the smallest where the
+// runs would be more than an eighth of the device's free memory.
+uint32_t defer_run_cap(uint64_t m, uint32_t tshift, uint32_t tiles, bool lean) {
+  const uint64_t tile = 1ull << tshift;
   uint64_t slots = (kDeferBudget + m - 1) / m;
   const uint64_t most = lean ? (m <= (1ull << 23) ? 2 * kDeferSlots : kDeferSlots) : kDeferSlotsMax;
   slots = slots < kDeferSlots ? kDeferSlots : slots > most ? most : slots;
-  const uint64_t least = kDeferLeast / m;  // small pools: more a BDR
+  const uint64_t least = m >= kDeferMinM ? kDeferLeast / m : 0;  // smaller pools (packed): 16 a BDR are 256 KB a tile
   if (slots < least) slots = least;
+  uint64_t cap = slots * tile + (slots > kDeferSlots ? tile / 4 : 0);
   size_t free_b = 0, total_b = 0;
-  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b / 8 < slots * m * 4) slots = kDeferSlots;
-  const uint32_t tile = 1u << tshift;
-  return (uint32_t)slots * tile + (slots > kDeferSlots ? tile / 4 : 0);
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b / 8 < tiles * cap * 4) cap = kDeferSlots * tile;
+  return (uint32_t)cap;  // at most 64 slots of 2^12 BDRs or 16 of 2^15
 }
 
 // Hosts per block of the tiled estimate under the current tuning: the
@@ -2436,7 +2438,7 @@ int create_sketch(uint64_t m, uint32_t g, uint32_t k, uint64_t hash_seed, int la
       if (defer_scan_lds(tiles, kDeferPer) + 1024 <= (size_t)lds_max &&
           ((size_t)32 << (sk->tshift - 3)) + 24576 <= (size_t)lds_max) {
         sk->def_tiles = tiles;
-        sk->def_cap = defer_run_cap(m, sk->tshift, lean);
+        sk->def_cap = defer_run_cap(m, sk->tshift, tiles, lean);
         def_bytes = (uint64_t)tiles * sk->def_cap * 4 + (uint64_t)(tiles + 1) * 8;
       }
     }

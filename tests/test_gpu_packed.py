@@ -108,3 +108,26 @@ def test_packed_memory_and_refusals(V):
         packed.enable_pcsa(True)
     with pytest.raises(V.VbdrError):
         V.Sketch(1 << 22, 1024, 60, 1, "packed", Lc=24)
+
+
+@pytest.mark.parametrize("m,g", [(3, 2), (5, 4), (65, 16), (300, 64), (4097, 8), (65_000, 64)])
+def test_small_packed_pools_hold_small_runs(V, O, m, g):
+    """The record runs of a packed pool follow its (padded) size: at most 16 1/4
+    records of 4 bytes per BDR below 2^16, whatever m, beside the host workspaces
+    that every sketch holds.  A slice past them still matches the oracle."""
+    sk = V.Sketch(m, g, 3, 5, "packed", Lc=8)
+    ref = V.Sketch(1 << 15, g, 3, 5, "small")  # no runs: the host workspaces alone
+    tiles = (m + 4095) // 4096
+    assert sk.info().workspace_bytes - ref.info().workspace_bytes <= tiles * (65 * 4096 + 8) + 8
+    osk = O.Sketch(m, g, 3, 5, O.GPACKED, Lc=8)
+    rng = np.random.default_rng(m)
+    for n in (5000, 300_000, 0):
+        p_ = rng.integers(0, 2**32, (n, 2), dtype=np.uint64).astype(np.uint32)
+        p_[: n // 2] = p_[:1]
+        sk.scan_slice(V.to_device_u32(p_.reshape(-1)))
+        osk.scan(p_)
+        _equal(sk, osk, n)
+        sk.scan_slice(V.to_device_u32(p_.reshape(-1)))  # pending at the advance
+        sk.advance_slice()
+        osk.advance()
+        _equal(sk, osk, n)
