@@ -302,6 +302,19 @@ int vbdr_sketch_set_tuning(vbdr_sketch *sk, const vbdr_tuning *tuning);
 int vbdr_sketch_get_tuning(const vbdr_sketch *sk, vbdr_tuning *tuning);
 
 /*
+ * How vbdr_scan_slice would take a scan of n_pairs, and what the sketch's
+ * record runs hold (they shrink where little device memory is left at their
+ * allocation).  Host only, no device work.
+ */
+typedef struct vbdr_scan_route {
+    uint64_t run_records; /* records that a tile's run holds in a slice; the rest update the pool. 0: no runs */
+    uint32_t tile_bdrs;   /* BDRs per tile of the runs (BDR p is in tile p / tile_bdrs) */
+    uint32_t tiles;
+    int32_t records;      /* 1: the scan writes records; 0: it updates the pool itself */
+} vbdr_scan_route;
+int vbdr_sketch_scan_route(const vbdr_sketch *sk, uint64_t n_pairs, vbdr_scan_route *out);
+
+/*
  * Copy the sketch state to host memory in canonical form (synchronous:
  * waits for `stream`).  Any pointer may be NULL.
  *   dr_host   m*L bytes, dr_host[p*L + (r-1)] = DR of LBP1 r in BDR p;

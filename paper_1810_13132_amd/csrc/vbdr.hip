@@ -2154,6 +2154,17 @@ static bool has_runs(const vbdr_sketch* sk) {
   return sk->def_rec && (sk->tune.scan_defer == 1 || sk->layout == VBDR_LAYOUT_PACKED);
 }
 
+// Whether a scan of n pairs goes through the record runs.  Small slices of small
+// pools update the pool themselves (no saturation masks to keep there): a
+// chunk's sort and its run reservations take about 8 us (2^20 BDRs: 2^20 pairs
+// 13 us either way in the small layout, 2^22 pairs 54 us direct, 25 deferred;
+// fast layout, 2^18 BDRs: 2^17 pairs 10 us direct, 7 deferred).
+static bool scans_records(const vbdr_sketch* sk, uint64_t n) {
+  if (!has_runs(sk)) return false;
+  if (sk->m >= kPartMinM || sk->layout == VBDR_LAYOUT_PACKED) return true;
+  return n > (sk->layout == VBDR_LAYOUT_FAST ? kDirectFast : kDirectSmall);
+}
+
 // The word that says whether bsLBP1 planes may hold bits; NULL: they may.
 static const unsigned long long* direct_flag(const vbdr_sketch* sk) {
   return has_runs(sk) ? sk->def_fill + sk->def_tiles : nullptr;
@@ -2750,6 +2761,16 @@ int vbdr_sketch_get_tuning(const vbdr_sketch* sk, vbdr_tuning* tuning) {
   return VBDR_OK;
 }
 
+int vbdr_sketch_scan_route(const vbdr_sketch* sk, uint64_t n_pairs, vbdr_scan_route* out) {
+  if (!sk || !out) return vbdr_fail(VBDR_EINVAL, "NULL argument");
+  const bool runs = has_runs(sk);
+  out->run_records = runs ? sk->def_cap : 0;
+  out->tile_bdrs = runs ? 1u << sk->tshift : 0u;
+  out->tiles = runs ? sk->def_tiles : 0u;
+  out->records = scans_records(sk, n_pairs);
+  return VBDR_OK;
+}
+
 int vbdr_sketch_info(const vbdr_sketch* sk, vbdr_info* out) {
   if (!sk || !out) return vbdr_fail(VBDR_EINVAL, "NULL argument");
   out->m = sk->m, out->g = sk->g, out->b = sk->b, out->L = sk->L, out->k = sk->k;
@@ -2780,13 +2801,7 @@ int vbdr_scan_slice(vbdr_sketch* sk, const uint32_t* pairs_dev, uint64_t n, void
   const u32x2* p = reinterpret_cast<const u32x2*>(pairs_dev);
   const uint32_t m32 = (uint32_t)sk->m;
   const bool test = sk->tune.scan_test_first == 1;
-  // Small slices of small pools update the pool themselves (no saturation
-  // masks to keep there): a chunk's sort and its run reservations take about
-  // 8 us (2^20 BDRs: 2^20 pairs 13 us either way in the small layout, 2^22 pairs
-  // 54 us direct, 25 deferred; fast layout, 2^18 BDRs: 2^17 pairs 10 us direct, 7 deferred).
-  const bool direct = sk->m < kPartMinM && sk->layout != VBDR_LAYOUT_PACKED &&
-                      n <= (sk->layout == VBDR_LAYOUT_FAST ? kDirectFast : kDirectSmall);
-  if (has_runs(sk) && !direct) {
+  if (scans_records(sk, n)) {
     // the longest chunks that still give every CU one
     uint32_t per = 4;
     while (per < (uint32_t)kDeferPer && n >= (uint64_t)2 * per * kDeferBlock * (uint64_t)sk->n_cu) per *= 2;

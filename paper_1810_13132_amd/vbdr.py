@@ -45,6 +45,10 @@ class Tuning(C.Structure):
                 ("est_bin_cap", C.c_uint32), ("scan_defer", C.c_int32)]
 
 
+class ScanRoute(C.Structure):
+    _fields_ = [("run_records", C.c_uint64), ("tile_bdrs", C.c_uint32), ("tiles", C.c_uint32), ("records", C.c_int32)]
+
+
 class BatchParams(C.Structure):
     _fields_ = [("m", C.c_uint64), ("g", C.c_uint32), ("k", C.c_uint32), ("hash_seed", C.c_uint64),
                 ("layout", C.c_int32)]
@@ -65,7 +69,7 @@ EXPORTS = ["vbdr_sketch_create", "vbdr_sketch_create_layout", "vbdr_sketch_creat
            "vbdr_batch_set_tuning", "vbdr_batch_get_tuning", "vbdr_batch_step", "vbdr_select_hosts",
            "vbdr_export_now", "vbdr_import_now", "vbdr_now_max", "vbdr_enable_pcsa", "vbdr_estimate_kind",
            "vbdr_export_pcsa", "vbdr_test_fail_alloc", "vbdr_estimate_noalloc",
-           "vbdr_batch_set_mlp", "vbdr_mlp_set_plain_above"]
+           "vbdr_batch_set_mlp", "vbdr_mlp_set_plain_above", "vbdr_sketch_scan_route"]
 VOID_EXPORTS = ("vbdr_sketch_destroy", "vbdr_last_error", "vbdr_mlp_destroy", "vbdr_trainer_destroy",
                 "vbdr_batch_destroy", "vbdr_batch_sketch")
 MLP_IN, MLP_PARAMS = 67, 8577
@@ -96,6 +100,7 @@ def lib():
         L.vbdr_import_state.argtypes = [vp, vp, vp, vp, vp, u64, vp]
         L.vbdr_sketch_set_tuning.argtypes = [vp, C.POINTER(Tuning)]
         L.vbdr_sketch_get_tuning.argtypes = [vp, C.POINTER(Tuning)]
+        L.vbdr_sketch_scan_route.argtypes = [vp, u64, C.POINTER(ScanRoute)]
         L.vbdr_mlp_create.argtypes = [vp, vp, vp, C.POINTER(vp)]
         L.vbdr_mlp_destroy.argtypes = [vp]
         L.vbdr_mlp_set_plain_above.argtypes = [vp, C.c_float]
@@ -251,6 +256,12 @@ class Sketch:
                 "est_blocks_per_cu": t.est_blocks_per_cu, "scan_binned": t.scan_binned, "est_binned": t.est_binned,
                 "est_parts": t.est_parts, "est_bin_hosts": t.est_bin_hosts,
                 "est_bin_cap": t.est_bin_cap, "scan_defer": t.scan_defer}
+
+    def scan_route(self, n_pairs: int) -> ScanRoute:
+        """How a scan of n_pairs would go, and what the record runs hold (run_records a tile of tile_bdrs BDRs)."""
+        out = ScanRoute()
+        _check(lib().vbdr_sketch_scan_route(self._h, int(n_pairs), C.byref(out)))
+        return out
 
     @property
     def t(self) -> int:

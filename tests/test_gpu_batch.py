@@ -287,3 +287,39 @@ def test_batch_scan_chunks(V, g):
             reg, hist = sk.registers()
             assert np.array_equal(np.bincount(reg, minlength=33).astype(np.uint64), hist), (t, ms[i])
         sizes = sizes[1:] + sizes[:1]
+
+
+@pytest.mark.parametrize("layout", ["fast", "small"])
+def test_batch_member_runs_overflow(V, layout):
+    """Members whose record runs (their capacity asked of the library) are filled
+    exactly and passed, against the oracle after every step, beside a member that
+    scans without runs."""
+    from oracle import oracle as O
+    params = [dict(m=(1 << 20) + 3, g=256, k=3, hash_seed=9, layout=layout),
+              dict(m=1 << 18, g=64, k=2, hash_seed=10, layout=layout),
+              dict(m=5000, g=64, k=2, hash_seed=11, layout="small")]
+    rng = np.random.default_rng(12)
+    bt = V.Batch(params)
+    osks = [O.Sketch(p["m"], p["g"], p["k"], p["hash_seed"], O.GFAST if layout == "fast" and i < 2 else O.GSMALL)
+            for i, p in enumerate(params)]
+    caps = [int(sk.scan_route(1).run_records) for sk in bt.sketches]
+    assert caps[0] > 0 and caps[1] > 0 and caps[2] == 0
+    hosts = [np.concatenate([[77], rng.integers(0, 2**32, 100, dtype=np.uint64)]).astype(np.uint32) for _ in params]
+    hd = [V.to_device_u32(h) for h in hosts]
+    for over in ((0, 1), (1, 0), (20_000, 100_000), (-1, -5), (0, 300_000)):
+        step = []
+        for i, p in enumerate(params):
+            n = caps[i] + over[i] if i < 2 else 1000
+            flood = np.tile(np.array([[77, 5]], np.uint32), (n, 1))
+            if over[i % 2] > 1:  # other tiles and LBP1 values too
+                flood[-500:, 1] = rng.integers(0, 2**32, 500, dtype=np.uint64).astype(np.uint32)
+            step.append(flood)
+        outs = [torch.empty(len(h), dtype=torch.float32, device="cuda") for h in hosts]
+        bt.step([V.to_device_u32(s.reshape(-1)) for s in step], hd, outs)
+        for i, osk in enumerate(osks):
+            osk.scan(step[i])
+            osk.advance()
+            sb, so = bt.sketches[i].state(), osk.state()
+            for key in ("dr", "reg", "hist"):
+                assert np.array_equal(sb[key], so[key]), (over, i, key)
+            assert torch.equal(outs[i], bt.sketches[i].estimate(hd[i])), (over, i)

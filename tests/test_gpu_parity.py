@@ -596,6 +596,91 @@ def test_record_runs_at_their_capacity(V, O, layout):
         assert_state_equal(sk.state(), osk.state(), layout, f"runs of {sizes}")
 
 
+def _flood(O, m, g, seed, tile_bdrs, rng):
+    """A pair and a source of other pairs (n of them, none in its tile)."""
+    pair = np.array([[11, 12]], np.uint32)
+    tile = int(O.map_pairs(m, g, seed, pair)[0][0]) // tile_bdrs
+
+    def others(n):
+        p_ = rng.integers(0, 2**32, (2 * n + 4096, 2), dtype=np.uint64).astype(np.uint32)
+        p_ = p_[O.map_pairs(m, g, seed, p_)[0] // tile_bdrs != tile][:n]
+        assert len(p_) == n
+        return p_
+
+    return pair, others
+
+
+@pytest.mark.parametrize("layout,m", [("fast", (1 << 18) + 1), ("small", (1 << 19) + 1), ("packed", 9001), ("fast", 1 << 22),
+                                      ("small", 1 << 22)])
+def test_record_runs_filled_exactly(V, O, layout, m):
+    """A tile's run (its capacity asked of the library) filled to one record
+    less, exactly and one more; a call that starts with a full run; one whose
+    last records straddle the end, the tile's others in the run.  State
+    before and after the advance against the oracle."""
+    g, k, seed = 64, 3, 9
+    rng = np.random.default_rng(44)
+    Lc = 20 if layout == "packed" else 0
+    sk = V.Sketch(m, g, k, seed, layout, Lc=Lc)
+    osk = O.Sketch(m, g, k, seed, O.GPACKED if layout == "packed" else LAYOUT_CODE[layout], Lc=Lc)
+    pad = (1 << 20) + 1 if layout == "small" else 70_001  # other pairs of a call: enough for records
+    r = sk.scan_route(pad)
+    assert r.records == 1 and r.run_records > 0
+    cap = int(r.run_records)
+    pair, others = _flood(O, m, g, seed, int(r.tile_bdrs), rng)
+    mine = np.stack([np.full(1 << 16, 11, np.uint32), rng.integers(0, 2**32, 1 << 16, dtype=np.uint64).astype(np.uint32)], 1)
+    mine = mine[O.map_pairs(m, g, seed, mine)[0] // int(r.tile_bdrs) == int(O.map_pairs(m, g, seed, pair)[0][0]) // int(r.tile_bdrs)]
+    assert len(mine) > 20  # other LBP1 values of the same host in the tile
+    for t, floods in enumerate(((cap - 1,), (cap,), (cap + 1,), (cap, 100), (cap - 50, 200), (100, cap + 5000))):
+        for c, n in enumerate(floods):
+            p_ = np.concatenate([others(pad), np.tile(pair, (n, 1))])
+            if c:  # the last records carry other LBP1 values of that tile
+                p_ = np.concatenate([p_[:-len(mine)], mine])
+            if t % 2:
+                rng.shuffle(p_)
+            sk.scan_slice(_dev(V, p_.reshape(-1)))
+            osk.scan(p_)
+        if t == 4:  # pending records and direct updates joined by an export
+            assert_state_equal(sk.state(), osk.state(), layout, f"open slice, floods {floods}")
+        sk.advance_slice()
+        osk.advance()
+        assert_state_equal(sk.state(), osk.state(), layout, f"floods {floods} of {cap}")
+
+
+@pytest.mark.parametrize("layout", ["fast", "small", "packed"])
+def test_saturation_masks_after_a_full_run(V, O, layout):
+    """Direct updates of a full run reach DRs whose planes the saturation masks
+    call saturated: the next advance must read them.  Slices without overflow
+    before and after, so that masks are written, mistrusted and trusted again."""
+    m, g, k, seed = 1 << 22, 64, 2, 9
+    rng = np.random.default_rng(45)
+    Lc = 24 if layout == "packed" else 0
+    sk = V.Sketch(m, g, k, seed, layout, Lc=Lc)
+    osk = O.Sketch(m, g, k, seed, O.GPACKED if layout == "packed" else LAYOUT_CODE[layout], Lc=Lc)
+    r = sk.scan_route(1)
+    cap = int(r.run_records)
+    pair, others = _flood(O, m, g, seed, int(r.tile_bdrs), rng)
+    host = np.stack([np.full(1 << 14, 11, np.uint32), rng.integers(0, 2**32, 1 << 14, dtype=np.uint64).astype(np.uint32)], 1)
+    for n in (0, 0, cap + 1, 0, cap + 70_000, 0, 0):
+        p_ = np.concatenate([others(1 << 15), np.tile(pair, (n, 1)), host if n else host[:0]])
+        sk.scan_slice(_dev(V, p_.reshape(-1)))
+        osk.scan(p_)
+        sk.advance_slice()
+        osk.advance()
+        assert_state_equal(sk.state(), osk.state(), layout, f"{n} of {cap}")
+
+
+def test_scan_route(V):
+    """What scan_route says of pools with and without runs, small scans and switched-off runs."""
+    sk = V.Sketch(1 << 20, 64, 3, 1, "fast")
+    a, b = sk.scan_route(1 << 16), sk.scan_route((1 << 16) + 1)
+    assert (a.records, b.records) == (0, 1) and a.tiles * a.tile_bdrs == 1 << 20
+    assert a.run_records * a.tiles * 4 <= sk.info().workspace_bytes
+    sk.set_tuning(scan_defer=2)
+    assert sk.scan_route(1 << 20).records == 0 and sk.scan_route(1).run_records == 0
+    assert V.Sketch(1 << 15, 64, 3, 1, "fast").scan_route(1 << 20).records == 0
+    assert V.Sketch(5000, 64, 3, 1, "packed").scan_route(1).records == 1
+
+
 @pytest.mark.parametrize("layout", ["fast", "small"])
 @pytest.mark.parametrize("m,g,k", [((1 << 16) - 1, 64, 3), (1 << 16, 65536 // 64, 200), ((1 << 18) + 4097, 256, 2),
                                    ((1 << 20) - 7, 128, 129), ((1 << 20) + 1, 2, 128), ((1 << 21) + 9, 512, 254),
