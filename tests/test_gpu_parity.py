@@ -669,6 +669,44 @@ def test_saturation_masks_after_a_full_run(V, O, layout):
         assert_state_equal(sk.state(), osk.state(), layout, f"{n} of {cap}")
 
 
+def _us(f, reps=5):
+    """Least time of a call over reps, in us."""
+    f()
+    best = float("inf")
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("m,n", [(1 << 18, 1 << 22), (1 << 20, 1 << 24), (1 << 21, 1 << 26)])
+def test_a_flood_costs_no_multiple(V, m, n):
+    """A slice that one host floods (a few tiles' runs take and repeat everything)
+    against one of as many random pairs, which the runs hold: well under four times
+    (8 and more when every repeat was an atomic on one of a few words)."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    us = {}
+    for kind in ("random", "flood"):
+        p_ = torch.randint(-2**31, 2**31, (n, 2), dtype=torch.int64, device="cuda", generator=gen).to(torch.int32)
+        if kind == "flood":
+            p_[:, 0] = 11
+        p_ = p_.reshape(-1)
+        sk = V.Sketch(m, 256, 8, 3, "fast")
+
+        def step():
+            sk.scan_slice(p_)
+            sk.advance_slice()
+
+        us[kind] = _us(step)
+        sk.close()
+    assert us["flood"] < 4 * us["random"], us
+
+
 def test_scan_route(V):
     """What scan_route says of pools with and without runs, small scans and switched-off runs."""
     sk = V.Sketch(1 << 20, 64, 3, 1, "fast")
