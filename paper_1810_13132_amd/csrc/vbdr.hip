@@ -547,7 +547,14 @@ __global__ __launch_bounds__(kDeferBlock) void k_scan_defer(const u32x2* __restr
 // the tile).  The run starts 16-byte aligned (its capacity is a multiple of
 // 4), so each thread loads quads of records, four quads at a time, before the
 // LDS atomics: one load per record, waited for one at a time, left the
-// advance bound by load latency.
+// advance bound by load latency.  FLOOD: where kFloodLanes lanes of a wave
+// and more hold one BDR's records, as in a slice that one host floods, a bit is
+// read first: lanes that add to one LDS word are served one at a time (small
+// layout, 2^26 pairs of one host: 2^24 BDRs, step 543 -> 376 us, 2^22 372 -> 272;
+// random pairs the same).  Not in the packed layout, whose two waves a tile
+// wait for the reads instead (2^20 BDRs, 2^22 pairs: 77 -> 94 us with it).
+constexpr int kFloodLanes = 4;
+template <bool FLOOD>
 __device__ __forceinline__ void records_to_planes(const uint32_t* __restrict__ r, uint32_t n, uint32_t tshift,
                                                   uint32_t* pm) {
   const uint32_t mask = (1u << tshift) - 1, words = 1u << (tshift - 5);
@@ -558,18 +565,29 @@ __device__ __forceinline__ void records_to_planes(const uint32_t* __restrict__ r
       const uint32_t q = q0 + (uint32_t)u * blockDim.x;
       v[u] = 4 * q < n ? *reinterpret_cast<const u32x4*>(r + 4 * q) : u32x4{0u, 0u, 0u, 0u};
     }
+    auto apply = [&](auto test) __attribute__((always_inline)) {
+      constexpr bool TEST = decltype(test)::value;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const uint32_t q = q0 + (uint32_t)u * blockDim.x;
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t q = q0 + (uint32_t)u * blockDim.x;
+        uint32_t cur[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (4 * q + e < n) {
-          const uint32_t rec = v[u][e];
-          const uint32_t p = (rec >> 5) & mask;
-          atomicOr(&pm[(rec & 31u) * words + (p >> 5)], 1u << (p & 31));
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t rec = v[u][e], p = (rec >> 5) & mask;
+          cur[e] = TEST && 4 * q + e < n ? pm[(rec & 31u) * words + (p >> 5)] : 0u;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t rec = v[u][e], p = (rec >> 5) & mask, bit = 1u << (p & 31);
+          if (4 * q + e < n && !(TEST && (cur[e] & bit))) atomicOr(&pm[(rec & 31u) * words + (p >> 5)], bit);
         }
       }
-    }
+    };
+    const uint32_t p0 = v[0][0] >> 5;
+    if (FLOOD && __popcll(__builtin_amdgcn_ballot_w64(p0 == (uint32_t)__builtin_amdgcn_readfirstlane((int)p0))) >= kFloodLanes)
+      apply(TrueType{});
+    else
+      apply(FalseType{});
   }
 }
 
@@ -659,7 +677,7 @@ __device__ __forceinline__ void advance_tile(const AdvSketch& A, uint32_t tile, 
   const uint32_t sat_in = satw && live && !direct ? *satw : 0u;
   __syncthreads();
   if (threadIdx.x == 0 && A.fill) A.fill[tile] = 0;  // every thread has read it
-  if (n) records_to_planes(A.recs + (uint64_t)tile * A.cap, n, A.tshift, pm);
+  if (n) records_to_planes<true>(A.recs + (uint64_t)tile * A.cap, n, A.tshift, pm);
   __syncthreads();
   DrWords<W> R = {}, P = {};
   if (live) {
@@ -847,7 +865,7 @@ __global__ __launch_bounds__(kDeferBlock) void k_advance_packed(uint32_t* __rest
   __syncthreads();
   if (threadIdx.x == 0) fill[tile] = 0;  // every thread has read it
   const uint32_t* r = recs + (uint64_t)tile * cap;
-  records_to_planes(r, n, tshift, pm);
+  records_to_planes<false>(r, n, tshift, pm);
   __syncthreads();
   const uint64_t w = (uint64_t)tile * words + threadIdx.x;
   if (w < wstride) {
@@ -1451,7 +1469,7 @@ __global__ __launch_bounds__(kDeferBlock) void k_now_export(const uint32_t* __re
   if (recs) {
     const unsigned long long f = fill[tile];
     const uint32_t n = f < cap ? (uint32_t)f : cap;
-    records_to_planes(recs + (uint64_t)tile * cap, n, tshift, pm);
+    records_to_planes<true>(recs + (uint64_t)tile * cap, n, tshift, pm);
   }
   __syncthreads();
   const uint32_t bit = threadIdx.x * (4 * W);
