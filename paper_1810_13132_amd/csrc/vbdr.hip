@@ -2182,6 +2182,7 @@ int defer_flush(vbdr_sketch* sk, hipStream_t st) {
   hipLaunchKernelGGL(kern, dim3(sk->def_tiles), dim3(256), 0, st, sk->def_rec, sk->def_fill, sk->def_cap,
                      sk->def_tiles, sk->dr, sk->mstride, sk->seen, sk->wstride, sk->bits, sk->z);
   VBDR_LAUNCHED("k_defer_flush");
+  sk->open_records = 0;
   return VBDR_OK;
 }
 
@@ -2196,11 +2197,18 @@ static bool has_runs(const vbdr_sketch* sk) {
 // pools update the pool themselves (no saturation masks to keep there): a
 // chunk's sort and its run reservations take about 8 us (2^20 BDRs: 2^20 pairs
 // 13 us either way in the small layout, 2^22 pairs 54 us direct, 25 deferred;
-// fast layout, 2^18 BDRs: 2^17 pairs 10 us direct, 7 deferred).
+// fast layout, 2^18 BDRs: 2^17 pairs 10 us direct, 7 deferred).  So do scans of
+// fast pools below 2^20 BDRs, whose bits the caches hold, that bring the slice
+// past 7/4 of what the runs hold: sorting them first is lost there (steps at
+// 1.5, 2 and 5 times the runs' records, of 100 hosts: 2^16 BDRs 153, 256, 465 us
+// with records, 237, 250, 315 direct; 2^19 BDRs 182, 322, 429 and 180, 206, 349;
+// 2^20 BDRs 255, 288, 455 and 240, 290, 576).
 static bool scans_records(const vbdr_sketch* sk, uint64_t n) {
   if (!has_runs(sk)) return false;
   if (sk->m >= kPartMinM || sk->layout == VBDR_LAYOUT_PACKED) return true;
-  return n > (sk->layout == VBDR_LAYOUT_FAST ? kDirectFast : kDirectSmall);
+  if (sk->layout == VBDR_LAYOUT_SMALL) return n > kDirectSmall;
+  if (sk->m < kOverfullM && sk->open_records + n > (uint64_t)sk->def_tiles * sk->def_cap / 4 * 7) return false;
+  return n > kDirectFast;
 }
 
 // The word that says whether bsLBP1 planes may hold bits; NULL: they may.
@@ -2861,6 +2869,7 @@ int vbdr_scan_slice(vbdr_sketch* sk, const uint32_t* pairs_dev, uint64_t n, void
                        sk->s1, sk->g, sk->b, sk->A1, m32, sk->def_tiles, sk->def_cap, sk->def_rec, sk->def_fill, sk->dr,
                        sk->mstride, sk->seen, sk->wstride, sk->Lc, sk->bits, sk->z, sk->tshift);
     VBDR_LAUNCHED("k_scan_defer");
+    sk->open_records += n;
     return VBDR_OK;
   }
   if (sk->bins && sk->tune.scan_binned == 1) {
@@ -2913,7 +2922,7 @@ int vbdr_advance_slice(vbdr_sketch* sk, void* stream) {
                        sk->bits, sk->wstride, sk->z, sk->Lc, sk->k, sk->reg, sk->reg4, sk->m, sk->hist, sk->def_rec,
                        sk->def_fill, sk->def_cap, sk->def_tiles, sk->tshift, sk->sat);
     VBDR_LAUNCHED("k_advance_packed");
-    sk->t++;
+    sk->t++, sk->open_records = 0;
     return VBDR_OK;
   }
   AdvSketch a;
@@ -2931,7 +2940,7 @@ int vbdr_advance_slice(vbdr_sketch* sk, void* stream) {
   hipLaunchKernelGGL(kern, dim3(sk->tiles), dim3(kDeferBlock), vbdr_adv_lds(sk), st, a);
   VBDR_LAUNCHED("k_advance");
   if (sk->preg) sk->pcsa_valid = true;  // written by the launch above
-  sk->t++;
+  sk->t++, sk->open_records = 0;
   return VBDR_OK;
 }
 
@@ -3214,6 +3223,7 @@ int vbdr_import_now(vbdr_sketch* sk, const uint8_t* now_dev, void* stream) {
   if (sk->def_fill) {
     hipLaunchKernelGGL(k_defer_drop, dim3(1), dim3(1024), 0, st, sk->def_fill, sk->def_tiles);
     VBDR_LAUNCHED("k_defer_drop");
+    sk->open_records = 0;
   }
   return VBDR_OK;
 }
@@ -3370,7 +3380,7 @@ int vbdr_import_state(vbdr_sketch* sk, const uint8_t* dr_host, const uint32_t* b
                      sk->reg4, sk->mstride / 2);
   VBDR_LAUNCHED("k_pack_reg4");
   VBDR_HIP(hipStreamSynchronize(nullptr));
-  sk->t = t;
+  sk->t = t, sk->open_records = 0;
   sk->pcsa_valid = false;  // PCSA runs are not part of the canonical state: valid again after an advance
   return VBDR_OK;
 }

@@ -555,7 +555,7 @@ int vbdr_batch_step(vbdr_batch* bt, const uint32_t* const* pairs_dev, const uint
         return rc;
   VBDR_HIP(hipEventRecord(bt->ev_out, bt->st));
   VBDR_HIP(hipStreamWaitEvent(user, bt->ev_out, 0));
-  for (vbdr_sketch* k : bt->sk) k->t++;
+  for (vbdr_sketch* k : bt->sk) k->t++, k->open_records = 0;
   return VBDR_OK;
 }
 

@@ -29,6 +29,7 @@ constexpr uint32_t kDeferSlotsMax = 16;
 constexpr uint64_t kDeferLeast = 1ull << 22;   // record slots of a sketch, at least
 // Pairs of a scan up to which pools below 2^22 BDRs are updated directly.
 constexpr uint64_t kDirectSmall = 1ull << 20, kDirectFast = 1ull << 16;
+constexpr uint64_t kOverfullM = 1ull << 20;  // fast pools below scan directly where a slice is far past the runs
 
 // Which estimate gathers how (g <= kStageMaxG, no extra outputs), each line
 // with both sides measured at g = 512 (gathers a second, large host lists):
@@ -93,6 +94,7 @@ struct vbdr_sketch {
   uint32_t* sat;                  // deferred scans: [wstride] bit r-1 = DR[r] of all 32 BDRs saturated (255, or 2^z - 1)
   unsigned long long* def_fill;   // [def_tiles + 1] records per tile; the last word flags direct updates
   uint32_t def_tiles, def_cap;
+  uint64_t open_records;          // pairs that scans of the open slice put through the runs (chooses routes only)
   uint32_t tshift, tiles;         // the advance's tiles: 2^tshift BDRs, tiles of them (def_tiles of them have record runs)
   bool lean;                      // no optional workspaces (sketches owned by a batch)
   uint8_t* preg;                  // small layout, on request: PCSA run of each BDR, last closed window

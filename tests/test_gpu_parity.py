@@ -734,6 +734,44 @@ def test_a_flood_keeps_the_advance(V, layout, m, n):
     assert us["flood"] < 2.25 * us["random"], us
 
 
+@pytest.mark.parametrize("m", [(1 << 16) + 5, (1 << 18) + 1])
+def test_scans_far_past_the_runs(V, O, m):
+    """Fast pools below 2^20 BDRs: a scan that brings a slice past 7/4 of what the
+    runs hold goes direct, alone or after others; the next slice starts anew,
+    also after an import, a map's import and an export.  State of the mixed
+    slices against the oracle."""
+    g, k = 64, 2
+    rng = np.random.default_rng(46)
+    sk = V.Sketch(m, g, k, 9, "fast")
+    osk = O.Sketch(m, g, k, 9, O.GFAST)
+    r = sk.scan_route(1 << 17)
+    total = int(r.run_records) * int(r.tiles)
+    most = total // 4 * 7
+    assert (sk.scan_route(most).records, sk.scan_route(most + 1).records) == (1, 0)
+
+    def scan(n):
+        p_ = rng.integers(0, 2**32, (n, 2), dtype=np.uint64).astype(np.uint32)
+        sk.scan_slice(_dev(V, p_.reshape(-1)))
+        osk.scan(p_)
+
+    scan(most - (1 << 17))
+    assert (sk.scan_route(1 << 17).records, sk.scan_route((1 << 17) + 1).records) == (1, 0)
+    scan((1 << 17) + 1)
+    scan(1 << 17)
+    assert sk.scan_route(1 << 17).records == 0
+    sk.advance_slice()
+    osk.advance()
+    assert_state_equal(sk.state(), osk.state(), "fast", "mixed slice")
+    for reset in (lambda: sk.advance_slice(), lambda: sk.load_state(sk.state()), lambda: sk.state(),
+                  lambda: sk.import_now(sk.export_now())):
+        p_ = _dev(V, rng.integers(0, 2**32, 2 * most, dtype=np.uint64).astype(np.uint32))
+        sk.scan_slice(p_)
+        assert sk.scan_route(1 << 17).records == 0
+        reset()
+        assert sk.scan_route(1 << 17).records == 1
+        sk.advance_slice()
+
+
 def test_scan_route(V):
     """What scan_route says of pools with and without runs, small scans and switched-off runs."""
     sk = V.Sketch(1 << 20, 64, 3, 1, "fast")
