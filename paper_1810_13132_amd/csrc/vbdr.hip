@@ -337,6 +337,7 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_apply(const uint32_t* __res
 constexpr int kDeferBlock = 1024;
 constexpr int kHistCopies = 4;  // register histograms per wave in the advances (a power of two)
 constexpr int kDeferPer = 32;   // records per thread of a chunk, at most
+constexpr int kFloodLanes = 4;  // lanes of a wave with one BDR's records that tell a flood
 static_assert(kDeferChunk == kDeferBlock * kDeferPer, "a chunk of the longest");
 static_assert(kPad % (1u << kMinTileShift) == 0, "tiles start on whole bit words");
 
@@ -473,11 +474,16 @@ __device__ __forceinline__ void scan_defer_part(const u32x2* __restrict__ pairs,
       }
     }
   } else {  // a run is full: its records go to the pool
-    // A bsLBP1 bit is read first: a flood of one host's pairs fills a few tiles'
-    // runs and repeats bits that are set, each repeat an atomic on one of a few
-    // words (fast layout, 2^20 BDRs, 2^26 pairs of one host: 5.8 ms, now 0.43;
-    // as many random pairs: 1.37 and 0.98).
+    // bsLBP1 bits are read first while most of them prove set: a flood of one
+    // host's pairs fills a few tiles' runs and repeats set bits, each repeat an
+    // atomic on one of a few words (2^20 BDRs, 2^26 pairs of one host: 5.8 ms
+    // without, 0.45 with; of 100 hosts 1.42 and 0.50), while other slices' reads
+    // miss the caches and find little (a batch of 12 sketches: 1.16 ms without,
+    // 1.36 with a read for every record, 1.14 now).  A wave looks at its first
+    // group of records, on while three quarters of the bits it saw were set,
+    // and where four lanes hold one BDR's records.
     constexpr int kOut = 4;
+    bool look = true;
 #pragma unroll 1
     for (int u0 = 0; u0 < PER; u0 += kOut) {
       uint32_t r[kOut], cur[kOut];
@@ -489,14 +495,28 @@ __device__ __forceinline__ void scan_defer_part(const u32x2* __restrict__ pairs,
         const uint32_t t = r[v] >> (5 + tshift), at = cnt[t] + j;
         past[v] = (FULL || j < n) && at - t * cap >= cap;
         if ((FULL || j < n) && !past[v]) recs[at] = r[v];
+        cur[v] = 0;
+      }
+      if constexpr (FAST) {
+        const uint32_t p0 = r[0] >> 5;
+        const uint64_t same = __builtin_amdgcn_ballot_w64(p0 == (uint32_t)__builtin_amdgcn_readfirstlane((int)p0));
+        if (look || __popcll(same) >= kFloodLanes) {
+#pragma unroll
+          for (int v = 0; v < kOut; ++v)
+            if (past[v]) cur[v] = seen[(uint64_t)(r[v] & 31u) * wstride + (r[v] >> 10)];
+          int set = 0, all = 0;
+#pragma unroll
+          for (int v = 0; v < kOut; ++v) {
+            cur[v] = (cur[v] >> ((r[v] >> 5) & 31u)) & 1u;
+            set += __popcll(__builtin_amdgcn_ballot_w64(cur[v] != 0u));
+            all += __popcll(__builtin_amdgcn_ballot_w64(past[v]));
+          }
+          look = 4 * set >= 3 * all;
+        }
       }
 #pragma unroll
       for (int v = 0; v < kOut; ++v)
-        cur[v] = FAST && past[v] ? seen[(uint64_t)(r[v] & 31u) * wstride + (r[v] >> 10)] : 0u;
-#pragma unroll
-      for (int v = 0; v < kOut; ++v)
-        if (past[v] && !(FAST && ((cur[v] >> ((r[v] >> 5) & 31u)) & 1u)))
-          apply_record<FAST>(r[v], dr, mstride, seen, wstride, bits, z);
+        if (past[v] && !cur[v]) apply_record<FAST>(r[v], dr, mstride, seen, wstride, bits, z);
     }
     if (threadIdx.x == 0) fill[tiles] = 1ull;  // fast: the advance reads bsLBP1; small: its saturation masks are stale
   }
@@ -553,7 +573,6 @@ __global__ __launch_bounds__(kDeferBlock) void k_scan_defer(const u32x2* __restr
 // layout, 2^26 pairs of one host: 2^24 BDRs, step 543 -> 376 us, 2^22 372 -> 272;
 // random pairs the same).  Not in the packed layout, whose two waves a tile
 // wait for the reads instead (2^20 BDRs, 2^22 pairs: 77 -> 94 us with it).
-constexpr int kFloodLanes = 4;
 template <bool FLOOD>
 __device__ __forceinline__ void records_to_planes(const uint32_t* __restrict__ r, uint32_t n, uint32_t tshift,
                                                   uint32_t* pm) {
