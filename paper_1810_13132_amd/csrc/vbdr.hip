@@ -1084,7 +1084,7 @@ __global__ __launch_bounds__(TABLE ? kTabBlock : kRowBlock) void k_estimate_rows
   extern __shared__ uint32_t lds[];
   uint32_t* tab = lds;
   uint32_t* s1l = lds + (TABLE ? tab_n / 8 : 0);
-  constexpr int kBlock = TABLE ? kTabBlock : kRowBlock, kWaves = kBlock / 64;
+  const uint32_t kBlock = TABLE ? kTabBlock : blockDim.x, kWaves = kBlock / 64;
   if constexpr (TABLE) {  // tab_n: a multiple of 32 registers
     const u32x4* src = reinterpret_cast<const u32x4*>(reg4);
     for (uint32_t q = threadIdx.x; q < tab_n / 32; q += kBlock) reinterpret_cast<u32x4*>(tab)[q] = src[q];
@@ -1194,7 +1194,8 @@ __global__ __launch_bounds__(kEstBlock) void k_estimate_part(const uint32_t* __r
   }
 }
 
-// The same for g <= kStageMaxG without histograms, 16 lanes a host.
+// The same for g <= kStageMaxG without histograms, LPH lanes a host.
+template <int LPH>
 __global__ __launch_bounds__(kRowBlock) void k_estimate_part_rows(const uint32_t* __restrict__ hosts, uint32_t nh,
                                                                   uint32_t per_wave, const uint32_t* __restrict__ s1g,
                                                                   uint32_t g, uint32_t m,
@@ -1213,7 +1214,7 @@ __global__ __launch_bounds__(kRowBlock) void k_estimate_part_rows(const uint32_t
     const uint32_t n = nh - h < per_wave ? nh - h : per_wave;
     uint64_t U;
     uint32_t V;
-    gather_hosts<16, false, true>(hosts + h, n, lds, g, m, reg, reg4, nullptr, 0u, x, part_shift, U, V);
+    gather_hosts<LPH, false, true>(hosts + h, n, lds, g, m, reg, reg4, nullptr, 0u, x, part_shift, U, V);
     if (lane < n) {
       part_u[(uint64_t)x * pstride + h + lane] = U;
       part_v[(uint64_t)x * pstride + h + lane] = V;
@@ -2613,12 +2614,17 @@ int estimate_partitioned(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_
     const uint32_t nh = (uint32_t)(n_hosts - c < pstride ? n_hosts - c : pstride);
     const uint64_t cap = (uint64_t)sk->n_cu * sk->tune.est_blocks_per_cu / parts;
     if (stage) {
+      // A wave a host while 16 lanes would leave few waves, each with a long chain of gathers (4 ranges, g =
+      // 2048: 1000 hosts 20.5 us with 16 lanes, 15.9 with a wave; 8192: 74, 73; g = 128: 8192 hosts 12.2, 14.9).
+      // Four hosts a wave at most, so that the CUs even out (8 ranges, g = 1024, 30000 hosts: 187 us with 32
+      // hosts a wave, now 165).
+      const bool rows = nh >= 16 * (uint32_t)sk->n_cu || sk->g <= 256;
       const uint64_t waves = (uint64_t)sk->n_cu * 32 / parts;  // in flight on one range's CUs
-      const uint64_t per = ((nh + waves - 1) / waves + 3) / 4 * 4;
-      const uint32_t per_wave = (uint32_t)(per > 64 ? 64 : per);
+      const uint64_t per = (nh + waves - 1) / waves;
+      const uint32_t per_wave = rows || per > 4 ? 4u : (uint32_t)per;
       const uint64_t want = ((nh + per_wave - 1) / per_wave + kRowBlock / 64 - 1) / (kRowBlock / 64);
       const uint32_t tiles = (uint32_t)(want < cap ? want : (cap ? cap : 1));
-      hipLaunchKernelGGL(k_estimate_part_rows, dim3(tiles * parts), dim3(kRowBlock), lds, st, hosts_dev + c, nh,
+      hipLaunchKernelGGL((rows ? k_estimate_part_rows<16> : k_estimate_part_rows<64>), dim3(tiles * parts), dim3(kRowBlock), lds, st, hosts_dev + c, nh,
                          per_wave, sk->s1, sk->g, (uint32_t)sk->m, sk->reg, sk->reg4, parts, shift, part_u, part_v,
                          pstride);
       VBDR_LAUNCHED("k_estimate_part_rows");
@@ -2641,7 +2647,8 @@ int estimate_partitioned(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_
 // Estimates gathered from L2 (or memory): directly where the nibbles fit one
 // XCD's L2 or there are too few gathers for it to matter, else partitioned.
 bool gathers_direct(const vbdr_sketch* sk, uint64_t n_hosts) {
-  return vbdr_gather_parts(sk) == 1 || n_hosts * sk->g < kPartMinGathers;
+  const uint32_t parts = vbdr_gather_parts(sk);
+  return parts == 1 || n_hosts * sk->g < (parts == 2 ? kPartMinGathers : kPartMinGathers4);
 }
 
 // LDS bytes of k_estimate_rows.
@@ -2663,7 +2670,10 @@ int estimate_rows(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_hosts, 
   // BDRs, g = 2048: 127 and 106 us; 50000, 0.9 2^16, g = 128: 11.6 and 19.9).
   const uint64_t rounds16 = (n_hosts + 4 * fill - 1) / (4 * fill), rounds64 = (n_hosts + fill - 1) / fill;
   const bool rows = n_hosts >= 4 * fill && (!table || g <= 256 || 4 * rounds16 <= rounds64);
-  const uint32_t waves = table ? kTabBlock / 64 : kRowBlock / 64;
+  // Few hosts: a workgroup each, so that their gathers miss through as many CUs as there are (g = 8192, 1.9 2^24
+  // BDRs: 40 hosts 49 us with four a workgroup, 24; g = 2048, 100 hosts: 15.4, 8.7).
+  const bool few = !table && n_hosts <= 4 * (uint64_t)sk->n_cu;
+  const uint32_t waves = table ? kTabBlock / 64 : few ? 1 : kRowBlock / 64;
   const uint32_t least = rows ? 4 : 1;
   const uint64_t cap_waves = table ? fill : (uint64_t)sk->n_cu * (2048 / 64);
   uint64_t per = (n_hosts + cap_waves - 1) / cap_waves;
@@ -2677,7 +2687,7 @@ int estimate_rows(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_hosts, 
   const auto kern = table ? (rows ? k_estimate_rows<16, true, true> : k_estimate_rows<64, true, true>)
                   : stage ? (rows ? k_estimate_rows<16, false, true> : k_estimate_rows<64, false, true>)
                           : k_estimate_rows<64, false, false>;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(table ? kTabBlock : kRowBlock), lds, st, hosts_dev, n_hosts, per_wave,
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(waves * 64), lds, st, hosts_dev, n_hosts, per_wave,
                      sk->s1, g, (uint32_t)sk->m, sk->reg, sk->reg4, (uint32_t)tab, sk->hist, out_dev);
   VBDR_LAUNCHED("k_estimate_rows");
   return VBDR_OK;

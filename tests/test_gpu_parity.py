@@ -848,6 +848,41 @@ def test_estimate_routes(V, O, m, g):
         assert torch.equal(sk.estimate_noalloc(hd, torch.empty(n, dtype=torch.float32, device="cuda")), ref[:n]), n
 
 
+@pytest.mark.parametrize("m,parts", [((1 << 23) + 4097, 2), ((1 << 24) + 1, 4), ((1 << 25) + 3, 8)])
+@pytest.mark.parametrize("g", [128, 1024, 8192])
+def test_estimates_of_few_hosts_in_ranges(V, m, parts, g):
+    """Host counts around the fewest that take ranges and around the change from a
+    wave a host to 16 lanes, in 2, 4 and 8 ranges, small and large g: the bits of
+    estimate_ex."""
+    rng = np.random.default_rng(g + parts)
+    sk = V.Sketch(m, g, 3, 21, "small")
+    sk.set_tuning(est_binned=2)
+    for t in range(2):
+        sk.scan_slice(_dev(V, rng.integers(0, 2**32, m // 2 * 2, dtype=np.uint64).astype(np.uint32)))
+        sk.advance_slice()
+    least = (1 << 20 if parts == 2 else 3 << 17) // g
+    hosts = rng.integers(0, 2**32, max(least, 4096) + 1030, dtype=np.uint64).astype(np.uint32)
+    ref = sk.estimate_ex(_dev(V, hosts))[0]
+    for n in (1, least - 1, least, least + 1, 1023, 1025, 4095, 4096, 4097, len(hosts)):
+        hd = _dev(V, hosts[:n])
+        assert torch.equal(sk.estimate(hd), ref[:n]), n
+        assert torch.equal(sk.estimate_noalloc(hd, torch.empty(n, dtype=torch.float32, device="cuda")), ref[:n]), n
+
+
+def test_few_hosts_cost_few(V):
+    """40 and 200 hosts of g = 8192 on a pool in ranges against 2000: a third or so
+    of the time (0.58 and 0.93 when a few waves took them)."""
+    m = int(1.99 * 2**23)
+    sk = V.Sketch(m, 8192, 3, 21, "small")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    sk.scan_slice(torch.randint(-2**31, 2**31, (2 * m,), dtype=torch.int64, device="cuda", generator=gen).to(torch.int32))
+    sk.advance_slice()
+    hosts = torch.randint(-2**31, 2**31, (2000,), dtype=torch.int64, device="cuda", generator=gen).to(torch.int32)
+    us = {n: _us(lambda: sk.estimate(hosts[:n].contiguous()), 20) for n in (40, 200, 2000)}
+    assert us[40] < 0.5 * us[2000] and us[200] < 0.5 * us[2000], us
+
+
 @pytest.mark.parametrize("g", [64, 512, 1024, 2048, 16384])
 @pytest.mark.parametrize("m", [1 << 22, (1 << 22) + 4099])
 def test_tiled_chunks_and_zero_counts(V, O, m, g):
