@@ -203,9 +203,11 @@ void k_learned(uint32_t nh, uint32_t parts, uint32_t hstride, const uint32_t* __
       for (int e = lane; e < 16 * kBins; e += 64) {
         const int row = e / kBins, r = e - row * kBins;
         const uint32_t h = tile * 16 + row;
-        uint32_t c = 0;
-        if (h < nh)
-          for (uint32_t x = 0; x < parts; ++x) c += hws[((uint64_t)x * hstride + h) * kBins + r];
+        uint32_t v[8], c = 0;  // all loads before their sum (8 ranges, 20 hosts: 28.7 us one after the other, 24)
+#pragma unroll
+        for (uint32_t x = 0; x < 8; ++x) v[x] = h < nh && x < parts ? hws[((uint64_t)x * hstride + h) * kBins + r] : 0u;
+#pragma unroll
+        for (uint32_t x = 0; x < 8; ++x) c += v[x];
         H[row * kHistStride + r] = c;
       }
     }
@@ -614,7 +616,11 @@ int vbdr_estimate_learned(vbdr_sketch* sk, const vbdr_mlp* mlp, const uint32_t* 
   if (int rc = vbdr_check_device(sk)) return rc;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const uint32_t parts = vbdr_gather_parts(sk), chunk = vbdr_hist_chunk(sk);
-  if (parts == 1 && sk->g <= kStageMaxG && n_hosts < (1ull << 32)) {
+  // Few hosts of large g on a pool that fills the L2s: a workgroup that gathers 16 of them waits for its CU's misses, so
+  // the histogram pass spreads them wider (2^23 BDRs: g = 8192, 64 hosts 120 us in one launch, 48 in two; g = 2048,
+  // 600 hosts 35 and 26).  Smaller pools, which have always used no workspace here, stay with one launch.
+  const bool pass = sk->g >= 2048 && sk->m >= kPartMinM && n_hosts <= 4 * (uint64_t)sk->n_cu;
+  if (parts == 1 && sk->g <= kStageMaxG && n_hosts < (1ull << 32) && !pass) {
     // registers cache resident: one fused launch, gathers feed the MLP tile directly
     const uint32_t nh = (uint32_t)n_hosts;
     const uint32_t tiles = (uint32_t)((n_hosts + 15) / 16);

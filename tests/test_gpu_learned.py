@@ -218,3 +218,44 @@ def test_histogram_routes(V, M, m, g):
         assert torch.equal(f[:, 66], torch.full((n,), float(np.float32(np.log(g / m))), device="cuda")), n
         est, fb = sk.estimate_learned(mlp, hd, with_fallback=True)
         assert bool((fb == 1).all()) and torch.equal(est, plain[:n]), n
+
+
+@pytest.mark.parametrize("m,g", [(1 << 22, 2048), ((1 << 22) + 5, 8192), (1 << 23, 4096), ((1 << 25) + 5, 2048)])
+def test_learned_hosts_do_not_depend_on_their_list(V, M, m, g):
+    """Few hosts of large g go through the histogram pass, more in one launch: a
+    host's learned estimate and flag are the same bits either way."""
+    rng = np.random.default_rng(g)
+    sk = V.Sketch(m, g, 3, 21, "small")
+    sk.scan_slice(V.to_device_u32(rng.integers(0, 2**32, m // 2 * 2, dtype=np.uint64).astype(np.uint32)))
+    sk.advance_slice()
+    hosts = rng.integers(0, 2**32, 3_000, dtype=np.uint64).astype(np.uint32)
+    mlp = V.MLP(_random_params(M, 3))
+    out, fb = sk.estimate_learned(mlp, V.to_device_u32(hosts), with_fallback=True)
+    for n in (1, 15, 17, 1023, 1024, 1025):
+        o, f = sk.estimate_learned(mlp, V.to_device_u32(hosts[:n]), with_fallback=True)
+        assert torch.equal(o, out[:n]) and torch.equal(f, fb[:n]), n
+
+
+def test_few_learned_hosts_cost_few(V, M):
+    """64 hosts of g = 8192 on a pool that fills the L2s against 2000: half of the
+    time (more than all of it while four workgroups gathered them)."""
+    m, g = 1 << 23, 8192
+    sk = V.Sketch(m, g, 3, 21, "small")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    sk.scan_slice(torch.randint(-2**31, 2**31, (2 * m,), dtype=torch.int64, device="cuda", generator=gen).to(torch.int32))
+    sk.advance_slice()
+    hosts = torch.randint(-2**31, 2**31, (2000,), dtype=torch.int64, device="cuda", generator=gen).to(torch.int32)
+    mlp = V.MLP(_random_params(M, 3))
+    us = {}
+    for n in (64, 2000):
+        h, best = hosts[:n].contiguous(), float("inf")
+        for _ in range(20):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            sk.estimate_learned(mlp, h)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 1e3)
+        us[n] = best
+    assert us[64] < 0.75 * us[2000], us
