@@ -2616,12 +2616,13 @@ int estimate_partitioned(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_
     if (stage) {
       // A wave a host while 16 lanes would leave few waves, each with a long chain of gathers (4 ranges, g =
       // 2048: 1000 hosts 20.5 us with 16 lanes, 15.9 with a wave; 8192: 74, 73; g = 128: 8192 hosts 12.2, 14.9).
-      // Four hosts a wave at most, so that the CUs even out (8 ranges, g = 1024, 30000 hosts: 187 us with 32
-      // hosts a wave, now 165).
-      const bool rows = nh >= 16 * (uint32_t)sk->n_cu || sk->g <= 256;
+      // Eight rounds of waves and more, so that the CUs even out (8 ranges, g = 1024, 30000 hosts: 187 us with one
+      // round of 32 hosts a wave, now 165), one where g is small (4 ranges, g = 64, 1e6 hosts: 478 us with 4 hosts a
+      // wave, 423 with 64).
       const uint64_t waves = (uint64_t)sk->n_cu * 32 / parts;  // in flight on one range's CUs
-      const uint64_t per = (nh + waves - 1) / waves;
-      const uint32_t per_wave = rows || per > 4 ? 4u : (uint32_t)per;
+      const bool rows = nh >= 2 * waves || sk->g <= 256;
+      const uint64_t per = (nh + waves - 1) / waves, least = (sk->g <= 256 ? per + 3 : per / 8) / 4 * 4;
+      const uint32_t per_wave = rows ? (uint32_t)(least < 4 ? 4 : least > 64 ? 64 : least) : per > 4 ? 4u : (uint32_t)per;
       const uint64_t want = ((nh + per_wave - 1) / per_wave + kRowBlock / 64 - 1) / (kRowBlock / 64);
       const uint32_t tiles = (uint32_t)(want < cap ? want : (cap ? cap : 1));
       hipLaunchKernelGGL((rows ? k_estimate_part_rows<16> : k_estimate_part_rows<64>), dim3(tiles * parts), dim3(kRowBlock), lds, st, hosts_dev + c, nh,
@@ -2648,7 +2649,7 @@ int estimate_partitioned(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_
 // XCD's L2 or there are too few gathers for it to matter, else partitioned.
 bool gathers_direct(const vbdr_sketch* sk, uint64_t n_hosts) {
   const uint32_t parts = vbdr_gather_parts(sk);
-  return parts == 1 || n_hosts * sk->g < (parts == 2 ? kPartMinGathers : kPartMinGathers4);
+  return parts == 1 || n_hosts * sk->g < (parts == 2 ? kPartMinGathers : sk->g >= 1024 ? kPartMinLongG : kPartMinShortG);
 }
 
 // LDS bytes of k_estimate_rows.
@@ -2670,9 +2671,9 @@ int estimate_rows(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_hosts, 
   // BDRs, g = 2048: 127 and 106 us; 50000, 0.9 2^16, g = 128: 11.6 and 19.9).
   const uint64_t rounds16 = (n_hosts + 4 * fill - 1) / (4 * fill), rounds64 = (n_hosts + fill - 1) / fill;
   const bool rows = n_hosts >= 4 * fill && (!table || g <= 256 || 4 * rounds16 <= rounds64);
-  // Few hosts: a workgroup each, so that their gathers miss through as many CUs as there are (g = 8192, 1.9 2^24
+  // Few hosts of some g: a workgroup each, so that their gathers miss through as many CUs as there are (g = 8192, 1.9 2^24
   // BDRs: 40 hosts 49 us with four a workgroup, 24; g = 2048, 100 hosts: 15.4, 8.7).
-  const bool few = !table && n_hosts <= 4 * (uint64_t)sk->n_cu;
+  const bool few = !table && g >= 512 && n_hosts <= 4 * (uint64_t)sk->n_cu;
   const uint32_t waves = table ? kTabBlock / 64 : few ? 1 : kRowBlock / 64;
   const uint32_t least = rows ? 4 : 1;
   const uint64_t cap_waves = table ? fill : (uint64_t)sk->n_cu * (2048 / 64);

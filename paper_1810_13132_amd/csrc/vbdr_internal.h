@@ -38,7 +38,7 @@ constexpr uint64_t kOverfullM = 1ull << 20;  // fast pools below scan directly w
 //   up to 2^23 directly, the nibbles in every XCD's L2 (2.6e11; ranges on
 //     8 XCDs: 1.7e11);
 //   above in 2, 4 or 8 ranges by XCD (2^24: 2.6e11, 2^26: 2.0e11; 8 ranges:
-//     1.7e11, directly: 1.2e11, 0.65e11), directly below 2^20 or 3 2^17 gathers;
+//     1.7e11, directly: 1.2e11, 0.65e11), directly below 2^19 to 2^20 gathers;
 //   from 2^24 BDRs and enough gathers the LDS-tiled passes (2.9e11; 16384
 //     hosts at 2^24: tiled 58 us, ranges 41; 65536: 131 and 139; at 2^26 65
 //     and 59, 139 and 199).
@@ -46,10 +46,11 @@ constexpr uint64_t kTableMaxM = 1ull << 21;       // pools whose direct estimate
 constexpr uint64_t kTableMinUse = 6;              // gathers per register of that table, at least (2^18 BDRs: a step of 2^20
                                                   // pairs, 4096 hosts, g = 256 28.6 us with the table, 27.1 without)
 constexpr uint64_t kRangeBytes = 4ull << 20;      // nibbles of a range: an XCD's L2
-// Gathers of an estimate below which one range will do: where two would do else and above (1.05 2^23 BDRs, g = 512:
-// 800 hosts 6 us directly, 8 in ranges, 1500 8 and 9; 1.99 2^23: 1000 9 and 9; 0.95 2^25, g = 2048: 100 hosts 9 and 10,
-// 200 11 and 11, 500 18 and 13).
-constexpr uint64_t kPartMinGathers = 1ull << 20, kPartMinGathers4 = 3ull << 17;
+// Gathers of an estimate below which one range will do: of two; of more for g from 1024 and below, where a host's
+// chain of gathers is short (1.05 2^23 BDRs, g = 512: 800 hosts 6 us directly, 8 in ranges, 1500 8 and 9; 1.99 2^23: 1000
+// 9 and 9; 0.95 2^25, g = 2048: 100 hosts 9 and 10, 200 11 and 11, 500 18 and 13; 1.1 2^25, g = 512: 1000 11 and 12, 1500
+// 14 and 13).
+constexpr uint64_t kPartMinGathers = 1ull << 20, kPartMinLongG = 3ull << 17, kPartMinShortG = 5ull << 17;
 constexpr uint64_t kTileMinGathers = 3ull << 23, kTileMinGathers8 = 10ull << 20;  // from which tiles pay (8 ranges)
 
 struct vbdr_sketch {

@@ -860,10 +860,10 @@ def test_estimates_of_few_hosts_in_ranges(V, m, parts, g):
     for t in range(2):
         sk.scan_slice(_dev(V, rng.integers(0, 2**32, m // 2 * 2, dtype=np.uint64).astype(np.uint32)))
         sk.advance_slice()
-    least = (1 << 20 if parts == 2 else 3 << 17) // g
-    hosts = rng.integers(0, 2**32, max(least, 4096) + 1030, dtype=np.uint64).astype(np.uint32)
+    least = (1 << 20 if parts == 2 else (3 if g >= 1024 else 5) << 17) // g
+    hosts = rng.integers(0, 2**32, max(least, 8192) + 1030, dtype=np.uint64).astype(np.uint32)
     ref = sk.estimate_ex(_dev(V, hosts))[0]
-    for n in (1, least - 1, least, least + 1, 1023, 1025, 4095, 4096, 4097, len(hosts)):
+    for n in (1, least - 1, least, least + 1, 1023, 1025, 2047, 2048, 4095, 4096, 8191, 8192, len(hosts)):
         hd = _dev(V, hosts[:n])
         assert torch.equal(sk.estimate(hd), ref[:n]), n
         assert torch.equal(sk.estimate_noalloc(hd, torch.empty(n, dtype=torch.float32, device="cuda")), ref[:n]), n
