@@ -247,7 +247,8 @@ int vbdr_sketch_info(const vbdr_sketch *sk, vbdr_info *out);
  *                      update when it is already made; 2: always update
  *                      (default: the variant measured faster for the layout);
  *   scan_blocks_per_cu workgroups per compute unit of the scan (1..64);
- *   est_blocks_per_cu  workgroups per compute unit of the estimate (1..64);
+ *   est_blocks_per_cu  workgroups of 256 per compute unit of the estimates, at
+ *                      most (1..64; 64: as many as each kernel finds best);
  *   scan_binned        1: pools of 2^22..2^27 BDRs scan in two passes, the
  *                      pairs first binned by pool range so that each XCD
  *                      updates only its own range; 2: always scan directly

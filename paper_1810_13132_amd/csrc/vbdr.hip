@@ -2133,6 +2133,12 @@ uint32_t grid_cap(const vbdr_sketch* sk, uint64_t want, uint32_t per_cu) {
   return (uint32_t)(want < cap ? want : cap);
 }
 
+// Workgroups per CU of an estimate that takes `most` by itself: fewer where the
+// tuning asks for fewer than its most, 64 (the default).
+uint32_t est_per_cu(const vbdr_sketch* sk, uint32_t most) {
+  return sk->tune.est_blocks_per_cu < 64 && sk->tune.est_blocks_per_cu < most ? sk->tune.est_blocks_per_cu : most;
+}
+
 // LogLog constant alpha_q of Durand and Flajolet (2003),
 // (Gamma(-1/q) (1 - 2^(1/q)) / ln 2)^-q.  With x = 1/q, y = x ln 2,
 // |Gamma(-x)| = Gamma(1-x)/x and 2^x - 1 = y (1 + z), z = sum_k>=1 y^k/(k+1)!:
@@ -2305,7 +2311,7 @@ int vbdr_hist_pass(vbdr_sketch* sk, const uint32_t* hosts_dev, uint32_t nh, hipS
   while (parts > 1 && (1u << (32 - shift)) < parts) --shift;
   // four workgroups for each that fits the CUs, so that the CUs even out (30000 hosts, g = 2048, 2^24 BDRs, learned:
   // 311 us with one, in two rounds of which the second was not full, now 306; 65552: 646, 631)
-  const uint64_t cap = (uint64_t)sk->n_cu * 32 / parts;
+  const uint64_t fit = (uint64_t)sk->n_cu * est_per_cu(sk, 32) / parts, cap = fit ? fit : 1;
   if (g <= kStageMaxG && parts <= kHistRowsParts) {
     // 16 lanes a host (hist_hosts: at most 128 registers a lane); a wave a host while that keeps its waves
     // few (features of 64 hosts, g = 2048: 23.2 us with 16 lanes, 12.4 with a wave, host path included)
@@ -2682,7 +2688,7 @@ int estimate_rows(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_hosts, 
   const uint64_t most = table ? 64 : 4;  // without a table, many workgroups that the CUs even out
   const uint32_t per_wave = (uint32_t)(per < least ? least : per > most ? most : per);
   const uint64_t want = ((n_hosts + per_wave - 1) / per_wave + waves - 1) / waves;
-  const uint32_t grid = grid_cap(sk, want, table ? 1 : 1024);
+  const uint32_t grid = grid_cap(sk, want, table ? 1 : est_per_cu(sk, 1024));
   const bool stage = table || per_wave * waves >= 16;
   const size_t lds = (table ? tab / 2 : 0) + (stage ? (size_t)g * 4 : 0);
   const auto kern = table ? (rows ? k_estimate_rows<16, true, true> : k_estimate_rows<64, true, true>)
@@ -3188,7 +3194,8 @@ int vbdr_estimate_kind(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_ho
     uint64_t per = (nh + waves - 1) / waves;
     per = rows ? 4 : per > 4 ? 4 : per;
     const uint64_t want = ((nh + per - 1) / per + kRowBlock / 64 - 1) / (kRowBlock / 64);
-    const uint32_t grid = grid_cap(sk, want, 1024) * parts;
+    const uint64_t fit = (uint64_t)sk->n_cu * est_per_cu(sk, 1024 * parts) / parts, cap = fit ? fit : 1;
+    const uint32_t grid = (uint32_t)(want < cap ? want : cap) * parts;
     SumEst e = E;
     e.out += c;
     if (e.raw) e.raw += c;

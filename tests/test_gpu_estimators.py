@@ -177,3 +177,35 @@ def test_sums_share_nothing_between_streams(V, m, g, nh):
         torch.cuda.synchronize()
         for a, o, k in zip(alone, outs, kinds):
             assert torch.equal(a, o), k
+
+
+def test_est_blocks_per_cu_bounds_every_estimate(V):
+    """est_blocks_per_cu = 1 gives the plain, LogLog, PCSA and feature kernels one
+    workgroup per CU, directly and in ranges: the same bits, and more time than the
+    default takes (the same, within a few percent, where the bound has no effect)."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    for m in (3_000_000, 12_000_000):
+        sk = V.Sketch(m, 64, 3, 21, "small")
+        sk.enable_pcsa(True)
+        sk.scan_slice(torch.randint(-2**31, 2**31, (2 * m,), dtype=torch.int64, device="cuda", generator=gen).to(torch.int32))
+        sk.advance_slice()
+        hosts = torch.randint(-2**31, 2**31, (400_000,), dtype=torch.int64, device="cuda", generator=gen).to(torch.int32)
+        calls = {"hll": lambda: sk.estimate(hosts), "loglog": lambda: sk.estimate_kind(hosts, "loglog"),
+                 "pcsa": lambda: sk.estimate_kind(hosts, "pcsa"), "features": lambda: sk.features(hosts[:32_000])}
+        for name, f in calls.items():
+            us, outs = [], []
+            for b in (64, 1):
+                sk.set_tuning(est_blocks_per_cu=b)
+                outs.append(f())
+                best = float("inf")
+                for _ in range(10):
+                    x, y = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                    x.record()
+                    f()
+                    y.record()
+                    y.synchronize()
+                    best = min(best, x.elapsed_time(y) * 1e3)
+                us.append(best)
+            assert torch.equal(outs[0], outs[1]), (m, name)
+            assert name == "features" or us[1] > 1.15 * us[0], (m, name, us)  # half of its time is not the histograms
