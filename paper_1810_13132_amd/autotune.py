@@ -16,6 +16,14 @@ import torch
 DEFAULT_CANDIDATES = [(st, et, bpc) for st in (2048, 8192, 32768) for et in (16, 64, 256) for bpc in (4, 8, 16)]
 
 
+def default_candidates(batch):
+    """DEFAULT_CANDIDATES, less those that only differ in the scan tile and workgroups of a scan that is not launched:
+    members with record runs scan through those, and only the other members' scan reads the two."""
+    if any(sk.scan_route(1).run_records == 0 for sk in batch.sketches):
+        return DEFAULT_CANDIDATES
+    return [c for c in DEFAULT_CANDIDATES if c[0] == 8192 and c[2] == 8]
+
+
 def signature(params, n_pairs, n_hosts) -> str:
     dev = torch.cuda.get_device_properties(torch.cuda.current_device())
     arch = getattr(dev, "gcnArchName", dev.name)
@@ -52,7 +60,7 @@ def tune(batch, pairs, hosts, outs, candidates=None, reps: int = 3, cache_path: 
         batch.set_tuning(best["scan_tile"], best["est_tile"], best["blocks_per_cu"], True)
         return best, cache[key]["timings"]
     timings = {}
-    for st, et, bpc in candidates or DEFAULT_CANDIDATES:
+    for st, et, bpc in candidates or default_candidates(batch):
         batch.set_tuning(st, et, bpc, True)
         timings[f"{st},{et},{bpc}"] = time_steps(batch, pairs, hosts, outs, reps)
     best_key = min(timings, key=timings.get)
