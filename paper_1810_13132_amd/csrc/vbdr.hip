@@ -2385,9 +2385,10 @@ uint32_t tile_shift(uint64_t mstride, bool lean) {
 // that pools below 2^26 BDRs also hold slices of 2^27 pairs, with a quarter
 // tile to spare for uneven tiles; pools from 2^16 BDRs take 2^22 slots (16 MB)
 // at least.  Members of a batch (up to 256, each with its own runs) take twice
-// the smallest run up to 2^23 BDRs; any sketch takes the smallest where the
-// runs would be more than an eighth of the device's free memory.
-uint32_t defer_run_cap(uint64_t m, uint32_t tshift, uint32_t tiles, bool lean) {
+// the smallest run up to 2^23 BDRs.  Where the runs would be more than an
+// eighth of the device's free memory a sketch takes the smallest, and pools below
+// 2^22 BDRs, which can do without (0), none.
+uint32_t defer_run_cap(uint64_t m, uint32_t tshift, uint32_t tiles, bool lean, bool needed) {
   const uint64_t tile = 1ull << tshift;
   uint64_t slots = (kDeferBudget + m - 1) / m;
   const uint64_t most = lean ? (m <= (1ull << 23) ? 2 * kDeferSlots : kDeferSlots) : kDeferSlotsMax;
@@ -2396,7 +2397,8 @@ uint32_t defer_run_cap(uint64_t m, uint32_t tshift, uint32_t tiles, bool lean) {
   if (slots < least) slots = least;
   uint64_t cap = slots * tile + (slots > kDeferSlots ? tile / 4 : 0);
   size_t free_b = 0, total_b = 0;
-  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b / 8 < tiles * cap * 4) cap = kDeferSlots * tile;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b / 8 < tiles * cap * 4)
+    cap = needed || m >= kPartMinM ? kDeferSlots * tile : 0;
   return (uint32_t)cap;  // at most 64 slots of 2^12 BDRs or 16 of 2^15
 }
 
@@ -2520,9 +2522,8 @@ int create_sketch(uint64_t m, uint32_t g, uint32_t k, uint64_t hash_seed, int la
       const uint32_t tiles = sk->tiles;
       if (defer_scan_lds(tiles, kDeferPer) + 1024 <= (size_t)lds_max &&
           ((size_t)32 << (sk->tshift - 3)) + 24576 <= (size_t)lds_max) {
-        sk->def_tiles = tiles;
-        sk->def_cap = defer_run_cap(m, sk->tshift, tiles, lean);
-        def_bytes = (uint64_t)tiles * sk->def_cap * 4 + (uint64_t)(tiles + 1) * 8;
+        sk->def_cap = defer_run_cap(m, sk->tshift, tiles, lean, layout == VBDR_LAYOUT_PACKED);
+        if (sk->def_cap) sk->def_tiles = tiles, def_bytes = (uint64_t)tiles * sk->def_cap * 4 + (uint64_t)(tiles + 1) * 8;
       }
     }
     if (layout == VBDR_LAYOUT_PACKED && !def_bytes) {
@@ -2547,15 +2548,23 @@ int create_sketch(uint64_t m, uint32_t g, uint32_t k, uint64_t hash_seed, int la
         (part_bytes && vbdr_malloc(&sk->part_u, (uint64_t)sk->parts * kPartChunk * 8) != hipSuccess) ||
         (part_bytes && vbdr_malloc(&sk->part_v, (uint64_t)sk->parts * kPartChunk * 4) != hipSuccess) ||
         vbdr_malloc(&sk->hist_ws, (uint64_t)sk->parts * kLearnChunk * kBins * 4) != hipSuccess ||
-        vbdr_malloc(&sk->est_ws, (uint64_t)kLearnChunk * 4) != hipSuccess ||
-
-        (def_bytes && vbdr_malloc(&sk->def_rec, (uint64_t)sk->def_tiles * sk->def_cap * 4) != hipSuccess) ||
-        (def_bytes && vbdr_malloc(&sk->def_fill, (uint64_t)(sk->def_tiles + 1) * 8) != hipSuccess) ||
-        (def_bytes && wants_sat(sk) && vbdr_malloc(&sk->sat, sat_words(sk) * 4) != hipSuccess)) {
+        vbdr_malloc(&sk->est_ws, (uint64_t)kLearnChunk * 4) != hipSuccess) {
       (void)hipGetLastError();
       rc = vbdr_fail(VBDR_ENOMEM, "device allocation of %llu bytes failed",
                 (unsigned long long)(dr_bytes + seen_bytes + sk->mstride * 3 / 2 + part_bytes));
       break;
+    }
+    if (def_bytes && (vbdr_malloc(&sk->def_rec, (uint64_t)sk->def_tiles * sk->def_cap * 4) != hipSuccess ||
+                      vbdr_malloc(&sk->def_fill, (uint64_t)(sk->def_tiles + 1) * 8) != hipSuccess ||
+                      (wants_sat(sk) && vbdr_malloc(&sk->sat, sat_words(sk) * 4) != hipSuccess))) {
+      (void)hipGetLastError();
+      if (layout == VBDR_LAYOUT_PACKED) {
+        rc = vbdr_fail(VBDR_ENOMEM, "device allocation of %llu bytes failed", (unsigned long long)def_bytes);
+        break;
+      }
+      if (sk->def_rec) (void)hipFree(sk->def_rec);  // the other layouts' scans can update the pool themselves
+      if (sk->def_fill) (void)hipFree(sk->def_fill);
+      sk->def_rec = nullptr, sk->def_fill = nullptr, sk->def_tiles = sk->def_cap = 0, def_bytes = 0;
     }
     sk->state_only = dr_bytes + bits_bytes + seen_bytes + sk->mstride * 3 / 2 + kStatWords * sizeof(unsigned long long) +
                      (uint64_t)g * 4 + (sk->sat ? sat_words(sk) * 4 : 0);

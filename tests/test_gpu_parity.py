@@ -772,6 +772,49 @@ def test_scans_far_past_the_runs(V, O, m):
         sk.advance_slice()
 
 
+@pytest.mark.parametrize("layout,m", [("fast", (1 << 18) + 1), ("small", 1 << 22), ("fast", 1 << 22), ("packed", 9001)])
+def test_failed_runs_leave_a_whole_sketch(V, O, layout, m):
+    """A sketch whose record runs (or their lengths or saturation masks) cannot be
+    allocated scans its pool directly; only the packed layout needs them. Every
+    other failed allocation is reported."""
+    g, k = 64, 3
+    Lc = 20 if layout == "packed" else 0
+    whole = V.Sketch(m, g, k, 9, layout, Lc=Lc)
+    without, reported = [], 0
+    try:
+        for after in range(40):
+            V.fail_allocation_after(after)
+            try:
+                sk = V.Sketch(m, g, k, 9, layout, Lc=Lc)
+            except V.VbdrError as e:
+                assert e.code == -2
+                reported += 1
+                continue
+            V.fail_allocation_after(-1)
+            if sk.scan_route(1).run_records:
+                break  # past the last allocation
+            without.append(sk)
+    finally:
+        V.fail_allocation_after(-1)
+    assert sk.info().state_bytes == whole.info().state_bytes
+    assert reported >= 5 and len(without) == (0 if layout == "packed" else 3 if m >= 1 << 22 else 2)
+    rng = np.random.default_rng(47)
+    for sk in without:
+        assert sk.info().state_bytes < whole.info().state_bytes and sk.scan_route(1 << 24).records == 0
+        osk = O.Sketch(m, g, k, 9, LAYOUT_CODE[layout])
+        for n in (200_000, 0, 70_000):
+            p_ = rng.integers(0, 2**32, (n, 2), dtype=np.uint64).astype(np.uint32)
+            sk.scan_slice(_dev(V, p_.reshape(-1)))
+            osk.scan(p_)
+            if layout == "fast":
+                sk.import_now(sk.export_now())
+            sk.advance_slice()
+            osk.advance()
+            assert_state_equal(sk.state(), osk.state(), layout, n)
+        sk.set_tuning(scan_defer=2)
+        sk.set_tuning(scan_defer=1)
+
+
 def test_scan_route(V):
     """What scan_route says of pools with and without runs, small scans and switched-off runs."""
     sk = V.Sketch(1 << 20, 64, 3, 1, "fast")
