@@ -323,3 +323,40 @@ def test_batch_member_runs_overflow(V, layout):
             for key in ("dr", "reg", "hist"):
                 assert np.array_equal(sb[key], so[key]), (over, i, key)
             assert torch.equal(outs[i], bt.sketches[i].estimate(hd[i])), (over, i)
+
+
+@pytest.mark.parametrize("layout,k", [("fast", 3), ("small", 200)])
+def test_batch_with_a_member_past_2_25(V, layout, k):
+    """A member above 2^25 BDRs gives the batch's advance its kernel for tiles of 2^15,
+    which the members with smaller tiles then share: registers, pool histograms
+    and estimates of the same sketches stepped alone, one slice past the large
+    member's runs and one empty."""
+    params = [dict(m=(1 << 25) + 4099, g=1024, k=k, hash_seed=3, layout=layout),
+              dict(m=(1 << 24) + 5, g=512, k=2, hash_seed=4, layout=layout),
+              dict(m=70_001, g=64, k=k, hash_seed=5, layout="small"),
+              dict(m=(1 << 21) - 9, g=128, k=130, hash_seed=6, layout="fast"),
+              dict(m=5000, g=16, k=1, hash_seed=7, layout=layout)]
+    bt = V.Batch(params)
+    singles = [V.Sketch(p["m"], p["g"], p["k"], p["hash_seed"], p["layout"]) for p in params]
+    assert bt.sketches[0].scan_route(1).tile_bdrs == 1 << 15 and bt.sketches[1].scan_route(1).tile_bdrs == 1 << 14
+    cap = int(bt.sketches[0].scan_route(1).run_records)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(8)
+
+    def words(n):
+        return torch.randint(-2**31, 2**31, (n,), dtype=torch.int64, device="cuda", generator=gen).to(torch.int32)
+
+    hosts = [words(500) for _ in params]
+    for t, n0 in enumerate((1 << 22, cap + 5000, 0, 1 << 20)):
+        pd = [words(2 * n) for n in (n0, 1 << 20, 50_000, 1 << 18, 3000)]
+        if t == 1:  # one pair fills a run of the large member
+            pd[0].view(-1, 2)[:] = torch.tensor([11, 12], dtype=torch.int32, device="cuda")
+            pd[0].view(-1, 2)[-3000:, 1] = words(3000)
+        outs = [torch.empty(500, dtype=torch.float32, device="cuda") for _ in params]
+        bt.step(pd, hosts, outs)
+        for i, sk in enumerate(singles):
+            sk.scan_slice(pd[i])
+            sk.advance_slice()
+            assert torch.equal(outs[i], sk.estimate(hosts[i])), (t, i)
+            for a, b in zip(bt.sketches[i].registers(), sk.registers()):
+                assert np.array_equal(a, b), (t, i)
