@@ -417,7 +417,8 @@ def main():
     window = []
     buf = np.empty((w.pairs_per_slice, 2), dtype=np.uint32)
     slice0 = None
-    n_apply = 3 if info.scan_deferred else 0  # extra slices for the record-apply measurement
+    by_records = bool(sk.scan_route(w.pairs_per_slice).records)
+    n_apply = 3 if by_records else 0  # extra slices for the record-apply measurement
     t0 = time.time()
 
     def generate(t, keep):
@@ -557,11 +558,12 @@ def main():
     alg = algorithmic_bytes(dom, w, args.layout, L, units, sk.dr_bits)
     achieved = alg / (avg[dom] * 1e-3) / 1e9
     info = sk.info()
-    kernels = {"scan": "k_scan_defer" if info.scan_deferred else "k_scan",
+    kernels = {"scan": "k_scan_defer" if by_records else "k_scan",
                "advance": "k_advance_packed" if args.layout == "packed" else "k_advance",
                "estimate": ("k_est_tile_clear + k_est_tile_bin + k_est_tile_gather + k_est_tile_wide + k_est_tile_final"
                             if info.est_tiled else
-                            "k_estimate_part_rows + k_estimate_final" if info.est_parts > 1 else "k_estimate_rows")}
+                            "k_estimate_part_rows + k_estimate_final" if info.est_parts > 1 and w.m > 1 << 23 else
+                            "k_estimate_rows")}  # nibbles of up to 4 MB are gathered directly
     traffic = traffic_from_counters(f"{dom}:{args.layout}:{w.name}", units)
     roofline = {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel": kernels[dom],

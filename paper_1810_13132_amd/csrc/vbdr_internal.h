@@ -13,7 +13,8 @@ constexpr uint32_t kCusPerXcd = 32;         // gfx950: 8 XCDs x 32 CUs
 constexpr uint64_t kPartMinM = 1ull << 22;  // pools whose registers outgrow one XCD's L2
 constexpr uint32_t kPartChunk = 1u << 20;   // hosts per partitioned-estimate pass
 // Histograms counted in registers up to this many ranges, with LDS atomics above, where most lanes of a gather idle
-// (g = 2048: 2 ranges 2.4e11 gathers a second and 2.0e11, 8 ranges 1.2e11 and 1.6e11).
+// (g = 2048: 2 ranges 2.4e11 gathers a second and 2.0e11, 8 ranges 1.2e11 and 1.6e11; 4 ranges, 100,000 hosts on 1.5
+// 2^24 BDRs: 851 us and 843).
 constexpr uint32_t kHistRowsParts = 2;
 constexpr uint32_t kLearnChunk = 1u << 15;  // hosts per histogram pass whose histograms come in sk->parts ranges
 constexpr uint64_t kBinMaxM = 1ull << 27;   // binned scan records pack (pidx << 5) | (LBP1 - 1)
