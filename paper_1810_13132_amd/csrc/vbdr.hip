@@ -1426,14 +1426,21 @@ __device__ __forceinline__ void sum_estimate(const SumEst& E, double Em, uint64_
   if (E.raw) E.raw[h] = Es;
 }
 
-// LPH lanes a host, per_wave hosts a wave.  PART: workgroup b adds the values
-// of range b mod parts to the host's entry of out, a whole number until
-// k_sum_final makes the estimate of it (out, cleared before, is the call's own:
-// estimates on other streams share nothing with it); otherwise the estimates.  STAGE: seeds in LDS.  Gathers bound it, at an L2's tag rate
+// LPH lanes a host, per_wave hosts a wave.  PART: workgroup b sums the values
+// of range b mod parts into the host's entry of out, a whole number until
+// k_sum_final makes the estimate of it, so that estimates on other streams share
+// nothing with this one: with sum_halves two 16-bit sums, else an atomic sum of
+// entries cleared before (10750 hosts, g = 128, 7.1e6 runs: 13.2 us with halves
+// as with a workspace, 14.5 cleared; the last range to come making the estimate
+// 129 us for 82 at 200,000 hosts, g = 64).  Otherwise the estimates.  STAGE:
+// seeds in LDS.  Gathers bound it, at an L2's tag rate
 // where the values fit one: 20000 hosts, g = 512, 2^22 runs, call included,
 // 43.5 us (63.5 with four gathers in flight and the pool's sum read on the host
 // before the launch); 1e5 hosts, g = 2048, 0.9 2^25 runs: 819 us in 8 ranges,
 // 3062 directly.
+constexpr uint32_t kHalvesMaxG = 2048;
+static_assert(kHalvesMaxG * (33 - 11) < 1u << 16, "a host's sum: g values of at most 33 - log2 g");
+__host__ __device__ __forceinline__ bool sum_halves(uint32_t parts, uint32_t g) { return parts == 2 && g <= kHalvesMaxG; }
 template <int LPH, bool NIB, bool PART, bool STAGE>
 __global__ __launch_bounds__(kRowBlock) void k_estimate_sum(const uint32_t* __restrict__ hosts, uint64_t nh,
                                                             uint32_t per_wave, const uint32_t* __restrict__ s1g,
@@ -1453,15 +1460,21 @@ __global__ __launch_bounds__(kRowBlock) void k_estimate_sum(const uint32_t* __re
     const uint32_t n = nh - h < per_wave ? (uint32_t)(nh - h) : per_wave;
     const uint32_t S = sum_hosts<LPH, PART, NIB>(hosts + h, n, STAGE ? lds : s1g, g, m, val, val4, x, part_shift);
     if (lane < n) {
-      if constexpr (PART) atomicAdd(reinterpret_cast<uint32_t*>(E.out) + h + lane, S);
-      else sum_estimate(E, Em, h + lane, S, g, m);
+      if constexpr (PART) {
+        if (sum_halves(parts, g)) reinterpret_cast<uint16_t*>(E.out)[2 * (h + lane) + x] = (uint16_t)S;
+        else atomicAdd(reinterpret_cast<uint32_t*>(E.out) + h + lane, S);
+      } else {
+        sum_estimate(E, Em, h + lane, S, g, m);
+      }
     }
   }
 }
 
-__global__ __launch_bounds__(256) void k_sum_final(uint32_t nh, uint32_t g, uint32_t m, SumEst E) {
+__global__ __launch_bounds__(256) void k_sum_final(uint32_t nh, uint32_t g, uint32_t m, uint32_t parts, SumEst E) {
   const uint32_t h = blockIdx.x * 256 + threadIdx.x;
-  if (h < nh) sum_estimate(E, sum_pool(E, m), h, __float_as_uint(E.out[h]), g, m);
+  if (h >= nh) return;
+  const uint32_t v = __float_as_uint(E.out[h]);
+  sum_estimate(E, sum_pool(E, m), h, sum_halves(parts, g) ? (v & 0xFFFFu) + (v >> 16) : v, g, m);
 }
 
 // ------------------------------------------------- per-slice max-LBP1 map
@@ -3213,7 +3226,7 @@ int vbdr_estimate_kind(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_ho
         : rows    ? (nib ? k_estimate_sum<16, true, false, true> : k_estimate_sum<16, false, false, true>)
         : stage   ? (nib ? k_estimate_sum<64, true, false, true> : k_estimate_sum<64, false, false, true>)
                   : (nib ? k_estimate_sum<64, true, false, false> : k_estimate_sum<64, false, false, false>);
-    if (parts > 1) {
+    if (parts > 1 && !sum_halves(parts, sk->g)) {
       hipLaunchKernelGGL(k_fill_u32, dim3(grid_cap(sk, (nh + 255) / 256, 8)), dim3(256), 0, st,
                          reinterpret_cast<uint32_t*>(e.out), nh, 0u);
       VBDR_LAUNCHED("k_fill_u32(sums)");
@@ -3222,7 +3235,7 @@ int vbdr_estimate_kind(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_ho
                        val, sk->reg4, parts, shift, e);
     VBDR_LAUNCHED("k_estimate_sum");
     if (parts == 1) continue;
-    hipLaunchKernelGGL(k_sum_final, dim3((uint32_t)((nh + 255) / 256)), dim3(256), 0, st, (uint32_t)nh, sk->g, m32, e);
+    hipLaunchKernelGGL(k_sum_final, dim3((uint32_t)((nh + 255) / 256)), dim3(256), 0, st, (uint32_t)nh, sk->g, m32, parts, e);
     VBDR_LAUNCHED("k_sum_final");
   }
   return VBDR_OK;

@@ -155,7 +155,8 @@ def test_sum_routes(V, m, g):
             assert torch.equal(o, out[a:b]) and torch.equal(r, raw[a:b]), (kind, n)
 
 
-@pytest.mark.parametrize("m,g,nh", [((1 << 24) + 1, 256, 30_001), ((1 << 25) + 5, 1024, 9_000)])
+@pytest.mark.parametrize("m,g,nh", [((1 << 24) + 1, 256, 30_001), ((1 << 25) + 5, 1024, 9_000), ((1 << 23) + 5, 2048, 9_000),
+                                    ((1 << 23) + 5, 4096, 9_000)])
 def test_sums_share_nothing_between_streams(V, m, g, nh):
     """LogLog, PCSA and HyperLogLog estimates of one sketch on three streams at
     once, in pool ranges (different hosts each): the results of one after the other."""
