@@ -83,12 +83,14 @@ typedef struct vbdr_info {
     uint32_t A0, A1;      /* hash seeds derived from hash_seed */
     uint64_t t;           /* slices closed so far */
     uint64_t state_bytes; /* device bytes held by the sketch: window_state_bytes + workspace_bytes */
-    int32_t est_parts;    /* pool ranges of the estimate's XCD-partitioned gathers (1 = direct) */
+    int32_t est_parts;    /* pool ranges that the sketch's partial sums have room for: 8 for pools of 2^22 BDRs and
+                             more, else 1.  Estimates take 1, 2, 4 or 8 of them by pool and list */
     int32_t scan_deferred; /* 1 when all scans defer their updates to the advance (scan_defer = 1; pools of
-                              2^16 up to 2^22 BDRs decide by the size of the scan) */
+                              2^16 up to 2^22 BDRs decide by the size of the scan: vbdr_sketch_scan_route) */
     uint32_t Lc;          /* recorders per BDR (L except for the packed layout) */
     uint32_t dr_bits;     /* bits per DR: 8, or z for the packed layout */
-    int32_t est_tiled;    /* 1 when plain estimates take the LDS-tiled path (est_binned = 3, eligible pool) */
+    int32_t est_tiled;    /* 1 when plain estimates of enough gathers take the LDS-tiled path (est_binned = 3,
+                             eligible pool) */
     uint64_t window_state_bytes; /* the window's state: DRs (byte planes or packed bit-planes), bsLBP1
                                     bit-planes, registers (bytes and nibbles), saturation masks, pool
                                     histogram, seeds, PCSA runs (Sec. 4.2 Table 1 counts the DRs) */
@@ -263,7 +265,8 @@ int vbdr_sketch_info(const vbdr_sketch *sk, vbdr_info *out);
  *                      tile held in LDS, add per-tile sums (pools of at most
  *                      2^26 BDRs, 64 <= g <= 8192; elsewhere 3 acts as 2)
  *                      (default: 3 for pools of 2^24 BDRs and more, for
- *                      estimates of some 10^7 register gathers and more; else 2);
+ *                      estimates of some 10^7 register gathers and more; else
+ *                      2.  Set to 3, it takes the tiles for every list);
  *   est_parts          pool ranges of the XCD-partitioned estimate at most, 8
  *                      (default) or 4; it takes as few as its caches allow;
  *   est_bin_hosts      hosts per pass of the binned estimate (its gather
@@ -278,15 +281,21 @@ int vbdr_sketch_info(const vbdr_sketch *sk, vbdr_info *out);
  *                      tiled (per 2048 hosts and tile) estimate, at most the
  *                      default; entries beyond it are gathered directly by
  *                      the first pass;
- *   scan_defer         for pools of 2^22..2^27 BDRs: 1 = the scan only
+ *   scan_defer         for pools of 2^16 (fast layout), 2^19 (small) or any
+ *                      number (packed) up to 2^26 BDRs: 1 = the scan only
  *                      writes each pair's (pidx, LBP1) record, sorted by
- *                      tile of 2^15 BDRs, and the advance applies the records
- *                      from LDS while it streams the tile (default); 2 = the
- *                      scan updates the pool itself (direct or binned).
- *                      Up to 2 (pools of 2^26 BDRs) to 16 (2^23 and less)
- *                      records per BDR per slice are deferred; the
- *                      rest are applied by the scan.  The sketch state seen
- *                      through vbdr_export_state is the same either way.
+ *                      tile of 2^12 to 2^15 BDRs, and the advance applies the
+ *                      records from LDS while it streams the tile (default);
+ *                      small scans of pools below 2^22 BDRs, and scans far past
+ *                      the runs of fast pools below 2^20, update the pool
+ *                      themselves; 2 = all scans do (direct or binned).
+ *                      A slice's runs hold 2 records per BDR at 2^26 BDRs, 16
+ *                      up to 2^23, 2^22 in all at least from 2^16 on, at 4 bytes
+ *                      each (2^20 BDRs: 68 MB of workspace, allocated at
+ *                      creation and kept; fewer or none where little device
+ *                      memory is left); records past them are applied by the
+ *                      scan.  The sketch state seen through
+ *                      vbdr_export_state is the same either way.
  */
 typedef struct vbdr_tuning {
     int32_t scan_test_first;

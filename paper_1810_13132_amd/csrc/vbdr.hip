@@ -993,8 +993,8 @@ __global__ __launch_bounds__(256) void k_defer_flush(const uint32_t* __restrict_
   }
 }
 
-// Clear the direct-update flag after the advance (all tiles have read it), or
-// set it when bsLBP1 planes may hold bits the records do not know of.
+// Set the direct-update flag when bsLBP1 planes may hold bits that the records do
+// not know of (the advance that reads them clears it).
 __global__ void k_defer_flag(unsigned long long* __restrict__ fill, uint32_t tiles, unsigned long long v) {
   if (threadIdx.x == 0) fill[tiles] = v;
 }
@@ -1888,7 +1888,7 @@ __global__ __launch_bounds__(kTileBinBlock) __attribute__((amdgpu_waves_per_eu(4
 
 // Pass 2: one workgroup per tile.  LDS (dynamic, tile_gather_lds): the
 // tile's TR/2 nibble bytes at address 0, then two buffers of per-host sums
-// and zero counts: 152 KiB for tiles of 2^18.  A
+// and zero counts: 144 KiB for tiles of 2^18.  A
 // host's sum over one tile and sub-block is kept in 32 bits, exactly: the
 // nibble path's registers r < 15 add 2^(32-r) = 2^18 * 2^(14-r), and at most
 // g <= 8192 records add at most 2^13 * 2^14 < 2^32 in units of 2^18.  Zero
