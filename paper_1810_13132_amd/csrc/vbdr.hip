@@ -100,10 +100,10 @@ __global__ void k_seeds(uint32_t* __restrict__ s1, uint32_t g, uint32_t A0) {
 // E_m and the register sum from a histogram of which every lane's bin is in
 // `bins` (LDS), by one thread.
 __device__ __forceinline__ void pool_stats(const unsigned long long* bins, uint64_t m, unsigned long long* stats) {
-  unsigned long long sum = 0;
-  for (int r = 0; r < kBins; ++r) sum += bins[r] * (unsigned long long)r;
+  unsigned long long sum = 0, wide = 0;
+  for (int r = 0; r < kBins; ++r) sum += bins[r] * (unsigned long long)r, wide += r >= 15 ? bins[r] : 0ull;
   stats[kStatEm] = (unsigned long long)__double_as_longlong(pool_estimate(bins, (double)m));
-  stats[kStatSum] = sum;
+  stats[kStatSum] = sum, stats[kStatWide] = wide;
 }
 
 // Statistics of an empty pool (first: m) or, with first = 0, of the histogram in stats.
@@ -1083,11 +1083,12 @@ __global__ __launch_bounds__(TABLE ? kTabBlock : kRowBlock) void k_estimate_rows
     const unsigned long long* __restrict__ stats, float* __restrict__ out) {
   extern __shared__ uint32_t lds[];
   uint32_t* tab = lds;
-  uint32_t* s1l = lds + (TABLE ? tab_n / 8 : 0);
+  uint32_t* s1l = lds + (TABLE ? tab_n / (m <= kBytesTabM ? 4 : 8) : 0);
   const uint32_t kBlock = TABLE ? kTabBlock : blockDim.x, kWaves = kBlock / 64;
-  if constexpr (TABLE) {  // tab_n: a multiple of 32 registers
-    const u32x4* src = reinterpret_cast<const u32x4*>(reg4);
-    for (uint32_t q = threadIdx.x; q < tab_n / 32; q += kBlock) reinterpret_cast<u32x4*>(tab)[q] = src[q];
+  const bool bytes = TABLE ? m <= kBytesTabM && gather_bytes<kWideTab>(stats, m) : gather_bytes<kWideL2>(stats, m);
+  if constexpr (TABLE) {  // tab_n: a multiple of 32 registers; their bytes where the pool is small and calls for them
+    const u32x4* src = reinterpret_cast<const u32x4*>(bytes ? reg : reg4);
+    for (uint32_t q = threadIdx.x; q < tab_n / (bytes ? 16 : 32); q += kBlock) reinterpret_cast<u32x4*>(tab)[q] = src[q];
   }
   if constexpr (STAGE)
     for (uint32_t i = threadIdx.x; i < g; i += kBlock) s1l[i] = s1g[i];
@@ -1097,7 +1098,7 @@ __global__ __launch_bounds__(TABLE ? kTabBlock : kRowBlock) void k_estimate_rows
   for (uint64_t h = wave * per_wave; h < nh; h += step) {
     const uint32_t n = nh - h < per_wave ? (uint32_t)(nh - h) : per_wave;
     estimate_hosts<LPH, TABLE>(hosts + h, n, STAGE ? s1l : s1g, g, m, reg, reg4,
-                               reinterpret_cast<const uint8_t*>(tab), tab_n, Em, out + h);
+                               reinterpret_cast<const uint8_t*>(tab), tab_n, bytes, Em, out + h);
   }
 }
 
@@ -1214,7 +1215,7 @@ __global__ __launch_bounds__(kRowBlock) void k_estimate_part_rows(const uint32_t
     const uint32_t n = nh - h < per_wave ? nh - h : per_wave;
     uint64_t U;
     uint32_t V;
-    gather_hosts<LPH, false, true>(hosts + h, n, lds, g, m, reg, reg4, nullptr, 0u, x, part_shift, U, V);
+    gather_hosts<LPH, false, true>(hosts + h, n, lds, g, m, reg, reg4, nullptr, 0u, x, part_shift, false, U, V);
     if (lane < n) {
       part_u[(uint64_t)x * pstride + h + lane] = U;
       part_v[(uint64_t)x * pstride + h + lane] = V;
@@ -1229,8 +1230,9 @@ __global__ __launch_bounds__(kRowBlock) void k_hist_rows(const uint32_t* __restr
                                                          const uint32_t* __restrict__ s1g, uint32_t g, uint32_t m,
                                                          const uint8_t* __restrict__ reg,
                                                          const uint8_t* __restrict__ reg4, uint32_t parts,
-                                                         uint32_t part_shift, uint32_t* __restrict__ hout,
-                                                         uint32_t hstride) {
+                                                         uint32_t part_shift,
+                                                         const unsigned long long* __restrict__ stats,
+                                                         uint32_t* __restrict__ hout, uint32_t hstride) {
   extern __shared__ uint32_t lds[];
   constexpr int kRows = 64 / LPH, kWaves = kRowBlock / 64;
   __shared__ uint32_t rows[kWaves][kRows * kBins];
@@ -1239,9 +1241,10 @@ __global__ __launch_bounds__(kRowBlock) void k_hist_rows(const uint32_t* __restr
   for (uint32_t i = lane; i < kRows * kBins; i += 64) rows[wave][i] = 0;
   __syncthreads();
   const uint32_t x = blockIdx.x % parts, tiles = gridDim.x / parts;
+  const bool bytes = !PART && gather_bytes<kWideHist>(stats, m);
   for (uint32_t h0 = ((blockIdx.x / parts) * kWaves + wave) * kRows; h0 < nh; h0 += tiles * kWaves * kRows) {
     const uint32_t h = h0 + lane / LPH;
-    hist_hosts<LPH, PART>(mm3_key(hosts[h < nh ? h : nh - 1]), lds, g, m, reg, reg4, x, part_shift,
+    hist_hosts<LPH, PART>(mm3_key(hosts[h < nh ? h : nh - 1]), lds, g, m, reg, reg4, x, part_shift, bytes,
                           rows[wave] + lane / LPH * kBins);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -1455,10 +1458,12 @@ __global__ __launch_bounds__(kRowBlock) void k_estimate_sum(const uint32_t* __re
   const uint32_t x = PART ? blockIdx.x % parts : 0u, tile = PART ? blockIdx.x / parts : blockIdx.x;
   const uint32_t tiles = PART ? gridDim.x / parts : gridDim.x, lane = threadIdx.x & 63;
   const double Em = PART ? 0.0 : sum_pool(E, m);
+  const bool bytes = NIB && !PART && gather_bytes<kWideL2>(E.pool - kStatSum, m);
   const uint64_t step = (uint64_t)tiles * (kRowBlock / 64) * per_wave;
   for (uint64_t h = ((uint64_t)tile * (kRowBlock / 64) + (threadIdx.x >> 6)) * per_wave; h < nh; h += step) {
     const uint32_t n = nh - h < per_wave ? (uint32_t)(nh - h) : per_wave;
-    const uint32_t S = sum_hosts<LPH, PART, NIB>(hosts + h, n, STAGE ? lds : s1g, g, m, val, val4, x, part_shift);
+    const uint32_t S = bytes ? sum_hosts<LPH, PART, false>(hosts + h, n, STAGE ? lds : s1g, g, m, val, val4, x, part_shift)
+                             : sum_hosts<LPH, PART, NIB>(hosts + h, n, STAGE ? lds : s1g, g, m, val, val4, x, part_shift);
     if (lane < n) {
       if constexpr (PART) {
         if (sum_halves(parts, g)) reinterpret_cast<uint16_t*>(E.out)[2 * (h + lane) + x] = (uint16_t)S;
@@ -2335,7 +2340,7 @@ int vbdr_hist_pass(vbdr_sketch* sk, const uint32_t* hosts_dev, uint32_t nh, hipS
     const auto kern = parts > 1 ? (rows ? k_hist_rows<16, true> : k_hist_rows<64, true>)
                                 : (rows ? k_hist_rows<16, false> : k_hist_rows<64, false>);
     hipLaunchKernelGGL(kern, dim3(tiles * parts), dim3(kRowBlock), (size_t)g * 4, st, hosts_dev, nh, sk->s1, g,
-                       (uint32_t)sk->m, sk->reg, sk->reg4, parts, shift, sk->hist_ws, chunk);
+                       (uint32_t)sk->m, sk->reg, sk->reg4, parts, shift, sk->hist, sk->hist_ws, chunk);
     VBDR_LAUNCHED("k_hist_rows");
     return VBDR_OK;
   }
@@ -2712,7 +2717,7 @@ int estimate_rows(vbdr_sketch* sk, const uint32_t* hosts_dev, uint64_t n_hosts, 
   const uint64_t want = ((n_hosts + per_wave - 1) / per_wave + waves - 1) / waves;
   const uint32_t grid = grid_cap(sk, want, table ? 1 : est_per_cu(sk, 1024));
   const bool stage = table || per_wave * waves >= 16;
-  const size_t lds = (table ? tab / 2 : 0) + (stage ? (size_t)g * 4 : 0);
+  const size_t lds = (table ? sk->m <= kBytesTabM ? tab : tab / 2 : 0) + (stage ? (size_t)g * 4 : 0);
   const auto kern = table ? (rows ? k_estimate_rows<16, true, true> : k_estimate_rows<64, true, true>)
                   : stage ? (rows ? k_estimate_rows<16, false, true> : k_estimate_rows<64, false, true>)
                           : k_estimate_rows<64, false, false>;

@@ -156,21 +156,21 @@ __global__ __launch_bounds__(kEBlock) void k_batch_estimate(const BatchDesc* __r
       float* out = D.out + lo + h;
       if (TABLE) {
         estimate_hosts<16, true>(hosts, c, lds, g, D.m, D.reg, D.reg4, reinterpret_cast<const uint8_t*>(tab), D.tab_n,
-                                 stat_em(D.hist), out);
+                                 false, stat_em(D.hist), out);
       } else if (D.parts > 1) {
         const uint32_t part = xcd % D.parts;
         uint64_t U;
         uint32_t V;
-        gather_hosts<16, false, true>(hosts, c, lds, g, D.m, D.reg, D.reg4, nullptr, 0u, part, D.part_shift, U, V);
+        gather_hosts<16, false, true>(hosts, c, lds, g, D.m, D.reg, D.reg4, nullptr, 0u, part, D.part_shift, false, U, V);
         if (lane < c) {
           const uint64_t at = D.part_off + part * D.n_hosts + lo + h + lane;
           part_u[at] = U;
           part_v[at] = V;
         }
       } else if (staged) {
-        estimate_hosts<16, false>(hosts, c, lds, g, D.m, D.reg, D.reg4, nullptr, 0u, stat_em(D.hist), out);
+        estimate_hosts<16, false>(hosts, c, lds, g, D.m, D.reg, D.reg4, nullptr, 0u, false, stat_em(D.hist), out);
       } else {
-        estimate_hosts<16, false>(hosts, c, D.s1, g, D.m, D.reg, D.reg4, nullptr, 0u, stat_em(D.hist), out);
+        estimate_hosts<16, false>(hosts, c, D.s1, g, D.m, D.reg, D.reg4, nullptr, 0u, false, stat_em(D.hist), out);
       }
     }
   };

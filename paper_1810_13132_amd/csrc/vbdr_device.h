@@ -373,12 +373,21 @@ __device__ __forceinline__ double noise_removed(double Es, double Em, double m, 
 }
 
 // A sketch's pool statistics (kStatWords uint64): the register histogram of
-// the last closed window, its E_m (bits of a double) and the sum of all
-// registers; then the running sums of an advance in flight and its count of
+// the last closed window, its E_m (bits of a double), the sum of all registers
+// and how many are 15 and more; then the running sums of an advance in flight and its count of
 // finished workgroups, zero between advances.
-constexpr int kStatEm = 33, kStatSum = 34, kStatAcc = 64, kStatTicket = kStatAcc + kBins, kStatWords = 128;
+constexpr int kStatEm = 33, kStatSum = 34, kStatWide = 35, kStatAcc = 64, kStatTicket = kStatAcc + kBins, kStatWords = 128;
 __device__ __forceinline__ double stat_em(const unsigned long long* stats) {
   return __longlong_as_double((long long)stats[kStatEm]);
+}
+
+// Whether gathers read the registers' bytes and not their nibbles, of which each
+// 15 is read again: pools whose bytes an XCD's L2 holds and of which a share of
+// 1 / WIDE is 15 and more; in LDS, pools of up to kBytesTabM BDRs.
+constexpr uint32_t kBytesMaxM = 1u << 22, kBytesTabM = 1u << 16;
+template <uint32_t WIDE>
+__device__ __forceinline__ bool gather_bytes(const unsigned long long* stats, uint32_t m) {
+  return m <= kBytesMaxM && WIDE * stats[kStatWide] > m;
 }
 
 // E_m: the HyperLogLog estimate over all m registers from their histogram.
@@ -405,12 +414,13 @@ __device__ __forceinline__ T row_sum(T v) {
 // g 2^14 <= 2^30 in units of 2^18, to Us; the others add 2^(32-r) to Ux.  Each host's sums move to
 // the lane of its place (U and V of host `lane`), so that what follows runs
 // once for all of them, a lane per host.  PART: only registers of pool range
-// `part` (the hash's bits from part_shift up) are gathered.
+// `part` (the hash's bits from part_shift up) are gathered.  bytes: see gather_bytes.
 template <int LPH, bool TABLE, bool PART>
 __device__ __forceinline__ void gather_hosts(const uint32_t* __restrict__ hosts, uint32_t n, const uint32_t* s1,
                                              uint32_t g, uint32_t m, const uint8_t* __restrict__ reg,
                                              const uint8_t* __restrict__ reg4, const uint8_t* tab, uint32_t tab_n,
-                                             uint32_t part, uint32_t part_shift, uint64_t& U, uint32_t& V) {
+                                             uint32_t part, uint32_t part_shift, bool bytes, uint64_t& U,
+                                             uint32_t& V) {
   constexpr int kRows = 64 / LPH;  // hosts at a time
   const int lane = threadIdx.x & 63, q = lane / LPH, ql = lane % LPH;
   const uint32_t kmix = mm3_key((uint32_t)lane < n ? hosts[lane] : 0u);
@@ -420,8 +430,8 @@ __device__ __forceinline__ void gather_hosts(const uint32_t* __restrict__ hosts,
     const uint32_t km = (uint32_t)__shfl((int)kmix, (int)(t * kRows) + q);
     uint32_t Us = 0, Vs = 0;
     unsigned long long Ux = 0;
-    auto gathers = [&](auto guard, auto flight) __attribute__((always_inline)) {
-      constexpr bool GUARD = decltype(guard)::value;
+    auto gathers = [&](auto guard, auto flight, auto from_bytes) __attribute__((always_inline)) {
+      constexpr bool GUARD = decltype(guard)::value, BYTES = decltype(from_bytes)::value;
       constexpr int kFlight = decltype(flight)::value;  // gathers in flight per lane
       for (uint32_t i0 = (uint32_t)ql; i0 < g; i0 += LPH * kFlight) {
         uint32_t p[kFlight], nib[kFlight];
@@ -435,8 +445,19 @@ __device__ __forceinline__ void gather_hosts(const uint32_t* __restrict__ hosts,
         }
 #pragma unroll
         for (int u = 0; u < kFlight; ++u) {
-          if (TABLE) nib[u] = p[u] < tab_n ? (uint32_t)tab[p[u] >> 1] : (uint32_t)reg4[p[u] >> 1];
+          if (BYTES) nib[u] = TABLE ? (uint32_t)tab[p[u]] : (uint32_t)reg[p[u]];
+          else if (TABLE) nib[u] = p[u] < tab_n ? (uint32_t)tab[p[u] >> 1] : (uint32_t)reg4[p[u] >> 1];
           else nib[u] = !PART || mine[u] ? (uint32_t)reg4[p[u] >> 1] : 0u;
+        }
+        if constexpr (BYTES) {
+#pragma unroll
+          for (int u = 0; u < kFlight; ++u) {
+            const bool in = !GUARD || i0 + (uint32_t)(LPH * u) < g;
+            Us += in && nib[u] < 15u ? 0x4000u >> nib[u] : 0u;
+            Vs += in && nib[u] == 0u;
+            Ux += in && nib[u] >= 15u ? 1ull << (32 - nib[u]) : 0ull;
+          }
+          continue;
         }
         bool wide = false;
 #pragma unroll
@@ -453,9 +474,10 @@ __device__ __forceinline__ void gather_hosts(const uint32_t* __restrict__ hosts,
             if (nib[u] == 15u) Ux += 1ull << (32 - reg[p[u]]);
       }
     };
-    if (g % (LPH * 8) == 0) gathers(FalseType{}, Int<8>{});
-    else if (LPH == 16) gathers(TrueType{}, Int<8>{});
-    else gathers(TrueType{}, Int<4>{});
+    if (!PART && bytes) gathers(TrueType{}, Int<8>{}, TrueType{});
+    else if (g % (LPH * 8) == 0) gathers(FalseType{}, Int<8>{}, FalseType{});
+    else if (LPH == 16) gathers(TrueType{}, Int<8>{}, FalseType{});
+    else gathers(TrueType{}, Int<4>{}, FalseType{});
     Us = row_sum<LPH>(Us);
     Vs = row_sum<LPH>(Vs);
     // lane l keeps host l: row l % kRows of step l / kRows
@@ -516,14 +538,30 @@ __device__ __forceinline__ uint32_t sum_hosts(const uint32_t* __restrict__ hosts
 // value over eight gathers, then bytes (a lane sees at most 128 registers), then
 // the lanes' 16-bit sums, halving the values each lane keeps; registers of 15
 // and more are read from the byte array and counted with LDS atomics (an LDS
-// atomic per register kept whole waves on a few values).  PART as in
+// atomic per register kept whole waves on a few values), which take every register
+// where many are (bytes: see gather_bytes).  PART as in
 // gather_hosts.  g <= 128 LPH.
 template <int LPH, bool PART>
 __device__ __forceinline__ void hist_hosts(uint32_t kmix, const uint32_t* s1, uint32_t g, uint32_t m,
                                            const uint8_t* __restrict__ reg, const uint8_t* __restrict__ reg4,
-                                           uint32_t part, uint32_t part_shift, uint32_t* row) {
+                                           uint32_t part, uint32_t part_shift, bool bytes, uint32_t* row) {
   const uint32_t ql = threadIdx.x % LPH;
   uint64_t even = 0, odd = 0;  // byte j: count of value 2j, 2j + 1
+  if (!PART && bytes) {
+    constexpr int kFlight = 8;
+    for (uint32_t i0 = ql; i0 < g; i0 += LPH * kFlight) {
+      uint32_t r[kFlight];
+#pragma unroll
+      for (int u = 0; u < kFlight; ++u) {
+        const uint32_t i = i0 + (uint32_t)(LPH * u);
+        r[u] = i < g ? (uint32_t)reg[reduce_m(mm3_seeded(kmix, s1[i]), m)] : 255u;
+      }
+#pragma unroll
+      for (int u = 0; u < kFlight; ++u)
+        if (r[u] != 255u) atomicAdd(&row[r[u]], 1u);
+    }
+    return;
+  }
   auto gathers = [&](auto flight) __attribute__((always_inline)) {
     constexpr int kFlight = decltype(flight)::value;  // gathers in flight per lane
     for (uint32_t i0 = ql; i0 < g; i0 += LPH * kFlight) {
@@ -585,10 +623,10 @@ template <int LPH, bool TABLE>
 __device__ __forceinline__ void estimate_hosts(const uint32_t* __restrict__ hosts, uint32_t n, const uint32_t* s1,
                                                uint32_t g, uint32_t m, const uint8_t* __restrict__ reg,
                                                const uint8_t* __restrict__ reg4, const uint8_t* tab, uint32_t tab_n,
-                                               double Em, float* __restrict__ out) {
+                                               bool bytes, double Em, float* __restrict__ out) {
   uint64_t U;
   uint32_t V;
-  gather_hosts<LPH, TABLE, false>(hosts, n, s1, g, m, reg, reg4, tab, tab_n, 0u, 0u, U, V);
+  gather_hosts<LPH, TABLE, false>(hosts, n, s1, g, m, reg, reg4, tab, tab_n, 0u, 0u, bytes, U, V);
   const uint32_t lane = threadIdx.x & 63;
   if (lane < n) {
     const double Es = hll_estimate(U, V, (double)g);

@@ -54,6 +54,12 @@ constexpr uint64_t kRangeBytes = 4ull << 20;      // nibbles of a range: an XCD'
 constexpr uint64_t kPartMinGathers = 1ull << 20, kPartMinLongG = 3ull << 17, kPartMinShortG = 5ull << 17;
 constexpr uint64_t kTileMinGathers = 3ull << 23, kTileMinGathers8 = 10ull << 20;  // from which tiles pay (8 ranges)
 
+// Shares 1 / k of registers of 15 and more from which gathers read bytes (gather_bytes): from L2, from LDS, and for
+// histograms, which then count with LDS atomics alone.  200,000 hosts, g = 1024, 40,000 BDRs, most registers 15 and
+// more: LogLog 520 us by nibbles, 270 by bytes, learned 516 and 290, plain (LDS) 270 and 240; g = 256, 131,072 BDRs, one
+// in four: learned 212 and 165.
+constexpr uint32_t kWideL2 = 16, kWideTab = 4, kWideHist = 32;
+
 struct vbdr_sketch {
   int device;
   int n_cu;

@@ -166,6 +166,7 @@ void k_learned(uint32_t nh, uint32_t parts, uint32_t hstride, const uint32_t* __
   __syncthreads();
   const double Em = sem;
   const int pool_bad = spool_bad;
+  const bool bytes = DIRECT && gather_bytes<kWideHist>(hist, m);
   const float inv_g = 1.0f / (float)g;  // g is a power of two: c * inv_g == c / g exactly
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int col = lane & 15, q = lane >> 4;
@@ -182,20 +183,20 @@ void k_learned(uint32_t nh, uint32_t parts, uint32_t hstride, const uint32_t* __
       const uint32_t last = nh - 1;  // rows past it repeat its host and are not used
       if constexpr (SPREAD) {
         const uint32_t h = tile * 16 + wave;
-        hist_hosts<64, false>(mm3_key(hosts[h < last ? h : last]), s1_lds, g, m, reg, reg4, 0u, 0u,
+        hist_hosts<64, false>(mm3_key(hosts[h < last ? h : last]), s1_lds, g, m, reg, reg4, 0u, 0u, bytes,
                               H + wave * kHistStride);
         __syncthreads();
         if (wave != 0) continue;  // one tile a workgroup
       } else if (g <= 2048) {
         for (int r0 = 0; r0 < 16; r0 += 4) {
           const uint32_t h = tile * 16 + r0 + q;
-          hist_hosts<16, false>(mm3_key(hosts[h < last ? h : last]), s1_lds, g, m, reg, reg4, 0u, 0u,
+          hist_hosts<16, false>(mm3_key(hosts[h < last ? h : last]), s1_lds, g, m, reg, reg4, 0u, 0u, bytes,
                                 H + (r0 + q) * kHistStride);
         }
       } else {
         for (int row = 0; row < 16; ++row) {
           const uint32_t h = tile * 16 + row;
-          hist_hosts<64, false>(mm3_key(hosts[h < last ? h : last]), s1_lds, g, m, reg, reg4, 0u, 0u,
+          hist_hosts<64, false>(mm3_key(hosts[h < last ? h : last]), s1_lds, g, m, reg, reg4, 0u, 0u, bytes,
                                 H + row * kHistStride);
         }
       }

@@ -210,3 +210,55 @@ def test_est_blocks_per_cu_bounds_every_estimate(V):
                 us.append(best)
             assert torch.equal(outs[0], outs[1]), (m, name)
             assert name == "features" or us[1] > 1.15 * us[0], (m, name, us)  # half of its time is not the histograms
+
+
+@pytest.mark.parametrize("m,g", [(300, 16), (5003, 64), (1 << 16, 1024), ((1 << 16) + 1, 256), (200_001, 2048),
+                                 (100_000, 16384)])
+@pytest.mark.parametrize("share", [1 / 33, 1 / 31, 1 / 17, 1 / 15, 1 / 5, 1 / 3, 1.0])
+def test_pools_of_large_registers(V, m, g, share):
+    """Shares of registers of 15 and more around the ones from which the gathers read
+    bytes and not nibbles (from L2, from LDS, for histograms): plain estimates
+    and features are estimate_ex's, LogLog sums its histograms' up to the
+    rounding of the constant."""
+    rng = np.random.default_rng(g)
+    sk = V.Sketch(m, g, 3, 21, "small")
+    reg = rng.integers(0, min(sk.L, 14) + 1, m).astype(np.uint8)
+    wide = rng.permutation(m)[: int(m * share)]
+    reg[wide] = rng.integers(min(15, sk.L), sk.L + 1, len(wide))
+    sk.load_state({"dr": np.full((m, sk.L), 255, np.uint8), "reg": reg,
+                   "hist": np.bincount(reg, minlength=33).astype(np.uint64), "t": 1})
+    hosts = V.to_device_u32(rng.integers(0, 2**32, 17_001, dtype=np.uint64).astype(np.uint32))
+    ref, _, hist = sk.estimate_ex(hosts)
+    for n in (1, 5, 1025, 5000, 17_001):
+        h = hosts[:n].contiguous()
+        assert torch.equal(sk.estimate(h), ref[:n]), n
+        assert torch.equal(sk.features(h)[:, :33], (hist[:n].double() / g).float()), n
+        raw = sk.estimate_kind(h, "loglog", with_raw=True)[1].cpu().numpy()
+        S = (hist[:n].double().cpu() * torch.arange(33, dtype=torch.float64)).sum(1)
+        ratio = raw / (g * torch.exp2(S / g)).numpy()
+        assert np.ptp(ratio) <= 1e-13 * ratio[0], n
+
+
+def test_large_registers_cost_no_second_gather(V):
+    """Estimates of a pool whose registers are 15 and more against one of as many
+    small registers: about the same time (1.8 to 2 times while every gather of a
+    nibble of 15 was followed by one of its byte)."""
+    m, g = 40_000, 1024
+    rng = np.random.default_rng(1)
+    hosts = V.to_device_u32(rng.integers(0, 2**32, 100_000, dtype=np.uint64).astype(np.uint32))
+    us = {}
+    for lo in (2, 15):
+        sk = V.Sketch(m, g, 3, 21, "small")
+        reg = rng.integers(lo, lo + 4, m).astype(np.uint8)
+        sk.load_state({"dr": np.full((m, sk.L), 255, np.uint8), "reg": reg,
+                       "hist": np.bincount(reg, minlength=33).astype(np.uint64), "t": 1})
+        best = float("inf")
+        for _ in range(10):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            sk.estimate_kind(hosts, "loglog")
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 1e3)
+        us[lo] = best
+    assert us[15] < 1.4 * us[2], us
