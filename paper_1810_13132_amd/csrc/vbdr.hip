@@ -569,10 +569,12 @@ __global__ __launch_bounds__(kDeferBlock) void k_scan_defer(const u32x2* __restr
 // LDS atomics: one load per record, waited for one at a time, left the
 // advance bound by load latency.  FLOOD: where kFloodLanes lanes of a wave
 // and more hold one BDR's records, as in a slice that one host floods, a bit is
-// read first: lanes that add to one LDS word are served one at a time (small
-// layout, 2^26 pairs of one host: 2^24 BDRs, step 543 -> 376 us, 2^22 372 -> 272;
-// random pairs the same).  Not in the packed layout, whose two waves a tile
-// wait for the reads instead (2^20 BDRs, 2^22 pairs: 77 -> 94 us with it).
+// read first, from the block's second round on (the first sets what there is; a
+// pool with a few busy tiles took 3 % longer with it): lanes that add to one
+// LDS word are served one at a time (small layout, 2^26 pairs of one host: 2^24
+// BDRs, step 543 -> 376 us, 2^22 372 -> 272; random pairs the same).  Not in the
+// packed layout, whose two waves a tile wait for the reads instead (2^20 BDRs,
+// 2^22 pairs: 77 -> 94 us with it).
 template <bool FLOOD>
 __device__ __forceinline__ void records_to_planes(const uint32_t* __restrict__ r, uint32_t n, uint32_t tshift,
                                                   uint32_t* pm) {
@@ -603,7 +605,8 @@ __device__ __forceinline__ void records_to_planes(const uint32_t* __restrict__ r
       }
     };
     const uint32_t p0 = v[0][0] >> 5;
-    if (FLOOD && __popcll(__builtin_amdgcn_ballot_w64(p0 == (uint32_t)__builtin_amdgcn_readfirstlane((int)p0))) >= kFloodLanes)
+    if (FLOOD && q0 >= 4 * blockDim.x &&
+        __popcll(__builtin_amdgcn_ballot_w64(p0 == (uint32_t)__builtin_amdgcn_readfirstlane((int)p0))) >= kFloodLanes)
       apply(TrueType{});
     else
       apply(FalseType{});
